@@ -1,0 +1,95 @@
+"""GPU parity of the small-batch kernels (one-launch tables, weight-streaming GEMMs) at the edges of their ranges."""
+import numpy as np
+import pytest
+
+import gpu_util as G
+from paper_2605_05607_amd import binding as B
+from paper_2605_05607_amd import layer as L
+from paper_2605_05607_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def cfg_of(**kw):
+    base = dict(name="t", T=32, d=512, f=512, E=16, k=4, R=4, local_rank_begin=1, local_rank_end=3, dtype=wl.BF16,
+                router="normal", seed=11)
+    base.update(kw)
+    return wl.MoEConfig(**base)
+
+
+# pairs at and around one, two and four iterations of the workgroup; k that does not divide 64; tokens that straddle
+# waves; counters that just fit the LDS and that do not (the two-kernel form)
+@pytest.mark.parametrize("T,E,k,R", [(1, 1, 1, 1), (9, 8, 7, 8), (128, 256, 8, 8), (205, 64, 5, 4), (341, 12, 3, 12),
+                                     (146, 128, 7, 8), (512, 256, 8, 8), (513, 256, 8, 8), (585, 300, 7, 3),
+                                     (128, 32, 32, 4), (40, 1900, 20, 19), (40, 2048, 8, 2), (4096, 96, 1, 96)])
+def test_small_tables_bit_exact(oracle, T, E, k, R):
+    print(f"small tables T={T} E={E} k={k} R={R}", flush=True)
+    rng = np.random.default_rng(T * 13 + E)
+    logits = rng.standard_normal((T, E)).astype(np.float32)
+    logits[::3] = np.round(logits[::3] * 2) / 2
+    logits[1::4, E // 3:E // 3 + k] += 9.0  # many tokens on the same experts
+    cfg = cfg_of(T=T, E=E, k=k, R=R, d=8, f=8, local_rank_begin=0, local_rank_end=R)
+    lay, got = G.run_tables(cfg, logits)
+    G.assert_tables_equal(got, oracle, logits, cfg)
+
+
+EDGES = {
+    "one_token": dict(T=1),
+    "rows_31": dict(T=31, router="zipf"),
+    "rows_32_every_expert": dict(T=32, E=4, k=4, R=1, local_rank_begin=0, local_rank_end=1),
+    "rows_33": dict(T=33, E=2, k=2, R=1, local_rank_begin=0, local_rank_end=1, d=520, f=584),
+    "rows_64": dict(T=64, E=3, k=2, R=3, local_rank_begin=0, local_rank_end=3, d=1032, f=512),
+    "rows_65": dict(T=65, E=2, k=2, R=2, local_rank_begin=0, local_rank_end=2, d=512, f=776),
+    "rows_128_two_passes": dict(T=128, E=4, k=4, R=1, local_rank_begin=0, local_rank_end=1, d=544, f=552),
+    "no_local_row": dict(T=3, E=64, k=1, R=64, local_rank_begin=5, local_rank_end=6),
+    "many_experts": dict(T=100, E=512, k=6, R=1, local_rank_begin=0, local_rank_end=1),
+    "groups": dict(T=24, d=512, f=2048, E=32, k=16, R=1, local_rank_begin=0, local_rank_end=1),
+}
+
+
+@pytest.mark.parametrize("name", list(EDGES))
+def test_small_batch_forward(oracle, name):
+    import torch
+    cfg = cfg_of(**EDGES[name])
+    print(f"small-batch forward {name}", flush=True)
+    w = wl.make_workload(cfg)
+    lay = L.MoELayer(cfg)
+    lay.load_weights(w.W_gate, w.W_up, w.W_down)
+    x, lg = L.to_device(w.x), L.to_device(w.logits)
+    idx, tw = oracle.route_topk(w.logits, cfg.k)
+    ref = oracle.forward(w.x, idx, tw, w.W_gate, w.W_up, w.W_down, cfg.E, cfg.R, cfg.local_rank_begin,
+                         cfg.local_rank_end)
+    first = None
+    for fill in (0xFF, 0x3C):  # the workspace's contents before the call do not matter, and the result repeats
+        lay.forward_ws.fill_(fill)
+        lay.y.fill_(float("nan"))
+        lay.step(lg, x)
+        torch.cuda.synchronize()
+        G.check_y(lay.y_host(), ref, cfg.dtype)
+        first = lay.y.clone() if first is None else first
+        assert torch.equal(lay.y, first)
+        assert B.moe_forward_status(lay.forward_ws) == 0
+
+
+@pytest.mark.parametrize("name", ["one_token", "rows_33", "rows_128_two_passes", "groups"])
+def test_small_batch_fp8_forward(oracle, name):
+    import torch
+    kw = dict(EDGES[name])
+    kw["f"] = kw.get("f", 512) // 16 * 16
+    kw["d"] = kw.get("d", 512) // 16 * 16
+    cfg = cfg_of(**kw)
+    print(f"small-batch fp8 forward {name}", flush=True)
+    w = wl.make_workload(cfg)
+    hs = wl.fp8_h_scale(cfg)
+    lay = L.MoELayer(cfg)
+    lay.load_weights_fp8(w.W_gate, w.W_up, w.W_down, hs)
+    x, lg = L.to_device(w.x), L.to_device(w.logits)
+    lay.route(lg)
+    lay.build_dispatch()
+    lay.y.fill_(float("nan"))
+    lay.forward_fp8(x)
+    torch.cuda.synchronize()
+    idx, tw = oracle.route_topk(w.logits, cfg.k)
+    ref = oracle.forward_fp8(w.x, idx, tw, w.W_gate, w.W_up, w.W_down, hs, cfg.E, cfg.R, cfg.local_rank_begin,
+                             cfg.local_rank_end)
+    G.check_y(lay.y_host(), ref, cfg.dtype)
