@@ -185,6 +185,9 @@ MOE355_API int moe_pack_weights(const moe_shape *shape, const void *W_gate, cons
  * workgroups: a GEMM-2 tile starts as soon as the h rows of its 256-row tile are complete (per-tile readiness
  * counters in the workspace), the one-GPU form of the tile-granular GEMM-1 => GEMM-2 hand-over of the fused
  * kernel (Sec. IV-A, IV-B); otherwise the two GEMMs are two launches.  The result is the same either way.
+ * Small batches (bf16, T <= 128, d and f >= 512, few rows per expert) run two weight-streaming kernels instead, which
+ * need no tile table and no separate Combine; they split the reduction ranges, so their y can differ from the other
+ * forms' in the rounding of the fp32 sums.
  * A wait inside the resident kernel is bounded; if one gives up (corrupt tables; it cannot happen otherwise) the rows
  * computed from the incomplete tile are written as NaN and moe_forward_status reports 1 for this workspace.
  * `tables` must come from moe_build_dispatch on the same shape and topk_idx.
@@ -251,7 +254,7 @@ MOE355_API int moe_fused_forward_one_launch(const moe_shape *shape, const void *
  * (Sec. IV-B, IV-C) on one GPU.  A workgroup that finds no GEMM-1 item left takes GEMM-2 items (each waits for the
  * counter of its M tile's GEMM-1 items), and one that finds no GEMM-2 item left reduces tokens, one wave per token:
  * the wave waits for the counters of finished GEMM-2 items of every M tile that holds one of the token's rows, then
- * sums the rows in slot order.  y is bit-identical to moe_fused_forward's.  bf16 layers with at most 4091 local experts (the
+ * sums the rows in slot order.  y is bit-identical to the one- and two-launch forms'.  bf16 layers with at most 4091 local experts (the
  * tile table's LDS), MOE_ERR_UNSUPPORTED otherwise.  Arguments as
  * moe_fused_forward_one_launch ([2] and [3] of `events` are recorded together after the launch, [4] right after);
  * max_polls: bound on the polls of one wait (0 = the library's default of several seconds); wait_extra: every wait

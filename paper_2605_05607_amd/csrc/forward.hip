@@ -13,6 +13,7 @@
 #include "gemm_f32.h"
 #include "pack_kernels.h"
 #include "prep_kernel.h"
+#include "stream_gemm.h"
 #include "wgrad_bf16.h"
 
 namespace moe355 {
@@ -230,6 +231,85 @@ static int launch_combine(const moe_shape *s, const Derived &dv, const float *ro
   return launch_status();
 }
 
+// Small batches: the stream kernels (stream_gemm.h).  The reduction ranges have to give each of the eight waves work
+// (d, f >= 512).  A workgroup reads its expert's rows once per 32 columns, so with many rows per expert that traffic
+// catches up with the weights (2.8 GB of weights, T = 64 / 96 / 128 at 16 / 24 / 32 rows per expert: 0.99 / 0.91 / 0.81 of
+// the tile kernels' speed; 8 rows: 1.02 to 1.7 x): the line is at 12 rows on average, except where the whole layer is so
+// small (128 MB) that the launches saved outweigh it (50 MB, 16 rows: 1.45 x).
+static bool use_stream(const moe_shape *s, const Derived &dv, int elt) {
+  if (s->dtype != MOE_BF16 || s->T > kStreamTokens || dv.E_loc > kStreamExperts || s->d < 512 || s->f < 512 ||
+      stream2_lds_bytes(s->T, (int)dv.P_cap, dv.E_loc) > 160 * 1024)
+    return false;
+  return (int64_t)s->T * s->k <= 12 * (int64_t)s->E || (int64_t)dv.E_loc * 3 * s->d * s->f * elt <= (int64_t)128 << 20;
+}
+
+// Work groups per strip of GEMM-2: one, unless so few strips of 32 columns exist that a second launch (~5 us) costs less
+// than what the missing CUs would have pulled (a CU pulls ~55 GB/s, the chip ~6.5 TB/s, i.e. what ~120 CUs pull).
+static int stream_groups(const moe_shape *s, const Derived &dv, int elt) {
+  const int strips = ceil_div(s->d, 32);
+  const double busy = std::min<double>(dv.E_loc, (double)s->T * s->k * dv.E_loc / s->E);
+  const double us = busy * s->f * s->d * elt / 55e3;  // one CU, microseconds
+  int best = 1;
+  double t_best = us / std::min(strips, 120);
+  for (int g = 2; g <= std::min(8, std::min(s->k, dv.E_loc)); ++g) {  // (the partial sums live in the o rows)
+    const double t = us / std::min(strips * g, 120) + 5.0;
+    if (t < t_best) {
+      t_best = t;
+      best = g;
+    }
+  }
+  return best;
+}
+
+static int launch_stream(const moe_shape *s, const Derived &dv, const void *x, const float *topk_w,
+                         const moe_dispatch *tb, const void *packed_gu, const void *packed_down, const Ws &w, void *y,
+                         hipStream_t st, void *const *events, const Fp8Operands *q) {
+  auto mark = [&](int i) {
+    if (events && events[i]) (void)hipEventRecord((hipEvent_t)events[i], st);
+  };
+  StreamArgs g1{};
+  g1.A = q ? static_cast<const void *>(q->xq) : x;
+  g1.Bp = packed_gu; g1.out = w.h;
+  g1.offsets = tb->offsets; g1.perm = tb->perm; g1.topk_w = topk_w; g1.error = w.header + 24;
+  g1.T = s->T; g1.k = s->k; g1.e_lo = dv.e_lo; g1.E_loc = dv.E_loc; g1.P_cap = (int)dv.P_cap;
+  const int step = q ? kFp8KStep : kBK;
+  g1.K = s->d; g1.N = s->f; g1.n_ntiles = ceil_div(s->f, kBN / 2); g1.n_ktiles = ceil_div(s->d, step);
+  StreamArgs g2 = g1;
+  const int groups = stream_groups(s, dv, q ? 1 : 2);
+  g2.A = w.h; g2.Bp = packed_down; g2.out = groups > 1 ? static_cast<void *>(w.o) : y;
+  g2.K = s->f; g2.N = s->d; g2.n_ntiles = ceil_div(s->d, kBN); g2.n_ktiles = ceil_div(s->f, step);
+  if (q) {
+    g1.a_scale = q->x_scale; g1.b_scale = q->gu_scale; g1.h_scale = q->h_scale;
+    g2.b_scale = q->down_scale; g2.h_scale = q->h_scale;
+  }
+  mark(1);
+  const dim3 grid1((unsigned)ceil_div(s->f, 32), (unsigned)dv.E_loc), grid2((unsigned)ceil_div(s->d, 32), (unsigned)groups);
+  const size_t lds = stream2_lds_bytes(s->T, (int)dv.P_cap, dv.E_loc);
+#define MOE355_STREAM(FP8_, NB_, D1_, D2_)                                                                            \
+  do {                                                                                                                \
+    static std::atomic<uint64_t> done{0};                                                                             \
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&stream_gemm2_kernel<FP8_, NB_, D2_>), 160 * 1024, done))    \
+      return MOE_ERR_HIP;                                                                                             \
+    hipLaunchKernelGGL((stream_gemm1_kernel<FP8_, NB_, 8, D1_>), grid1, dim3(8 * 64), 0, st, g1);                     \
+    mark(2);                                                                                                          \
+    hipLaunchKernelGGL((stream_gemm2_kernel<FP8_, NB_, D2_>), grid2, dim3(kStream2Waves * 64), lds, st, g2);          \
+  } while (0)
+  if (q) {
+    if (s->T <= 32) MOE355_STREAM(true, 1, 3, 5); else MOE355_STREAM(true, 2, 2, 3);
+  } else {
+    if (s->T <= 32) MOE355_STREAM(false, 1, 3, 5); else MOE355_STREAM(false, 2, 2, 3);
+  }
+#undef MOE355_STREAM
+  mark(3);
+  if (groups > 1) {
+    const int n4 = s->T * (s->d / 4);
+    hipLaunchKernelGGL(stream_reduce_kernel, dim3((unsigned)ceil_div(n4, 256)), dim3(256), 0, st, w.o,
+                       static_cast<bf16_t *>(y), n4, groups);
+  }
+  mark(4);
+  return launch_status();
+}
+
 static bool tables_ok(const moe_dispatch *t) {
   return t && t->counts && t->offsets && t->perm && t->inv_perm && t->rank_counts && t->rank_offsets &&
          t->dedup_tok && t->dedup_mask && t->pair_to_dedup;
@@ -339,6 +419,10 @@ static int forward_common(const moe_shape *shape, const void *x, const int32_t *
                                                    align_up(fp8_tile_bytes(shape, dv, 1), 256));
     q.h_scale = h_scale;
   }
+  // the stream kernels are the form the library picks for a small batch; the forms a caller asks for by name (and the
+  // training forward, which keeps its rows) run the tile kernels
+  if (fused && !keep && gemm_launches == 0 && use_stream(shape, dv, fp8 ? 1 : 2))
+    return launch_stream(shape, dv, x, topk_w, tables, packed_gate_up, packed_down, w, y, st, events, fp8 ? &q : nullptr);
   if ((rc = launch_prep(shape, dv, tables, topk_idx, topk_w, w, sole, st, with_combine)) != MOE_OK) return rc;
   mark(1);
   if (fused) {

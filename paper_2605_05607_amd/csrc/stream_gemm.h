@@ -1,0 +1,350 @@
+// The forward pass of a small batch (decode): every expert has few rows, so the layer is a read of the busy experts'
+// weights and nothing else.  Two kernels, no tile table, no work lists, no separate Combine.
+//
+// What bounds it: HBM (the weights of the busy experts), and below ~50 MB the latencies of the launches.  The tile
+// kernels of gemm_bf16.h give one workgroup a 256-column panel over the whole reduction range; with a handful of busy
+// experts that is a few dozen workgroups, each at the 50-60 GB/s one CU can pull.  Here a workgroup owns 32 h columns
+// (GEMM-1) or 32 output columns (GEMM-2), its waves share the reduction range, and the weights go from memory straight
+// into the registers the matrix instructions read: the packed tile stores an operand as one contiguous KiB, so there is
+// nothing for the LDS to rearrange.  The waves' partial sums meet in the LDS, in wave order.
+// Measured, forward step, before (tile table + tile kernels + Combine) -> here: 0.7 GB of weights for one token 262 ->
+// 133 us (5.3 TB/s), 34 MB for 16 tokens 67 -> 28 us, 2.3 GB for 96 tokens 417 -> 357 us (6.5 TB/s), 0.24 GB of FP8
+// weights for 48 tokens 115 -> 76 us.
+#pragma once
+#include "gemm_bf16.h"
+
+namespace moe355 {
+
+constexpr int kStreamTokens = 128;   // largest batch (GEMM-2 keeps one fp32 row of 32 columns per token and wave)
+constexpr int kStreamExperts = 512;  // most local experts (GEMM-2 lists the busy ones in the LDS)
+constexpr int kStream2Waves = 8;
+
+struct StreamArgs {
+  const void *A;    // GEMM-1: x [T, K] (bf16, or codes); GEMM-2: h [rows, K]
+  const void *Bp;   // packed tiles
+  void *out;        // GEMM-1: h [rows, N]; GEMM-2: y [T, N] bf16 (one group) or partial sums [groups][T][N] fp32
+  const int32_t *offsets, *perm;
+  const float *topk_w;
+  int32_t *error;   // status word of the workspace (cleared by GEMM-1: no wait can give up here)
+  int T, k, e_lo, E_loc, P_cap;
+  int K, N, n_ntiles, n_ktiles;
+  const float *a_scale, *b_scale, *h_scale;  // FP8 only (see GemmArgs)
+};
+
+// Fragments of one k-step for up to NB 32-row blocks and NC 32-column blocks.
+template <int NB, int NC>
+struct StreamSlab {
+  bf16x8 a[NB][4], b[NC][4];
+};
+
+template <bool FP8>
+struct StreamElt {
+  typedef typename std::conditional<FP8, uint8_t, bf16_t>::type type;
+};
+
+// Operands come in through buffer loads: the descriptor and everything that depends on the k-step are scalars, so a slab
+// costs no vector registers for addresses (with flat addresses the compiler kept one per load and spilled).
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t stream_rsrc(const void *base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00027000);
+}
+__device__ __forceinline__ bf16x8 stream_fetch(rsrc_t r, uint32_t voff, uint32_t soff) {
+  return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+}
+__device__ __forceinline__ bf16x8 stream_fetch_once(rsrc_t r, uint32_t voff, uint32_t soff) {  // non-temporal
+  return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 2));
+}
+
+// Loads of k-step kt.  b: the column block in tile 0 (lane * 16 is the lane's operand); a: the rows' matrix, a_off[mi]
+// this lane's row plus its half of the reduction chunk, in bytes.  Chunks past K meet zeros in the packed tile; what they
+// read is the following row, or zero past the end of the matrix (the descriptor's bound): finite either way.
+template <bool FP8, int NB, int NC>
+__device__ __forceinline__ void stream_load(StreamSlab<NB, NC> &s, rsrc_t a, const uint32_t (&a_off)[NB], rsrc_t b,
+                                            uint32_t lane16, int kt, int nb) {
+#pragma unroll
+  for (int j = 0; j < NC; ++j)
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+      s.b[j][kk] = stream_fetch_once(b, lane16 + kk * 1024, kt * kTileBytes + j * 4096);
+#pragma unroll
+  for (int mi = 0; mi < NB; ++mi)
+    if (NB == 1 || mi < nb) {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) s.a[mi][kk] = stream_fetch(a, a_off[mi] + kk * 32, kt * 128);
+    }
+}
+
+template <bool FP8, int NB, int NC>
+__device__ __forceinline__ void stream_multiply(const StreamSlab<NB, NC> &s, f32x16 (&acc)[NB][NC], int nb) {
+  __builtin_amdgcn_sched_barrier(0);  // one slab after the other: its products, then its reload
+#pragma unroll
+  for (int mi = 0; mi < NB; ++mi)
+    if (NB == 1 || mi < nb) {
+#pragma unroll
+      for (int j = 0; j < NC; ++j) {
+        if constexpr (FP8) {
+          acc[mi][j] = mfma_fp8_pair(s.a[mi][0], s.a[mi][1], s.b[j][0], s.b[j][1], acc[mi][j]);
+          acc[mi][j] = mfma_fp8_pair(s.a[mi][2], s.a[mi][3], s.b[j][2], s.b[j][3], acc[mi][j]);
+        } else {
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk) acc[mi][j] = mfma_bf16(s.a[mi][kk], s.b[j][kk], acc[mi][j]);
+        }
+      }
+    }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int NB, int NC>
+__device__ __forceinline__ void stream_clear(f32x16 (&acc)[NB][NC]) {
+#pragma unroll
+  for (int mi = 0; mi < NB; ++mi)
+#pragma unroll
+    for (int j = 0; j < NC; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mi][j][r] = 0.f;
+}
+
+// acc += k-steps [kt0, kt1) of one block, D slabs in flight.
+template <bool FP8, int NB, int NC, int D>
+__device__ __forceinline__ void stream_range(f32x16 (&acc)[NB][NC], rsrc_t a, const uint32_t (&a_off)[NB], rsrc_t b,
+                                             uint32_t lane16, int kt0, int kt1, int nb) {
+  if (kt0 >= kt1) return;
+  StreamSlab<NB, NC> s[D];
+#pragma unroll
+  for (int i = 0; i < D; ++i)
+    if (i == 0 || kt0 + i < kt1) stream_load<FP8>(s[i], a, a_off, b, lane16, kt0 + i, nb);
+  int kt = kt0;
+  for (; kt + 2 * D <= kt1; kt += D) {
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      stream_multiply<FP8>(s[i], acc, nb);
+      stream_load<FP8>(s[i], a, a_off, b, lane16, kt + D + i, nb);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < D; ++i)
+    if (kt + i < kt1) {
+      stream_multiply<FP8>(s[i], acc, nb);
+      if (kt + D + i < kt1) stream_load<FP8>(s[i], a, a_off, b, lane16, kt + D + i, nb);
+    }
+#pragma unroll
+  for (int i = 0; i < D - 1; ++i)
+    if (kt + D + i < kt1) stream_multiply<FP8>(s[i], acc, nb);
+}
+
+// Token of a layout row (perm holds pair ids; clamped, so that a corrupt table stays inside x).
+__device__ __forceinline__ int stream_pair(const StreamArgs &g, int row) {
+  const int p = g.perm[row];
+  return min(max(p, 0), g.T * g.k - 1);
+}
+
+// ------------------------------------------------------------------------------------------------
+// GEMM-1: one workgroup per (32 h columns = one wave column of the packed tile, local expert).  Wave w of NW takes the
+// k-steps [w KT / NW, (w + 1) KT / NW), D of them in flight; NB = 32-row blocks per pass (an expert with more rows takes
+// another pass over its weights, which then come from the caches).
+// ------------------------------------------------------------------------------------------------
+template <bool FP8, int NB, int NW, int D>
+__global__ __launch_bounds__(NW * 64, 2) void stream_gemm1_kernel(const StreamArgs g) {
+  typedef typename StreamElt<FP8>::type elt_t;
+  __shared__ float red[NW][2][32][32];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l31 = lane & 31, khalf = lane >> 5;
+  const int c = blockIdx.x, le = blockIdx.y;
+  if (c == 0 && le == 0 && tid == 0) *g.error = 0;
+  const int base = g.offsets[g.e_lo];
+  const int start = min(max(g.offsets[g.e_lo + le] - base, 0), g.P_cap);
+  const int rows_all = min(max(g.offsets[g.e_lo + le + 1] - base, 0), g.P_cap) - start;
+  if (rows_all <= 0) return;  // whole workgroup
+  const int kt0 = w * g.n_ktiles / NW, kt1 = (w + 1) * g.n_ktiles / NW;
+  const rsrc_t b = stream_rsrc(static_cast<const unsigned char *>(g.Bp) +
+                                   ((size_t)(le * g.n_ntiles + (c >> 2)) * g.n_ktiles) * kTileBytes + (c & 3) * 8192,
+                               g.n_ktiles * kTileBytes - (c & 3) * 8192);
+  const rsrc_t a = stream_rsrc(g.A, (uint32_t)g.T * g.K * sizeof(elt_t));
+  for (int m0 = 0; m0 < rows_all; m0 += NB * 32) {
+    const int rows = min(NB * 32, rows_all - m0);
+    const int nb = (rows + 31) >> 5;
+    uint32_t a_off[NB];
+#pragma unroll
+    for (int mi = 0; mi < NB; ++mi) {
+      const int r = start + m0 + min(mi * 32 + l31, rows - 1);
+      a_off[mi] = (uint32_t)(stream_pair(g, base + r) / g.k) * g.K * sizeof(elt_t) + khalf * 16;
+    }
+    f32x16 acc[NB][2];
+    stream_clear(acc);
+    stream_range<FP8, NB, 2, D>(acc, a, a_off, b, lane * 16, kt0, kt1, nb);
+    // the waves' parts of one 32-row block at a time: rows that exist only
+#pragma unroll
+    for (int mi = 0; mi < NB; ++mi) {
+      if (mi >= nb) break;  // (uniform)
+      const int live = min(32, rows - mi * 32);
+      if (mi > 0 || m0 > 0) __syncthreads();
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int rl = (r >> 2) * 8 + khalf * 4 + (r & 3);
+        if (rl < live) {
+          red[w][0][rl][l31] = acc[mi][0][r];
+          red[w][1][rl][l31] = acc[mi][1][r];
+        }
+      }
+      __syncthreads();
+      for (int i = tid; i < live * 32; i += NW * 64) {
+        const int rl = i >> 5, cl = i & 31, col = c * 32 + cl;
+        float gv = 0.f, uv = 0.f;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+          gv += red[q][0][rl][cl];
+          uv += red[q][1][rl][cl];
+        }
+        if (col >= g.N) continue;
+        const size_t row = (size_t)(start + m0 + mi * 32 + rl);
+        if constexpr (FP8) {
+          const float sx = g.a_scale[stream_pair(g, base + (int)row) / g.k];
+          const float *bs = g.b_scale + (size_t)le * 2 * g.N;
+          gv *= sx * bs[col];
+          uv *= sx * bs[g.N + col];
+          static_cast<uint8_t *>(g.out)[row * g.N + col] =
+              to_e4m3((gv * __builtin_amdgcn_rcpf(1.0f + __expf(-gv))) * uv * __builtin_amdgcn_rcpf(g.h_scale[le]));
+        } else {
+          static_cast<bf16_t *>(g.out)[row * g.N + col] =
+              (bf16_t)((gv * __builtin_amdgcn_rcpf(1.0f + __expf(-gv))) * uv);
+        }
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// GEMM-2 with Combine: one workgroup per strip of 32 output columns (and per group of the work, see below).  The k-steps
+// of all busy experts of the strip form one list, cut into equal runs over the waves (and groups).  When a wave leaves an
+// expert it adds weight * sum to its own fp32 row of each token in the LDS; at the end the waves' rows are added in wave order and written once: tokens without
+// a local slot come out as zeros, and no row of o ever exists.  groups > 1 (strips too few to pull the weights at the
+// chip's rate): the groups' sums go to partial[group] and stream_reduce_kernel adds them in group order.
+// ------------------------------------------------------------------------------------------------
+// LDS: the waves' token rows | token and weight of every local row | the busy list
+constexpr int kStreamPasses = 2;  // passes an expert can need: 32 NB rows each, at most kStreamTokens rows
+constexpr size_t stream2_lds_bytes(int T, int P_cap, int E_loc) {
+  return (size_t)kStream2Waves * T * 32 * 4 + (size_t)kStreamPasses * E_loc * 16 + (size_t)P_cap * 8 + 16;
+}
+
+template <bool FP8, int NB, int D>
+__global__ __launch_bounds__(kStream2Waves * 64, 2) void stream_gemm2_kernel(const StreamArgs g) {
+  typedef typename StreamElt<FP8>::type elt_t;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  float *ysum = reinterpret_cast<float *>(smem);                                // [waves][T][32]
+  int4 *seg = reinterpret_cast<int4 *>(ysum + kStream2Waves * g.T * 32);        // (expert, first row, rows, -)
+  int *row_tok = reinterpret_cast<int *>(seg + kStreamPasses * g.E_loc);        // [P_cap]
+  float *row_w = reinterpret_cast<float *>(row_tok + g.P_cap);                  // [P_cap]
+  int *n_seg_s = reinterpret_cast<int *>(row_w + g.P_cap);
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l31 = lane & 31, khalf = lane >> 5;
+  const int c = blockIdx.x;
+  const int base = g.offsets[g.e_lo];
+  const int P = min(max(g.offsets[g.e_lo + g.E_loc] - base, 0), g.P_cap);
+  float *mine = ysum + (size_t)w * g.T * 32;
+  if (w == 0) {  // busy experts in order; one with more than 32 NB rows appears once per pass
+    int n = 0;
+    for (int e0 = 0; e0 < g.E_loc; e0 += 64) {
+      const int le = e0 + lane;
+      int start = 0, rows = 0;
+      if (le < g.E_loc) {
+        start = min(max(g.offsets[g.e_lo + le] - base, 0), P);
+        rows = min(max(min(max(g.offsets[g.e_lo + le + 1] - base, 0), P) - start, 0), kStreamPasses * NB * 32);
+      }
+      const int passes = (rows + NB * 32 - 1) / (NB * 32);
+      const int inc = wave_inclusive_scan(passes);
+      for (int q = 0; q < passes; ++q)
+        seg[n + inc - passes + q] = make_int4(le, start + q * NB * 32, min(NB * 32, rows - q * NB * 32), 0);
+      n += __builtin_amdgcn_readlane(inc, 63);
+    }
+    if (lane == 0) *n_seg_s = n;
+  }
+  for (int r = tid; r < P; r += kStream2Waves * 64) {
+    const int p = stream_pair(g, base + r);
+    row_tok[r] = p / g.k;
+    row_w[r] = g.topk_w[p];
+  }
+  for (int i = lane; i < g.T * 32; i += 64) mine[i] = 0.f;
+  __syncthreads();
+  const int KT = g.n_ktiles;
+  const long long total = (long long)__builtin_amdgcn_readfirstlane(*n_seg_s) * KT;
+  const int parts = kStream2Waves * gridDim.y, part = blockIdx.y * kStream2Waves + w;
+  const int s0 = __builtin_amdgcn_readfirstlane((int)(total * part / parts));
+  const int s1 = __builtin_amdgcn_readfirstlane((int)(total * (part + 1) / parts));
+
+  const rsrc_t a = stream_rsrc(g.A, (uint32_t)P * g.K * sizeof(elt_t));
+  for (int st = s0; st < s1;) {
+    const int sg = st / KT, kt0 = st - sg * KT, kt1 = min(KT, kt0 + s1 - st);
+    st += kt1 - kt0;
+    const int4 v = seg[sg];
+    const int le = __builtin_amdgcn_readfirstlane(v.x), start = __builtin_amdgcn_readfirstlane(v.y);
+    const int rows = __builtin_amdgcn_readfirstlane(v.z), nb = (rows + 31) >> 5;
+    uint32_t a_off[NB];
+#pragma unroll
+    for (int mi = 0; mi < NB; ++mi)
+      a_off[mi] = (uint32_t)(start + min(mi * 32 + l31, rows - 1)) * g.K * sizeof(elt_t) + khalf * 16;
+    const rsrc_t b = stream_rsrc(static_cast<const unsigned char *>(g.Bp) +
+                                     ((size_t)(le * g.n_ntiles + (c >> 3)) * KT) * kTileBytes + (c & 7) * 4096,
+                                 KT * kTileBytes - (c & 7) * 4096);
+    float cs = 1.f;  // FP8: scale of the expert's h times the scale of this lane's column
+    if constexpr (FP8) cs = g.h_scale[le] * g.b_scale[(size_t)le * g.N + min(c * 32 + l31, g.N - 1)];
+    f32x16 acc[NB][1];
+    stream_clear(acc);
+    stream_range<FP8, NB, 1, D>(acc, a, a_off, b, lane * 16, kt0, kt1, nb);
+    // weight * sum to this wave's token rows (the rows of an expert are distinct tokens: all reads, then all writes)
+#pragma unroll
+    for (int mi = 0; mi < NB; ++mi) {
+      if (NB > 1 && mi >= nb) break;
+      int at[16];
+      float sum[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int rl = min(mi * 32 + (r >> 2) * 8 + khalf * 4 + (r & 3), rows - 1);
+        at[r] = row_tok[start + rl] * 32 + l31;
+        sum[r] = fmaf(FP8 ? acc[mi][0][r] * cs : acc[mi][0][r], row_w[start + rl], mine[at[r]]);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (mi * 32 + (r >> 2) * 8 + khalf * 4 + (r & 3) < rows) mine[at[r]] = sum[r];
+    }
+  }
+  __syncthreads();
+  const int tot = g.T * 8;  // four columns per thread
+  for (int i = tid; i < tot; i += kStream2Waves * 64) {
+    const int t = i >> 3, col = c * 32 + (i & 7) * 4;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < kStream2Waves; ++q) {
+      const f32x4 o = *reinterpret_cast<const f32x4 *>(ysum + ((size_t)q * g.T + t) * 32 + (i & 7) * 4);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] += o[u];
+    }
+    if (col >= g.N) continue;
+    if (gridDim.y == 1) {
+      bf16x4 o;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) o[u] = (bf16_t)v[u];
+      *reinterpret_cast<bf16x4 *>(static_cast<bf16_t *>(g.out) + (size_t)t * g.N + col) = o;
+    } else {
+      *reinterpret_cast<f32x4 *>(static_cast<float *>(g.out) + ((size_t)blockIdx.y * g.T + t) * g.N + col) = v;
+    }
+  }
+}
+
+// y = partial[0] + partial[1] + ... in that order, rounded once.
+__global__ __launch_bounds__(256) void stream_reduce_kernel(const float *__restrict__ partial, bf16_t *__restrict__ y,
+                                                            int n4, int groups) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n4) return;
+  f32x4 v = reinterpret_cast<const f32x4 *>(partial)[i];
+  for (int q = 1; q < groups; ++q) {
+    const f32x4 o = reinterpret_cast<const f32x4 *>(partial)[(size_t)q * n4 + i];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] += o[u];
+  }
+  bf16x4 o;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) o[u] = (bf16_t)v[u];
+  reinterpret_cast<bf16x4 *>(y)[i] = o;
+}
+
+}  // namespace moe355
