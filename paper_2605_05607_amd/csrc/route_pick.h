@@ -26,10 +26,38 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   return step(step(a, b), step(c, d));
 }
 
-// The k picks of one token whose logits sit in registers, lane l owning experts [l * PER, l * PER + PER) (val = logit,
-// key = ordered_key(logit), 0 for experts past E).  Ties resolve to the lower expert index because a lane scans its
-// run upwards with a strict comparison and, across lanes, the lowest lane holding the wave maximum wins.  Lanes
-// 0..k-1 write the picks (slot order = pick order) and their softmax weights renormalised over the picks.
+// The largest key of a row in registers, lane l owning experts [l * PER, l * PER + PER): returns its expert (the lowest on
+// ties: a lane scans its run upwards with a strict comparison and, across lanes, the lowest lane that holds the maximum
+// wins), its value in `v`, and clears its key.  The same in every lane.
+template <int PER>
+__device__ __forceinline__ int pick_largest(const float (&val)[PER], uint32_t (&key)[PER], int E, float &v) {
+  const int lane = lane_id();
+  uint32_t bk = 0;
+  int bs = 0;
+  float bv = 0.f;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    if (key[i] > bk) {
+      bk = key[i];
+      bs = i;
+      bv = val[i];
+    }
+  }
+  const uint32_t top = wave_max_u32(bk);
+  const unsigned long long holders = __ballot(bk == top);
+  const int win = holders ? __builtin_ctzll(holders) : 0;
+  const int slot = __builtin_amdgcn_readlane(bs, win);
+  v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bv), win));
+  const int e = win * PER + slot;
+#pragma unroll
+  for (int i = 0; i < PER; ++i)
+    if (lane == win && i == slot) key[i] = 0u;  // picked
+  // k <= E, so an unpicked expert always exists; the clamp only guards against non-finite input
+  return e < E ? e : 0;
+}
+
+// The k picks of one token whose logits sit in registers (val = logit, key = ordered_key(logit), 0 for experts past E).
+// Lanes 0..k-1 write the picks (slot order = pick order) and their softmax weights renormalised over the picks.
 template <int PER>
 __device__ __forceinline__ void route_pick_registers(float (&val)[PER], uint32_t (&key)[PER], int E, int k, int t,
                                                      int32_t *__restrict__ topk_idx, float *__restrict__ topk_w) {
@@ -37,33 +65,13 @@ __device__ __forceinline__ void route_pick_registers(float (&val)[PER], uint32_t
   int my_e = 0;
   float my_x = 0.f, first = 0.f, sum = 0.f;
   for (int j = 0; j < k; ++j) {
-    uint32_t bk = 0;
-    int bs = 0;
-    float bv = 0.f;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      if (key[i] > bk) {
-        bk = key[i];
-        bs = i;
-        bv = val[i];
-      }
-    }
-    const uint32_t top = wave_max_u32(bk);
-    const unsigned long long holders = __ballot(bk == top);
-    const int win = holders ? __builtin_ctzll(holders) : 0;
-    const int slot = __builtin_amdgcn_readlane(bs, win);
-    const float v_best = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bv), win));
-    // k <= E, so an unpicked expert always exists; the clamp only guards against non-finite input
-    int e_best = win * PER + slot;
-    e_best = e_best < E ? e_best : 0;
-#pragma unroll
-    for (int i = 0; i < PER; ++i)
-      if (lane == win && i == slot) key[i] = 0u;  // picked
-    if (j == 0) first = v_best;                    // the largest logit: softmax shift
-    const float x = expf(v_best - first);
+    float v = 0.f;
+    const int e = pick_largest<PER>(val, key, E, v);
+    if (j == 0) first = v;                         // the largest logit: softmax shift
+    const float x = expf(v - first);
     sum += x;                                      // slot order
     if (lane == j) {
-      my_e = e_best;
+      my_e = e;
       my_x = x;
     }
   }
