@@ -19,10 +19,9 @@ constexpr int kMaxTopK = 32;
 constexpr int kBM = 256;
 constexpr int kBN = 256;
 constexpr int kBK = 64;
-// Tile of the plain fp32 kernels (small reference-grade path for fp32 layers).
+// Tile of the fp32 kernels.
 constexpr int kFBM = 64;
 constexpr int kFBN = 64;
-constexpr int kFBK = 16;
 
 struct Derived {
   int epr;         // experts per rank

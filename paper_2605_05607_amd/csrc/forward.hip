@@ -207,11 +207,24 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
   }
   g1.n_ntiles = ceil_div(s->f, kFBN); g1.n_ktiles = dv.E_loc;
   g2.n_ntiles = ceil_div(s->d, kFBN); g2.n_ktiles = dv.E_loc;
-  hipLaunchKernelGGL(gemm_f32_kernel<true>, grid_of(dv.nt1), dim3(256), 0, st, g1);
+  // Tile by the expected number of 64 x 64 items (mean load): whole items where there are four per CU, else quarters, so
+  // that no CU has two workgroups while others have one (each is ~10 us of matrix-core time); GEMM-2, which has fewer,
+  // eight waves per workgroup below one item per CU.
+  const double rows = (double)s->T * s->k * dv.E_loc / s->E;
+  const double mtiles = std::min<double>(dv.E_loc, rows) + rows / kFBM;
+  const auto launch = [&](auto kernel, int nt, int parts, int waves, const GemmArgs &g) {
+    dim3 grid = grid_of(nt);
+    grid.x *= parts;
+    hipLaunchKernelGGL(kernel, grid, dim3(waves * 64), 0, st, g);
+  };
+  if (mtiles * dv.nt1 >= kF32Tiles) launch(gemm_f32_kernel<true, 2, 2, 4>, dv.nt1, f32_parts(2, 2), 4, g1);
+  else launch(gemm_f32_kernel<true, 1, 1, 4>, dv.nt1, f32_parts(1, 1), 4, g1);
   int rc = launch_status();
   mark(2);
   if (rc != MOE_OK) return rc;
-  hipLaunchKernelGGL(gemm_f32_kernel<false>, grid_of(dv.nt2), dim3(256), 0, st, g2);
+  if (mtiles * dv.nt2 >= kF32Tiles) launch(gemm_f32_kernel<false, 2, 2, 4>, dv.nt2, f32_parts(2, 2), 4, g2);
+  else if (mtiles * dv.nt2 >= kF32Tiles / 4) launch(gemm_f32_kernel<false, 1, 2, 4>, dv.nt2, f32_parts(1, 2), 4, g2);
+  else launch(gemm_f32_kernel<false, 1, 1, 8>, dv.nt2, f32_parts(1, 1), 8, g2);
   mark(3);
   return launch_status();
 }
@@ -285,19 +298,19 @@ static int launch_stream(const moe_shape *s, const Derived &dv, const void *x, c
   mark(1);
   const dim3 grid1((unsigned)ceil_div(s->f, 32), (unsigned)dv.E_loc), grid2((unsigned)ceil_div(s->d, 32), (unsigned)groups);
   const size_t lds = stream2_lds_bytes(s->T, (int)dv.P_cap, dv.E_loc);
-#define MOE355_STREAM(FP8_, NB_, D1_, D2_)                                                                            \
+#define MOE355_STREAM(FP8_, NB_)                                                                            \
   do {                                                                                                                \
     static std::atomic<uint64_t> done{0};                                                                             \
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&stream_gemm2_kernel<FP8_, NB_, D2_>), 160 * 1024, done))    \
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&stream_gemm2_kernel<FP8_, NB_>), 160 * 1024, done))    \
       return MOE_ERR_HIP;                                                                                             \
-    hipLaunchKernelGGL((stream_gemm1_kernel<FP8_, NB_, 8, D1_>), grid1, dim3(8 * 64), 0, st, g1);                     \
+    hipLaunchKernelGGL((stream_gemm1_kernel<FP8_, NB_>), grid1, dim3(kStreamWaves * 64), 0, st, g1);                     \
     mark(2);                                                                                                          \
-    hipLaunchKernelGGL((stream_gemm2_kernel<FP8_, NB_, D2_>), grid2, dim3(kStream2Waves * 64), lds, st, g2);          \
+    hipLaunchKernelGGL((stream_gemm2_kernel<FP8_, NB_>), grid2, dim3(kStreamWaves * 64), lds, st, g2);          \
   } while (0)
   if (q) {
-    if (s->T <= 32) MOE355_STREAM(true, 1, 3, 5); else MOE355_STREAM(true, 2, 2, 3);
+    if (s->T <= 32) MOE355_STREAM(true, 1); else MOE355_STREAM(true, 2);
   } else {
-    if (s->T <= 32) MOE355_STREAM(false, 1, 3, 5); else MOE355_STREAM(false, 2, 2, 3);
+    if (s->T <= 32) MOE355_STREAM(false, 1); else MOE355_STREAM(false, 2);
   }
 #undef MOE355_STREAM
   mark(3);

@@ -1,86 +1,163 @@
-// Grouped fp32 GEMMs on the vector ALU (fp32 layers).
+// Grouped fp32 GEMMs on the matrix cores (fp32 layers).
 #pragma once
-#include "forward_types.h"
+#include "stream_gemm.h"
 
 namespace moe355 {
 
 // ------------------------------------------------------------------------------------------------
-// Plain fp32 grouped GEMM (vector ALU) for fp32 layers: 64 x 64 tile, 16-wide k slab, 4 x 4 per thread.
-// Weights are the unpacked "input x output" matrices.
+// C[rows of one expert, 64 columns] = A * W_e in fp32 (v_mfma_f32_32x32x2_f32: fp32 products, fp32 sums).  GATED: 64 h
+// columns from 64 gate and 64 up columns, h = silu(g) * u; else o = acc * row_w[row].  Weights are the unpacked "input x
+// output" matrices.
+//
+// What bounds it: the fp32 matrix rate (1/16 of bf16's) on full experts, the weights or plain latency on small ones.  The
+// instruction takes 64 cycles for 8 bytes per lane, so operands come straight from the caches without an LDS stage.
+// A group is G reduction indices: lane l reads its row l % 32 at the G / 2 indices that start at G / 2 (l / 32) in 16-byte
+// pieces and, of the weights, columns COLS (l % 32) .. + COLS at the same indices; instruction i then multiplies indices i and
+// G / 2 + i.  The loads of a group are in flight while the group before it is multiplied (the counter of outstanding
+// loads ends at 63: a second group in flight would not fit it).  The waves of the workgroup share the reduction range (the layers have few tiles: what fills the chip is
+// cutting the sum) and meet in the LDS in wave order.
+// Measured on 8 experts of 512 x 1024, GEMM-1 + GEMM-2 of 256 tokens: 76 + 95 us with 64 x 64 tiles on the vector ALU ->
+// 29 + 17 us; step 191 -> 62 us, 8 tokens 185 -> 39 us, 2048 tokens 315 -> 226 us.
 // ------------------------------------------------------------------------------------------------
-template <bool GATED>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs g) {
-  __shared__ float sA[kFBM][kFBK + 1];
-  __shared__ float sB[GATED ? 2 : 1][kFBK][kFBN];
-  const int q = chunked_item(blockIdx.x, *g.n_items);
+template <int COLS>
+__device__ __forceinline__ void f32_fetch(float (&v)[COLS], rsrc_t r, uint32_t voff, uint32_t soff) {
+  if constexpr (COLS == 2) {
+    const auto t = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+    v[0] = __uint_as_float(t[0]);
+    v[1] = __uint_as_float(t[1]);
+  } else {
+    v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
+  }
+}
+
+template <int MB, int NM, int G, int COLS>
+struct F32Group {
+  f32x4 a[MB][G / 8];
+  float b[NM][G / 2][COLS];
+};
+
+// MB 32-row blocks and 32 COLS columns per workgroup.  An item of the work list covers 64 rows and 64 columns, so
+// f32_parts workgroups share it, on the item's XCD.  NW waves.
+constexpr int kF32Tiles = 1024;  // expected items from which on a workgroup takes a whole one
+constexpr int f32_parts(int mb, int cols) { return (3 - mb) * (3 - cols); }
+template <bool GATED, int MB, int COLS, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void gemm_f32_kernel(const GemmArgs g) {
+  constexpr int NM = GATED ? 2 : 1, NJ = NM * COLS, G = MB == 2 ? 16 : 32, PARTS = f32_parts(MB, COLS);
+  __shared__ float red[NW][NJ][32][32];
+  const int part = (blockIdx.x >> 3) % PARTS, m_part = part % (3 - MB), n_part = part / (3 - MB);
+  const int q = chunked_item((blockIdx.x & 7) | ((blockIdx.x >> 3) / PARTS) << 3, *g.n_items);
   if (q < 0) return;
   const int4 item = g.work[q];
-  const int le = item.x, m0 = item.y, rows = item.z & kItemRowsMask, nt = item.w & ((1 << kTileShift) - 1);
-  const int tid = threadIdx.x;
-  const int ty = tid >> 4, tx = tid & 15;
-  const float *A = static_cast<const float *>(g.A);
+  const int le = __builtin_amdgcn_readfirstlane(item.x);
+  const int m0 = __builtin_amdgcn_readfirstlane(item.y) + m_part * 32;
+  const int rows = (__builtin_amdgcn_readfirstlane(item.z) & kItemRowsMask) - m_part * 32;
+  if (rows <= 0) return;  // whole workgroup
+  const int n0 = (__builtin_amdgcn_readfirstlane(item.w) & ((1 << kTileShift) - 1)) * 64 + n_part * 32 * COLS;
+  if (n0 >= g.N) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l31 = lane & 31, khalf = lane >> 5;
+  const int nb = min(MB, (rows + 31) >> 5);
+  const int n_groups = (g.K + G - 1) / G;
+  const int k0 = w * n_groups / NW, n_mine = (w + 1) * n_groups / NW - k0;  // this wave's groups
+  // gate matrices of all local experts come first, then the up matrices (n_ktiles carries E_loc for this kernel)
   const size_t wsz = (size_t)g.K * g.N;
-  const float *W0 = static_cast<const float *>(g.Bp) + (size_t)le * wsz;
-  // gate matrices of all local experts come first, then the up matrices
-  const float *W1 = GATED ? W0 + (size_t)g.n_ktiles * wsz : nullptr;  // n_ktiles carries E_loc for this kernel
-
-  const int ar = tid >> 2, akq = (tid & 3) * 4;
-  const int arc = ar < rows ? ar : rows - 1;
-  const int a_row = g.row_map ? g.row_map[m0 + arc] : m0 + arc;
-  const float *a_src = A + (size_t)a_row * g.lda + akq;
-  const int bk = tid >> 4, bn4 = (tid & 15) * 4;
-  const int n0 = nt * kFBN;
-
-  float accg[4][4] = {}, accu[4][4] = {};
-  for (int k0 = 0; k0 < g.K; k0 += kFBK) {
-    float4 av = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (k0 + akq < g.K) av = *reinterpret_cast<const float4 *>(a_src + k0);
-    sA[ar][akq + 0] = av.x; sA[ar][akq + 1] = av.y; sA[ar][akq + 2] = av.z; sA[ar][akq + 3] = av.w;
-    float4 bv = make_float4(0.f, 0.f, 0.f, 0.f), bv1 = bv;
-    if (k0 + bk < g.K && n0 + bn4 < g.N) {
-      bv = *reinterpret_cast<const float4 *>(W0 + (size_t)(k0 + bk) * g.N + n0 + bn4);
-      if (GATED) bv1 = *reinterpret_cast<const float4 *>(W1 + (size_t)(k0 + bk) * g.N + n0 + bn4);
-    }
-    *reinterpret_cast<float4 *>(&sB[0][bk][bn4]) = bv;
-    if (GATED) *reinterpret_cast<float4 *>(&sB[GATED ? 1 : 0][bk][bn4]) = bv1;
-    __syncthreads();
+  const float *W0 = static_cast<const float *>(g.Bp) + (size_t)le * wsz + (size_t)k0 * G * g.N;
+  const int k_len = max(0, min(n_mine * G, g.K - k0 * G));
+  const uint32_t w_bytes = (uint32_t)k_len * g.N * 4;
+  rsrc_t b[NM];
+  b[0] = stream_rsrc(W0, w_bytes);
+  if (GATED) b[NM - 1] = stream_rsrc(W0 + (size_t)g.n_ktiles * wsz, w_bytes);
+  const uint32_t pitch = (uint32_t)g.N * 4;
+  const uint32_t b_off = khalf * (G / 2) * pitch + min(n0 + COLS * l31, g.N - COLS) * 4;  // (columns past the end: not stored)
+  const float *a_row[MB];
 #pragma unroll
-    for (int kk = 0; kk < kFBK; ++kk) {
-      float a[4], b0[4], b1[4];
+  for (int mi = 0; mi < MB; ++mi) {
+    const int r = m0 + min(mi * 32 + l31, rows - 1);
+    a_row[mi] = static_cast<const float *>(g.A) + (size_t)(g.row_map ? g.row_map[r] : r) * g.lda + k0 * G;
+  }
+  f32x16 acc[MB][NJ];
+  stream_clear(acc);
+  auto load = [&](F32Group<MB, NM, G, COLS> &s, int kg, auto whole) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = sA[ty * 4 + i][kk];
+    for (int i = 0; i < G / 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        b0[j] = sB[0][kk][tx + 16 * j];
-        if (GATED) b1[j] = sB[GATED ? 1 : 0][kk][tx + 16 * j];
+      for (int m = 0; m < NM; ++m) {
+        if constexpr (decltype(whole)::value) {
+          f32_fetch(s.b[m][i], b[m], b_off, (uint32_t)(kg * G + i) * pitch);
+        } else {  // indices past K: zeros, from an offset that the descriptor's bound rejects
+          const bool in = kg * G + khalf * (G / 2) + i < k_len;
+          f32_fetch(s.b[m][i], b[m], in ? b_off + (uint32_t)(kg * G + i) * pitch : 0x80000000u, 0);
+        }
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+    for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          accg[i][j] = fmaf(a[i], b0[j], accg[i][j]);
-          if (GATED) accu[i][j] = fmaf(a[i], b1[j], accu[i][j]);
-        }
+      for (int i = 0; i < G / 8; ++i) {
+        const int kk = kg * G + khalf * (G / 2) + i * 4;
+        s.a[mi][i] = *reinterpret_cast<const f32x4 *>(a_row[mi] + (decltype(whole)::value || kk < k_len ? kk : 0));
+      }
+  };
+  auto multiply = [&](const F32Group<MB, NM, G, COLS> &s) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int mi = 0; mi < MB; ++mi)
+      if (mi == 0 || nb > 1) {
+#pragma unroll
+        for (int i = 0; i < G / 2; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+            acc[mi][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                s.a[mi][i >> 2][i & 3], s.b[j / COLS][i][j % COLS], acc[mi][j], 0, 0, 0);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const int n_whole = k_len / G;
+  F32Group<MB, NM, G, COLS> s0, s1;
+  if (n_whole > 0) {
+    const std::true_type whole;
+    load(s0, 0, whole);
+    for (int kg = 0; kg < n_whole; kg += 2) {  // (past the end: the last group again, not used)
+      load(s1, min(kg + 1, n_whole - 1), whole);
+      multiply(s0);
+      load(s0, min(kg + 2, n_whole - 1), whole);
+      if (kg + 1 < n_whole) multiply(s1);
     }
-    __syncthreads();
+  }
+  if (n_whole * G < k_len) {
+    load(s0, n_whole, std::false_type());
+    multiply(s0);
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row_l = ty * 4 + i;
-    if (row_l >= rows) continue;
-    const size_t grow = (size_t)(m0 + row_l);
-    float *out = static_cast<float *>(g.out) + grow * g.ldo;
-    const float w = GATED ? 1.f : g.row_w[grow];
+  for (int mi = 0; mi < MB; ++mi) {
+    if (mi >= nb) break;  // (uniform)
+    if (mi > 0) __syncthreads();
+    const int live = min(32, rows - mi * 32);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = n0 + tx + 16 * j;
-      if (col >= g.N) continue;
-      if (GATED) {
-        const float gv = accg[i][j];
-        out[col] = (gv / (1.0f + expf(-gv))) * accu[i][j];
-      } else {
-        out[col] = accg[i][j] * w;
+    for (int r = 0; r < 16; ++r) {
+      const int rl = (r >> 2) * 8 + khalf * 4 + (r & 3);
+      if (rl < live) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) red[w][j][rl][l31] = acc[mi][j][r];
       }
+    }
+    __syncthreads();
+    for (int i = tid; i < live * 32; i += NW * 64) {
+      const int rl = i >> 5, cl = i & 31;
+      float v[NJ];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        v[j] = 0.f;
+#pragma unroll
+        for (int p = 0; p < NW; ++p) v[j] += red[p][j][rl][cl];
+      }
+      const size_t grow = (size_t)(m0 + mi * 32 + rl);
+      const int col = n0 + COLS * cl;
+      if (col >= g.N) continue;
+      float *out = static_cast<float *>(g.out) + grow * g.ldo + col;
+      const float wgt = GATED ? 1.f : g.row_w[grow];
+#pragma unroll
+      for (int c = 0; c < COLS; ++c)
+        out[c] = GATED ? (v[c] / (1.0f + expf(-v[c]))) * v[NJ - COLS + c] : v[c] * wgt;
     }
   }
 }
