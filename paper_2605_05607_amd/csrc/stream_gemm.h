@@ -17,7 +17,7 @@ namespace moe355 {
 
 constexpr int kStreamTokens = 128;   // largest batch (GEMM-2 keeps one fp32 row of 32 columns per token and wave)
 constexpr int kStreamExperts = 512;  // most local experts (GEMM-2 lists the busy ones in the LDS)
-constexpr int kStream2Waves = 8;
+constexpr int kStreamWaves = 8;
 
 struct StreamArgs {
   const void *A;    // GEMM-1: x [T, K] (bf16, or codes); GEMM-2: h [rows, K]
@@ -56,11 +56,11 @@ __device__ __forceinline__ bf16x8 stream_fetch_once(rsrc_t r, uint32_t voff, uin
 }
 
 // Loads of k-step kt.  b: the column block in tile 0 (lane * 16 is the lane's operand); a: the rows' matrix, a_off[mi]
-// this lane's row plus its half of the reduction chunk, in bytes.  Chunks past K meet zeros in the packed tile; what they
-// read is the following row, or zero past the end of the matrix (the descriptor's bound): finite either way.
-template <bool FP8, int NB, int NC>
+// this lane's row plus khalf * 16, in bytes; row_bytes: bytes of a row.  A chunk past the row's end meets zeros in the
+// packed tile and is read as zeros itself (an offset the descriptor's bound rejects), never from the next row.
+template <bool FP8, bool WHOLE, int NB, int NC>
 __device__ __forceinline__ void stream_load(StreamSlab<NB, NC> &s, rsrc_t a, const uint32_t (&a_off)[NB], rsrc_t b,
-                                            uint32_t lane16, int kt, int nb) {
+                                            uint32_t lane16, int kt, int row_bytes, int khalf16) {
 #pragma unroll
   for (int j = 0; j < NC; ++j)
 #pragma unroll
@@ -68,27 +68,26 @@ __device__ __forceinline__ void stream_load(StreamSlab<NB, NC> &s, rsrc_t a, con
       s.b[j][kk] = stream_fetch_once(b, lane16 + kk * 1024, kt * kTileBytes + j * 4096);
 #pragma unroll
   for (int mi = 0; mi < NB; ++mi)
-    if (NB == 1 || mi < nb) {
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) s.a[mi][kk] = stream_fetch(a, a_off[mi] + kk * 32, kt * 128);
+    for (int kk = 0; kk < 4; ++kk) {
+      const bool in = WHOLE || kt * 128 + kk * 32 + khalf16 < row_bytes;
+      s.a[mi][kk] = stream_fetch(a, in ? a_off[mi] + kk * 32 : 0x80000000u, kt * 128);
     }
 }
 
 template <bool FP8, int NB, int NC>
-__device__ __forceinline__ void stream_multiply(const StreamSlab<NB, NC> &s, f32x16 (&acc)[NB][NC], int nb) {
+__device__ __forceinline__ void stream_multiply(const StreamSlab<NB, NC> &s, f32x16 (&acc)[NB][NC]) {
   __builtin_amdgcn_sched_barrier(0);  // one slab after the other: its products, then its reload
 #pragma unroll
   for (int mi = 0; mi < NB; ++mi)
-    if (NB == 1 || mi < nb) {
 #pragma unroll
-      for (int j = 0; j < NC; ++j) {
-        if constexpr (FP8) {
-          acc[mi][j] = mfma_fp8_pair(s.a[mi][0], s.a[mi][1], s.b[j][0], s.b[j][1], acc[mi][j]);
-          acc[mi][j] = mfma_fp8_pair(s.a[mi][2], s.a[mi][3], s.b[j][2], s.b[j][3], acc[mi][j]);
-        } else {
+    for (int j = 0; j < NC; ++j) {
+      if constexpr (FP8) {
+        acc[mi][j] = mfma_fp8_pair(s.a[mi][0], s.a[mi][1], s.b[j][0], s.b[j][1], acc[mi][j]);
+        acc[mi][j] = mfma_fp8_pair(s.a[mi][2], s.a[mi][3], s.b[j][2], s.b[j][3], acc[mi][j]);
+      } else {
 #pragma unroll
-          for (int kk = 0; kk < 4; ++kk) acc[mi][j] = mfma_bf16(s.a[mi][kk], s.b[j][kk], acc[mi][j]);
-        }
+        for (int kk = 0; kk < 4; ++kk) acc[mi][j] = mfma_bf16(s.a[mi][kk], s.b[j][kk], acc[mi][j]);
       }
     }
   __builtin_amdgcn_sched_barrier(0);
@@ -107,29 +106,54 @@ __device__ __forceinline__ void stream_clear(f32x16 (&acc)[NB][NC]) {
 // acc += k-steps [kt0, kt1) of one block, D slabs in flight.
 template <bool FP8, int NB, int NC, int D>
 __device__ __forceinline__ void stream_range(f32x16 (&acc)[NB][NC], rsrc_t a, const uint32_t (&a_off)[NB], rsrc_t b,
-                                             uint32_t lane16, int kt0, int kt1, int nb) {
+                                             uint32_t lane16, int kt0, int kt1, int row_bytes, int khalf16) {
   if (kt0 >= kt1) return;
   StreamSlab<NB, NC> s[D];
+  if (kt1 * 128 > row_bytes) {  // the range ends with the row's last, partial k-step: that one on its own
+    --kt1;
+    stream_load<FP8, false>(s[0], a, a_off, b, lane16, kt1, row_bytes, khalf16);
+    stream_multiply<FP8>(s[0], acc);
+    if (kt0 == kt1) return;
+  }
 #pragma unroll
   for (int i = 0; i < D; ++i)
-    if (i == 0 || kt0 + i < kt1) stream_load<FP8>(s[i], a, a_off, b, lane16, kt0 + i, nb);
+    if (i == 0 || kt0 + i < kt1) stream_load<FP8, true>(s[i], a, a_off, b, lane16, kt0 + i, row_bytes, khalf16);
   int kt = kt0;
   for (; kt + 2 * D <= kt1; kt += D) {
 #pragma unroll
     for (int i = 0; i < D; ++i) {
-      stream_multiply<FP8>(s[i], acc, nb);
-      stream_load<FP8>(s[i], a, a_off, b, lane16, kt + D + i, nb);
+      stream_multiply<FP8>(s[i], acc);
+      stream_load<FP8, true>(s[i], a, a_off, b, lane16, kt + D + i, row_bytes, khalf16);
     }
   }
 #pragma unroll
   for (int i = 0; i < D; ++i)
     if (kt + i < kt1) {
-      stream_multiply<FP8>(s[i], acc, nb);
-      if (kt + D + i < kt1) stream_load<FP8>(s[i], a, a_off, b, lane16, kt + D + i, nb);
+      stream_multiply<FP8>(s[i], acc);
+      if (kt + D + i < kt1) stream_load<FP8, true>(s[i], a, a_off, b, lane16, kt + D + i, row_bytes, khalf16);
     }
 #pragma unroll
   for (int i = 0; i < D - 1; ++i)
-    if (kt + D + i < kt1) stream_multiply<FP8>(s[i], acc, nb);
+    if (kt + D + i < kt1) stream_multiply<FP8>(s[i], acc);
+}
+
+// The same for nb <= NB row blocks that hold rows: the usual single block runs the deeper pipeline D1 (its slabs are
+// smaller; also, loads that are only sometimes issued would make every wait a wait for all of them).
+template <bool FP8, int NB, int NC, int D1, int D2>
+__device__ __forceinline__ void stream_blocks(f32x16 (&acc)[NB][NC], rsrc_t a, const uint32_t (&a_off)[NB], rsrc_t b,
+                                              uint32_t lane16, int kt0, int kt1, int nb, int row_bytes, int khalf16) {
+  if constexpr (NB == 2) {
+    if (nb == 2) {
+      stream_range<FP8, 2, NC, D2>(acc, a, a_off, b, lane16, kt0, kt1, row_bytes, khalf16);
+      return;
+    }
+  }
+  f32x16 one[1][NC];
+  const uint32_t off[1] = {a_off[0]};
+  stream_clear(one);
+  stream_range<FP8, 1, NC, D1>(one, a, off, b, lane16, kt0, kt1, row_bytes, khalf16);
+#pragma unroll
+  for (int j = 0; j < NC; ++j) acc[0][j] = one[0][j];
 }
 
 // Token of a layout row (perm holds pair ids; clamped, so that a corrupt table stays inside x).
@@ -139,14 +163,14 @@ __device__ __forceinline__ int stream_pair(const StreamArgs &g, int row) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// GEMM-1: one workgroup per (32 h columns = one wave column of the packed tile, local expert).  Wave w of NW takes the
-// k-steps [w KT / NW, (w + 1) KT / NW), D of them in flight; NB = 32-row blocks per pass (an expert with more rows takes
+// GEMM-1: one workgroup per (32 h columns = one wave column of the packed tile, local expert).  Wave w of n takes the
+// k-steps [w KT / n, (w + 1) KT / n); NB = 32-row blocks per pass (an expert with more rows takes
 // another pass over its weights, which then come from the caches).
 // ------------------------------------------------------------------------------------------------
-template <bool FP8, int NB, int NW, int D>
-__global__ __launch_bounds__(NW * 64, 2) void stream_gemm1_kernel(const StreamArgs g) {
+template <bool FP8, int NB>
+__global__ __launch_bounds__(kStreamWaves * 64, 2) void stream_gemm1_kernel(const StreamArgs g) {
   typedef typename StreamElt<FP8>::type elt_t;
-  __shared__ float red[NW][2][32][32];
+  __shared__ float red[kStreamWaves][2][32][32];
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l31 = lane & 31, khalf = lane >> 5;
   const int c = blockIdx.x, le = blockIdx.y;
@@ -155,7 +179,7 @@ __global__ __launch_bounds__(NW * 64, 2) void stream_gemm1_kernel(const StreamAr
   const int start = min(max(g.offsets[g.e_lo + le] - base, 0), g.P_cap);
   const int rows_all = min(max(g.offsets[g.e_lo + le + 1] - base, 0), g.P_cap) - start;
   if (rows_all <= 0) return;  // whole workgroup
-  const int kt0 = w * g.n_ktiles / NW, kt1 = (w + 1) * g.n_ktiles / NW;
+  const int kt0 = w * g.n_ktiles / kStreamWaves, kt1 = (w + 1) * g.n_ktiles / kStreamWaves;
   const rsrc_t b = stream_rsrc(static_cast<const unsigned char *>(g.Bp) +
                                    ((size_t)(le * g.n_ntiles + (c >> 2)) * g.n_ktiles) * kTileBytes + (c & 3) * 8192,
                                g.n_ktiles * kTileBytes - (c & 3) * 8192);
@@ -171,7 +195,7 @@ __global__ __launch_bounds__(NW * 64, 2) void stream_gemm1_kernel(const StreamAr
     }
     f32x16 acc[NB][2];
     stream_clear(acc);
-    stream_range<FP8, NB, 2, D>(acc, a, a_off, b, lane * 16, kt0, kt1, nb);
+    stream_blocks<FP8, NB, 2, 3, 2>(acc, a, a_off, b, lane * 16, kt0, kt1, nb, g.K * (int)sizeof(elt_t), khalf * 16);
     // the waves' parts of one 32-row block at a time: rows that exist only
 #pragma unroll
     for (int mi = 0; mi < NB; ++mi) {
@@ -187,11 +211,11 @@ __global__ __launch_bounds__(NW * 64, 2) void stream_gemm1_kernel(const StreamAr
         }
       }
       __syncthreads();
-      for (int i = tid; i < live * 32; i += NW * 64) {
+      for (int i = tid; i < live * 32; i += kStreamWaves * 64) {
         const int rl = i >> 5, cl = i & 31, col = c * 32 + cl;
         float gv = 0.f, uv = 0.f;
 #pragma unroll
-        for (int q = 0; q < NW; ++q) {
+        for (int q = 0; q < kStreamWaves; ++q) {
           gv += red[q][0][rl][cl];
           uv += red[q][1][rl][cl];
         }
@@ -223,15 +247,15 @@ __global__ __launch_bounds__(NW * 64, 2) void stream_gemm1_kernel(const StreamAr
 // LDS: the waves' token rows | token and weight of every local row | the busy list
 constexpr int kStreamPasses = 2;  // passes an expert can need: 32 NB rows each, at most kStreamTokens rows
 constexpr size_t stream2_lds_bytes(int T, int P_cap, int E_loc) {
-  return (size_t)kStream2Waves * T * 32 * 4 + (size_t)kStreamPasses * E_loc * 16 + (size_t)P_cap * 8 + 16;
+  return (size_t)kStreamWaves * T * 32 * 4 + (size_t)kStreamPasses * E_loc * 16 + (size_t)P_cap * 8 + 16;
 }
 
-template <bool FP8, int NB, int D>
-__global__ __launch_bounds__(kStream2Waves * 64, 2) void stream_gemm2_kernel(const StreamArgs g) {
+template <bool FP8, int NB>
+__global__ __launch_bounds__(kStreamWaves * 64, 2) void stream_gemm2_kernel(const StreamArgs g) {
   typedef typename StreamElt<FP8>::type elt_t;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   float *ysum = reinterpret_cast<float *>(smem);                                // [waves][T][32]
-  int4 *seg = reinterpret_cast<int4 *>(ysum + kStream2Waves * g.T * 32);        // (expert, first row, rows, -)
+  int4 *seg = reinterpret_cast<int4 *>(ysum + kStreamWaves * g.T * 32);        // (expert, first row, rows, -)
   int *row_tok = reinterpret_cast<int *>(seg + kStreamPasses * g.E_loc);        // [P_cap]
   float *row_w = reinterpret_cast<float *>(row_tok + g.P_cap);                  // [P_cap]
   int *n_seg_s = reinterpret_cast<int *>(row_w + g.P_cap);
@@ -258,7 +282,7 @@ __global__ __launch_bounds__(kStream2Waves * 64, 2) void stream_gemm2_kernel(con
     }
     if (lane == 0) *n_seg_s = n;
   }
-  for (int r = tid; r < P; r += kStream2Waves * 64) {
+  for (int r = tid; r < P; r += kStreamWaves * 64) {
     const int p = stream_pair(g, base + r);
     row_tok[r] = p / g.k;
     row_w[r] = g.topk_w[p];
@@ -267,7 +291,7 @@ __global__ __launch_bounds__(kStream2Waves * 64, 2) void stream_gemm2_kernel(con
   __syncthreads();
   const int KT = g.n_ktiles;
   const long long total = (long long)__builtin_amdgcn_readfirstlane(*n_seg_s) * KT;
-  const int parts = kStream2Waves * gridDim.y, part = blockIdx.y * kStream2Waves + w;
+  const int parts = kStreamWaves * gridDim.y, part = blockIdx.y * kStreamWaves + w;
   const int s0 = __builtin_amdgcn_readfirstlane((int)(total * part / parts));
   const int s1 = __builtin_amdgcn_readfirstlane((int)(total * (part + 1) / parts));
 
@@ -289,7 +313,7 @@ __global__ __launch_bounds__(kStream2Waves * 64, 2) void stream_gemm2_kernel(con
     if constexpr (FP8) cs = g.h_scale[le] * g.b_scale[(size_t)le * g.N + min(c * 32 + l31, g.N - 1)];
     f32x16 acc[NB][1];
     stream_clear(acc);
-    stream_range<FP8, NB, 1, D>(acc, a, a_off, b, lane * 16, kt0, kt1, nb);
+    stream_blocks<FP8, NB, 1, 5, 3>(acc, a, a_off, b, lane * 16, kt0, kt1, nb, g.K * (int)sizeof(elt_t), khalf * 16);
     // weight * sum to this wave's token rows (the rows of an expert are distinct tokens: all reads, then all writes)
 #pragma unroll
     for (int mi = 0; mi < NB; ++mi) {
@@ -309,11 +333,11 @@ __global__ __launch_bounds__(kStream2Waves * 64, 2) void stream_gemm2_kernel(con
   }
   __syncthreads();
   const int tot = g.T * 8;  // four columns per thread
-  for (int i = tid; i < tot; i += kStream2Waves * 64) {
+  for (int i = tid; i < tot; i += kStreamWaves * 64) {
     const int t = i >> 3, col = c * 32 + (i & 7) * 4;
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int q = 0; q < kStream2Waves; ++q) {
+    for (int q = 0; q < kStreamWaves; ++q) {
       const f32x4 o = *reinterpret_cast<const f32x4 *>(ysum + ((size_t)q * g.T + t) * 32 + (i & 7) * 4);
 #pragma unroll
       for (int u = 0; u < 4; ++u) v[u] += o[u];
