@@ -109,6 +109,9 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
   g2.row_sole = sole; g2.y = y;
   g2.K = s->f; g2.N = s->d; g2.lda = s->f; g2.ldo = s->d;
   g2.n_items = w.header + 3; g2.work = w.work2;
+  const int64_t a_elt = q ? 1 : dv.elt;
+  g1.a_far = (a1_map ? (int64_t)s->T : dv.P_cap) * a1_ld * a_elt >= (int64_t)1 << 32;
+  g2.a_far = dv.P_cap * s->f * a_elt >= (int64_t)1 << 32;
   if (keep_gu) {  // training forward: g and u are kept, and every weighted row goes to the kept o
     g1.aux = keep_gu;
     g2.out = keep_o;
@@ -116,9 +119,9 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
   const auto grid_of = [&](int nt) { return dim3((unsigned)(((size_t)dv.max_mtiles * nt + 255) / 256 * 256)); };
   if (q) {
     static std::atomic<uint64_t> done1{0}, done2{0}, done_pipe{0};
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<true, true>), 2 * kStageBytes, done1) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<false, true>), 2 * kStageBytes, done2) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_fp8_pipeline_kernel), 2 * kStageBytes, done_pipe))
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<true, true>), kGemmLds, done1) ||
+        !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<false, true>), kGemmLds, done2) ||
+        !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_fp8_pipeline_kernel), kGemmLds, done_pipe))
       return MOE_ERR_HIP;
     g1.A = q->xq; g1.a_scale = q->x_scale; g1.b_scale = q->gu_scale; g1.h_scale = q->h_scale;
     g2.b_scale = q->down_scale; g2.h_scale = q->h_scale;
@@ -131,25 +134,25 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
       pa.g1 = g1; pa.g2 = g2;
       pa.tickets = w.header + 8; pa.tile_ready = w.tile_ready; pa.error = w.header + 24; pa.nt1 = dv.nt1 + wait_extra;
       pa.max_polls = max_polls;
-      hipLaunchKernelGGL(gemm_fp8_pipeline_kernel, dim3((unsigned)n_cu), dim3(kGemmThreads), 2 * kStageBytes, st, pa);
+      hipLaunchKernelGGL(gemm_fp8_pipeline_kernel, dim3((unsigned)n_cu), dim3(kGemmThreads), kGemmLds, st, pa);
       mark(2);
       mark(3);
       return launch_status();
     }
-    hipLaunchKernelGGL((gemm_bf16_kernel<true, true>), grid_of(dv.nt1), dim3(kGemmThreads), 2 * kStageBytes, st, g1);
+    hipLaunchKernelGGL((gemm_bf16_kernel<true, true>), grid_of(dv.nt1), dim3(kGemmThreads), kGemmLds, st, g1);
     int rc = launch_status();
     mark(2);
     if (rc != MOE_OK) return rc;
-    hipLaunchKernelGGL((gemm_bf16_kernel<false, true>), grid_of(dv.nt2), dim3(kGemmThreads), 2 * kStageBytes, st, g2);
+    hipLaunchKernelGGL((gemm_bf16_kernel<false, true>), grid_of(dv.nt2), dim3(kGemmThreads), kGemmLds, st, g2);
     mark(3);
     return launch_status();
   }
   if (s->dtype == MOE_BF16) {
     // the two LDS stages (128 KiB) exceed the default dynamic limit; raising it is a per-function attribute
     static std::atomic<uint64_t> done1{0}, done2{0}, done_pipe{0};
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<true>), 2 * kStageBytes, done1) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<false>), 2 * kStageBytes, done2) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_pipeline_kernel), 2 * kStageBytes, done_pipe))
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<true>), kGemmLds, done1) ||
+        !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<false>), kGemmLds, done2) ||
+        !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_pipeline_kernel), kGemmLds, done_pipe))
       return MOE_ERR_HIP;
     g1.n_ntiles = ceil_div(s->f, kBN / 2); g1.n_ktiles = ceil_div(s->d, kBK);
     g2.n_ntiles = ceil_div(s->d, kBN);     g2.n_ktiles = ceil_div(s->f, kBK);
@@ -163,24 +166,24 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
       pa.max_polls = max_polls;
       if (keep_gu) {
         static std::atomic<uint64_t> done_tp{0};
-        if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_train_pipeline_kernel), 2 * kStageBytes, done_tp))
+        if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_train_pipeline_kernel), kGemmLds, done_tp))
           return MOE_ERR_HIP;
-        hipLaunchKernelGGL(gemm_train_pipeline_kernel, dim3((unsigned)n_cu), dim3(kGemmThreads), 2 * kStageBytes, st,
+        hipLaunchKernelGGL(gemm_train_pipeline_kernel, dim3((unsigned)n_cu), dim3(kGemmThreads), kGemmLds, st,
                            pa);
       } else if (combine_tb) {
         // Combine as the third stage of the same launch (wait_extra also raises its target, for the give-up test)
         static std::atomic<uint64_t> done_c{0};
-        if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_combine_kernel), 2 * kStageBytes, done_c))
+        if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_combine_kernel), kGemmLds, done_c))
           return MOE_ERR_HIP;
         pa.tile_done = w.tile_done; pa.row_tile = w.row_tile;
         pa.topk_idx = topk_idx; pa.inv_perm = combine_tb->inv_perm; pa.offsets = combine_tb->offsets;
         pa.header = w.header;
         pa.T = s->T; pa.k = s->k; pa.e_lo = dv.e_lo; pa.E_loc = dv.E_loc; pa.P_cap = (int)dv.P_cap;
         pa.nt2 = dv.nt2 + wait_extra; pa.n_mtiles_cap = dv.max_mtiles;
-        hipLaunchKernelGGL(gemm_bf16_combine_kernel, dim3((unsigned)n_cu), dim3(kGemmThreads), 2 * kStageBytes, st,
+        hipLaunchKernelGGL(gemm_bf16_combine_kernel, dim3((unsigned)n_cu), dim3(kGemmThreads), kGemmLds, st,
                            pa);
       } else {
-        hipLaunchKernelGGL(gemm_bf16_pipeline_kernel, dim3((unsigned)n_cu), dim3(kGemmThreads), 2 * kStageBytes, st,
+        hipLaunchKernelGGL(gemm_bf16_pipeline_kernel, dim3((unsigned)n_cu), dim3(kGemmThreads), kGemmLds, st,
                            pa);
       }
       mark(2);
@@ -189,18 +192,18 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
     }
     if (keep_gu) {
       static std::atomic<uint64_t> done_t{0};
-      if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<true, false, true>), 2 * kStageBytes,
+      if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<true, false, true>), kGemmLds,
                              done_t))
         return MOE_ERR_HIP;
-      hipLaunchKernelGGL((gemm_bf16_kernel<true, false, true>), grid_of(dv.nt1), dim3(kGemmThreads), 2 * kStageBytes,
+      hipLaunchKernelGGL((gemm_bf16_kernel<true, false, true>), grid_of(dv.nt1), dim3(kGemmThreads), kGemmLds,
                          st, g1);
     } else {
-      hipLaunchKernelGGL(gemm_bf16_kernel<true>, grid_of(dv.nt1), dim3(kGemmThreads), 2 * kStageBytes, st, g1);
+      hipLaunchKernelGGL(gemm_bf16_kernel<true>, grid_of(dv.nt1), dim3(kGemmThreads), kGemmLds, st, g1);
     }
     int rc = launch_status();
     mark(2);
     if (rc != MOE_OK) return rc;
-    hipLaunchKernelGGL(gemm_bf16_kernel<false>, grid_of(dv.nt2), dim3(kGemmThreads), 2 * kStageBytes, st,
+    hipLaunchKernelGGL(gemm_bf16_kernel<false>, grid_of(dv.nt2), dim3(kGemmThreads), kGemmLds, st,
                        g2);
     mark(3);
     return launch_status();
@@ -864,9 +867,9 @@ extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const v
                      d_topk_w);
   if ((rc = launch_status()) != MOE_OK) return join(rc);
   static std::atomic<uint64_t> done_b1{0}, done_b2{0};
-  if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<false, false, true>), 2 * kStageBytes,
+  if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<false, false, true>), kGemmLds,
                          done_b1) ||
-      !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<false>), 2 * kStageBytes, done_b2))
+      !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<false>), kGemmLds, done_b2))
     return join(MOE_ERR_HIP);
   const auto grid_of = [&](int nt) { return dim3((unsigned)(((size_t)dvb.max_mtiles * nt + 255) / 256 * 256)); };
   // dh_raw = dy[token of the row] Wd^T, then the SwiGLU derivative with the kept g and u
@@ -876,7 +879,8 @@ extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const v
   g1.n_items = w.header + 0; g1.work = w.work1;
   g1.K = shape->d; g1.N = shape->f; g1.lda = shape->d; g1.ldo = 2 * shape->f;
   g1.n_ntiles = dvb.nt1; g1.n_ktiles = ceil_div(shape->d, kBK);
-  hipLaunchKernelGGL((gemm_bf16_kernel<false, false, true>), grid_of(dvb.nt1), dim3(kGemmThreads), 2 * kStageBytes, st,
+  g1.a_far = (int64_t)shape->T * shape->d * 2 >= (int64_t)1 << 32;
+  hipLaunchKernelGGL((gemm_bf16_kernel<false, false, true>), grid_of(dvb.nt1), dim3(kGemmThreads), kGemmLds, st,
                      g1);
   if ((rc = launch_status()) != MOE_OK) return join(rc);
   if (wgrad) {  // dg, du and w h are there: their transposes run beside the second GEMM
@@ -893,7 +897,8 @@ extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const v
   g2.n_items = w.header + 3; g2.work = w.work2;
   g2.K = 2 * shape->f; g2.N = shape->d; g2.lda = 2 * shape->f; g2.ldo = shape->d;
   g2.n_ntiles = dvb.nt2; g2.n_ktiles = 2 * (shape->f / kBK);
-  hipLaunchKernelGGL(gemm_bf16_kernel<false>, grid_of(dvb.nt2), dim3(kGemmThreads), 2 * kStageBytes, st, g2);
+  g2.a_far = dv.P_cap * 2 * shape->f * 2 >= (int64_t)1 << 32;
+  hipLaunchKernelGGL(gemm_bf16_kernel<false>, grid_of(dvb.nt2), dim3(kGemmThreads), kGemmLds, st, g2);
   if ((rc = launch_status()) != MOE_OK) return join(rc);
   if ((rc = launch_combine(shape, dv, dxr, topk_idx, tables, dx, true, st)) != MOE_OK || !wgrad) return join(rc);
   // weight gradients: one grouped product per weight matrix, over the transposed operands

@@ -5,6 +5,7 @@
 
 #include "combine_kernels.h"
 #include "forward_types.h"
+#include "gemm_pingpong.h"
 
 namespace moe355 {
 
@@ -14,32 +15,11 @@ namespace moe355 {
 //   B tiles  : packed in operand order (pack_kernels.h), streamed linearly into the LDS and read linearly from it.
 //   GATED    : epilogue h = silu(g) * u, written as bf16   (GEMM-1)
 //   !GATED   : epilogue o = acc * row_w[row], written fp32 (GEMM-2, gate weight of Sec. III-C)
-// Tile 256 x 256 x 64, one workgroup of 512 threads per CU.  Every operand byte enters the CU once (global ->
-// registers -> LDS) because the L2 -> CU path, not the matrix core, is what saturates first on this chip;
-// sharing goes through the LDS, which has bandwidth to spare.  8 waves = 2 (rows) x 4 (columns), each wave
-// owns 128 x 64 as 4 x 2 MFMA 32x32x16 accumulators; two waves per SIMD cover each other's LDS latency.
-// LDS is double buffered (2 x 64 KiB) with one barrier per k-step; the next slab is in flight in registers
-// while the current one is multiplied.  NB = number of 32-row blocks of this wave that hold valid rows (the
-// others are skipped: small experts are weight-streaming bound and need no padding math).
+// Tile 256 x 256 x 64, one workgroup of 512 threads (8 waves = 2 rows x 4 columns) per CU.  Every operand byte enters the
+// CU once (memory -> LDS) because the L2 -> CU path saturates soon on this chip.  RW = rows of a wave row (32 .. 128): the
+// tile's 32-row blocks are split evenly over the two wave rows; NB = the blocks of this wave that hold valid rows (the
+// others are skipped).  The main loops are in gemm_pingpong.h; this function sets up the operands and runs the epilogue.
 // ------------------------------------------------------------------------------------------------
-
-__device__ __forceinline__ f32x16 mfma_bf16(bf16x8 a, bf16x8 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
-// FP8 operands (E4M3): a 16-byte fragment holds 16 reduction indices per lane; two fragments (32 bytes per lane)
-// feed one 32x32x64 instruction.  Which reduction indices share an instruction, and where in the operand they sit,
-// does not matter as long as A and B agree: both put the same two 16-byte chunks of the reduction range side by side.
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x8 __attribute__((ext_vector_type(8)));
-__device__ __forceinline__ f32x16 mfma_fp8_pair(bf16x8 a_lo, bf16x8 a_hi, bf16x8 b_lo, bf16x8 b_hi, f32x16 c) {
-  const i32x8 a = __builtin_shufflevector(__builtin_bit_cast(i32x4, a_lo), __builtin_bit_cast(i32x4, a_hi), 0, 1, 2, 3,
-                                          4, 5, 6, 7);
-  const i32x8 b = __builtin_shufflevector(__builtin_bit_cast(i32x4, b_lo), __builtin_bit_cast(i32x4, b_hi), 0, 1, 2, 3,
-                                          4, 5, 6, 7);
-  // both operands E4M3 (format selectors 0), no block scales (all scale operands 0)
-  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
-}
 
 constexpr int kGemmThreads = 512;
 
@@ -52,12 +32,12 @@ constexpr int kGemmThreads = 512;
 #error "the explicit s_waitcnt encodings of the hand-over are written for gfx950"
 #endif
 constexpr int kWaitVmcnt0 = 0x0F70;
-constexpr int kAStageBytes = kBM * kBK * 2;               // 32 KiB
-constexpr int kStageBytes = kAStageBytes + kTileBytes;    // 64 KiB: A slab then B slab
+constexpr int kGemmLds = 3 * (kBM / 2 * kBK * 2 + kTileBytes);  // 144 KiB: the ring of the 128-row tiles (two 64 KiB stages
+                                                                // and the epilogues take less)
 constexpr int kPatchBytes = 32 * 288;                     // per-wave epilogue patch (fits 8 x in the stages)
 
 // FP8: A and the packed B hold E4M3 codes; a k-step then covers 128 reduction indices in the same 128 bytes per row,
-// so the staging, the LDS image and the fragment reads are byte for byte those of the bf16 tile.  The scales
+// so the slabs, the LDS image and the fragment reads are byte for byte those of the bf16 tile.  The scales
 // (g.a_scale per token, g.b_scale per expert and output column, g.h_scale per expert) are applied in the epilogues
 // and GEMM-1 writes h as codes.
 // TRAIN selects the epilogues of the training path (bf16 only):
@@ -65,9 +45,10 @@ constexpr int kPatchBytes = 32 * 288;                     // per-wave epilogue p
 //   !GATED : the first GEMM of the backward pass, dh_raw = dy Wd^T (N = f).  With the kept g, u and the gate weight w:
 //            dh = w dh_raw, dg = dh u silu'(g), du = dh silu(g)  ->  g.out = dgu [rows, 2 N] bf16 (dg, then du), and
 //            g.aux2 = w silu(g) u [rows, N] bf16 (the h operand of the down-projection weight gradient, weight folded in).
-template <bool GATED, bool RESIDENT, int NB, int NA, int DEPTH, bool FP8 = false, bool TRAIN = false, bool LONE = false>
+template <bool GATED, bool RESIDENT, int NB, int RW, bool FP8 = false, bool TRAIN = false, bool LONE = false,
+          bool FAR = false>
 __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char *smem, int nt, int le, int m0,
-                                               int rows, int nblk_total, int poison = 0,
+                                               int rows, int poison = 0,
                                                int32_t *pre_ctr = nullptr, int *pre_slot = nullptr) {
   // RESIDENT (the kernel that loops over items): the thread index goes through an empty asm so that nothing
   // derived from it counts as loop invariant; hoisting those values across items costs more registers than the
@@ -78,79 +59,6 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
   const int w8 = tid >> 6;
   const int wm = w8 >> 2, wn = w8 & 3;
 
-  // ---- global -> register staging (scalars, not arrays, so nothing lands in scratch) ----
-  // A: thread t stages chunk t & 7 (8 reduction indices) of rows (t >> 3) + 64 i; B: chunks t + 512 i
-  const int a_chunk = tid & 7;
-  const int a_row0 = tid >> 3;  // 0..63
-  typedef typename std::conditional<FP8, uint8_t, bf16_t>::type elt_t;
-  constexpr int EPC = FP8 ? 16 : 8;    // elements per 16-byte chunk
-  constexpr int KS = FP8 ? 128 : kBK;  // reduction indices per k-step
-  const elt_t *a_base = static_cast<const elt_t *>(g.A) + a_chunk * EPC;
-#define MOE355_A_ROW(i)                                                                          \
-  const int a_rc##i = a_row0 + 64 * i < rows ? a_row0 + 64 * i : rows - 1; /* padding: a valid row */ \
-  const uint32_t a_off##i =                                                                      \
-      (uint32_t)(g.row_map ? g.row_map[m0 + a_rc##i] : m0 + a_rc##i) * (uint32_t)g.lda;
-  MOE355_A_ROW(0) MOE355_A_ROW(1) MOE355_A_ROW(2) MOE355_A_ROW(3)
-#undef MOE355_A_ROW
-  // LDS destination of row a_row0; row + 64 i lies 8192 bytes further (64 i keeps the swizzle bits)
-  const int a_dst = (a_row0 * 8 + (a_chunk ^ ((a_row0 >> 1) & 7))) * 16;
-  const unsigned char *b_src =
-      static_cast<const unsigned char *>(g.Bp) + ((size_t)(le * g.n_ntiles + nt) * g.n_ktiles) * kTileBytes + tid * 16;
-
-  // Register slab sets.  Set x always exists; set y is used when DEPTH == 2 (two slabs in flight: tiles with at
-  // most 64 rows are pure weight streaming, their accumulators are small, and what limits them is the number of
-  // bytes a CU keeps in flight towards HBM).
-  u32x4 ra0x, ra1x, ra2x, ra3x, rb0x, rb1x, rb2x, rb3x;
-  u32x4 ra0y, ra1y, ra2y, ra3y, rb0y, rb1y, rb2y, rb3y;
-  // A slab is moved in three portions: {ra0, ra1, rb0}, {ra2, ra3, rb1}, {rb2, rb3}
-  // k tail: a chunk past K is replaced by chunk 0 of the same row (valid memory, finite data); the packed B
-  // tile is zero there, so it contributes nothing and no select has to wait on the load
-#define MOE355_A_OFF(KT) ((KT) * KS + a_chunk * EPC < g.K ? (KT) * KS : -a_chunk * EPC)
-  // NA = row loads per thread that reach valid rows (1: rows < 64, 2: rows < 128, 4: all); the others are skipped
-  // Weight tiles of a streaming item (at most 64 rows), and of any item that is its expert's only M tile (LONE), are
-  // read once by one workgroup: loaded with the non-temporal hint so that they do not push the operands that other
-  // tiles share out of the L2.
-#define MOE355_B_LOAD(PTR)                                                                          \
-  ((NA == 1 || LONE) ? __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(PTR))                        \
-           : *reinterpret_cast<const u32x4 *>(PTR))
-#define MOE355_LOAD_P0(S, KT)                                                                       \
-  do {                                                                                              \
-    ra0##S = *reinterpret_cast<const u32x4 *>(a_base + a_off0 + MOE355_A_OFF(KT));                  \
-    if (NA > 1) ra1##S = *reinterpret_cast<const u32x4 *>(a_base + a_off1 + MOE355_A_OFF(KT));      \
-    rb0##S = MOE355_B_LOAD(b_src + (size_t)(KT) * kTileBytes);                                      \
-  } while (0)
-#define MOE355_LOAD_P1(S, KT)                                                                       \
-  do {                                                                                              \
-    if (NA > 2) ra2##S = *reinterpret_cast<const u32x4 *>(a_base + a_off2 + MOE355_A_OFF(KT));      \
-    if (NA > 2) ra3##S = *reinterpret_cast<const u32x4 *>(a_base + a_off3 + MOE355_A_OFF(KT));      \
-    rb1##S = MOE355_B_LOAD(b_src + (size_t)(KT) * kTileBytes + 8192);                               \
-  } while (0)
-#define MOE355_LOAD_P2(S, KT)                                                                       \
-  do {                                                                                              \
-    rb2##S = MOE355_B_LOAD(b_src + (size_t)(KT) * kTileBytes + 16384);                              \
-    rb3##S = MOE355_B_LOAD(b_src + (size_t)(KT) * kTileBytes + 24576);                              \
-  } while (0)
-#define MOE355_STORE_P0(S, BUF)                                                                     \
-  do {                                                                                              \
-    unsigned char *s_ = smem + (BUF) * kStageBytes;                                                 \
-    *reinterpret_cast<u32x4 *>(s_ + a_dst) = ra0##S;                                                \
-    if (NA > 1) *reinterpret_cast<u32x4 *>(s_ + a_dst + 8192) = ra1##S;                             \
-    *reinterpret_cast<u32x4 *>(s_ + kAStageBytes + tid * 16) = rb0##S;                              \
-  } while (0)
-#define MOE355_STORE_P1(S, BUF)                                                                     \
-  do {                                                                                              \
-    unsigned char *s_ = smem + (BUF) * kStageBytes;                                                 \
-    if (NA > 2) *reinterpret_cast<u32x4 *>(s_ + a_dst + 16384) = ra2##S;                            \
-    if (NA > 2) *reinterpret_cast<u32x4 *>(s_ + a_dst + 24576) = ra3##S;                            \
-    *reinterpret_cast<u32x4 *>(s_ + kAStageBytes + tid * 16 + 8192) = rb1##S;                       \
-  } while (0)
-#define MOE355_STORE_P2(S, BUF)                                                                     \
-  do {                                                                                              \
-    unsigned char *s_ = smem + (BUF) * kStageBytes;                                                 \
-    *reinterpret_cast<u32x4 *>(s_ + kAStageBytes + tid * 16 + 16384) = rb2##S;                      \
-    *reinterpret_cast<u32x4 *>(s_ + kAStageBytes + tid * 16 + 24576) = rb3##S;                      \
-  } while (0)
-
   f32x16 acc[NB > 0 ? NB : 1][2];
 #pragma unroll
   for (int mi = 0; mi < NB; ++mi)
@@ -159,175 +67,56 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[mi][j][r] = 0.f;
 
-  // ---- LDS -> MFMA operand addressing: lane l reads row l & 31 of a 32-row block, k half l >> 5 ----
-  const int l31 = lane & 31, khalf = lane >> 5, sw = (lane >> 1) & 7;
-  const int a_rd = (wm * 128 + l31) * 128;                  // + mi * 4096
-  const int b_rd = kAStageBytes + wn * 8192 + lane * 16;    // + j * 4096 + kk * 1024: operands are stored per lane
-
-  constexpr int NF = NB > 0 ? NB : 1;
-  bf16x8 fa0[NF], fb0[2], fa1[NF], fb1[2];  // operand fragments of two consecutive k-substeps
-#define MOE355_READ_FRAGS(FA, FB, STAGE, KK)                                                           \
-  do {                                                                                                 \
-    const int slot_ = (((KK) * 2 + khalf) ^ sw) * 16;                                                  \
-    _Pragma("unroll") for (int mi = 0; mi < NB; ++mi) FA[mi] =                                         \
-        *reinterpret_cast<const bf16x8 *>((STAGE) + a_rd + mi * 4096 + slot_);                         \
-    if (NB > 0) {                                                                                      \
-      FB[0] = *reinterpret_cast<const bf16x8 *>((STAGE) + b_rd + (KK) * 1024);                         \
-      FB[1] = *reinterpret_cast<const bf16x8 *>((STAGE) + b_rd + 4096 + (KK) * 1024);                  \
-    }                                                                                                  \
-  } while (0)
-#define MOE355_MFMAS(FA, FB)                                                                           \
-  do {                                                                                                 \
-    _Pragma("unroll") for (int mi = 0; mi < NB; ++mi) {                                                \
-      acc[mi][0] = mfma_bf16(FA[mi], FB[0], acc[mi][0]);                                               \
-      acc[mi][1] = mfma_bf16(FA[mi], FB[1], acc[mi][1]);                                               \
-    }                                                                                                  \
-  } while (0)
-
-  // Pipeline.  At the top of k-step kt: LDS stage kt & 1 holds slab kt, a register set holds slab kt + 1 (its
-  // loads were issued DEPTH k-steps ago, in three portions), and fa0 / fb0 hold the operands of substep 0.
-  // Substeps 0..2 each multiply, fetch the next substep's operands, move one portion of the register set into the
-  // other stage and reissue that portion's loads for slab kt + 1 + DEPTH, so the global loads, the LDS stores and
-  // the LDS reads are all spread under the MFMAs instead of forming a burst around the barrier.  The single
-  // barrier sits before substep 3, whose operands are already in registers; substep 3 also fetches substep 0 of
-  // the next slab.  Reloads past the last k-step repeat the last slab: in bounds, never used.
-  // Requested instruction order (sched_group_barrier masks: 0x008 MFMA, 0x020 VMEM read, 0x100 DS read,
-  // 0x200 DS write).
-#define MOE355_ORDER(NW)                                                                                \
-  do {                                                                                                 \
-    if (NB >= 3) {                                                                                     \
-      /* the LDS reads two behind each of the first MFMAs, then one staging store and one global load  \
-         behind each of the next ones, the rest of the MFMAs last: the LDS queue never sees more than  \
-         two requests in a row (measured 3-4 % faster than all reads, all MFMAs, all stores, all       \
-         loads; the stores as early as the reads: 7 % slower, they wait for the global loads) */       \
-      _Pragma("unroll") for (int i_ = 0; i_ < (NB + 2) / 2; ++i_) {                                    \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                             \
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);                                             \
-      }                                                                                                \
-      if ((NB + 2) & 1) {                                                                              \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                             \
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                             \
-      }                                                                                                \
-      _Pragma("unroll") for (int i_ = 0; i_ < (NW); ++i_) {                                            \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                             \
-        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);                                             \
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                             \
-      }                                                                                                \
-      if (2 * NB - (NB + 3) / 2 - (NW) > 0)                                                            \
-        __builtin_amdgcn_sched_group_barrier(0x008, 2 * NB - (NB + 3) / 2 - (NW), 0);                  \
-    } else {                                                                                           \
-      if (NB > 0) {                                                                                    \
-        __builtin_amdgcn_sched_group_barrier(0x100, NB + 2, 0);                                        \
-        __builtin_amdgcn_sched_group_barrier(0x008, 2 * NB, 0);                                        \
-      }                                                                                                \
-      if ((NW) > 0) {                                                                                  \
-        __builtin_amdgcn_sched_group_barrier(0x200, (NW), 0);                                          \
-        __builtin_amdgcn_sched_group_barrier(0x020, (NW), 0);                                          \
-      }                                                                                                \
-    }                                                                                                  \
-  } while (0)
-#define MOE355_KSTEP(S, KT_, KPRE)                                                                      \
-  do {                                                                                                 \
-    const unsigned char *sCur = smem + ((KT_) & 1) * kStageBytes;                                      \
-    const int nxt = ((KT_) & 1) ^ 1;                                                                   \
-    const int kp_ = min((KPRE), kt_last);                                                              \
-    MOE355_READ_FRAGS(fa1, fb1, sCur, 1);                                                              \
-    MOE355_MFMAS(fa0, fb0);                                                                            \
-    MOE355_STORE_P0(S, nxt);                                                                           \
-    MOE355_LOAD_P0(S, kp_);                                                                            \
-    MOE355_READ_FRAGS(fa0, fb0, sCur, 2);                                                              \
-    MOE355_MFMAS(fa1, fb1);                                                                            \
-    MOE355_STORE_P1(S, nxt);                                                                           \
-    MOE355_LOAD_P1(S, kp_);                                                                            \
-    MOE355_READ_FRAGS(fa1, fb1, sCur, 3);                                                              \
-    MOE355_MFMAS(fa0, fb0);                                                                            \
-    MOE355_STORE_P2(S, nxt);                                                                           \
-    MOE355_LOAD_P2(S, kp_);                                                                            \
-    MOE355_ORDER(NA > 1 ? 3 : 2);                                                                      \
-    MOE355_ORDER(NA > 2 ? 3 : 1);                                                                      \
-    MOE355_ORDER(2);                                                                                   \
-    __syncthreads();                                                                                   \
-    MOE355_READ_FRAGS(fa0, fb0, smem + nxt * kStageBytes, 0);                                          \
-    MOE355_MFMAS(fa1, fb1);                                                                            \
-    MOE355_ORDER(0);                                                                                   \
-  } while (0)
-
-  // FP8 k-step: the operands of substeps 0 and 1 (then 2 and 3) sit in fa0 / fa1 and go into one instruction per
-  // accumulator; the fragments of the next pair are read once those instructions have been issued, the staging
-  // traffic is spread between the two groups as above, and the barrier again sits in front of the last group.
-#define MOE355_MFMAS8()                                                                                \
-  do {                                                                                                 \
-    _Pragma("unroll") for (int mi = 0; mi < NB; ++mi) {                                                \
-      acc[mi][0] = mfma_fp8_pair(fa0[mi], fa1[mi], fb0[0], fb1[0], acc[mi][0]);                        \
-      acc[mi][1] = mfma_fp8_pair(fa0[mi], fa1[mi], fb0[1], fb1[1], acc[mi][1]);                        \
-    }                                                                                                  \
-  } while (0)
-#define MOE355_KSTEP8(S, KT_, KPRE)                                                                     \
-  do {                                                                                                 \
-    const unsigned char *sCur = smem + ((KT_) & 1) * kStageBytes;                                      \
-    const int nxt = ((KT_) & 1) ^ 1;                                                                   \
-    const int kp_ = min((KPRE), kt_last);                                                              \
-    MOE355_MFMAS8();                                                                                   \
-    MOE355_STORE_P0(S, nxt);                                                                           \
-    MOE355_LOAD_P0(S, kp_);                                                                            \
-    MOE355_READ_FRAGS(fa0, fb0, sCur, 2);                                                              \
-    MOE355_READ_FRAGS(fa1, fb1, sCur, 3);                                                              \
-    MOE355_STORE_P1(S, nxt);                                                                           \
-    MOE355_LOAD_P1(S, kp_);                                                                            \
-    MOE355_STORE_P2(S, nxt);                                                                           \
-    MOE355_LOAD_P2(S, kp_);                                                                            \
-    __syncthreads();                                                                                   \
-    MOE355_MFMAS8();                                                                                   \
-    MOE355_READ_FRAGS(fa0, fb0, smem + nxt * kStageBytes, 0);                                          \
-    MOE355_READ_FRAGS(fa1, fb1, smem + nxt * kStageBytes, 1);                                          \
-  } while (0)
-
-  const int KT = g.n_ktiles;
-  const int kt_last = KT - 1;
-  MOE355_LOAD_P0(x, 0); MOE355_LOAD_P1(x, 0); MOE355_LOAD_P2(x, 0);
-  MOE355_STORE_P0(x, 0); MOE355_STORE_P1(x, 0); MOE355_STORE_P2(x, 0);
-  {
-    const int k1 = min(1, kt_last);
-    MOE355_LOAD_P0(x, k1); MOE355_LOAD_P1(x, k1); MOE355_LOAD_P2(x, k1);
-    if (DEPTH == 2) {
-      const int k2 = min(2, kt_last);
-      MOE355_LOAD_P0(y, k2); MOE355_LOAD_P1(y, k2); MOE355_LOAD_P2(y, k2);
+  const int l31 = lane & 31, khalf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(w8);
+  // Weight tiles of a streaming item (at most 64 rows), and of any item that is its expert's only M tile (LONE), are
+  // read once by one workgroup: requested with the non-temporal hint so that they do not push the operands that other
+  // tiles share out of the L2.
+  typename std::conditional<(RW > 64), PingPong<FP8, (NB > 0 ? NB : 1), RW, LONE, FAR>,
+                            SlabRing<FP8, NB, (RW > 64 ? 64 : RW), LONE || RW == 32>>::type loop;
+  loop.rows.init(g);
+  loop.rb = lds_load_rsrc(static_cast<const unsigned char *>(g.Bp) + ((size_t)(le * g.n_ntiles + nt) * g.n_ktiles) * kTileBytes,
+                          (uint32_t)g.n_ktiles * kTileBytes);
+  loop.lds = lds_address(smem);
+  loop.smem = smem;
+  // LDS -> operand addressing: lane l reads row l & 31 of a 32-row block, k half l >> 5
+  loop.khalf = khalf;
+  loop.sw = (lane >> 1) & 7;
+  loop.a_rd = (wm * RW + l31) * 128;
+  loop.b_rd = wn * 8192 + lane * 16;
+  loop.b_voff = lane * 16;
+  const auto a_row = [&](int row) {  // row of the matrix behind row `row` of the tile (padding: the last valid one)
+    const int r = m0 + min(row, rows - 1);
+    return (uint32_t)(g.row_map ? g.row_map[r] : r);
+  };
+  if constexpr (RW > 64) {
+    typedef PingPong<FP8, 1, RW, false, FAR> PP;
+    loop.b_rd += PP::kB;
+    loop.b_soff = (wave >> 1) * 8192 + (wave & 1) * 2048;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int n = h == 0 ? 2 : PP::I1;  // requests of eight rows: wave's share of its wave row's A0 or A1
+      const int row0 = (wave >> 2) * RW + h * 64 + (wave & 3) * 8 * n;
+      loop.a_lds[h] = row0 * 128;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (i < n) {
+          const int row = row0 + i * 8 + (lane >> 3);
+          loop.rows.set(h, i, row, a_row(row), lane);
+        }
     }
-  }
-  __syncthreads();
-  MOE355_READ_FRAGS(fa0, fb0, smem, 0);
-  if (FP8) MOE355_READ_FRAGS(fa1, fb1, smem, 1);
-
-  if (FP8 && DEPTH == 1) {
-    for (int kt = 0; kt < KT; ++kt) MOE355_KSTEP8(x, kt, kt + 2);
-  } else if (FP8) {
-    for (int kt = 0; kt < KT; kt += 2) {
-      MOE355_KSTEP8(x, kt, kt + 3);
-      if (kt + 1 < KT) MOE355_KSTEP8(y, kt + 1, kt + 4);
-    }
-  } else if (DEPTH == 1) {
-    for (int kt = 0; kt < KT; ++kt) MOE355_KSTEP(x, kt, kt + 2);
+    loop.run(acc, g.n_ktiles, g.K, wave >> 2);
   } else {
-    // set x carries the odd slabs, set y the even ones
-    for (int kt = 0; kt < KT; kt += 2) {
-      MOE355_KSTEP(x, kt, kt + 3);
-      if (kt + 1 < KT) MOE355_KSTEP(y, kt + 1, kt + 4);
+    constexpr int n = RW / 32;
+    loop.a_lds = wave * n * 1024;
+    loop.b_soff = wave * 4096;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+      const int row = (wave * n + i) * 8 + (lane >> 3);
+      loop.rows.set(0, i, row, a_row(row), lane);
     }
+    loop.run(acc, g.n_ktiles, g.K);
   }
-#undef MOE355_KSTEP
-#undef MOE355_KSTEP8
-#undef MOE355_MFMAS8
-#undef MOE355_ORDER
-#undef MOE355_READ_FRAGS
-#undef MOE355_MFMAS
-#undef MOE355_LOAD_P0
-#undef MOE355_B_LOAD
-#undef MOE355_LOAD_P1
-#undef MOE355_LOAD_P2
-#undef MOE355_STORE_P0
-#undef MOE355_STORE_P1
-#undef MOE355_STORE_P2
-#undef MOE355_A_OFF
 
   // ---- epilogue ----
   // Accumulator register r of lane l holds C[8*(r/4) + 4*(l/32) + r%4][l%32] of its 32x32 block, i.e. a lane
@@ -346,7 +135,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
   if (!GATED && !TRAIN && NB > 0) {
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-      const int row_l = wm * 128 + hh * 64 + lane;
+      const int row_l = wm * RW + hh * 64 + lane;
       meta_w[hh * 64 + lane] = row_l < rows ? (g.row_w ? g.row_w[m0 + row_l] : 1.f) : 0.f;
       meta_s[hh * 64 + lane] = (g.row_sole && row_l < rows) ? g.row_sole[m0 + row_l] : -1;
     }
@@ -360,7 +149,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
     meta_w = reinterpret_cast<float *>(smem + w8 * 16384 + 13824);
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-      const int row_l = wm * 128 + hh * 64 + lane;
+      const int row_l = wm * RW + hh * 64 + lane;
       meta_w[hh * 64 + lane] = row_l < rows ? g.row_w[m0 + row_l] : 0.f;
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -371,7 +160,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
     // FP8 GEMM-1: the same for the scales of the tokens behind this wave's rows (rows past the end repeat the last)
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-      const int row_l = min(wm * 128 + hh * 64 + lane, rows - 1);
+      const int row_l = min(wm * RW + hh * 64 + lane, rows - 1);
       meta_w[hh * 64 + lane] = g.a_scale[g.row_map ? g.row_map[m0 + row_l] : m0 + row_l];
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -397,7 +186,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
   }
 #pragma unroll
   for (int mi = 0; mi < NB; ++mi) {
-    const int blk_row0 = wm * 128 + mi * 32;  // first tile row of this 32-row block
+    const int blk_row0 = wm * RW + mi * 32;  // first tile row of this 32-row block
     if (!GATED && TRAIN) {
       // This wave's 32 x 64 block of g and of u comes in through the LDS in 16-byte pieces (row pitch 144 bytes, g
       // at 0, u at 4608 of a private 16 KiB region: the stages are dead), every lane replaces the elements it holds
@@ -595,23 +384,26 @@ __device__ __forceinline__ void gemm_bf16_item(const GemmArgs &g, unsigned char 
   // the variants with streaming weight loads: in the per-item kernels they cost six more registers, and those
   // kernels leave 16 registers per SIMD to the kernels that run beside them in the backward pass.
   const bool lone = (item.z & kItemLone) != 0;
-  const int nblk_total = (rows + 31) >> 5;                        // 1..8
-  const int wm = threadIdx.x >> 8;                                // wave row (wave-uniform)
-  const int nb = max(0, min(4, nblk_total - 4 * wm));             // valid 32-row blocks of this wave
-#define MOE355_TILE_(NB_, NA_, LONE_)                                                                              \
-  gemm_bf16_tile<GATED, RESIDENT, NB_, NA_, (NA_ == 1 ? 2 : 1), FP8, TRAIN, LONE_>(g, smem, nt, le, m0, rows, nblk_total, \
-                                                                                 poison, pre_ctr, pre_slot)
-#define MOE355_TILE(NB_, NA_)                                                                  \
-  do {                                                                                         \
-    if (RESIDENT && NA_ > 1 && lone) MOE355_TILE_(NB_, NA_, (RESIDENT && NA_ > 1)); else MOE355_TILE_(NB_, NA_, false); \
+  const int nblk = (rows + 31) >> 5;                                     // 1..8 blocks of 32 rows
+  const int wm = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);  // wave row
+  const int per_row = (nblk + 1) >> 1;                                   // blocks per wave row
+  const int nb = max(0, min(per_row, nblk - per_row * wm));              // those of this wave that hold rows
+#define MOE355_TILE_(NB_, RW_, LONE_) \
+  gemm_bf16_tile<GATED, RESIDENT, NB_, RW_, FP8, TRAIN, LONE_>(g, smem, nt, le, m0, rows, poison, pre_ctr, pre_slot)
+#define MOE355_TILE(NB_, RW_)                                                                                       \
+  do {                                                                                                              \
+    if (RESIDENT && RW_ > 32 && lone) MOE355_TILE_(NB_, RW_, (RESIDENT && RW_ > 32)); else MOE355_TILE_(NB_, RW_, false); \
   } while (0)
-  if (nblk_total <= 2) {
-    if (nb == 2) MOE355_TILE(2, 1); else if (nb == 1) MOE355_TILE(1, 1); else MOE355_TILE(0, 1);
-  } else if (nblk_total <= 4) {
-    if (nb == 4) MOE355_TILE(4, 2); else if (nb == 3) MOE355_TILE(3, 2); else MOE355_TILE(0, 2);
+  if (g.a_far) {  // (rare: a matrix of 4 GiB or more; padding rows are multiplied, not stored)
+    gemm_bf16_tile<GATED, RESIDENT, 4, 128, FP8, TRAIN, false, true>(g, smem, nt, le, m0, rows, poison, pre_ctr, pre_slot);
+  } else if (nblk <= 2) {
+    if (nb == 1) MOE355_TILE(1, 32); else MOE355_TILE(0, 32);
+  } else if (nblk <= 4) {
+    if (nb == 2) MOE355_TILE(2, 64); else MOE355_TILE(1, 64);  // (the second wave row holds at most one block less)
+  } else if (nblk <= 6) {
+    if (nb == 3) MOE355_TILE(3, 96); else MOE355_TILE(2, 96);
   } else {
-    if (nb == 4) MOE355_TILE(4, 4); else if (nb == 3) MOE355_TILE(3, 4); else if (nb == 2) MOE355_TILE(2, 4);
-    else MOE355_TILE(1, 4);
+    if (nb == 4) MOE355_TILE(4, 128); else MOE355_TILE(3, 128);
   }
 #undef MOE355_TILE
 #undef MOE355_TILE_

@@ -1,0 +1,336 @@
+// Main loops of the grouped GEMM tile: operands straight from memory into the LDS, slabs requested several k-steps ahead.
+#pragma once
+#include <type_traits>
+
+#include "forward_types.h"
+
+namespace moe355 {
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ f32x16 mfma_bf16(bf16x8 a, bf16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// FP8 operands (E4M3): a 16-byte fragment holds 16 reduction indices per lane; two fragments (32 bytes per lane)
+// feed one 32x32x64 instruction.  Which reduction indices share an instruction, and where in the operand they sit,
+// does not matter as long as A and B agree: both put the same two 16-byte chunks of the reduction range side by side.
+__device__ __forceinline__ f32x16 mfma_fp8_pair(bf16x8 a_lo, bf16x8 a_hi, bf16x8 b_lo, bf16x8 b_hi, f32x16 c) {
+  const i32x8 a = __builtin_shufflevector(__builtin_bit_cast(i32x4, a_lo), __builtin_bit_cast(i32x4, a_hi), 0, 1, 2, 3,
+                                          4, 5, 6, 7);
+  const i32x8 b = __builtin_shufflevector(__builtin_bit_cast(i32x4, b_lo), __builtin_bit_cast(i32x4, b_hi), 0, 1, 2, 3,
+                                          4, 5, 6, 7);
+  // both operands E4M3 (format selectors 0), no block scales (all scale operands 0)
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
+}
+
+// ---- loads into the LDS ----
+// 16 bytes per lane from memory to LDS address lds + 16 lane.  Assembler, because the compiler would wait for every such
+// load in front of any LDS read that it cannot tell apart from its target; the waits are placed by hand instead (the main
+// loops have no other vector-memory operation).
+__device__ __forceinline__ i32x4 lds_load_rsrc(const void *base, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(base);
+  i32x4 r;
+  r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+  r[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+  r[2] = __builtin_amdgcn_readfirstlane((int)bytes);
+  r[3] = 0x00027000;
+  return r;
+}
+template <bool NT = false>  // NT: with the non-temporal hint
+__device__ __forceinline__ void load_to_lds(i32x4 rsrc, uint32_t lds, uint32_t voff, uint32_t soff) {
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                 :
+                 : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory");
+}
+__device__ __forceinline__ void load_to_lds_far(const void *src, uint32_t lds) {  // a 64-bit address per lane
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(src) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char *)p;
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {  // at most N of this wave's vector-memory operations outstanding
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void slot_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// The rows of A as this wave requests them: instruction i of region h moves eight rows (128 bytes each, lane = row by
+// chunk).  The stage image is [row][128 bytes] with the eight 16-byte chunks of a row permuted by (row >> 1) & 7 (gfx950's
+// LDS has 64 banks and serves a 128-bit read 16 lanes at a time); the LDS side of the load is linear in the lane, so the
+// permutation is applied to the memory side.  A chunk past K repeats a chunk of the same row in the last k-step (the
+// packed tile holds zeros there).  FAR: matrices of 4 GiB and more, row numbers instead of byte offsets.
+template <bool FP8, int H, int I, bool FAR>
+struct RowRequests {
+  static constexpr int EPC = FP8 ? 16 : 8, KS = FP8 ? 128 : kBK;
+  i32x4 rsrc;
+  const unsigned char *base;
+  uint32_t at[H][I];
+  uint32_t pitch;   // bytes of a row of A
+  uint32_t chunks;  // this lane's chunk of instruction i, region h: 4 bits each
+  __device__ __forceinline__ void init(const GemmArgs &g) {
+    base = static_cast<const unsigned char *>(g.A);
+    pitch = (uint32_t)g.lda * (FP8 ? 1 : 2);
+    rsrc = lds_load_rsrc(base, 0xFFFFFFFFu);
+    chunks = 0;
+  }
+  // row = row of the tile (image position), a_row = row of the matrix
+  __device__ __forceinline__ void set(int h, int i, int row, uint32_t a_row, int lane) {
+    const uint32_t chunk = (lane & 7) ^ ((row >> 1) & 7);
+    chunks |= chunk << (4 * (h * I + i));
+    at[h][i] = FAR ? a_row : a_row * pitch + chunk * 16;
+  }
+  __device__ __forceinline__ uint32_t chunk_of(int h, int i) const { return (chunks >> (4 * (h * I + i))) & 7; }
+  // call before the first request of the last k-step
+  __device__ __forceinline__ void clip(int K, int kt_last) {
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+      for (int i = 0; i < I; ++i) {
+        const uint32_t c = chunk_of(h, i);
+        if (kt_last * KS + (int)c * EPC >= K) {
+          if (FAR) chunks &= ~(7u << (4 * (h * I + i))); else at[h][i] -= c * 16;
+        }
+      }
+  }
+  __device__ __forceinline__ void request(int h, int i, uint32_t lds, int kt) const {
+    if constexpr (FAR)
+      load_to_lds_far(base + (uint64_t)at[h][i] * pitch + chunk_of(h, i) * 16 + (uint32_t)kt * 128, lds);
+    else
+      load_to_lds(rsrc, lds, at[h][i], kt * 128);
+  }
+};
+
+// ------------------------------------------------------------------------------------------------
+// Full tiles (more than 128 rows): 256 x 256 outputs, two 64 KiB stages, 8 waves = 2 rows x 4 columns of RW x 64: RW = 128,
+// or 96 for tiles of at most 192 rows.
+// What bounds it: the matrix cores (2048 cycles per k-step and SIMD) and, as close, the LDS (192 KiB of fragment reads
+// and 64 KiB of slab per k-step), so both have to run all the time.  The wave rows take turns: while one row's four waves
+// (one per SIMD) issue the matrix instructions of a phase, the other row's read their next operands from the LDS and
+// request slabs from memory; a barrier ends each such slot and the rows swap.  A k-step is four phases, the quadrants of
+// the wave's block: rows 0-63 (A0) or the rest (A1) by columns 0-31 (B0) or 32-63 (B1), in the order A0 B0, A0 B1, A1 B1,
+// A1 B0, so that every operand is read once per k-step and the memory slots are about equal:
+//     M0: read B0(kt)            request A0(kt + 2)     then multiply A0 B0
+//     M1: read B1(kt), half A1   request B0(kt + 2)                   A0 B1
+//     M2: read the rest of A1    request B1(kt + 2)                   A1 B1
+//     M3: read A0(kt + 1)        request A1(kt + 2)                   A1 B0
+// A region of a stage is requested again right after both rows have read it, so a slab has 12 to 14 of the 16 slots of
+// two k-steps to arrive.  Each wave requests two KiB of every region (A1 of RW = 96: one); it waits for its own requests (the counts below are
+// the requests it has issued since) in a slot before the one in which either row reads the region, and the barrier at
+// that slot's end tells the others.
+// Measured: 16 384 rows x 4096 x 14336 (two GEMMs), dense rows: 1.22 PFLOP/s with slabs staged through registers, one
+// barrier per k-step and all waves in step -> 1.42 PFLOP/s (the vendor library's dense product reaches 1.44 to 1.50 on
+// the box); whole prefill step of that layer 9.73 -> 8.40 ms.
+// ------------------------------------------------------------------------------------------------
+template <bool FP8, int NB, int RW, bool LONE, bool FAR>
+struct PingPong {
+  static constexpr int kStage = 65536, kB = 32768;
+  static constexpr int NB0 = NB < 2 ? NB : 2, NB1 = NB > 2 ? NB - 2 : 0;  // row blocks with valid rows in A0, A1
+  static constexpr int I1 = RW == 128 ? 2 : 1;  // requests of A1 per wave
+  RowRequests<FP8, 2, 2, FAR> rows;
+  i32x4 rb;
+  uint32_t b_voff;
+  uint32_t a_lds[2], b_soff;  // offsets of the first KiB this wave requests: of A0 and A1, of B0 (B1: 4 KiB further)
+  uint32_t lds;            // LDS address of the stages
+  const unsigned char *smem;
+  int a_rd, b_rd;  // this lane's row / operand in a stage
+  int khalf, sw;
+  bf16x8 fa[2][2][4], fb[2][4];
+
+  __device__ __forceinline__ void request_a(int h, int kt) const {
+    const uint32_t l = lds + (kt & 1) * kStage + a_lds[h];
+    rows.request(h, 0, l, kt);
+    if (h == 0 || I1 == 2) rows.request(h, 1, l + 1024, kt);
+  }
+  __device__ __forceinline__ void request_b(int j, int kt) const {
+    const uint32_t l = lds + (kt & 1) * kStage + kB + b_soff + j * 4096, s = kt * kTileBytes + b_soff + j * 4096;
+    load_to_lds<LONE>(rb, l, b_voff, s);
+    load_to_lds<LONE>(rb, l + 1024, b_voff, s + 1024);
+  }
+  __device__ __forceinline__ void read_a(int h, int i, int kt) {
+    const unsigned char *s = smem + (kt & 1) * kStage + a_rd + (h * 2 + i) * 4096;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) fa[h][i][kk] = *reinterpret_cast<const bf16x8 *>(s + ((kk * 2 + khalf) ^ sw) * 16);
+  }
+  __device__ __forceinline__ void read_b(int j, int kt) {
+    const unsigned char *s = smem + (kt & 1) * kStage + b_rd + j * 4096;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) fb[j][kk] = *reinterpret_cast<const bf16x8 *>(s + kk * 1024);
+  }
+  template <int H, int J>
+  __device__ __forceinline__ void multiply(f32x16 (&acc)[NB][2]) {
+    constexpr int n = H == 0 ? NB0 : NB1;
+    if constexpr (n > 0) {
+      __builtin_amdgcn_s_setprio(1);
+      if constexpr (FP8) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+          for (int i = 0; i < n; ++i)
+            acc[H * 2 + i][J] = mfma_fp8_pair(fa[H][i][2 * p], fa[H][i][2 * p + 1], fb[J][2 * p], fb[J][2 * p + 1],
+                                              acc[H * 2 + i][J]);
+      } else {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+          for (int i = 0; i < n; ++i) acc[H * 2 + i][J] = mfma_bf16(fa[H][i][kk], fb[J][kk], acc[H * 2 + i][J]);
+      }
+      __builtin_amdgcn_s_setprio(0);
+    }
+    slot_barrier();
+  }
+  // LEFT: k-steps behind this one, 2 standing for two or more
+  template <int LEFT>
+  __device__ __forceinline__ void k_step(f32x16 (&acc)[NB][2], int kt) {
+    read_b(0, kt);
+    if (LEFT == 2) request_a(0, kt + 2);
+    wait_loads<LEFT == 2 ? 8 + I1 : LEFT == 1 ? 6 + I1 : 0>();
+    wait_lds_reads();
+    slot_barrier();
+    multiply<0, 0>(acc);
+    read_b(1, kt);
+    if (NB > 2) read_a(1, 0, kt);
+    if (LEFT == 2) request_b(0, kt + 2);
+    wait_lds_reads();
+    slot_barrier();
+    multiply<0, 1>(acc);
+    if (NB > 3) read_a(1, 1, kt);
+    if (LEFT == 2) request_b(1, kt + 2);
+    if (LEFT >= 1) wait_loads<LEFT == 2 ? 10 + I1 : 4 + I1>();
+    wait_lds_reads();
+    slot_barrier();
+    multiply<1, 1>(acc);
+    if (LEFT >= 1) {
+      read_a(0, 0, kt + 1);
+      if (NB > 1) read_a(0, 1, kt + 1);
+    }
+    if (LEFT == 2) request_a(1, kt + 2);
+    if (LEFT >= 1) wait_loads<LEFT == 2 ? 8 + 2 * I1 : 2 + I1>();
+    wait_lds_reads();
+    slot_barrier();
+    multiply<1, 0>(acc);
+  }
+  // K: reduction length; wm: wave row (scalar)
+  __device__ __forceinline__ void run(f32x16 (&acc)[NB][2], int KT, int K, int wm) {
+    const bool tail = K % RowRequests<FP8, 2, 2, FAR>::KS != 0;
+    auto slab = [&](int kt) {
+      if (tail && kt == KT - 1) rows.clip(K, KT - 1);
+      request_a(0, kt);
+      request_b(0, kt);
+      request_b(1, kt);
+      request_a(1, kt);
+    };
+    slab(0);
+    if (KT > 1) {
+      slab(1);
+      wait_loads<6 + I1>();
+    } else {
+      wait_loads<0>();
+    }
+    slot_barrier();
+    read_a(0, 0, 0);
+    if (NB > 1) read_a(0, 1, 0);
+    wait_lds_reads();
+    slot_barrier();
+    if (wm == 1) slot_barrier();  // the second row starts one slot later ...
+    int kt = 0;
+    for (; kt + 2 < KT; ++kt) {
+      if (tail && kt + 2 == KT - 1) rows.clip(K, KT - 1);
+      k_step<2>(acc, kt);
+    }
+    if (KT > 1) k_step<1>(acc, kt++);
+    k_step<0>(acc, kt);
+    if (wm == 0) slot_barrier();  // ... and the first row waits for it at the end
+  }
+};
+
+// ------------------------------------------------------------------------------------------------
+// Tiles of at most 128 rows: bound by the weight stream, so what counts is the bytes a CU keeps in flight.  A ring of
+// three stages (RW = 64: 16 KiB of rows and 32 KiB of weights; RW = 32, at most 64 rows: 8 and 32 KiB): two slabs are on
+// the way while the third is multiplied, one barrier per k-step.  The wave rows share the rows, RW each, so that all
+// four SIMDs have work.
+// ------------------------------------------------------------------------------------------------
+template <bool FP8, int NB, int RW, bool LONE>
+struct SlabRing {
+  static constexpr int kA = RW * 2 * 128, kStage = kA + kTileBytes, kStages = 3;
+  static constexpr int kRowLoads = RW / 32;                  // KiB of rows each wave requests per slab
+  static constexpr int kLoads = kRowLoads + 4;
+  RowRequests<FP8, 1, kRowLoads, false> rows;
+  i32x4 rb;
+  uint32_t b_voff, a_lds, b_soff, lds;
+  const unsigned char *smem;
+  int a_rd, b_rd, khalf, sw;
+
+  __device__ __forceinline__ void request(int stage, int kt) const {
+    const uint32_t l = lds + stage * kStage;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_to_lds<LONE>(rb, l + kA + b_soff + i * 1024, b_voff, kt * kTileBytes + b_soff + i * 1024);
+#pragma unroll
+    for (int i = 0; i < kRowLoads; ++i) rows.request(0, i, l + a_lds + i * 1024, kt);
+  }
+  __device__ __forceinline__ void multiply(f32x16 (&acc)[NB > 0 ? NB : 1][2], int stage) const {
+    if constexpr (NB > 0) {
+      const unsigned char *sa = smem + stage * kStage + a_rd, *sb = smem + stage * kStage + kA + b_rd;
+      bf16x8 fa[NB][4], fb[2][4];
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) fb[j][kk] = *reinterpret_cast<const bf16x8 *>(sb + j * 4096 + kk * 1024);
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+          fa[i][kk] = *reinterpret_cast<const bf16x8 *>(sa + i * 4096 + ((kk * 2 + khalf) ^ sw) * 16);
+      }
+      if constexpr (FP8) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+          for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              acc[i][j] = mfma_fp8_pair(fa[i][2 * p], fa[i][2 * p + 1], fb[j][2 * p], fb[j][2 * p + 1], acc[i][j]);
+      } else {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+          for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16(fa[i][kk], fb[j][kk], acc[i][j]);
+      }
+    }
+  }
+  __device__ __forceinline__ void run(f32x16 (&acc)[NB > 0 ? NB : 1][2], int KT, int K) {
+    const bool tail = K % RowRequests<FP8, 1, kRowLoads, false>::KS != 0;
+    auto ask = [&](int stage, int kt) {
+      if (tail && kt == KT - 1) rows.clip(K, KT - 1);
+      request(stage, kt);
+    };
+    ask(0, 0);
+    if (KT > 1) ask(1, 1);
+    int stage = 0;
+    for (int kt = 0; kt < KT; ++kt) {
+      // slab kt is here (this wave's part; the barrier: everybody's), and everybody has read slab kt - 1
+      if (kt + 1 < KT) wait_loads<kLoads>(); else wait_loads<0>();
+      wait_lds_reads();
+      slot_barrier();
+      const int next = stage == 0 ? 2 : stage - 1;  // the stage of slab kt - 1
+      if (kt + 2 < KT) ask(next, kt + 2);
+      multiply(acc, stage);
+      stage = stage == 2 ? 0 : stage + 1;
+    }
+  }
+};
+
+}  // namespace moe355

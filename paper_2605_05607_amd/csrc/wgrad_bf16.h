@@ -96,6 +96,7 @@ struct WgradArgs {
 // Experts with at most kThinSteps blocks of 64 rows are left to wgrad_thin_bf16_kernel (those without rows to
 // wgrad_zero_empty_kernel): their cost is writing the output, and that kernel's small workgroups overlap the stores of
 // one tile with the loads of the next on the same CU.
+constexpr int kStageBytes = 2 * kBM * kBK * 2;  // 64 KiB: A slab then B slab
 constexpr int kThinSteps = 2;
 constexpr int kThinTiles = 4;  // output tiles per workgroup of wgrad_thin_bf16_kernel
 
