@@ -74,7 +74,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
   // tiles share out of the L2.
   typename std::conditional<(RW > 64), PingPong<FP8, (NB > 0 ? NB : 1), RW, LONE, FAR>,
                             SlabRing<FP8, NB, (RW > 64 ? 64 : RW), LONE || RW == 32>>::type loop;
-  loop.rows.init(g);
+  loop.rows.init(g.A, g.lda);
   loop.rb = lds_load_rsrc(static_cast<const unsigned char *>(g.Bp) + ((size_t)(le * g.n_ntiles + nt) * g.n_ktiles) * kTileBytes,
                           (uint32_t)g.n_ktiles * kTileBytes);
   loop.lds = lds_address(smem);

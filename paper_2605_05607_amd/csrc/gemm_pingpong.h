@@ -81,9 +81,9 @@ struct RowRequests {
   uint32_t at[H][I];
   uint32_t pitch;   // bytes of a row of A
   uint32_t chunks;  // this lane's chunk of instruction i, region h: 4 bits each
-  __device__ __forceinline__ void init(const GemmArgs &g) {
-    base = static_cast<const unsigned char *>(g.A);
-    pitch = (uint32_t)g.lda * (FP8 ? 1 : 2);
+  __device__ __forceinline__ void init(const void *A, int lda) {
+    base = static_cast<const unsigned char *>(A);
+    pitch = (uint32_t)lda * (FP8 ? 1 : 2);
     rsrc = lds_load_rsrc(base, 0xFFFFFFFFu);
     chunks = 0;
   }
@@ -259,8 +259,8 @@ struct PingPong {
 
 // ------------------------------------------------------------------------------------------------
 // Tiles of at most 128 rows: bound by the weight stream, so what counts is the bytes a CU keeps in flight.  A ring of
-// three stages (RW = 64: 16 KiB of rows and 32 KiB of weights; RW = 32, at most 64 rows: 8 and 32 KiB): two slabs are on
-// the way while the third is multiplied, one barrier per k-step.  The wave rows share the rows, RW each, so that all
+// three stages (RW = 64: 16 KiB of rows and 32 KiB of weights; RW = 32, at most 64 rows: 8 and 32 KiB); a k-step reads all
+// its operands into registers first, so that the stage is free again and three slabs are on the way while it multiplies.  The wave rows share the rows, RW each, so that all
 // four SIMDs have work.
 // ------------------------------------------------------------------------------------------------
 template <bool FP8, int NB, int RW, bool LONE>
@@ -281,53 +281,54 @@ struct SlabRing {
 #pragma unroll
     for (int i = 0; i < kRowLoads; ++i) rows.request(0, i, l + a_lds + i * 1024, kt);
   }
-  __device__ __forceinline__ void multiply(f32x16 (&acc)[NB > 0 ? NB : 1][2], int stage) const {
-    if constexpr (NB > 0) {
-      const unsigned char *sa = smem + stage * kStage + a_rd, *sb = smem + stage * kStage + kA + b_rd;
-      bf16x8 fa[NB][4], fb[2][4];
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) fb[j][kk] = *reinterpret_cast<const bf16x8 *>(sb + j * 4096 + kk * 1024);
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-          fa[i][kk] = *reinterpret_cast<const bf16x8 *>(sa + i * 4096 + ((kk * 2 + khalf) ^ sw) * 16);
-      }
-      if constexpr (FP8) {
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
-#pragma unroll
-          for (int i = 0; i < NB; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-              acc[i][j] = mfma_fp8_pair(fa[i][2 * p], fa[i][2 * p + 1], fb[j][2 * p], fb[j][2 * p + 1], acc[i][j]);
-      } else {
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-          for (int i = 0; i < NB; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16(fa[i][kk], fb[j][kk], acc[i][j]);
-      }
-    }
-  }
   __device__ __forceinline__ void run(f32x16 (&acc)[NB > 0 ? NB : 1][2], int KT, int K) {
     const bool tail = K % RowRequests<FP8, 1, kRowLoads, false>::KS != 0;
     auto ask = [&](int stage, int kt) {
       if (tail && kt == KT - 1) rows.clip(K, KT - 1);
       request(stage, kt);
     };
-    ask(0, 0);
-    if (KT > 1) ask(1, 1);
+#pragma unroll
+    for (int i = 0; i < kStages; ++i)
+      if (i < KT) ask(i, i);
     int stage = 0;
     for (int kt = 0; kt < KT; ++kt) {
-      // slab kt is here (this wave's part; the barrier: everybody's), and everybody has read slab kt - 1
-      if (kt + 1 < KT) wait_loads<kLoads>(); else wait_loads<0>();
+      // slab kt is here (this wave's part; the barrier: everybody's)
+      if (kt + 2 < KT) wait_loads<2 * kLoads>(); else if (kt + 1 < KT) wait_loads<kLoads>(); else wait_loads<0>();
+      slot_barrier();
+      bf16x8 fa[NB > 0 ? NB : 1][4], fb[2][4];
+      if constexpr (NB > 0) {
+        const unsigned char *sa = smem + stage * kStage + a_rd, *sb = smem + stage * kStage + kA + b_rd;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+#pragma unroll
+          for (int j = 0; j < 2; ++j) fb[j][kk] = *reinterpret_cast<const bf16x8 *>(sb + j * 4096 + kk * 1024);
+#pragma unroll
+          for (int i = 0; i < NB; ++i)
+            fa[i][kk] = *reinterpret_cast<const bf16x8 *>(sa + i * 4096 + ((kk * 2 + khalf) ^ sw) * 16);
+        }
+      }
+      // everybody has read it: its stage takes the slab three steps on
       wait_lds_reads();
       slot_barrier();
-      const int next = stage == 0 ? 2 : stage - 1;  // the stage of slab kt - 1
-      if (kt + 2 < KT) ask(next, kt + 2);
-      multiply(acc, stage);
+      if (kt + kStages < KT) ask(stage, kt + kStages);
+      if constexpr (NB > 0) {
+        if constexpr (FP8) {
+#pragma unroll
+          for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+              for (int j = 0; j < 2; ++j)
+                acc[i][j] = mfma_fp8_pair(fa[i][2 * p], fa[i][2 * p + 1], fb[j][2 * p], fb[j][2 * p + 1], acc[i][j]);
+        } else {
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+              for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16(fa[i][kk], fb[j][kk], acc[i][j]);
+        }
+      }
       stage = stage == 2 ? 0 : stage + 1;
     }
   }

@@ -16,8 +16,7 @@ __global__ __launch_bounds__(256) void route_topk_reg_kernel(const float *__rest
   const int t = blockIdx.x * (blockDim.x >> 6) + wave;
   if (t >= T) return;  // whole wave leaves together
   const float *row = logits + (size_t)t * E;
-  uint32_t key[PER];
-  float val[PER];
+  RowPicker<PER> pick;
   if (PER % 4 == 0 && (E & 3) == 0) {
 #pragma unroll
     for (int q = 0; q < PER / 4; ++q) {
@@ -26,20 +25,16 @@ __global__ __launch_bounds__(256) void route_topk_reg_kernel(const float *__rest
       if (e0 < E) v = *reinterpret_cast<const float4 *>(row + e0);  // E % 4 == 0: the four are inside together
       const float vv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        val[q * 4 + u] = vv[u];
-        key[q * 4 + u] = e0 < E ? ordered_key(vv[u]) : 0u;
-      }
+      for (int u = 0; u < 4; ++u) pick.key[q * 4 + u] = e0 < E ? ordered_key(vv[u]) : 0u;
     }
   } else {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int e = lane * PER + i;
-      val[i] = e < E ? row[e] : 0.f;
-      key[i] = e < E ? ordered_key(val[i]) : 0u;
+      pick.key[i] = e < E ? ordered_key(row[e]) : 0u;
     }
   }
-  route_pick_registers<PER>(val, key, E, k, t, topk_idx, topk_w);
+  route_pick_registers<PER>(pick, E, k, t, topk_idx, topk_w);
 }
 
 constexpr int kRouteWaves = 4;  // waves (token rows) per block; fewer when E is large enough to crowd the LDS
@@ -171,7 +166,7 @@ __global__ __launch_bounds__(256) void route_topk_gate_reg_kernel(const float *_
   const int t = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (t >= T) return;  // whole wave leaves together
   const float *row = logits + (size_t)t * E;
-  uint32_t key[PER];
+  RowPicker<PER> pick;
   float val[PER], sel[PER];
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
@@ -182,19 +177,18 @@ __global__ __launch_bounds__(256) void route_topk_gate_reg_kernel(const float *_
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     const float base = gate == 0 ? val[i] : 1.0f / (1.0f + expf(-val[i]));
-    key[i] = lane * PER + i < E ? ordered_key(base + sel[i]) : 0u;
+    pick.key[i] = lane * PER + i < E ? ordered_key(base + sel[i]) : 0u;
   }
+  pick.sort();
   int my_e = 0;
-  float my_l = 0.f, m = 0.f;
   for (int j = 0; j < k; ++j) {
-    float l = 0.f;
-    const int e = pick_largest<PER>(val, key, E, l);
-    m = j == 0 ? l : fmaxf(m, l);
-    if (lane == j) {
-      my_e = e;
-      my_l = l;
-    }
+    uint32_t top;
+    const int e = pick.next(E, top);
+    if (lane == j) my_e = e;
   }
+  const float my_l = row[my_e];  // the logit behind the pick
+  float m = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_l), 0));
+  for (int j = 1; j < k; ++j) m = fmaxf(m, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_l), j)));
   const float mine = gate == 0 ? expf(my_l - m) : 1.0f / (1.0f + expf(-my_l));
   float sum = 0.f;
   for (int j = 0; j < k; ++j) sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), j));  // slot order

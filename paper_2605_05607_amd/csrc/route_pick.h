@@ -26,58 +26,76 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   return step(step(a, b), step(c, d));
 }
 
-// The largest key of a row in registers, lane l owning experts [l * PER, l * PER + PER): returns its expert (the lowest on
-// ties: a lane scans its run upwards with a strict comparison and, across lanes, the lowest lane that holds the maximum
-// wins), its value in `v`, and clears its key.  The same in every lane.
-template <int PER>
-__device__ __forceinline__ int pick_largest(const float (&val)[PER], uint32_t (&key)[PER], int E, float &v) {
-  const int lane = lane_id();
-  uint32_t bk = 0;
-  int bs = 0;
-  float bv = 0.f;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    if (key[i] > bk) {
-      bk = key[i];
-      bs = i;
-      bv = val[i];
-    }
-  }
-  const uint32_t top = wave_max_u32(bk);
-  const unsigned long long holders = __ballot(bk == top);
-  const int win = holders ? __builtin_ctzll(holders) : 0;
-  const int slot = __builtin_amdgcn_readlane(bs, win);
-  v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bv), win));
-  const int e = win * PER + slot;
-#pragma unroll
-  for (int i = 0; i < PER; ++i)
-    if (lane == win && i == slot) key[i] = 0u;  // picked
-  // k <= E, so an unpicked expert always exists; the clamp only guards against non-finite input
-  return e < E ? e : 0;
-}
+// The value behind a key (-0 comes back as +0).
+__device__ __forceinline__ float key_value(uint32_t k) { return __uint_as_float((k & 0x80000000u) ? k ^ 0x80000000u : ~k); }
 
-// The k picks of one token whose logits sit in registers (val = logit, key = ordered_key(logit), 0 for experts past E).
-// Lanes 0..k-1 write the picks (slot order = pick order) and their softmax weights renormalised over the picks.
+// A token row in registers, lane l owning experts [l * PER, l * PER + PER), from which the largest is picked again and
+// again (key = ordered_key(value), 0 for experts past E).  Every lane sorts its run once (adjacent exchanges on strict
+// comparison: equal keys keep the lower index in front), so that a pick only compares the lanes' heads.  Ties across lanes
+// go to the lowest lane.  (Scanning the run and clearing a key for every pick was two thirds of the routing kernel's
+// instructions, and those, not the logits, are what it takes its time for.)
 template <int PER>
-__device__ __forceinline__ void route_pick_registers(float (&val)[PER], uint32_t (&key)[PER], int E, int k, int t,
+struct RowPicker {
+  uint32_t key[PER];
+  int idx[PER];
+  __device__ __forceinline__ void sort() {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) idx[i] = i;
+#pragma unroll
+    for (int n = PER - 1; n > 0; --n)
+#pragma unroll
+      for (int i = 0; i < n; ++i) {
+        const bool up = key[i + 1] > key[i];
+        const uint32_t k = key[i];
+        const int x = idx[i];
+        key[i] = up ? key[i + 1] : k;
+        idx[i] = up ? idx[i + 1] : x;
+        key[i + 1] = up ? k : key[i + 1];
+        idx[i + 1] = up ? x : idx[i + 1];
+      }
+  }
+  // Expert and key of the largest value left; the same in every lane.
+  __device__ __forceinline__ int next(int E, uint32_t &top) {
+    top = wave_max_u32(key[0]);
+    const unsigned long long holders = __ballot(key[0] == top);
+    const int win = __builtin_ctzll(holders);  // (some lane holds the maximum)
+    const int e = win * PER + __builtin_amdgcn_readlane(idx[0], win);
+    const bool mine = lane_id() == win;
+#pragma unroll
+    for (int i = 0; i + 1 < PER; ++i) {
+      key[i] = mine ? key[i + 1] : key[i];
+      idx[i] = mine ? idx[i + 1] : idx[i];
+    }
+    key[PER - 1] = mine ? 0u : key[PER - 1];
+    // k <= E, so an unpicked expert always exists; the clamp only guards against non-finite input
+    return e < E ? e : 0;
+  }
+};
+
+// The k picks of one token whose logits' keys sit in `row`.  Lanes 0..k-1 write the picks (slot order = pick order) and
+// their softmax weights renormalised over the picks.
+template <int PER>
+__device__ __forceinline__ void route_pick_registers(RowPicker<PER> &row, int E, int k, int t,
                                                      int32_t *__restrict__ topk_idx, float *__restrict__ topk_w) {
   const int lane = lane_id();
+  row.sort();
   int my_e = 0;
-  float my_x = 0.f, first = 0.f, sum = 0.f;
+  uint32_t my_key = 0, first = 0;
   for (int j = 0; j < k; ++j) {
-    float v = 0.f;
-    const int e = pick_largest<PER>(val, key, E, v);
-    if (j == 0) first = v;                         // the largest logit: softmax shift
-    const float x = expf(v - first);
-    sum += x;                                      // slot order
+    uint32_t top;
+    const int e = row.next(E, top);
+    if (j == 0) first = top;  // the largest logit: softmax shift
     if (lane == j) {
       my_e = e;
-      my_x = x;
+      my_key = top;
     }
   }
+  const float x = expf(key_value(my_key) - key_value(first));
+  float sum = 0.f;
+  for (int j = 0; j < k; ++j) sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j));  // slot order
   if (lane < k) {
     topk_idx[(size_t)t * k + lane] = my_e;
-    topk_w[(size_t)t * k + lane] = my_x / sum;
+    topk_w[(size_t)t * k + lane] = x / sum;
   }
 }
 

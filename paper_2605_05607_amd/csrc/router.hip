@@ -2,144 +2,127 @@
 // the gate network"; reading: a bias-free linear map, one row of W_r per expert).  logits[T,E] = x[T,d] * W_r[E,d]^T
 // in fp32, summed in a fixed order, so that the routing built on it is reproducible.
 #include <algorithm>
+#include <cmath>
 
+#include "gemm_pingpong.h"
 #include "route_pick.h"
 
 namespace moe355 {
 
-typedef __bf16 rbf16_t;
-typedef rbf16_t rbf16x8 __attribute__((ext_vector_type(8)));
-typedef float rf32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t ru32x4 __attribute__((ext_vector_type(4)));
+constexpr int kRouterThreads = 512;  // 8 waves = 2 (token blocks) x 4 (expert blocks)
+constexpr int kRouterMaxSplit = 32;
+constexpr int kRouterStages = 3;
+// LDS bytes of one stage for a tile of BM tokens x BN experts: x slab then W_r slab
+constexpr int router_stage_bytes(int BM, int BN) { return (BM + BN) * kBK * 2; }
 
-constexpr int kRouterBN = 256;      // experts per workgroup
-constexpr int kRouterBK = 64;       // reduction indices per k-step
-constexpr int kRouterThreads = 512; // 8 waves = 2 (token blocks) x 4 (expert blocks of 64)
-constexpr int kRouterMaxSplit = 8;
-// LDS bytes of one stage for a tile of BM tokens: A slab then B slab
-constexpr int router_stage_bytes(int BM) { return (BM + kRouterBN) * kRouterBK * 2; }
-
-// One workgroup owns BM (64 or 128) tokens x 256 experts x one contiguous part of the reduction range (blockIdx.z): the
+// One workgroup owns BM tokens (64, 128, or 256) x BN experts (128 or 256) x one contiguous part of the reduction range: the
 // product is skinny (a few hundred experts), so its cost is reading x once, and cutting the reduction range is
-// what gives the chip enough workgroups.  Both operands have the reduction index contiguous in memory; a k-step
-// moves BM x 64 of x and 256 x 64 of W_r through the LDS (16 bytes per lane, coalesced along the rows, chunks
-// XOR-swizzled by (row >> 1) & 7 as in the expert GEMMs), double buffered, with the next four slabs in flight in
-// registers.  A part's block is written as fp32 to partial[part][T][E]; router_reduce_kernel adds the parts in
-// the order 0, 1, 2, ... so that the logits, and the routing built on them, are reproducible.  Every workgroup
-// streams its whole W_r part from the L2, so the 128-token tile halves the bytes that cross the L2 -> CU path (the
-// cost of this skinny product next to reading x once); the 64-token tile is for layers with too few tokens to
-// give every CU a workgroup otherwise.
-template <int BM>
-__global__ __launch_bounds__(kRouterThreads) void router_logits_bf16_kernel(const rbf16_t *__restrict__ x,
-                                                                            const rbf16_t *__restrict__ W,
+// what gives the chip enough workgroups.  What bounds it: every workgroup pulls its whole W_r part through its CU's L2
+// port next to its rows of x, (BM + BN) x 128 bytes per k-step at some 50 GB/s, and the partial sums are written and read
+// back; router_plan weighs the two.  Both operands have the reduction index contiguous in memory and go straight into the LDS (chunks
+// permuted as in the expert GEMMs), a ring of three stages.  A part's block is written as fp32
+// to partial[part][T][E]; the kernels below add the parts in the order 0, 1, 2, ... so that the logits, and the routing
+// built on them, are reproducible.
+template <int BM, int BN, bool FAR>
+__global__ __launch_bounds__(kRouterThreads) void router_logits_bf16_kernel(const bf16_t *__restrict__ x,
+                                                                            const bf16_t *__restrict__ W,
                                                                             float *__restrict__ partial, int T, int d,
-                                                                            int E, int steps_per_part) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // 2 stages
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                                                                            int E, int steps_per_part, int parts) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
   const int l31 = lane & 31, khalf = lane >> 5, sw = (lane >> 1) & 7;
-  constexpr int kStage = router_stage_bytes(BM);
-  constexpr int MB = BM / 64;  // 32-row token blocks per wave, and x rows staged per thread
-  const int t0 = blockIdx.y * BM, e0 = blockIdx.x * kRouterBN;
-  const int KT = (d + kRouterBK - 1) / kRouterBK;
-  const int kt_begin = min(KT, (int)blockIdx.z * steps_per_part), kt_end = min(KT, kt_begin + steps_per_part);
-
-  // staging: thread t moves 16-byte chunk t & 7 of x row t >> 3 and of W_r rows (t >> 3) + 64 i
-  const int chunk = tid & 7, row = tid >> 3;
-  const rbf16_t *xa0 = x + (size_t)min(t0 + row, T - 1) * d + chunk * 8;  // rows past the end: the last row, unused
-  const rbf16_t *xa1 = x + (size_t)min(t0 + row + 64, T - 1) * d + chunk * 8;
-  const rbf16_t *wb0 = W + (size_t)min(e0 + row, E - 1) * d + chunk * 8;
-  const rbf16_t *wb1 = W + (size_t)min(e0 + row + 64, E - 1) * d + chunk * 8;
-  const rbf16_t *wb2 = W + (size_t)min(e0 + row + 128, E - 1) * d + chunk * 8;
-  const rbf16_t *wb3 = W + (size_t)min(e0 + row + 192, E - 1) * d + chunk * 8;
-  const int dst = (row * 8 + (chunk ^ ((row >> 1) & 7))) * 16;  // + 8192 per 64 rows
-  // Register ring of kRing slabs: the slab of k-step kt is requested four steps before it moves to the LDS, so that
-  // the latency of the loads (x comes from HBM) is covered by four steps of work instead of one.  Every load is
-  // unconditional (past the end it repeats the last k-step) and a slab past the end of this part, or a chunk past d,
-  // is replaced by zeros in x when it is stored: the loop then has no data-dependent branch and a fixed number of
-  // loads between a load and its use.
-  constexpr int kRing = 4;
-  ru32x4 ra0[kRing], ra1[kRing], rb0[kRing], rb1[kRing], rb2[kRing], rb3[kRing];
-  const ru32x4 zero4 = {0u, 0u, 0u, 0u};
-#define MOE355_ROUTER_LOAD(S_, KT_)                                                 \
-  do {                                                                              \
-    const int kc_ = min((KT_), KT - 1);                                             \
-    const int off_ = kc_ * kRouterBK + chunk * 8 < d ? kc_ * kRouterBK : -chunk * 8; /* past d: chunk 0, valid */ \
-    ra0[S_] = *reinterpret_cast<const ru32x4 *>(xa0 + off_);                        \
-    if (MB > 1) ra1[S_] = *reinterpret_cast<const ru32x4 *>(xa1 + off_);            \
-    rb0[S_] = *reinterpret_cast<const ru32x4 *>(wb0 + off_);                        \
-    rb1[S_] = *reinterpret_cast<const ru32x4 *>(wb1 + off_);                        \
-    rb2[S_] = *reinterpret_cast<const ru32x4 *>(wb2 + off_);                        \
-    rb3[S_] = *reinterpret_cast<const ru32x4 *>(wb3 + off_);                        \
-  } while (0)
-#define MOE355_ROUTER_STORE(S_, STAGE, KT_)                                         \
-  do {                                                                              \
-    const bool live_ = (KT_) < kt_end && (KT_) * kRouterBK + chunk * 8 < d;         \
-    unsigned char *s_ = smem + (STAGE) * kStage;                                    \
-    *reinterpret_cast<ru32x4 *>(s_ + dst) = live_ ? ra0[S_] : zero4;                \
-    if (MB > 1) *reinterpret_cast<ru32x4 *>(s_ + 8192 + dst) = live_ ? ra1[S_] : zero4; \
-    *reinterpret_cast<ru32x4 *>(s_ + BM * 128 + dst) = rb0[S_];                     \
-    *reinterpret_cast<ru32x4 *>(s_ + BM * 128 + 8192 + dst) = rb1[S_];              \
-    *reinterpret_cast<ru32x4 *>(s_ + BM * 128 + 16384 + dst) = rb2[S_];             \
-    *reinterpret_cast<ru32x4 *>(s_ + BM * 128 + 24576 + dst) = rb3[S_];             \
-  } while (0)
-
-  rf32x16 acc[MB][2];
+  constexpr int kStage = router_stage_bytes(BM, BN), kA = BM * 128;
+  constexpr int MB = BM / 64;  // 32-row token blocks per wave, and KiB of x each wave requests per slab
+  constexpr int NJ = BN / 128, NW = BN / 64;  // 32-expert blocks per wave; KiB of W_r each wave requests per slab
+  constexpr int kLoads = MB + NW;
+  // consecutive workgroups (one per XCD) take the parts of one token tile: an XCD's L2 then holds its parts of W_r only
+  const int part = blockIdx.x % parts, t0 = blockIdx.x / parts * BM, e0 = blockIdx.y * BN;
+  const int KT = (d + kBK - 1) / kBK;
+  const int kt_begin = min(KT, part * steps_per_part), kt_end = min(KT, kt_begin + steps_per_part);
+  RowRequests<false, 1, MB, FAR> xr;
+  RowRequests<false, 1, NW, false> wr;
+  xr.init(x, d);
+  wr.init(W, d);
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    const int row = (wave * MB + i) * 8 + (lane >> 3);
+    xr.set(0, i, row, min(t0 + row, T - 1), lane);  // rows past the end: the last one, not stored
+  }
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    const int row = (wave * NW + i) * 8 + (lane >> 3);
+    wr.set(0, i, row, min(e0 + row, E - 1), lane);
+  }
+  const uint32_t lds = lds_address(smem);
+  const bool tail = d % kBK != 0;
+  auto request = [&](int stage, int kt) {
+    if (tail && kt == KT - 1) {
+      xr.clip(d, KT - 1);
+      wr.clip(d, KT - 1);
+    }
+    const uint32_t l = lds + stage * kStage;
+#pragma unroll
+    for (int i = 0; i < MB; ++i) xr.request(0, i, l + (wave * MB + i) * 1024, kt);
+#pragma unroll
+    for (int i = 0; i < NW; ++i) wr.request(0, i, l + kA + (wave * NW + i) * 1024, kt);
+  };
+  f32x16 acc[MB][NJ];
 #pragma unroll
   for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[mi][j][r] = 0.f;
-
-  // Step I_ of a round of four (k-step KT_): multiply the slab in stage I_ & 1, move the next slab from its ring slot
-  // to the other stage (last read before the previous barrier) and request that slot again five k-steps ahead.
-#define MOE355_ROUTER_STEP(I_, KT_)                                                                     \
-  do {                                                                                                  \
-    const unsigned char *sA = smem + ((I_) & 1) * kStage + (wm * (BM / 2) + l31) * 128;                 \
-    const unsigned char *sB = smem + ((I_) & 1) * kStage + BM * 128 + (wn * 64 + l31) * 128;            \
-    _Pragma("unroll") for (int kk = 0; kk < 4; ++kk) {                                                  \
-      const int slot = ((kk * 2 + khalf) ^ sw) * 16;                                                    \
-      const rbf16x8 fb0 = *reinterpret_cast<const rbf16x8 *>(sB + slot);                                \
-      const rbf16x8 fb1 = *reinterpret_cast<const rbf16x8 *>(sB + 4096 + slot);                         \
-      _Pragma("unroll") for (int mi = 0; mi < MB; ++mi) {                                               \
-        const rbf16x8 fa = *reinterpret_cast<const rbf16x8 *>(sA + mi * 4096 + slot);                   \
-        acc[mi][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb0, acc[mi][0], 0, 0, 0);             \
-        acc[mi][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb1, acc[mi][1], 0, 0, 0);             \
-      }                                                                                                 \
-    }                                                                                                   \
-    MOE355_ROUTER_STORE(((I_) + 1) % kRing, ((I_) + 1) & 1, (KT_) + 1);                                 \
-    MOE355_ROUTER_LOAD(((I_) + 1) % kRing, (KT_) + 1 + kRing);                                          \
-    __syncthreads();                                                                                    \
-  } while (0)
-  if (kt_begin < kt_end) {
-    MOE355_ROUTER_LOAD(0, kt_begin);
-    MOE355_ROUTER_LOAD(1, kt_begin + 1);
-    MOE355_ROUTER_LOAD(2, kt_begin + 2);
-    MOE355_ROUTER_LOAD(3, kt_begin + 3);
-    MOE355_ROUTER_STORE(0, 0, kt_begin);
-    MOE355_ROUTER_LOAD(0, kt_begin + kRing);
-    __syncthreads();
-    // whole rounds: a k-step past the end multiplies zeros
-    for (int kt = kt_begin; kt < kt_end; kt += kRing) {
-      MOE355_ROUTER_STEP(0, kt);
-      MOE355_ROUTER_STEP(1, kt + 1);
-      MOE355_ROUTER_STEP(2, kt + 2);
-      MOE355_ROUTER_STEP(3, kt + 3);
+#pragma unroll
+  for (int i = 0; i < kRouterStages; ++i)
+    if (kt_begin + i < kt_end) request(i, kt_begin + i);
+  int stage = 0;
+  for (int kt = kt_begin; kt < kt_end; ++kt) {
+    // slab kt is here (this wave's part; the barrier: everybody's)
+    if (kt + 2 < kt_end) wait_loads<2 * kLoads>(); else if (kt + 1 < kt_end) wait_loads<kLoads>(); else wait_loads<0>();
+    slot_barrier();
+    const unsigned char *sA = smem + stage * kStage + (wm * (BM / 2) + l31) * 128;
+    const unsigned char *sB = smem + stage * kStage + kA + (wn * 32 * NJ + l31) * 128;
+    bf16x8 fa[MB][4], fb[NJ][4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const int slot = ((kk * 2 + khalf) ^ sw) * 16;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) fb[j][kk] = *reinterpret_cast<const bf16x8 *>(sB + j * 4096 + slot);
+#pragma unroll
+      for (int mi = 0; mi < MB; ++mi) fa[mi][kk] = *reinterpret_cast<const bf16x8 *>(sA + mi * 4096 + slot);
     }
+    // everybody has read it: its stage takes the slab three steps on, so that three are on the way while this one is
+    // multiplied
+    wait_lds_reads();
+    slot_barrier();
+    if (kt + kRouterStages < kt_end) request(stage, kt + kRouterStages);
+    if (tail && kt == KT - 1) {  // chunks past d repeat another chunk in both operands: zero those of x
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+        if (kt * kBK + kk * 16 + khalf * 8 >= d) {
+#pragma unroll
+          for (int mi = 0; mi < MB; ++mi) fa[mi][kk] = bf16x8{};
+        }
+    }
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[mi][j] = mfma_bf16(fa[mi][kk], fb[j][kk], acc[mi][j]);
+    stage = stage == 2 ? 0 : stage + 1;
   }
-#undef MOE355_ROUTER_STEP
-#undef MOE355_ROUTER_LOAD
-#undef MOE355_ROUTER_STORE
   // accumulator register r of lane l is C[8 * (r / 4) + 4 * (l / 32) + r % 4][l % 32] of its 32 x 32 block
-  float *out = partial + (size_t)blockIdx.z * T * E;
+  float *out = partial + (size_t)part * T * E;
 #pragma unroll
   for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int t = t0 + wm * (BM / 2) + mi * 32 + 8 * (r >> 2) + 4 * khalf + (r & 3), e = e0 + wn * 64 + j * 32 + l31;
+        const int t = t0 + wm * (BM / 2) + mi * 32 + 8 * (r >> 2) + 4 * khalf + (r & 3), e = e0 + (wn * NJ + j) * 32 + l31;
         if (t < T && e < E) out[(size_t)t * E + e] = acc[mi][j][r];
       }
 }
@@ -156,8 +139,7 @@ __global__ __launch_bounds__(256) void router_reduce_topk_kernel(const float *__
   const int t = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (t >= T) return;  // whole wave leaves together
   const float *row = partial + (size_t)t * E;
-  uint32_t key[PER];
-  float val[PER];
+  RowPicker<PER> pick;
   if (PER % 4 == 0 && (E & 3) == 0) {
 #pragma unroll
     for (int q = 0; q < PER / 4; ++q) {
@@ -165,18 +147,22 @@ __global__ __launch_bounds__(256) void router_reduce_topk_kernel(const float *__
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
       if (e0 < E) {  // E % 4 == 0: the four are inside together
         v = *reinterpret_cast<const float4 *>(row + e0);
-        for (int p = 1; p < parts; ++p) {
-          const float4 a = *reinterpret_cast<const float4 *>(row + (size_t)p * n + e0);
-          v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
+        for (int p = 1; p < parts; p += 8) {  // eight parts' loads in flight
+          float4 a[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (p + u < parts) a[u] = *reinterpret_cast<const float4 *>(row + (size_t)(p + u) * n + e0);
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (p + u < parts) {
+              v.x += a[u].x; v.y += a[u].y; v.z += a[u].z; v.w += a[u].w;
+            }
         }
         if (logits) *reinterpret_cast<float4 *>(logits + (size_t)t * E + e0) = v;
       }
       const float vv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        val[q * 4 + u] = vv[u];
-        key[q * 4 + u] = e0 < E ? ordered_key(vv[u]) : 0u;
-      }
+      for (int u = 0; u < 4; ++u) pick.key[q * 4 + u] = e0 < E ? ordered_key(vv[u]) : 0u;
     }
   } else {
 #pragma unroll
@@ -185,14 +171,21 @@ __global__ __launch_bounds__(256) void router_reduce_topk_kernel(const float *__
       float v = 0.f;
       if (e < E) {
         v = row[e];
-        for (int p = 1; p < parts; ++p) v += row[(size_t)p * n + e];
+        for (int p = 1; p < parts; p += 8) {
+          float a[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (p + u < parts) a[u] = row[(size_t)(p + u) * n + e];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (p + u < parts) v += a[u];
+        }
         if (logits) logits[(size_t)t * E + e] = v;
       }
-      val[i] = v;
-      key[i] = e < E ? ordered_key(v) : 0u;
+      pick.key[i] = e < E ? ordered_key(v) : 0u;
     }
   }
-  route_pick_registers<PER>(val, key, E, k, t, topk_idx, topk_w);
+  route_pick_registers<PER>(pick, E, k, t, topk_idx, topk_w);
 }
 
 // logits = partial[0] + partial[1] + ... in that order.
@@ -200,7 +193,15 @@ __global__ __launch_bounds__(256) void router_reduce_topk_kernel(const float *__
 __global__ __launch_bounds__(256) void router_reduce_kernel(const float *partial, float *logits, size_t n, int parts) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
     float v = partial[i];
-    for (int q = 1; q < parts; ++q) v += partial[(size_t)q * n + i];
+    for (int p = 1; p < parts; p += 8) {  // eight parts' loads in flight
+      float a[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (p + u < parts) a[u] = partial[(size_t)(p + u) * n + i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (p + u < parts) v += a[u];
+    }
     logits[i] = v;
   }
 }
@@ -222,64 +223,83 @@ __global__ __launch_bounds__(256) void router_logits_f32_kernel(const float *__r
 
 using namespace moe355;
 
-// Token tile of the bf16 kernel: 128 where that still gives every CU a workgroup, else 64.
-static int router_tile(const moe_shape *s) {
-  const int kt = ceil_div(s->d, kRouterBK);
-  const int wgs128 = ceil_div(s->E, kRouterBN) * ceil_div(s->T > 0 ? s->T : 1, 128) * std::min(kRouterMaxSplit, kt);
-  return wgs128 >= 512 ? 128 : 64;
+// Tile and number of parts of the bf16 product, by estimated time: rounds of 256 workgroups, each some 3 us of start and
+// then its k-steps at what a CU pulls through its L2 port (56 GB/s) or all of them together pull of x (4.3 TB/s), plus the
+// partial sums written and read back (and 0.08 us each for the latency of adding them).
+// (Measured on E = 256, d = 7168: 1000 tokens 64 x 256 tiles and 16 parts 16.0 us against 20.2 us for 128 x 256 and 32 parts;
+// 4096 tokens 30.0 us (4 parts) against 32.7 us (8 parts); 16384 tokens 84 us with 128 x 256 against 96 us with 64 x 256;
+// E = 128, d = 2880, 8000 tokens: 24.5 us with 252 workgroups, 32.2 us with 315.)
+struct RouterPlan {
+  int bm, bn, parts;
+};
+static RouterPlan router_plan(const moe_shape *s) {
+  const int T = s->T > 0 ? s->T : 1, kt = ceil_div(s->d, kBK);
+  const int bn = s->E <= 128 ? 128 : 256;
+  RouterPlan best{64, bn, 1};
+  double t_best = 1e30;
+  for (int bm = 64; bm <= (bn == 128 ? 256 : 128); bm *= 2) {
+    const double tiles = (double)ceil_div(s->E, bn) * ceil_div(T, bm);
+    for (int parts = 1; parts <= std::min(kRouterMaxSplit, kt); ++parts) {
+      const double rounds = std::ceil(tiles * parts / 256);
+      const double cus = tiles * parts > 128 ? 256 : tiles * parts;
+      const double step = std::max({0.35, (bm + bn) * 128 / 56e3, cus * bm * 128 / 4.3e6});
+      const double t = rounds * (3.0 + ceil_div(kt, parts) * step) + 8.0 * parts * T * s->E / 4.2e6 + 0.08 * parts;
+      if (t < t_best) {
+        t_best = t;
+        best = {bm, bn, parts};
+      }
+    }
+  }
+  return best;
 }
 
-// Parts the reduction range is cut into: enough to give every CU a workgroup, at most kRouterMaxSplit, and never
-// more than there are k-steps.
-static int router_split(const moe_shape *s) {
-  const int tiles = ceil_div(s->E, kRouterBN) * ceil_div(s->T > 0 ? s->T : 1, router_tile(s));
-  const int kt = ceil_div(s->d, kRouterBK);
-  return std::max(1, std::min(std::min(kRouterMaxSplit, kt), ceil_div(256, tiles)));
+static size_t router_bytes(const moe_shape *s, int parts) {
+  return align_up((size_t)parts * (size_t)(s->T > 0 ? s->T : 1) * s->E * sizeof(float) + 1, 256);
 }
 
 extern "C" size_t moe_router_workspace_bytes(const moe_shape *shape) {
   Derived dv;
   if (check_shape(shape, &dv) != MOE_OK) return 0;
   if (shape->dtype != MOE_BF16) return 256;
-  const int parts = router_split(shape);
-  return align_up((parts > 1 ? (size_t)parts : 0) * (size_t)(shape->T > 0 ? shape->T : 1) * shape->E * sizeof(float) + 1,
-                  256);
+  const int parts = router_plan(shape).parts;
+  return router_bytes(shape, parts > 1 ? parts : 0);
 }
 
 extern "C" size_t moe_route_from_x_workspace_bytes(const moe_shape *shape) {
   Derived dv;
   if (check_shape(shape, &dv) != MOE_OK) return 0;
   // the partial sums of every part (one part at least: the logits need not be stored anywhere else)
-  const int parts = shape->dtype == MOE_BF16 ? router_split(shape) : 1;
-  return align_up((size_t)parts * (size_t)(shape->T > 0 ? shape->T : 1) * shape->E * sizeof(float), 256);
+  return router_bytes(shape, shape->dtype == MOE_BF16 ? router_plan(shape).parts : 1);
 }
 
 // The product into `partial` (parts > 1) or straight into `direct` (one part).
-static int launch_router_gemm(const moe_shape *shape, const void *x, const void *W_r, float *partial, float *direct,
-                              int *parts_out, hipStream_t st) {
-  const int parts = router_split(shape);
-  *parts_out = parts;
-  const int bm = router_tile(shape);
-  const int steps_per_part = ceil_div(ceil_div(shape->d, kRouterBK), parts);
-  const dim3 grid(ceil_div(shape->E, kRouterBN), ceil_div(shape->T, bm), parts);
-  if (grid.y > 65535) return MOE_ERR_UNSUPPORTED;
+static int launch_router_gemm(const moe_shape *shape, const RouterPlan &plan, const void *x, const void *W_r,
+                              float *partial, float *direct, hipStream_t st) {
+  const int parts = plan.parts;
+  const int steps_per_part = ceil_div(ceil_div(shape->d, kBK), parts);
+  const dim3 grid((unsigned)ceil_div(shape->T, plan.bm) * parts, ceil_div(shape->E, plan.bn));
   float *out = parts > 1 ? partial : direct;
-  static std::atomic<uint64_t> done64{0}, done128{0};
-  if (bm == 128) {
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&router_logits_bf16_kernel<128>), 2 * router_stage_bytes(128),
-                           done128))
-      return MOE_ERR_HIP;
-    hipLaunchKernelGGL(router_logits_bf16_kernel<128>, grid, dim3(kRouterThreads), 2 * router_stage_bytes(128), st,
-                       static_cast<const rbf16_t *>(x), static_cast<const rbf16_t *>(W_r), out, shape->T, shape->d,
-                       shape->E, steps_per_part);
+  const bool far = (int64_t)shape->T * shape->d * 2 >= (int64_t)1 << 32;
+#define MOE355_ROUTER_(BM_, BN_, FAR_)                                                                                 \
+  do {                                                                                                                 \
+    static std::atomic<uint64_t> done{0};                                                                              \
+    const int lds = kRouterStages * router_stage_bytes(BM_, BN_);                                                      \
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&router_logits_bf16_kernel<BM_, BN_, FAR_>), lds, done))      \
+      return MOE_ERR_HIP;                                                                                              \
+    hipLaunchKernelGGL((router_logits_bf16_kernel<BM_, BN_, FAR_>), grid, dim3(kRouterThreads), lds, st,               \
+                       static_cast<const bf16_t *>(x), static_cast<const bf16_t *>(W_r), out, shape->T, shape->d,      \
+                       shape->E, steps_per_part, parts);                                                               \
+  } while (0)
+#define MOE355_ROUTER(BM_, BN_) \
+  do { if (far) MOE355_ROUTER_(BM_, BN_, true); else MOE355_ROUTER_(BM_, BN_, false); } while (0)
+  if (plan.bn == 128) {
+    if (plan.bm == 64) MOE355_ROUTER(64, 128); else if (plan.bm == 128) MOE355_ROUTER(128, 128);
+    else MOE355_ROUTER(256, 128);
   } else {
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&router_logits_bf16_kernel<64>), 2 * router_stage_bytes(64),
-                           done64))
-      return MOE_ERR_HIP;
-    hipLaunchKernelGGL(router_logits_bf16_kernel<64>, grid, dim3(kRouterThreads), 2 * router_stage_bytes(64), st,
-                       static_cast<const rbf16_t *>(x), static_cast<const rbf16_t *>(W_r), out, shape->T, shape->d,
-                       shape->E, steps_per_part);
+    if (plan.bm == 64) MOE355_ROUTER(64, 256); else MOE355_ROUTER(128, 256);
   }
+#undef MOE355_ROUTER
+#undef MOE355_ROUTER_
   return launch_status();
 }
 
@@ -290,14 +310,14 @@ extern "C" int moe_router_logits(const moe_shape *shape, const void *x, const vo
   if (rc != MOE_OK) return rc;
   if (!x || !W_r || !logits) return MOE_ERR_INVALID_ARG;
   if ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(W_r)) % 16 != 0) return MOE_ERR_INVALID_ARG;
-  if (!workspace || workspace_bytes < moe_router_workspace_bytes(shape)) return MOE_ERR_WORKSPACE;
+  const RouterPlan plan = shape->dtype == MOE_BF16 ? router_plan(shape) : RouterPlan{0, 0, 1};
+  const int parts = plan.parts;
+  if (!workspace || workspace_bytes < router_bytes(shape, parts > 1 ? parts : 0)) return MOE_ERR_WORKSPACE;
   if (shape->T == 0) return MOE_OK;
   hipStream_t st = (hipStream_t)stream;
   begin_launches();
   if (shape->dtype == MOE_BF16) {
-    int parts = 1;
-    if ((rc = launch_router_gemm(shape, x, W_r, static_cast<float *>(workspace), logits, &parts, st)) != MOE_OK)
-      return rc;
+    if ((rc = launch_router_gemm(shape, plan, x, W_r, static_cast<float *>(workspace), logits, st)) != MOE_OK) return rc;
     if (parts > 1) {
       const size_t n = (size_t)shape->T * shape->E;
       hipLaunchKernelGGL(router_reduce_kernel, dim3((unsigned)std::min<size_t>(2048, (n + 255) / 256)), dim3(256), 0,
@@ -322,16 +342,17 @@ extern "C" int moe_route_from_x(const moe_shape *shape, const void *x, const voi
   if (rc != MOE_OK) return rc;
   if (!x || !W_r || !topk_idx || !topk_w) return MOE_ERR_INVALID_ARG;
   if ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(W_r)) % 16 != 0) return MOE_ERR_INVALID_ARG;
-  if (!workspace || workspace_bytes < moe_route_from_x_workspace_bytes(shape)) return MOE_ERR_WORKSPACE;
+  const RouterPlan plan = shape->dtype == MOE_BF16 ? router_plan(shape) : RouterPlan{0, 0, 1};
+  const int parts = plan.parts;
+  if (!workspace || workspace_bytes < router_bytes(shape, parts)) return MOE_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(workspace) % 16 != 0) return MOE_ERR_INVALID_ARG;
   if (shape->T == 0) return MOE_OK;
   hipStream_t st = (hipStream_t)stream;
   begin_launches();
   float *partial = static_cast<float *>(workspace);
   const size_t n = (size_t)shape->T * shape->E;
-  int parts = 1;
   if (shape->dtype == MOE_BF16) {
-    if ((rc = launch_router_gemm(shape, x, W_r, partial, partial, &parts, st)) != MOE_OK) return rc;
+    if ((rc = launch_router_gemm(shape, plan, x, W_r, partial, partial, st)) != MOE_OK) return rc;
   } else {
     hipLaunchKernelGGL(router_logits_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
                        static_cast<const float *>(x), static_cast<const float *>(W_r), partial, shape->T, shape->d,
