@@ -260,15 +260,15 @@ static bool use_stream(const moe_shape *s, const Derived &dv, int elt) {
 }
 
 // Work groups per strip of GEMM-2: one, unless so few strips of 32 columns exist that a second launch (~5 us) costs less
-// than what the missing CUs would have pulled (a CU pulls ~55 GB/s, the chip ~6.5 TB/s, i.e. what ~120 CUs pull).
+// than what the missing CUs would have pulled (a CU pulls ~36 GB/s here, the chip ~6.5 TB/s, i.e. what ~180 CUs pull).
 static int stream_groups(const moe_shape *s, const Derived &dv, int elt) {
   const int strips = ceil_div(s->d, 32);
   const double busy = std::min<double>(dv.E_loc, (double)s->T * s->k * dv.E_loc / s->E);
-  const double us = busy * s->f * s->d * elt / 55e3;  // one CU, microseconds
+  const double us = busy * s->f * s->d * elt / 36e3;  // one CU, microseconds
   int best = 1;
-  double t_best = us / std::min(strips, 120);
+  double t_best = us / std::min(strips, 180);
   for (int g = 2; g <= std::min(8, std::min(s->k, dv.E_loc)); ++g) {  // (the partial sums live in the o rows)
-    const double t = us / std::min(strips * g, 120) + 5.0;
+    const double t = us / std::min(strips * g, 180) + 5.0;
     if (t < t_best) {
       t_best = t;
       best = g;
