@@ -243,43 +243,116 @@ __global__ __launch_bounds__(kTableThreads) void dispatch_place_kernel(
 }
 
 // ------------------------------------------------------------------------------------------------
-// Small batches: all tables in ONE launch of one workgroup.  Pair p = it * 1024 + thread; the pairs of one wave in one
-// iteration form a "virtual wave" v.  Lanes with the same expert are found with one ballot per bit of the expert id, the
-// group's first lane writes its size to sub[v][expert] (no atomics), an exclusive sum over v and a scan over the experts
-// turn the sizes into first rows, and the rank of a lane in its group does the rest; the same for (token, rank) entries
-// over the lanes that hold the first slot of their token on a rank.  What bounds it is latency: one read of topk_idx and
-// six barriers (measured at T = 96, k = 8: 5.5 us against 4.7 + 10.5 us for the two kernels above, which pay a second
-// launch and a round trip of the histograms through memory).
+// One thread per pair: the form used where a workgroup's share of the pairs and its counters fit the LDS.  Pair it * 1024 +
+// thread of the workgroup; the pairs of one wave in one iteration form a "virtual wave" v.  Lanes with the same expert are
+// found with one ballot per bit of the expert id, the group's first lane writes its size to sub[v][expert] (no atomics),
+// an exclusive sum over v and a scan over the experts turn the sizes into first rows, and the rank of a lane in its group
+// does the rest; the same for (token, rank) entries over the lanes that hold the first slot of their token on a rank.
+// What bounds it is latency: one read of topk_idx and six barriers, where the walk above makes a serial pass per wave.
+//   CHUNKED = false: small batches, all tables in ONE launch of one workgroup (96 tokens, k = 8: 5.5 us against 4.7 + 10.5 us
+//   for the two kernels above, which pay a second launch and a round trip of the histograms through memory);
+//   CHUNKED = true: one workgroup per chunk of whole tokens, on the chunk histograms of dispatch_hist_pairs_kernel (8192
+//   tokens, k = 8, 128 experts: 5.1 + 11.4 us against 5.2 + 14.8 us; 5003 tokens, k = 4: 5.1 + 9.1 against 5.1 + 11.3 us).
 // ------------------------------------------------------------------------------------------------
 constexpr int kSmallThreads = 1024;
-constexpr int kSmallPairs = 4096;              // most pairs
-constexpr size_t kSmallLds = 128 * 1024;       // most LDS
+constexpr int kSmallPairs = 4096;         // most pairs of the one-launch form
+constexpr size_t kSmallLds = 128 * 1024;  // most LDS
 
 // [ITERS][1024] expert ids | [virtual waves][E + R] counts, then first rows | [E + R] totals | [18] scan scratch
 constexpr size_t small_lds_bytes(int iters, int E, int R) {
   return ((size_t)iters * (kSmallThreads + (kSmallThreads / kWave) * (E + R)) + (E + R) + 18) * sizeof(int);
 }
 
+// Slots of this pair's token that lie on rank r, among the first n ones; s_e holds the expert ids of the token at p0.
+__device__ __forceinline__ uint32_t slots_on_rank(const int *s_e, int p0, int n, int r, int epr) {
+  uint32_t m = 0;
+  for (int jj = 0; jj < n; ++jj) {
+    const int e = s_e[p0 + jj];
+    if (e >= r * epr && e < (r + 1) * epr) m |= 1u << jj;
+  }
+  return m;
+}
+
+// Chunk histograms, one thread per pair (LDS counters); layout of dispatch_hist_kernel's.
 template <int ITERS>
-__global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(
-    const int32_t *__restrict__ topk_idx, int T, int E, int k, int R, int ebits, int rbits, int32_t *__restrict__ counts,
+__global__ __launch_bounds__(kSmallThreads) void dispatch_hist_pairs_kernel(const int32_t *__restrict__ topk_idx, int T,
+                                                                            int E, int k, int R, int tpc,
+                                                                            int32_t *__restrict__ chunk_cnt,
+                                                                            int32_t *__restrict__ chunk_rcnt) {
+  extern __shared__ int sm[];
+  int *cnt = sm, *s_e = sm + E + R;  // [E + R] | [ITERS * 1024]
+  const int tid = threadIdx.x, c = blockIdx.x, epr = E / R;
+  const int n = min(T - c * tpc, tpc) * k;
+  const int32_t *src = topk_idx + (size_t)c * tpc * k;
+  int e[ITERS];
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it) {
+    const int p = it * kSmallThreads + tid;
+    e[it] = p < n ? src[p] : -1;
+  }
+  for (int i = tid; i < E + R; i += kSmallThreads) cnt[i] = 0;
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it) s_e[it * kSmallThreads + tid] = e[it];
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it) {
+    if (e[it] < 0 || e[it] >= E) continue;
+    const int p = it * kSmallThreads + tid, j = p % k, r = e[it] / epr;
+    atomicAdd(&cnt[e[it]], 1);
+    if (slots_on_rank(s_e, p - j, j, r, epr) == 0) atomicAdd(&cnt[E + r], 1);  // first slot of its (token, rank)
+  }
+  __syncthreads();
+  for (int i = tid; i < E; i += kSmallThreads) chunk_cnt[(size_t)i * kMaxChunks + c] = cnt[i];
+  for (int i = tid; i < R; i += kSmallThreads) chunk_rcnt[(size_t)i * kMaxChunks + c] = cnt[E + i];
+}
+
+template <int ITERS, bool CHUNKED>
+__global__ __launch_bounds__(kSmallThreads) void dispatch_pairs_kernel(
+    const int32_t *__restrict__ topk_idx, int T, int E, int k, int R, int tpc, int nch, int ebits, int rbits,
+    const int32_t *__restrict__ chunk_cnt, const int32_t *__restrict__ chunk_rcnt, int32_t *__restrict__ counts,
     int32_t *__restrict__ offsets, int32_t *__restrict__ rank_counts, int32_t *__restrict__ rank_offsets,
     int32_t *__restrict__ perm, int32_t *__restrict__ inv_perm, int32_t *__restrict__ dedup_tok,
     uint32_t *__restrict__ dedup_mask, int32_t *__restrict__ pair_to_dedup) {
   extern __shared__ int sm[];
   constexpr int kWaves = kSmallThreads / kWave, NV = ITERS * kWaves;
-  int *s_e = sm;                              // expert of every pair
-  int *sub = s_e + ITERS * kSmallThreads;     // [NV][E + R]
-  int *tot = sub + NV * (E + R);
+  int *s_e = sm;                           // expert of every pair of this workgroup
+  int *sub = s_e + ITERS * kSmallThreads;  // [NV][E + R]
+  int *tot = sub + NV * (E + R);           // totals over all pairs
   int *scratch = tot + E + R;
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-  const int n = T * k, epr = E / R, C = E + R;
+  const int epr = E / R, C = E + R, c = CHUNKED ? blockIdx.x : 0;
+  const int base = CHUNKED ? c * tpc * k : 0;  // first pair of this workgroup: whole tokens
+  const int n = CHUNKED ? min(T - c * tpc, tpc) * k : T * k;
   int e[ITERS];
 #pragma unroll
   for (int it = 0; it < ITERS; ++it) {
     const int p = it * kSmallThreads + tid;
-    e[it] = p < n ? topk_idx[p] : -1;
+    e[it] = p < n ? topk_idx[base + p] : -1;
     if (e[it] >= E) e[it] = -1;
+  }
+  int before = 0;  // pairs of column tid in earlier chunks
+  if constexpr (CHUNKED) {
+    if (tid < C) {  // (C <= 1024)
+      const int4 *row = reinterpret_cast<const int4 *>(tid < E ? chunk_cnt + (size_t)tid * kMaxChunks
+                                                               : chunk_rcnt + (size_t)(tid - E) * kMaxChunks);
+      int4 v[kMaxChunks / 4];
+#pragma unroll
+      for (int q = 0; q < kMaxChunks / 4; ++q)
+        if (q * 4 < nch) v[q] = row[q];
+      int total = 0;
+#pragma unroll
+      for (int q = 0; q < kMaxChunks / 4; ++q) {
+        if (q * 4 >= nch) continue;
+        const int vals[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int val = q * 4 + u < nch ? vals[u] : 0;  // slots of chunks that do not exist hold stale workspace bytes
+          total += val;
+          before += q * 4 + u < c ? val : 0;
+        }
+      }
+      tot[tid] = total;
+    }
   }
   for (int i = tid; i < NV * C; i += kSmallThreads) sub[i] = 0;
 #pragma unroll
@@ -296,15 +369,8 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(
     const unsigned long long grp = match_lanes(valid, e[it], ebits);
     in_grp[it] = __popcll(grp & lower);
     if (valid && in_grp[it] == 0) sub[v * C + e[it]] = __popcll(grp);
-    // slots of the same token on the same rank
-    const int j = p % k, p0 = p - j;
-    const int r = valid ? e[it] / epr : -1;
-    uint32_t m = 0;
-    if (valid)
-      for (int jj = 0; jj < k; ++jj) {
-        const int ee = s_e[p0 + jj];
-        if (ee >= r * epr && ee < (r + 1) * epr) m |= 1u << jj;
-      }
+    const int j = p % k, r = valid ? e[it] / epr : -1;
+    const uint32_t m = valid ? slots_on_rank(s_e, p - j, k, r, epr) : 0;
     r_of[it] = r;
     slots[it] = m;
     first[it] = valid && (m & ((1u << j) - 1u)) == 0;
@@ -313,7 +379,7 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(
     if (first[it] && r_in_grp[it] == 0) sub[v * C + E + r] = __popcll(rgrp);
   }
   __syncthreads();
-  // one scan over experts, then ranks: thread i owns columns i * ipt ..; the ranks' part starts from zero again
+  // columns (experts, then ranks): thread i owns columns i * ipt ..; exclusive sums over the virtual waves
   const int ipt = (C + kSmallThreads - 1) / kSmallThreads;
   const int lo = min(C, tid * ipt), hi = min(C, lo + ipt);
   int local = 0;
@@ -321,17 +387,17 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(
     int run = 0;
 #pragma unroll 16
     for (int v = 0; v < NV; ++v) {
-      const int c = sub[v * C + i];
+      const int x = sub[v * C + i];
       sub[v * C + i] = run;
-      run += c;
+      run += x;
     }
-    tot[i] = run;
-    local += run;
+    if (!CHUNKED) tot[i] = run;
+    local += CHUNKED ? tot[i] : run;
   }
+  // one scan over all columns; the ranks' part starts from zero again
   int total;
   int off = block_exclusive_scan(local, scratch, &total);
-  // pairs with a valid expert = the part of the scan that belongs to the experts
-  if (lo <= E && E < hi) {
+  if (lo <= E && E < hi) {  // pairs with a valid expert = the part of the scan that belongs to the experts
     int o = off;
     for (int i = lo; i < E; ++i) o += tot[i];
     scratch[17] = o;
@@ -341,39 +407,41 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(
   for (int i = lo; i < hi; ++i) {
     const int mine = tot[i];
     const int first_row = i < E ? off : off - n_valid;
-    if (i < E) {
-      counts[i] = mine;
-      offsets[i] = first_row;
-    } else {
-      rank_counts[i - E] = mine;
-      rank_offsets[i - E] = first_row;
+    if (c == 0) {
+      if (i < E) {
+        counts[i] = mine;
+        offsets[i] = first_row;
+      } else {
+        rank_counts[i - E] = mine;
+        rank_offsets[i - E] = first_row;
+      }
     }
 #pragma unroll 16
-    for (int v = 0; v < NV; ++v) sub[v * C + i] += first_row;
+    for (int v = 0; v < NV; ++v) sub[v * C + i] += first_row + before;
     off += mine;
   }
-  if (tid == 0) {
+  if (c == 0 && tid == 0) {
     offsets[E] = n_valid;
     rank_offsets[R] = total - n_valid;
   }
   __syncthreads();
-  const int ndedup = T * min(k, R);
+  const int npairs = T * k, ndedup = T * min(k, R);
 #pragma unroll
   for (int it = 0; it < ITERS; ++it) {
     const int p = it * kSmallThreads + tid, v = it * kWaves + wave;
     if (e[it] >= 0) {
       const int row = sub[v * C + e[it]] + in_grp[it];
-      inv_perm[p] = row;
-      perm[row] = p;
+      inv_perm[base + p] = row;
+      if (row >= 0 && row < npairs) perm[row] = base + p;
     } else if (p < n) {
-      inv_perm[p] = -1;
-      pair_to_dedup[p] = -1;
+      inv_perm[base + p] = -1;
+      pair_to_dedup[base + p] = -1;
     }
     int pos = -1;
     if (first[it]) {
       pos = sub[v * C + E + r_of[it]] + r_in_grp[it];
-      if (pos < ndedup) {
-        dedup_tok[pos] = p / k;
+      if (pos >= 0 && pos < ndedup) {
+        dedup_tok[pos] = (base + p) / k;
         dedup_mask[pos] = slots[it];
       }
     }
@@ -383,7 +451,7 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_small_kernel(
 #pragma unroll
   for (int it = 0; it < ITERS; ++it) {
     const int p = it * kSmallThreads + tid;
-    if (e[it] >= 0) pair_to_dedup[p] = s_e[p - p % k + __builtin_ctz(slots[it])];
+    if (e[it] >= 0) pair_to_dedup[base + p] = s_e[p - p % k + __builtin_ctz(slots[it])];
   }
 }
 
@@ -414,24 +482,53 @@ static int build_dispatch_launches(const moe_shape *shape, const int32_t *topk_i
   int ebits = 0, rbits = 0;
   while ((1 << ebits) < E) ++ebits;
   while ((1 << rbits) < R) ++rbits;
-  // Small batches (up to kSmallPairs pairs whose counters fit the LDS): one launch of one workgroup.
-  const int iters = T > 0 && (int64_t)T * k <= kSmallPairs ? (T * k <= kSmallThreads ? 1 : T * k <= 2 * kSmallThreads ? 2 : 4) : 0;
-  if (iters && small_lds_bytes(iters, E, R) <= kSmallLds) {
-    begin_launches();
-    static std::atomic<uint64_t> done1{0}, done2{0}, done4{0};
-#define MOE355_SMALL(ITERS_, DONE_)                                                                              \
-  do {                                                                                                           \
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&dispatch_small_kernel<ITERS_>), (int)kSmallLds, DONE_)) \
-      return MOE_ERR_HIP;                                                                                        \
-    hipLaunchKernelGGL(dispatch_small_kernel<ITERS_>, dim3(1), dim3(kSmallThreads),                              \
-                       small_lds_bytes(ITERS_, E, R), st, topk_idx, T, E, k, R, ebits, rbits,    \
-                       out->counts, out->offsets, out->rank_counts, out->rank_offsets, out->perm, out->inv_perm, \
-                       out->dedup_tok, out->dedup_mask, out->pair_to_dedup);                                     \
+#define MOE355_PAIRS(ITERS_, CHUNKED_, GRID_, TPC_, NCH_, CNT_, RCNT_)                                              \
+  do {                                                                                                              \
+    static std::atomic<uint64_t> done{0};                                                                           \
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&dispatch_pairs_kernel<ITERS_, CHUNKED_>), (int)kSmallLds, \
+                           done))                                                                                   \
+      return MOE_ERR_HIP;                                                                                           \
+    hipLaunchKernelGGL((dispatch_pairs_kernel<ITERS_, CHUNKED_>), dim3(GRID_), dim3(kSmallThreads),                 \
+                       small_lds_bytes(ITERS_, E, R), st, topk_idx, T, E, k, R, TPC_, NCH_, ebits, rbits, CNT_,     \
+                       RCNT_, out->counts, out->offsets, out->rank_counts, out->rank_offsets, out->perm,            \
+                       out->inv_perm, out->dedup_tok, out->dedup_mask, out->pair_to_dedup);                         \
   } while (0)
-    if (iters == 1) MOE355_SMALL(1, done1); else if (iters == 2) MOE355_SMALL(2, done2); else MOE355_SMALL(4, done4);
-#undef MOE355_SMALL
+  // Small batches (up to kSmallPairs pairs whose counters fit the LDS): one launch of one workgroup.
+  const auto iters_of = [](int64_t pairs) { return pairs <= 1024 ? 1 : pairs <= 2048 ? 2 : pairs <= 4096 ? 4 : 8; };
+  if (T > 0 && (int64_t)T * k <= kSmallPairs && small_lds_bytes(iters_of(T * k), E, R) <= kSmallLds) {
+    begin_launches();
+    const int iters = iters_of(T * k);
+    const int32_t *none = nullptr;
+    if (iters == 1) MOE355_PAIRS(1, false, 1, T, 1, none, none);
+    else if (iters == 2) MOE355_PAIRS(2, false, 1, T, 1, none, none);
+    else MOE355_PAIRS(4, false, 1, T, 1, none, none);
     return launch_status();
   }
+  // One thread per pair, as few chunks as keep a workgroup's share at 1024 pairs, up to the chunk limit; beyond eight
+  // pairs per thread, or with more counters than fit, the kernels that walk (below).
+  if (T > 0 && E + R <= kSmallThreads) {
+    const int tpc_p = std::max(ceil_div(T, kMaxChunks), std::max(1, kSmallThreads / k)), nch_p = ceil_div(T, tpc_p);
+    const int64_t pairs = (int64_t)tpc_p * k;
+    const int iters = iters_of(pairs);
+    if (pairs <= 8 * kSmallThreads && small_lds_bytes(iters, E, R) <= kSmallLds) {
+      begin_launches();
+      int32_t *cnt = chunk_ws, *rcnt = chunk_ws + (size_t)kMaxChunks * E;
+      const size_t lds_hist = (size_t)(E + R + iters * kSmallThreads) * sizeof(int);
+#define MOE355_CHUNKED(ITERS_)                                                                                     \
+  do {                                                                                                             \
+    hipLaunchKernelGGL(dispatch_hist_pairs_kernel<ITERS_>, dim3(nch_p), dim3(kSmallThreads), lds_hist, st, topk_idx, \
+                       T, E, k, R, tpc_p, cnt, rcnt);                                                              \
+    int rc_;                                                                                                       \
+    if ((rc_ = launch_status()) != MOE_OK) return rc_;                                                             \
+    MOE355_PAIRS(ITERS_, true, nch_p, tpc_p, nch_p, cnt, rcnt);                                                    \
+  } while (0)
+      if (iters == 1) MOE355_CHUNKED(1); else if (iters == 2) MOE355_CHUNKED(2); else if (iters == 4) MOE355_CHUNKED(4);
+      else MOE355_CHUNKED(8);
+#undef MOE355_CHUNKED
+      return launch_status();
+    }
+  }
+#undef MOE355_PAIRS
   const int nch = chunking(T, &tpc);
   int32_t *chunk_cnt = chunk_ws;
   int32_t *chunk_rcnt = chunk_cnt + (size_t)kMaxChunks * E;

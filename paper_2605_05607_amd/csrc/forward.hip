@@ -46,9 +46,9 @@ static Ws carve(void *workspace, const FwdLayout &L) {
   return w;
 }
 
-// LDS of the tile-table kernel: three (with the row -> tile map: four) per-expert arrays and the scan scratch.
+// LDS of the tile-table kernel: four (with the row -> tile map: five) per-expert arrays, a counter and the scan scratch.
 static size_t prep_lds_bytes(const Derived &dv, bool combine_tables) {
-  return (size_t)((combine_tables ? 4 : 3) * dv.E_loc + 1 + 17) * sizeof(int);
+  return (size_t)((combine_tables ? 5 : 4) * dv.E_loc + 2 + 1 + 17) * sizeof(int);
 }
 
 // sole != nullptr: also mark the rows GEMM-2 may write straight to y (see the GEMM-2 epilogue);
@@ -56,10 +56,13 @@ static size_t prep_lds_bytes(const Derived &dv, bool combine_tables) {
 static int launch_prep(const moe_shape *s, const Derived &dv, const moe_dispatch *tb, const int32_t *topk_idx,
                        const float *topk_w, const Ws &w, int32_t *sole, hipStream_t st,
                        bool combine_tables = false) {
-  const int blocks = (int)std::min<int64_t>(1024, std::max<int64_t>(1, (dv.P_cap + 255) / 256));
-  hipLaunchKernelGGL(fwd_prep_kernel, dim3(blocks), dim3(256), prep_lds_bytes(dv, combine_tables), st,
+  static std::atomic<uint64_t> done{0};
+  static_assert((5 * kMaxExperts + 20) * sizeof(int) <= 96 * 1024, "per-expert tables fit the LDS");
+  if (!allow_dynamic_lds(reinterpret_cast<const void *>(&fwd_prep_kernel), 96 * 1024, done)) return MOE_ERR_HIP;
+  const int blocks = (int)std::min<int64_t>(512, std::max<int64_t>(1, (dv.P_cap + 255) / 256));
+  hipLaunchKernelGGL(fwd_prep_kernel, dim3(2 * blocks), dim3(256), prep_lds_bytes(dv, combine_tables), st,
                      tb->offsets, tb->perm, topk_w, s->T, s->k, dv.e_lo, dv.E_loc, dv.bm, (int)dv.P_cap, dv.max_mtiles,
-                     dv.nt1, dv.nt2, w.header, w.work1, w.work2, w.row_tok, w.row_w, topk_idx, sole, w.tile_ready,
+                     dv.nt1, dv.nt2, blocks, w.header, w.work1, w.work2, w.row_tok, w.row_w, topk_idx, sole, w.tile_ready,
                      combine_tables ? w.row_tile : nullptr, combine_tables ? w.tile_done : nullptr);
   return launch_status();
 }
@@ -393,7 +396,7 @@ static int forward_common(const moe_shape *shape, const void *x, const int32_t *
   if ((gemm_launches == 1 || gemm_launches == 3) && shape->dtype != MOE_BF16) return MOE_ERR_UNSUPPORTED;
   const bool with_combine = gemm_launches == 3;
   if (with_combine && (!fused || fp8 || keep)) return MOE_ERR_UNSUPPORTED;
-  if (with_combine && prep_lds_bytes(dv, true) > 64 * 1024) return MOE_ERR_UNSUPPORTED;  // the tile table's LDS
+  if (with_combine && dv.E_loc > 4091) return MOE_ERR_UNSUPPORTED;  // (bound of this form)
   const bool pipelined = with_combine || (gemm_launches ? gemm_launches : moe_forward_gemm_launches(shape)) == 1;
   // a work item packs its N tile and its M-tile id into one word
   if (std::max(dv.nt1, dv.nt2) >= 1 << kTileShift || dv.max_mtiles >= 1 << (31 - kTileShift)) return MOE_ERR_UNSUPPORTED;

@@ -30,90 +30,107 @@ namespace moe355 {
 // the matrix cores.
 constexpr int kStreamRows = 64;
 
+// Two kinds of blocks run side by side, since each is a short chain of dependent reads and together they made one twice as
+// long: the first list_blocks blocks write the work lists (each rebuilds the small per-expert tables in its LDS), the others
+// the per-row metadata.  (8192 tokens, k = 8, 128 experts: 9.6 us with every block doing both, one after the other, and
+// looking each item's expert up in `offsets`; 6.3 us.)
 __global__ __launch_bounds__(256) void fwd_prep_kernel(const int32_t *__restrict__ offsets,
                                                        const int32_t *__restrict__ perm,
                                                        const float *__restrict__ topk_w, int T, int k, int e_lo,
                                                        int E_loc, int bm, int P_cap, int max_mtiles, int nt1, int nt2,
-                                                       int32_t *__restrict__ header, int4 *__restrict__ work1,
-                                                       int4 *__restrict__ work2, int32_t *__restrict__ row_tok,
-                                                       float *__restrict__ row_w,
+                                                       int list_blocks, int32_t *__restrict__ header,
+                                                       int4 *__restrict__ work1, int4 *__restrict__ work2,
+                                                       int32_t *__restrict__ row_tok, float *__restrict__ row_w,
                                                        const int32_t *__restrict__ topk_idx,
                                                        int32_t *__restrict__ row_sole,
                                                        int32_t *__restrict__ tile_ready,
                                                        int32_t *__restrict__ row_tile,
                                                        int32_t *__restrict__ tile_done) {
-  // LDS: full0[E_loc + 1] first full M tile of each expert | part[E_loc] rows of its partial tile (0 = none) |
-  //      order[E_loc] partial tiles: first the large ones (> kStreamRows rows), largest first, then the
-  //      streaming ones, largest first | only with row_tile: pos[E_loc] place of each expert's partial tile in
-  //      `order` | 17 ints of scan scratch
-  extern __shared__ int lds[];
-  int *full0 = lds;
-  int *part = full0 + E_loc + 1;
-  int *order = part + E_loc;
-  int *pos = order + E_loc;
-  int *scratch = row_tile ? pos + E_loc : pos;
-  const int base = offsets[e_lo];
-  const int P = max(0, min(P_cap, offsets[e_lo + E_loc] - base));
-  const long long npairs = (long long)T * k;
-  for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < P; r += gridDim.x * blockDim.x) {
-    int p = perm[base + r];
-    p = p < 0 ? 0 : (p >= npairs ? (int)(npairs - 1) : p);
-    const int t = p / k;
-    row_tok[r] = t;
-    row_w[r] = topk_w[p];
-    if (row_sole) {
-      // a row that is its token's only local slot needs no reduction: GEMM-2 writes it straight to y
-      int n_local = 0;
-      for (int j = 0; j < k; ++j) {
-        const int e = topk_idx[(size_t)t * k + j];
-        n_local += e >= e_lo && e < e_lo + E_loc;
+  const int base = offsets[e_lo], end = offsets[e_lo + E_loc];
+  const int P = max(0, min(P_cap, end - base));
+  if ((int)blockIdx.x >= list_blocks) {
+    const long long npairs = (long long)T * k;
+    const int stride = (gridDim.x - list_blocks) * blockDim.x;
+    for (int r = (blockIdx.x - list_blocks) * blockDim.x + threadIdx.x; r < P; r += stride) {
+      int p = perm[base + r];
+      p = p < 0 ? 0 : (p >= npairs ? (int)(npairs - 1) : p);
+      const int t = p / k;
+      row_tok[r] = t;
+      row_w[r] = topk_w[p];
+      if (row_sole) {
+        // a row that is its token's only local slot needs no reduction: GEMM-2 writes it straight to y
+        int n_local = 0;
+#pragma unroll 8
+        for (int j = 0; j < k; ++j) {
+          const int e = topk_idx[(size_t)t * k + j];
+          n_local += e >= e_lo && e < e_lo + E_loc;
+        }
+        row_sole[r] = n_local == 1 ? t : -1;
       }
-      row_sole[r] = n_local == 1 ? t : -1;
     }
+    return;
   }
-  // Every block rebuilds the small per-expert tables (cheap) so that the lists can be written grid-wide.
+  // LDS: part[E_loc] per expert: rows of its partial tile (0 = none) << 16 | E_loc - expert, i.e. ordered by rows, then by
+  //      lower expert | start[E_loc + 1] first row | full0[E_loc + 1] first tile of class F | order[E_loc] experts with a
+  //      streaming partial tile, largest first | only with row_tile: pos[E_loc] place of each expert's partial tile in
+  //      `order` | number of streaming tiles | 17 ints of scan scratch
+  extern __shared__ int lds[];
+  int *part = lds;
+  int *start = part + E_loc;
+  int *full0 = start + E_loc + 1;
+  int *order = full0 + E_loc + 1;
+  int *pos = order + E_loc;
+  int *s_small = row_tile ? pos + E_loc : pos;
+  int *scratch = s_small + 1;
+  const int nthr = list_blocks * blockDim.x, me = blockIdx.x * blockDim.x + threadIdx.x;
+  for (int le = threadIdx.x; le <= E_loc; le += blockDim.x) start[le] = min(P, offsets[e_lo + le] - base);
+  if (threadIdx.x == 0) *s_small = 0;
+  __syncthreads();
   // An expert with cnt rows has cnt / bm full tiles and, if cnt % bm != 0, one partial tile.
   const int ipt = (E_loc + blockDim.x - 1) / blockDim.x;
   const int lo = min(E_loc, (int)threadIdx.x * ipt);
   const int hi = min(E_loc, lo + ipt);
+  const auto tiles_of = [&](int le) {  // tiles of class F: a large partial tile walks with the expert's full tiles
+    const int cnt = max(0, start[le + 1] - start[le]);
+    return cnt / bm + ((cnt % bm) > kStreamRows);
+  };
   int local_full = 0, local_small = 0;
   for (int le = lo; le < hi; ++le) {
-    const int cnt = max(0, min(P, offsets[e_lo + le + 1] - base) - min(P, offsets[e_lo + le] - base));
-    part[le] = cnt % bm;
-    local_full += cnt / bm + ((cnt % bm) > kStreamRows);  // a large partial tile walks with the expert's full tiles
-    local_small += (cnt % bm) != 0 && (cnt % bm) <= kStreamRows;
+    const int rest = max(0, start[le + 1] - start[le]) % bm;
+    part[le] = rest << 16 | (E_loc - le);
+    local_full += tiles_of(le);
+    local_small += rest != 0 && rest <= kStreamRows;
   }
-  int n_full, n_big, n_small;
-  int run = block_exclusive_scan(local_full, scratch, &n_full);
+  if (local_small) atomicAdd(s_small, local_small);
+  int n_full;
+  int run = block_exclusive_scan(local_full, scratch, &n_full);  // (its barriers publish part[] and the count as well)
   for (int le = lo; le < hi; ++le) {
-    const int cnt = max(0, min(P, offsets[e_lo + le + 1] - base) - min(P, offsets[e_lo + le] - base));
     full0[le] = run;
-    run += cnt / bm + ((cnt % bm) > kStreamRows);
+    run += tiles_of(le);
   }
   if (threadIdx.x == 0) full0[E_loc] = n_full;
-  n_big = 0;  // (no separate class any more: see the list order below)
-  (void)block_exclusive_scan(local_small, scratch, &n_small);
-  __syncthreads();
-  // rank sort of the streaming partial tiles (for very many experts keep the expert order)
+  // rank sort of the streaming partial tiles: how many of them compare larger
   for (int le = lo; le < hi; ++le) {
     const int mine = part[le];
-    if (mine == 0 || mine > kStreamRows) continue;
-    int rank = 0;
-    for (int o = 0; o < E_loc; ++o) {
-      const int po = part[o];
-      if (po == 0 || po > kStreamRows) continue;
-      rank += E_loc <= 1024 ? (po > mine || (po == mine && o < le)) : (o < le);
+    if ((mine >> 16) == 0 || (mine >> 16) > kStreamRows) continue;
+    const unsigned above = ((kStreamRows + 1) << 16) - mine - 1;  // keys of streaming tiles lie below (kStreamRows + 1) << 16
+    int rank = 0, o = 0;
+#pragma unroll 4
+    for (; o + 4 <= E_loc; o += 4) {
+      const int4 v = *reinterpret_cast<const int4 *>(part + o);
+      rank += ((unsigned)(v.x - mine - 1) < above) + ((unsigned)(v.y - mine - 1) < above) +
+              ((unsigned)(v.z - mine - 1) < above) + ((unsigned)(v.w - mine - 1) < above);
     }
+    for (; o < E_loc; ++o) rank += (unsigned)(part[o] - mine - 1) < above;
     order[rank] = le;
     if (row_tile) pos[le] = rank;
   }
   __syncthreads();
   n_full = min(n_full, max_mtiles);
-  n_big = min(n_big, max_mtiles - n_full);
-  n_small = min(n_small, max_mtiles - n_full - n_big);
-  const int n_tiles = n_full + n_big + n_small;
+  const int n_small = min(*s_small, max_mtiles - n_full);
+  const int n_tiles = n_full + n_small;
   const int n1 = n_tiles * nt1, n2 = n_tiles * nt2;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (me == 0) {
     header[0] = n1;
     header[1] = P;
     header[2] = base;
@@ -121,54 +138,52 @@ __global__ __launch_bounds__(256) void fwd_prep_kernel(const int32_t *__restrict
     header[4] = n_tiles;
     for (int i = 8; i <= 24; ++i) header[i] = 0;
   }
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_tiles; i += gridDim.x * blockDim.x) {
+  for (int i = me; i < n_tiles; i += nthr) {
     tile_ready[i] = 0;
     if (tile_done) tile_done[i] = 0;
   }
   // M tile of every local row (the resident kernel's Combine stage looks up the tile whose GEMM-2 items it waits for)
   if (row_tile) {
-    for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < P; r += gridDim.x * blockDim.x) {
+    for (int r = me; r < P; r += nthr) {
       // expert of row r: largest le whose first row is <= r
       int a = 0, b = E_loc;
       while (b - a > 1) {
         const int mid = (a + b) >> 1;
-        if (min(P, offsets[e_lo + mid] - base) <= r) a = mid; else b = mid;
+        if (start[mid] <= r) a = mid; else b = mid;
       }
-      const int start = min(P, offsets[e_lo + a] - base);
-      const int cnt = min(P, offsets[e_lo + a + 1] - base) - start;
-      const int mt = (r - start) / bm;
-      const int tile = (mt < cnt / bm || part[a] > kStreamRows) ? full0[a] + mt : n_full + pos[a];
+      const int cnt = start[a + 1] - start[a];
+      const int mt = (r - start[a]) / bm;
+      const int tile = (mt < cnt / bm || (part[a] >> 16) > kStreamRows) ? full0[a] + mt : n_full + pos[a];
       row_tile[r] = min(tile, max(n_tiles - 1, 0));
     }
   }
-  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n1 + n2; q += gridDim.x * blockDim.x) {
+  for (int q = me; q < n1 + n2; q += nthr) {
     const bool second = q >= n1;
     const int Nt = second ? nt2 : nt1;
     const int qq = second ? q - n1 : q;
-    // List order.  Classes: F = full tiles and partial tiles of more than kStreamRows rows, S = streaming partial
-    // tiles (class B, partial tiles as a list of their own, is empty: n_big = 0).
+    // List order.  Classes: F = full tiles and partial tiles of more than kStreamRows rows, S = streaming partial tiles.
     //   [ mixed chunks: each 32-item chunk holds 8 items of S, then 24 items of F, so that some CUs of every XCD
     //     stream weights from HBM while the others multiply; only when S is at least half as large as F,
     //     otherwise the few S items would just push full tiles into an extra round ]
-    //   [ rest of F ] [ B, largest first ] [ rest of S ]          -- the launch ends with its shortest items
-    const int nF = n_full * Nt, nS = n_small * Nt, nB = n_big * Nt;
+    //   [ rest of F ] [ rest of S, largest first ]  -- the launch ends with its shortest items
+    const int nF = n_full * Nt, nS = n_small * Nt;
     constexpr int nsc = 8, nfc = kChunk - nsc;
     const int n_mix = (nF > 0 && 2 * nS >= nF) ? min(nF / nfc, nS / nsc) : 0;
     // F items that share operands form groups of gsz consecutive list positions; gsz follows the F share of a chunk
     const int gsz = n_mix > 0 ? nfc : kChunk;
-    int cls, idx;  // class 0 = F, 1 = B, 2 = S; idx = position inside the class list
+    bool streams;  // class S
+    int idx;       // position inside the class list
     if (qq < n_mix * kChunk) {
       const int c = qq / kChunk, sl = qq % kChunk;
-      if (sl < nsc) { cls = 2; idx = c * nsc + sl; } else { cls = 0; idx = c * nfc + (sl - nsc); }
+      streams = sl < nsc;
+      idx = streams ? c * nsc + sl : c * nfc + (sl - nsc);
     } else {
-      int r = qq - n_mix * kChunk;
-      const int f_rem = nF - n_mix * nfc;
-      if (r < f_rem) { cls = 0; idx = n_mix * nfc + r; }
-      else if ((r -= f_rem) < nB) { cls = 1; idx = r; }
-      else { cls = 2; idx = n_mix * nsc + (r - nB); }
+      const int r = qq - n_mix * kChunk, f_rem = nF - n_mix * nfc;
+      streams = r >= f_rem;
+      idx = streams ? n_mix * nsc + (r - f_rem) : n_mix * nfc + r;
     }
-    int le, mt, nt, rows, tile;
-    if (cls == 0) {
+    int le, mt, nt, tile;
+    if (!streams) {
       // expert that owns F position idx: largest le with full0[le] * Nt <= idx
       int a = 0, b = E_loc;
       while (b - a > 1) {
@@ -200,24 +215,16 @@ __global__ __launch_bounds__(256) void fwd_prep_kernel(const int32_t *__restrict
         mt = mg * Mg + r % Mcur;
         nt = ng * G + r / Mcur;
       }
-      rows = bm;
       tile = full0[le] + mt;
     } else {
-      le = order[(cls == 2 ? n_big : 0) + idx / Nt];
-      tile = n_full + (cls == 2 ? n_big : 0) + idx / Nt;
+      le = order[idx / Nt];
+      tile = n_full + idx / Nt;
       nt = idx % Nt;
-      const int cnt = min(P, offsets[e_lo + le + 1] - base) - min(P, offsets[e_lo + le] - base);
-      mt = cnt / bm;
-      rows = part[le];
+      mt = (start[le + 1] - start[le]) / bm;
     }
-    if (cls == 0) {
-      // the expert's last tile of this class may be its large partial tile
-      const int cnt = min(P, offsets[e_lo + le + 1] - base) - min(P, offsets[e_lo + le] - base);
-      if (mt >= cnt / bm) rows = part[le];
-    }
-    const int start = min(P, offsets[e_lo + le] - base);
-    const int cnt_le = min(P, offsets[e_lo + le + 1] - base) - start;
-    const int4 item = make_int4(le, start + mt * bm, rows | (cnt_le <= bm ? kItemLone : 0), nt | (tile << kTileShift));
+    const int first = start[le], cnt = start[le + 1] - first;
+    const int rows = mt < cnt / bm ? bm : part[le] >> 16;  // the last tile of class F may be the expert's large partial tile
+    const int4 item = make_int4(le, first + mt * bm, rows | (cnt <= bm ? kItemLone : 0), nt | (tile << kTileShift));
     if (second) work2[qq] = item; else work1[qq] = item;
   }
 }

@@ -33,6 +33,15 @@ def test_small_tables_bit_exact(oracle, T, E, k, R):
     G.assert_tables_equal(got, oracle, logits, cfg)
 
 
+# the same tables from chunks of whole tokens: one chunk more than the one-launch form, the last chunk short, one to eight
+# pairs per thread around their edges, counters that just fit (E + R = 1024) and that do not
+@pytest.mark.parametrize("T,E,k,R", [(513, 128, 8, 8), (640, 512, 7, 8), (8192, 256, 8, 8), (8193, 256, 8, 4),
+                                     (16385, 64, 8, 2), (32769, 32, 8, 1), (65600, 16, 8, 1), (700, 1016, 6, 8),
+                                     (700, 1017, 6, 9), (300, 64, 32, 4), (9000, 1000, 8, 8)])
+def test_chunked_tables_bit_exact(oracle, T, E, k, R):
+    test_small_tables_bit_exact(oracle, T, E, k, R)
+
+
 EDGES = {
     "one_token": dict(T=1),
     "rows_31": dict(T=31, router="zipf"),
