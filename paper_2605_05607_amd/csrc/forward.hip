@@ -259,6 +259,9 @@ static bool use_stream(const moe_shape *s, const Derived &dv, int elt) {
   if (s->dtype != MOE_BF16 || s->T > kStreamTokens || dv.E_loc > kStreamExperts || s->d < 512 || s->f < 512 ||
       stream2_lds_bytes(s->T, (int)dv.P_cap, dv.E_loc) > 160 * 1024)
     return false;
+  // 32-bit offsets into the rows (2 GiB) and into one packed panel of 256 columns (512 bytes per reduction index)
+  const int64_t widest = std::max(s->d, s->f);
+  if (std::max<int64_t>(s->T, dv.P_cap) * widest * elt >= (int64_t)1 << 31 || widest >= 1 << 22) return false;
   return (int64_t)s->T * s->k <= 12 * (int64_t)s->E || (int64_t)dv.E_loc * 3 * s->d * s->f * elt <= (int64_t)128 << 20;
 }
 

@@ -63,10 +63,6 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_kernel(const GemmArgs g) 
   const size_t wsz = (size_t)g.K * g.N;
   const float *W0 = static_cast<const float *>(g.Bp) + (size_t)le * wsz + (size_t)k0 * G * g.N;
   const int k_len = max(0, min(n_mine * G, g.K - k0 * G));
-  const uint32_t w_bytes = (uint32_t)k_len * g.N * 4;
-  rsrc_t b[NM];
-  b[0] = stream_rsrc(W0, w_bytes);
-  if (GATED) b[NM - 1] = stream_rsrc(W0 + (size_t)g.n_ktiles * wsz, w_bytes);
   const uint32_t pitch = (uint32_t)g.N * 4;
   const uint32_t b_off = khalf * (G / 2) * pitch + min(n0 + COLS * l31, g.N - COLS) * 4;  // (columns past the end: not stored)
   const float *a_row[MB];
@@ -78,15 +74,19 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_kernel(const GemmArgs g) 
   f32x16 acc[MB][NJ];
   stream_clear(acc);
   auto load = [&](F32Group<MB, NM, G, COLS> &s, int kg, auto whole) {
+    // a descriptor per group: its offsets fit 32 bits whatever the size of the matrix
+    const uint32_t bytes = (uint32_t)min(G, k_len - kg * G) * pitch;
+    rsrc_t b[NM];
+#pragma unroll
+    for (int m = 0; m < NM; ++m) b[m] = stream_rsrc(W0 + m * g.n_ktiles * wsz + (size_t)kg * G * g.N, bytes);
 #pragma unroll
     for (int i = 0; i < G / 2; ++i)
 #pragma unroll
       for (int m = 0; m < NM; ++m) {
         if constexpr (decltype(whole)::value) {
-          f32_fetch(s.b[m][i], b[m], b_off, (uint32_t)(kg * G + i) * pitch);
-        } else {  // indices past K: zeros, from an offset that the descriptor's bound rejects
-          const bool in = kg * G + khalf * (G / 2) + i < k_len;
-          f32_fetch(s.b[m][i], b[m], in ? b_off + (uint32_t)(kg * G + i) * pitch : 0x80000000u, 0);
+          f32_fetch(s.b[m][i], b[m], b_off, (uint32_t)i * pitch);
+        } else {  // indices past K: zeros, from offsets that the descriptor's bound rejects
+          f32_fetch(s.b[m][i], b[m], b_off + (uint32_t)i * pitch, 0);
         }
       }
 #pragma unroll
@@ -95,6 +95,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_kernel(const GemmArgs g) 
       for (int i = 0; i < G / 8; ++i) {
         const int kk = kg * G + khalf * (G / 2) + i * 4;
         s.a[mi][i] = *reinterpret_cast<const f32x4 *>(a_row[mi] + (decltype(whole)::value || kk < k_len ? kk : 0));
+        if (!decltype(whole)::value && kk >= k_len) s.a[mi][i] = f32x4{0.f, 0.f, 0.f, 0.f};  // (an infinity times 0)
       }
   };
   auto multiply = [&](const F32Group<MB, NM, G, COLS> &s) {

@@ -102,3 +102,25 @@ def test_small_batch_fp8_forward(oracle, name):
     ref = oracle.forward_fp8(w.x, idx, tw, w.W_gate, w.W_up, w.W_down, hs, cfg.E, cfg.R, cfg.local_rank_begin,
                              cfg.local_rank_end)
     G.check_y(lay.y_host(), ref, cfg.dtype)
+
+
+# fp32 reductions that end inside a load group: the padding must not meet an infinity of the row (0 * inf)
+@pytest.mark.parametrize("T,d,f", [(4, 264, 40), (200, 264, 264), (4, 24, 8)])
+def test_f32_reduction_tail_beside_an_infinity(T, d, f):
+    import torch
+    cfg = cfg_of(T=T, d=d, f=f, E=2, k=2, R=1, local_rank_begin=0, local_rank_end=1, dtype=wl.F32)
+    print(f"fp32 tail T={T} d={d} f={f}", flush=True)
+    rng = np.random.default_rng(d)
+    x, wg, wu, wd = (rng.uniform(0.1, 1.0, sh).astype(np.float32) for sh in ((T, d), (2, d, f), (2, d, f), (2, f, d)))
+    finite = x.copy()
+    x[0] = np.inf  # all weights are positive: every output of this token is +inf
+    lay = L.MoELayer(cfg)
+    lay.load_weights(wg, wu, wd)
+    lg = L.to_device(np.zeros((T, 2), np.float32))
+    ys = []
+    for v in (x, finite):
+        lay.step(lg, L.to_device(v))
+        torch.cuda.synchronize()
+        ys.append(lay.y_host().copy())
+    assert np.all(np.isposinf(ys[0][0]))
+    assert np.array_equal(ys[0][1:], ys[1][1:]) and np.all(np.isfinite(ys[1]))
