@@ -135,7 +135,9 @@ struct RowRequests {
 // barrier per k-step and all waves in step -> 1.42 PFLOP/s (the vendor library's dense product reaches 1.44 to 1.50 on
 // the box); whole prefill step of that layer 9.73 -> 8.40 ms.
 // ------------------------------------------------------------------------------------------------
-template <bool FP8, int NB, int RW, bool LONE, bool FAR>
+// GRAD (weight gradients, wgrad_bf16.h): both operands are slabs of [column][128 bytes], `step` bytes from one k-step to the
+// next, and both are requested and read as A is.
+template <bool FP8, int NB, int RW, bool LONE, bool FAR, bool GRAD = false>
 struct PingPong {
   static constexpr int kStage = 65536, kB = 32768;
   static constexpr int NB0 = NB < 2 ? NB : 2, NB1 = NB > 2 ? NB - 2 : 0;  // row blocks with valid rows in A0, A1
@@ -149,14 +151,30 @@ struct PingPong {
   int a_rd, b_rd;  // this lane's row / operand in a stage
   int khalf, sw;
   bf16x8 fa[2][2][4], fb[2][4];
+  const unsigned char *slab_a, *slab_b;  // GRAD: slab 0 of this workgroup's columns
+  size_t step_a, step_b;
+  uint32_t va[2][2], vb[2][2];           // this lane's offsets in them, by region and instruction
 
+  __device__ __forceinline__ void request_slab(const unsigned char *slab, const uint32_t (&v)[2], uint32_t l) const {
+    const i32x4 r = lds_load_rsrc(slab, 0xFFFFFFFFu);
+    load_to_lds(r, l, v[0], 0);
+    load_to_lds(r, l + 1024, v[1], 0);
+  }
   __device__ __forceinline__ void request_a(int h, int kt) const {
     const uint32_t l = lds + (kt & 1) * kStage + a_lds[h];
+    if constexpr (GRAD) {
+      request_slab(slab_a + kt * step_a, va[h], l);
+      return;
+    }
     rows.request(h, 0, l, kt);
     if (h == 0 || I1 == 2) rows.request(h, 1, l + 1024, kt);
   }
   __device__ __forceinline__ void request_b(int j, int kt) const {
     const uint32_t l = lds + (kt & 1) * kStage + kB + b_soff + j * 4096, s = kt * kTileBytes + b_soff + j * 4096;
+    if constexpr (GRAD) {
+      request_slab(slab_b + kt * step_b, vb[j], l);
+      return;
+    }
     load_to_lds<LONE>(rb, l, b_voff, s);
     load_to_lds<LONE>(rb, l + 1024, b_voff, s + 1024);
   }
@@ -168,7 +186,8 @@ struct PingPong {
   __device__ __forceinline__ void read_b(int j, int kt) {
     const unsigned char *s = smem + (kt & 1) * kStage + b_rd + j * 4096;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) fb[j][kk] = *reinterpret_cast<const bf16x8 *>(s + kk * 1024);
+    for (int kk = 0; kk < 4; ++kk)
+      fb[j][kk] = *reinterpret_cast<const bf16x8 *>(s + (GRAD ? ((kk * 2 + khalf) ^ sw) * 16 : kk * 1024));
   }
   template <int H, int J>
   __device__ __forceinline__ void multiply(f32x16 (&acc)[NB][2]) {
@@ -225,7 +244,7 @@ struct PingPong {
   }
   // K: reduction length; wm: wave row (scalar)
   __device__ __forceinline__ void run(f32x16 (&acc)[NB][2], int KT, int K, int wm) {
-    const bool tail = K % RowRequests<FP8, 2, 2, FAR>::KS != 0;
+    const bool tail = !GRAD && K % RowRequests<FP8, 2, 2, FAR>::KS != 0;
     auto slab = [&](int kt) {
       if (tail && kt == KT - 1) rows.clip(K, KT - 1);
       request_a(0, kt);

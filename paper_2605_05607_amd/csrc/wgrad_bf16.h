@@ -119,7 +119,10 @@ __global__ __launch_bounds__(256) void wgrad_zero_empty_kernel(const int32_t *__
 // shares, out of the L2s (measured: -9 % of the weight-gradient time on the GPT-OSS-shaped layer, -6.5 % on the
 // Mixtral-shaped one, -9 % on the Qwen3-shaped one, -2 % on the DeepSeek-shaped one).
 // One workgroup per (local expert, 256 x 256 output tile); 8 waves = 2 x 4, each 128 x 64 as 4 x 2 accumulators.
-// LDS: two stages of (A 256 x 64, B 256 x 64), rows of 128 bytes with the forward tile's chunk swizzle.
+// LDS: two stages of (A 256 x 64, B 256 x 64), rows of 128 bytes with the forward tile's chunk swizzle; main loop of the
+// forward's full tiles (slabs straight into the LDS, wave rows half a step apart) instead of slabs staged through registers
+// with all waves in step.  What bounds it is the short reduction (8 k-steps for 512 rows) between a two-slab prologue and the
+// store of 128 KiB: training step of 8192 tokens on 16 experts of 4096 x 1536 1290 -> 1267 us.
 __global__ __launch_bounds__(kGemmThreads, 1) void wgrad_bf16_kernel(const WgradArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, w8 = tid >> 6;
@@ -130,17 +133,6 @@ __global__ __launch_bounds__(kGemmThreads, 1) void wgrad_bf16_kernel(const Wgrad
   const int kb0 = a.kb[le], KT = a.kb[le + 1] - kb0;
   if (KT <= kThinSteps) return;  // whole workgroup: the thin kernel owns this expert
 
-  const int chunk = tid & 7, row0 = tid >> 3;  // rows row0 + 64 i
-  const bf16_t *ap[4], *bp[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    ap[i] = a.AT + ((size_t)kb0 * a.lda + a.a0 + min(m0 + row0 + 64 * i, a.M - 1)) * 64 + chunk * 8;
-    bp[i] = a.BT + ((size_t)kb0 * a.ldb + a.b0 + min(n0 + row0 + 64 * i, a.N - 1)) * 64 + chunk * 8;
-  }
-  const int dst = (row0 * 8 + (chunk ^ ((row0 >> 1) & 7))) * 16;  // + 8192 per 64 rows; B stage 32768 further
-  const size_t a_step = (size_t)a.lda * 64, b_step = (size_t)a.ldb * 64;  // elements from one block to the next
-  u32x4 ra[4], rb[4];
-
   f32x16 acc[4][2];
 #pragma unroll
   for (int mi = 0; mi < 4; ++mi)
@@ -149,96 +141,35 @@ __global__ __launch_bounds__(kGemmThreads, 1) void wgrad_bf16_kernel(const Wgrad
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[mi][j][r] = 0.f;
 
-  const int l31 = lane & 31, khalf = lane >> 5, sw = (lane >> 1) & 7;
-  const int a_rd = (wm * 128 + l31) * 128;            // + mi * 4096
-  const int b_rd = 32768 + (wn * 64 + l31) * 128;     // + j * 4096
-  bf16x8 fa0[4], fb0[2], fa1[4], fb1[2];  // operand fragments of two consecutive substeps
-#define MOE355_W_READ(FA, FB, STAGE, KK)                                                           \
-  do {                                                                                             \
-    const int slot_ = (((KK) * 2 + khalf) ^ sw) * 16;                                              \
-    _Pragma("unroll") for (int mi = 0; mi < 4; ++mi) FA[mi] =                                      \
-        *reinterpret_cast<const bf16x8 *>((STAGE) + a_rd + mi * 4096 + slot_);                     \
-    FB[0] = *reinterpret_cast<const bf16x8 *>((STAGE) + b_rd + slot_);                             \
-    FB[1] = *reinterpret_cast<const bf16x8 *>((STAGE) + b_rd + 4096 + slot_);                      \
-  } while (0)
-#define MOE355_W_MFMAS(FA, FB)                                                                     \
-  do {                                                                                             \
-    _Pragma("unroll") for (int mi = 0; mi < 4; ++mi) {                                             \
-      acc[mi][0] = mfma_bf16(FA[mi], FB[0], acc[mi][0]);                                           \
-      acc[mi][1] = mfma_bf16(FA[mi], FB[1], acc[mi][1]);                                           \
-    }                                                                                              \
-  } while (0)
-  // the slab in flight moves in three portions {a0, a1, b0}, {a2, a3, b1}, {b2, b3}: stored into the other stage and
-  // reloaded for the slab after it, spread under the matrix instructions as in the forward tile
-#define MOE355_W_STORE(NX, I0, I1, J0, J1)                                                         \
-  do {                                                                                             \
-    if ((I0) >= 0) *reinterpret_cast<u32x4 *>((NX) + dst + 8192 * (I0)) = ra[(I0) < 0 ? 0 : (I0)]; \
-    if ((I1) >= 0) *reinterpret_cast<u32x4 *>((NX) + dst + 8192 * (I1)) = ra[(I1) < 0 ? 0 : (I1)]; \
-    *reinterpret_cast<u32x4 *>((NX) + 32768 + dst + 8192 * (J0)) = rb[(J0)];                       \
-    if ((J1) >= 0) *reinterpret_cast<u32x4 *>((NX) + 32768 + dst + 8192 * (J1)) = rb[(J1) < 0 ? 0 : (J1)]; \
-  } while (0)
-#define MOE355_W_LOAD(KP, I0, I1, J0, J1)                                                          \
-  do {                                                                                             \
-    if ((I0) >= 0) ra[(I0) < 0 ? 0 : (I0)] = *reinterpret_cast<const u32x4 *>(ap[(I0) < 0 ? 0 : (I0)] + (size_t)(KP) * a_step); \
-    if ((I1) >= 0) ra[(I1) < 0 ? 0 : (I1)] = *reinterpret_cast<const u32x4 *>(ap[(I1) < 0 ? 0 : (I1)] + (size_t)(KP) * a_step); \
-    rb[(J0)] = *reinterpret_cast<const u32x4 *>(bp[(J0)] + (size_t)(KP) * b_step);                 \
-    if ((J1) >= 0) rb[(J1) < 0 ? 0 : (J1)] = *reinterpret_cast<const u32x4 *>(bp[(J1) < 0 ? 0 : (J1)] + (size_t)(KP) * b_step); \
-  } while (0)
-  /* order as in the forward tile: reads two behind each of the first three MFMAs, a store and a load behind each of
-     the next NW, the remaining MFMAs last */
-#define MOE355_W_ORDER(NW)                                                                         \
-  do {                                                                                             \
-    _Pragma("unroll") for (int i_ = 0; i_ < 3; ++i_) {                                             \
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                           \
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);                                           \
-    }                                                                                              \
-    _Pragma("unroll") for (int i_ = 0; i_ < (NW); ++i_) {                                          \
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                           \
-      __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);                                           \
-      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                           \
-    }                                                                                              \
-    __builtin_amdgcn_sched_group_barrier(0x008, 5 - (NW), 0);                                      \
-  } while (0)
-  {
-    const int kt_last = KT - 1;  // KT > kThinSteps >= 1
-    MOE355_W_LOAD(0, 0, 1, 0, -1); MOE355_W_LOAD(0, 2, 3, 1, -1); MOE355_W_LOAD(0, -1, -1, 2, 3);
-    MOE355_W_STORE(smem, 0, 1, 0, -1); MOE355_W_STORE(smem, 2, 3, 1, -1); MOE355_W_STORE(smem, -1, -1, 2, 3);
-    {
-      const int k1 = min(1, kt_last);
-      MOE355_W_LOAD(k1, 0, 1, 0, -1); MOE355_W_LOAD(k1, 2, 3, 1, -1); MOE355_W_LOAD(k1, -1, -1, 2, 3);
-    }
-    __syncthreads();
-    MOE355_W_READ(fa0, fb0, smem, 0);
-    for (int kt = 0; kt < KT; ++kt) {
-      const unsigned char *cur = smem + (kt & 1) * kStageBytes;
-      unsigned char *nx = smem + ((kt & 1) ^ 1) * kStageBytes;
-      const int kp = min(kt + 2, kt_last);  // past the end: the last slab again (in bounds, never used)
-      MOE355_W_READ(fa1, fb1, cur, 1);
-      MOE355_W_MFMAS(fa0, fb0);
-      MOE355_W_STORE(nx, 0, 1, 0, -1);
-      MOE355_W_LOAD(kp, 0, 1, 0, -1);
-      MOE355_W_READ(fa0, fb0, cur, 2);
-      MOE355_W_MFMAS(fa1, fb1);
-      MOE355_W_STORE(nx, 2, 3, 1, -1);
-      MOE355_W_LOAD(kp, 2, 3, 1, -1);
-      MOE355_W_READ(fa1, fb1, cur, 3);
-      MOE355_W_MFMAS(fa0, fb0);
-      MOE355_W_STORE(nx, -1, -1, 2, 3);
-      MOE355_W_LOAD(kp, -1, -1, 2, 3);
-      MOE355_W_ORDER(3);
-      MOE355_W_ORDER(3);
-      MOE355_W_ORDER(2);
-      __syncthreads();
-      MOE355_W_READ(fa0, fb0, nx, 0);
-      MOE355_W_MFMAS(fa1, fb1);
-      MOE355_W_ORDER(0);
+  const int l31 = lane & 31, khalf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(w8);
+  typedef PingPong<false, 4, 128, false, false, true> Loop;
+  Loop loop;
+  loop.lds = lds_address(smem);
+  loop.smem = smem;
+  loop.khalf = khalf;
+  loop.sw = (lane >> 1) & 7;
+  loop.a_rd = (wm * 128 + l31) * 128;
+  loop.b_rd = Loop::kB + (wn * 64 + l31) * 128;
+  loop.b_soff = (wave >> 1) * 8192 + (wave & 1) * 2048;
+  loop.step_a = (size_t)a.lda * 128;
+  loop.step_b = (size_t)a.ldb * 128;
+  loop.slab_a = reinterpret_cast<const unsigned char *>(a.AT) + ((size_t)kb0 * a.lda + a.a0 + m0) * 128;
+  loop.slab_b = reinterpret_cast<const unsigned char *>(a.BT) + ((size_t)kb0 * a.ldb + a.b0 + n0) * 128;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    // sixteen columns of region h of either operand: eight per instruction, lane = column by 16-byte chunk; columns past
+    // the end repeat the last one (not stored)
+    const int row_a = (wave >> 2) * 128 + h * 64 + (wave & 3) * 16, row_b = (loop.b_soff >> 7) + h * 32;
+    loop.a_lds[h] = row_a * 128;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int ra = row_a + i * 8 + (lane >> 3), rb = row_b + i * 8 + (lane >> 3);
+      loop.va[h][i] = min(ra, a.M - 1 - m0) * 128 + ((lane & 7) ^ ((ra >> 1) & 7)) * 16;
+      loop.vb[h][i] = min(rb, a.N - 1 - n0) * 128 + ((lane & 7) ^ ((rb >> 1) & 7)) * 16;
     }
   }
-#undef MOE355_W_READ
-#undef MOE355_W_MFMAS
-#undef MOE355_W_STORE
-#undef MOE355_W_LOAD
-#undef MOE355_W_ORDER
+  loop.run(acc, KT, KT * kBK, wave >> 2);
   // epilogue: each wave turns its 32 x 64 blocks around through a private LDS patch (fp32, row pitch 288 bytes) so
   // that a row leaves as contiguous bf16
   __syncthreads();
