@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256) void wgrad_zero_empty_kernel(const int32_t *__
 // LDS: two stages of (A 256 x 64, B 256 x 64), rows of 128 bytes with the forward tile's chunk swizzle; main loop of the
 // forward's full tiles (slabs straight into the LDS, wave rows half a step apart) instead of slabs staged through registers
 // with all waves in step.  What bounds it is the short reduction (8 k-steps for 512 rows) between a two-slab prologue and the
-// store of 128 KiB: training step of 8192 tokens on 16 experts of 4096 x 1536 1290 -> 1267 us.
+// store of 128 KiB: training step of 8192 tokens on 16 experts of 4096 x 1536 about 1277 -> 1267 us.
 __global__ __launch_bounds__(kGemmThreads, 1) void wgrad_bf16_kernel(const WgradArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, w8 = tid >> 6;
