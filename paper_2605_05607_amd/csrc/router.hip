@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kRouterThreads) void router_logits_bf16_kernel(cons
   const int KT = (d + kBK - 1) / kBK;
   const int kt_begin = min(KT, part * steps_per_part), kt_end = min(KT, kt_begin + steps_per_part);
   RowRequests<false, 1, MB, FAR> xr;
-  RowRequests<false, 1, NW, false> wr;
+  RowRequests<false, 1, NW, FAR> wr;
   xr.init(x, d);
   wr.init(W, d);
 #pragma unroll
@@ -279,7 +279,8 @@ static int launch_router_gemm(const moe_shape *shape, const RouterPlan &plan, co
   const int steps_per_part = ceil_div(ceil_div(shape->d, kBK), parts);
   const dim3 grid((unsigned)ceil_div(shape->T, plan.bm) * parts, ceil_div(shape->E, plan.bn));
   float *out = parts > 1 ? partial : direct;
-  const bool far = (int64_t)shape->T * shape->d * 2 >= (int64_t)1 << 32;
+  // 32-bit offsets reach 4 GiB of either operand
+  const bool far = (int64_t)std::max(shape->T, shape->E) * shape->d * 2 >= (int64_t)1 << 32;
 #define MOE355_ROUTER_(BM_, BN_, FAR_)                                                                                 \
   do {                                                                                                                 \
     static std::atomic<uint64_t> done{0};                                                                              \
