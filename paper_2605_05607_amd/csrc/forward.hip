@@ -317,9 +317,9 @@ static int launch_stream(const moe_shape *s, const Derived &dv, const void *x, c
     hipLaunchKernelGGL((stream_gemm2_kernel<FP8_, NB_>), grid2, dim3(kStreamWaves * 64), lds, st, g2);          \
   } while (0)
   if (q) {
-    if (s->T <= 32) MOE355_STREAM(true, 1); else MOE355_STREAM(true, 2);
+    if (stream_row_blocks(s->T) == 1) MOE355_STREAM(true, 1); else MOE355_STREAM(true, 2);
   } else {
-    if (s->T <= 32) MOE355_STREAM(false, 1); else MOE355_STREAM(false, 2);
+    if (stream_row_blocks(s->T) == 1) MOE355_STREAM(false, 1); else MOE355_STREAM(false, 2);
   }
 #undef MOE355_STREAM
   mark(3);

@@ -244,10 +244,13 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void stream_gemm1_kernel(cons
 // a local slot come out as zeros, and no row of o ever exists.  groups > 1 (strips too few to pull the weights at the
 // chip's rate): the groups' sums go to partial[group] and stream_reduce_kernel adds them in group order.
 // ------------------------------------------------------------------------------------------------
-// LDS: the waves' token rows | token and weight of every local row | the busy list
-constexpr int kStreamPasses = 2;  // passes an expert can need: 32 NB rows each, at most kStreamTokens rows
+// LDS: the waves' token rows | the busy list | token and weight of every local row
+constexpr int stream_row_blocks(int T) { return T <= 32 ? 1 : 2; }  // NB: 32-row blocks per pass
+// Entries of the busy list: a pass of 32 NB rows each, and every expert's last one may be partial.
+constexpr int stream_passes(int P_cap, int E_loc, int nb) { return P_cap / (32 * nb) + E_loc; }
 constexpr size_t stream2_lds_bytes(int T, int P_cap, int E_loc) {
-  return (size_t)kStreamWaves * T * 32 * 4 + (size_t)kStreamPasses * E_loc * 16 + (size_t)P_cap * 8 + 16;
+  return (size_t)kStreamWaves * T * 32 * 4 + (size_t)stream_passes(P_cap, E_loc, stream_row_blocks(T)) * 16 +
+         (size_t)P_cap * 8 + 16;
 }
 
 template <bool FP8, int NB>
@@ -256,7 +259,8 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void stream_gemm2_kernel(cons
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   float *ysum = reinterpret_cast<float *>(smem);                                // [waves][T][32]
   int4 *seg = reinterpret_cast<int4 *>(ysum + kStreamWaves * g.T * 32);        // (expert, first row, rows, -)
-  int *row_tok = reinterpret_cast<int *>(seg + kStreamPasses * g.E_loc);        // [P_cap]
+  const int n_max = stream_passes(g.P_cap, g.E_loc, NB);                        // (more only in corrupt tables)
+  int *row_tok = reinterpret_cast<int *>(seg + n_max);                          // [P_cap]
   float *row_w = reinterpret_cast<float *>(row_tok + g.P_cap);                  // [P_cap]
   int *n_seg_s = reinterpret_cast<int *>(row_w + g.P_cap);
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -272,15 +276,15 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void stream_gemm2_kernel(cons
       int start = 0, rows = 0;
       if (le < g.E_loc) {
         start = min(max(g.offsets[g.e_lo + le] - base, 0), P);
-        rows = min(max(min(max(g.offsets[g.e_lo + le + 1] - base, 0), P) - start, 0), kStreamPasses * NB * 32);
+        rows = max(min(max(g.offsets[g.e_lo + le + 1] - base, 0), P) - start, 0);
       }
       const int passes = (rows + NB * 32 - 1) / (NB * 32);
       const int inc = wave_inclusive_scan(passes);
-      for (int q = 0; q < passes; ++q)
+      for (int q = 0; q < passes && n + inc - passes + q < n_max; ++q)
         seg[n + inc - passes + q] = make_int4(le, start + q * NB * 32, min(NB * 32, rows - q * NB * 32), 0);
       n += __builtin_amdgcn_readlane(inc, 63);
     }
-    if (lane == 0) *n_seg_s = n;
+    if (lane == 0) *n_seg_s = min(n, n_max);
   }
   for (int r = tid; r < P; r += kStreamWaves * 64) {
     const int p = stream_pair(g, base + r);
@@ -314,10 +318,28 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void stream_gemm2_kernel(cons
     f32x16 acc[NB][1];
     stream_clear(acc);
     stream_blocks<FP8, NB, 1, 5, 3>(acc, a, a_off, b, lane * 16, kt0, kt1, nb, g.K * (int)sizeof(elt_t), khalf * 16);
-    // weight * sum to this wave's token rows (the rows of an expert are distinct tokens: all reads, then all writes)
+    // weight * sum to this wave's token rows.  An expert's rows are in token order, and usually distinct tokens: all reads,
+    // then all writes.  Picks that name an expert twice for a token put equal tokens side by side: one row after the other.
 #pragma unroll
     for (int mi = 0; mi < NB; ++mi) {
       if (NB > 1 && mi >= nb) break;
+      const int my = mi * 32 + l31;
+      const int last = start + min(my, rows - 1);
+      if (__any(l31 > 0 && my < rows && row_tok[last] == row_tok[last - (l31 > 0)])) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+          for (int kh = 0; kh < 2; ++kh) {
+            const int rl = mi * 32 + (r >> 2) * 8 + kh * 4 + (r & 3);
+            if (rl < rows && khalf == kh) {
+              float *at = mine + row_tok[start + rl] * 32 + l31;
+              *at = fmaf(FP8 ? acc[mi][0][r] * cs : acc[mi][0][r], row_w[start + rl], *at);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+          }
+        continue;
+      }
       int at[16];
       float sum[16];
 #pragma unroll

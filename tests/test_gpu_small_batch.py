@@ -124,3 +124,28 @@ def test_f32_reduction_tail_beside_an_infinity(T, d, f):
         ys.append(lay.y_host().copy())
     assert np.all(np.isposinf(ys[0][0]))
     assert np.array_equal(ys[0][1:], ys[1][1:]) and np.all(np.isfinite(ys[1]))
+
+
+# picks that name one expert several times for a token: every slot counts, as in the tile kernels (rows of one expert beyond
+# two passes, equal tokens side by side at every place of a 32-row block)
+@pytest.mark.parametrize("T,k,f", [(1, 4, 512), (20, 7, 520), (32, 8, 512), (40, 5, 512), (128, 4, 1032)])
+def test_small_batch_repeated_picks(oracle, T, k, f):
+    import torch
+    cfg = cfg_of(T=T, E=12, k=k, R=1, f=f, local_rank_begin=0, local_rank_end=1)
+    print(f"small-batch forward, repeated picks T={T} k={k} f={f}", flush=True)
+    w = wl.make_workload(cfg)
+    rng = np.random.default_rng(T)
+    idx = rng.integers(0, cfg.E, size=(T, k)).astype(np.int32)
+    idx[T // 4:] = idx[T // 4:, :1]  # most tokens: every slot the same expert
+    idx[T // 2:] = 3                 # and half of them the same one
+    tw = rng.uniform(0.1, 1.0, size=(T, k)).astype(np.float32)
+    lay = L.MoELayer(cfg)
+    lay.load_weights(w.W_gate, w.W_up, w.W_down)
+    lay.topk_idx.copy_(torch.from_numpy(idx).reshape(lay.topk_idx.shape))
+    lay.topk_w.copy_(torch.from_numpy(tw).reshape(lay.topk_w.shape))
+    lay.build_dispatch()
+    lay.y.fill_(float("nan"))
+    lay.forward(L.to_device(w.x))
+    torch.cuda.synchronize()
+    ref = oracle.forward(w.x, idx, tw, w.W_gate, w.W_up, w.W_down, cfg.E, cfg.R, 0, 1)
+    G.check_y(lay.y_host(), ref, cfg.dtype)
