@@ -91,6 +91,33 @@ static size_t fp8_tile_bytes(const moe_shape *s, const Derived &dv, int which) {
   return (size_t)dv.E_loc * ceil_div(s->d, kBN) * ceil_div(s->f, kFp8KStep) * kTileBytes;
 }
 
+// The per-item GEMM kernel: one workgroup per item of the list, `far` (A has 4 GiB or more) with 64-bit row addresses.
+template <bool GATED, bool FP8, bool TRAIN, bool FAR, bool BESIDE>
+static bool launch_items_(const GemmArgs &g, dim3 grid, hipStream_t st) {
+  static std::atomic<uint64_t> done{0};
+  const auto kernel = &gemm_bf16_kernel<GATED, FP8, TRAIN, FAR, BESIDE>;
+  const int lds = BESIDE ? kGemmLdsBeside : kGemmLds;  // more than the default dynamic limit: raised per function
+  if (!allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds, done)) return false;
+  hipLaunchKernelGGL(kernel, grid, dim3(kGemmThreads), lds, st, g);
+  return true;
+}
+template <bool GATED, bool FP8, bool TRAIN, bool BESIDE = false>
+static int launch_items(const GemmArgs &g, bool far, dim3 grid, hipStream_t st) {
+  const bool ok = !FP8 && far ? launch_items_<GATED, FP8, TRAIN, !FP8, BESIDE>(g, grid, st)
+                              : launch_items_<GATED, FP8, TRAIN, false, BESIDE>(g, grid, st);
+  return ok ? launch_status() : (int)MOE_ERR_HIP;
+}
+
+// A resident kernel: one workgroup per CU (each takes most of a CU's LDS).
+template <void (*KERNEL)(PipelineArgs)>
+static int launch_resident(const PipelineArgs &pa, hipStream_t st) {
+  static std::atomic<uint64_t> done{0};
+  const int n_cu = compute_units();
+  if (n_cu < 1 || !allow_dynamic_lds(reinterpret_cast<const void *>(KERNEL), kGemmLds, done)) return MOE_ERR_HIP;
+  hipLaunchKernelGGL(KERNEL, dim3((unsigned)n_cu), dim3(kGemmThreads), kGemmLds, st, pa);
+  return launch_status();
+}
+
 // GEMM-1 (gated) then GEMM-2 on the rows described by the tile table.  a1 / a1_map select the A operand of
 // GEMM-1: the token matrix with the row -> token map (fused gather) or a materialised copy (map == nullptr).
 static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, const int32_t *a1_map, int a1_ld,
@@ -112,104 +139,59 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
   g2.row_sole = sole; g2.y = y;
   g2.K = s->f; g2.N = s->d; g2.lda = s->f; g2.ldo = s->d;
   g2.n_items = w.header + 3; g2.work = w.work2;
-  const int64_t a_elt = q ? 1 : dv.elt;
-  g1.a_far = (a1_map ? (int64_t)s->T : dv.P_cap) * a1_ld * a_elt >= (int64_t)1 << 32;
-  g2.a_far = dv.P_cap * s->f * a_elt >= (int64_t)1 << 32;
+  // (bf16 only: an operand has less than 2^32 elements, see forward_common)
+  const bool far1 = (a1_map ? (int64_t)s->T : dv.P_cap) * a1_ld * 2 >= (int64_t)1 << 32;
+  const bool far2 = dv.P_cap * s->f * 2 >= (int64_t)1 << 32;
   if (keep_gu) {  // training forward: g and u are kept, and every weighted row goes to the kept o
     g1.aux = keep_gu;
     g2.out = keep_o;
   }
   const auto grid_of = [&](int nt) { return dim3((unsigned)(((size_t)dv.max_mtiles * nt + 255) / 256 * 256)); };
-  if (q) {
-    static std::atomic<uint64_t> done1{0}, done2{0}, done_pipe{0};
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<true, true>), kGemmLds, done1) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<false, true>), kGemmLds, done2) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_fp8_pipeline_kernel), kGemmLds, done_pipe))
-      return MOE_ERR_HIP;
-    g1.A = q->xq; g1.a_scale = q->x_scale; g1.b_scale = q->gu_scale; g1.h_scale = q->h_scale;
-    g2.b_scale = q->down_scale; g2.h_scale = q->h_scale;
-    g1.n_ntiles = ceil_div(s->f, kBN / 2); g1.n_ktiles = ceil_div(s->d, kFp8KStep);
-    g2.n_ntiles = ceil_div(s->d, kBN);     g2.n_ktiles = ceil_div(s->f, kFp8KStep);
-    if (pipelined) {
-      const int n_cu = compute_units();
-      if (n_cu < 1) return MOE_ERR_HIP;
-      PipelineArgs pa;
-      pa.g1 = g1; pa.g2 = g2;
-      pa.tickets = w.header + 8; pa.tile_ready = w.tile_ready; pa.error = w.header + 24; pa.nt1 = dv.nt1 + wait_extra;
-      pa.max_polls = max_polls;
-      hipLaunchKernelGGL(gemm_fp8_pipeline_kernel, dim3((unsigned)n_cu), dim3(kGemmThreads), kGemmLds, st, pa);
-      mark(2);
-      mark(3);
-      return launch_status();
-    }
-    hipLaunchKernelGGL((gemm_bf16_kernel<true, true>), grid_of(dv.nt1), dim3(kGemmThreads), kGemmLds, st, g1);
-    int rc = launch_status();
-    mark(2);
-    if (rc != MOE_OK) return rc;
-    hipLaunchKernelGGL((gemm_bf16_kernel<false, true>), grid_of(dv.nt2), dim3(kGemmThreads), kGemmLds, st, g2);
-    mark(3);
-    return launch_status();
-  }
   if (s->dtype == MOE_BF16) {
-    // the two LDS stages (128 KiB) exceed the default dynamic limit; raising it is a per-function attribute
-    static std::atomic<uint64_t> done1{0}, done2{0}, done_pipe{0};
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<true>), kGemmLds, done1) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<false>), kGemmLds, done2) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_pipeline_kernel), kGemmLds, done_pipe))
-      return MOE_ERR_HIP;
-    g1.n_ntiles = ceil_div(s->f, kBN / 2); g1.n_ktiles = ceil_div(s->d, kBK);
-    g2.n_ntiles = ceil_div(s->d, kBN);     g2.n_ktiles = ceil_div(s->f, kBK);
+    const int step = q ? kFp8KStep : kBK;
+    if (q) {
+      g1.A = q->xq; g1.a_scale = q->x_scale; g1.b_scale = q->gu_scale; g1.h_scale = q->h_scale;
+      g2.b_scale = q->down_scale; g2.h_scale = q->h_scale;
+    }
+    g1.n_ntiles = ceil_div(s->f, kBN / 2); g1.n_ktiles = ceil_div(s->d, step);
+    g2.n_ntiles = ceil_div(s->d, kBN);     g2.n_ktiles = ceil_div(s->f, step);
+    int rc;
     if (pipelined) {
-      // one resident workgroup per CU (each takes most of a CU's LDS)
-      const int n_cu = compute_units();
-      if (n_cu < 1) return MOE_ERR_HIP;
-      PipelineArgs pa;
+      PipelineArgs pa{};
       pa.g1 = g1; pa.g2 = g2;
       pa.tickets = w.header + 8; pa.tile_ready = w.tile_ready; pa.error = w.header + 24; pa.nt1 = dv.nt1 + wait_extra;
       pa.max_polls = max_polls;
-      if (keep_gu) {
-        static std::atomic<uint64_t> done_tp{0};
-        if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_train_pipeline_kernel), kGemmLds, done_tp))
-          return MOE_ERR_HIP;
-        hipLaunchKernelGGL(gemm_train_pipeline_kernel, dim3((unsigned)n_cu), dim3(kGemmThreads), kGemmLds, st,
-                           pa);
+      const bool far = far1 || far2;
+#define MOE355_RESIDENT(KERNEL_) (far ? launch_resident<KERNEL_<true>>(pa, st) : launch_resident<KERNEL_<false>>(pa, st))
+      if (q) {
+        rc = launch_resident<gemm_fp8_pipeline_kernel>(pa, st);
+      } else if (keep_gu) {
+        rc = MOE355_RESIDENT(gemm_train_pipeline_kernel);
       } else if (combine_tb) {
         // Combine as the third stage of the same launch (wait_extra also raises its target, for the give-up test)
-        static std::atomic<uint64_t> done_c{0};
-        if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_combine_kernel), kGemmLds, done_c))
-          return MOE_ERR_HIP;
         pa.tile_done = w.tile_done; pa.row_tile = w.row_tile;
         pa.topk_idx = topk_idx; pa.inv_perm = combine_tb->inv_perm; pa.offsets = combine_tb->offsets;
         pa.header = w.header;
         pa.T = s->T; pa.k = s->k; pa.e_lo = dv.e_lo; pa.E_loc = dv.E_loc; pa.P_cap = (int)dv.P_cap;
         pa.nt2 = dv.nt2 + wait_extra; pa.n_mtiles_cap = dv.max_mtiles;
-        hipLaunchKernelGGL(gemm_bf16_combine_kernel, dim3((unsigned)n_cu), dim3(kGemmThreads), kGemmLds, st,
-                           pa);
+        rc = MOE355_RESIDENT(gemm_bf16_combine_kernel);
       } else {
-        hipLaunchKernelGGL(gemm_bf16_pipeline_kernel, dim3((unsigned)n_cu), dim3(kGemmThreads), kGemmLds, st,
-                           pa);
+        rc = MOE355_RESIDENT(gemm_bf16_pipeline_kernel);
       }
+#undef MOE355_RESIDENT
       mark(2);
       mark(3);
-      return launch_status();
+      return rc;
     }
-    if (keep_gu) {
-      static std::atomic<uint64_t> done_t{0};
-      if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<true, false, true>), kGemmLds,
-                             done_t))
-        return MOE_ERR_HIP;
-      hipLaunchKernelGGL((gemm_bf16_kernel<true, false, true>), grid_of(dv.nt1), dim3(kGemmThreads), kGemmLds,
-                         st, g1);
-    } else {
-      hipLaunchKernelGGL(gemm_bf16_kernel<true>, grid_of(dv.nt1), dim3(kGemmThreads), kGemmLds, st, g1);
-    }
-    int rc = launch_status();
+    if (q) rc = launch_items<true, true, false>(g1, false, grid_of(dv.nt1), st);
+    else if (keep_gu) rc = launch_items<true, false, true>(g1, far1, grid_of(dv.nt1), st);
+    else rc = launch_items<true, false, false>(g1, far1, grid_of(dv.nt1), st);
     mark(2);
     if (rc != MOE_OK) return rc;
-    hipLaunchKernelGGL(gemm_bf16_kernel<false>, grid_of(dv.nt2), dim3(kGemmThreads), kGemmLds, st,
-                       g2);
+    if (q) rc = launch_items<false, true, false>(g2, false, grid_of(dv.nt2), st);
+    else rc = launch_items<false, false, false>(g2, far2, grid_of(dv.nt2), st);
     mark(3);
-    return launch_status();
+    return rc;
   }
   g1.n_ntiles = ceil_div(s->f, kFBN); g1.n_ktiles = dv.E_loc;
   g2.n_ntiles = ceil_div(s->d, kFBN); g2.n_ktiles = dv.E_loc;
@@ -872,11 +854,6 @@ extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const v
                      kept_o, static_cast<const bf16_t *>(dy), w.header, w.row_tok, w.row_w, tables->perm, shape->d,
                      d_topk_w);
   if ((rc = launch_status()) != MOE_OK) return join(rc);
-  static std::atomic<uint64_t> done_b1{0}, done_b2{0};
-  if (!allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<false, false, true>), kGemmLds,
-                         done_b1) ||
-      !allow_dynamic_lds(reinterpret_cast<const void *>(&gemm_bf16_kernel<false>), kGemmLds, done_b2))
-    return join(MOE_ERR_HIP);
   const auto grid_of = [&](int nt) { return dim3((unsigned)(((size_t)dvb.max_mtiles * nt + 255) / 256 * 256)); };
   // dh_raw = dy[token of the row] Wd^T, then the SwiGLU derivative with the kept g and u
   GemmArgs g1{};
@@ -885,10 +862,8 @@ extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const v
   g1.n_items = w.header + 0; g1.work = w.work1;
   g1.K = shape->d; g1.N = shape->f; g1.lda = shape->d; g1.ldo = 2 * shape->f;
   g1.n_ntiles = dvb.nt1; g1.n_ktiles = ceil_div(shape->d, kBK);
-  g1.a_far = (int64_t)shape->T * shape->d * 2 >= (int64_t)1 << 32;
-  hipLaunchKernelGGL((gemm_bf16_kernel<false, false, true>), grid_of(dvb.nt1), dim3(kGemmThreads), kGemmLds, st,
-                     g1);
-  if ((rc = launch_status()) != MOE_OK) return join(rc);
+  const bool far1 = (int64_t)shape->T * shape->d * 2 >= (int64_t)1 << 32;
+  if ((rc = launch_items<false, false, true, true>(g1, far1, grid_of(dvb.nt1), st)) != MOE_OK) return join(rc);
   if (wgrad) {  // dg, du and w h are there: their transposes run beside the second GEMM
     if (hipEventRecord(side->mid, st) != hipSuccess || hipStreamWaitEvent(side->stream, side->mid, 0) != hipSuccess)
       return join(MOE_ERR_HIP);
@@ -903,9 +878,8 @@ extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const v
   g2.n_items = w.header + 3; g2.work = w.work2;
   g2.K = 2 * shape->f; g2.N = shape->d; g2.lda = 2 * shape->f; g2.ldo = shape->d;
   g2.n_ntiles = dvb.nt2; g2.n_ktiles = 2 * (shape->f / kBK);
-  g2.a_far = dv.P_cap * 2 * shape->f * 2 >= (int64_t)1 << 32;
-  hipLaunchKernelGGL(gemm_bf16_kernel<false>, grid_of(dvb.nt2), dim3(kGemmThreads), kGemmLds, st, g2);
-  if ((rc = launch_status()) != MOE_OK) return join(rc);
+  const bool far2 = dv.P_cap * 2 * shape->f * 2 >= (int64_t)1 << 32;
+  if ((rc = launch_items<false, false, false, true>(g2, far2, grid_of(dvb.nt2), st)) != MOE_OK) return join(rc);
   if ((rc = launch_combine(shape, dv, dxr, topk_idx, tables, dx, true, st)) != MOE_OK || !wgrad) return join(rc);
   // weight gradients: one grouped product per weight matrix, over the transposed operands
   static std::atomic<uint64_t> done_w{0};

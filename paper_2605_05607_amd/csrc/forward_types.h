@@ -54,7 +54,6 @@ struct GemmArgs {
   const int32_t *n_items;  // device: number of work items of this GEMM
   const int4 *work;        // device: work list
   int K, N, lda, ldo, n_ntiles, n_ktiles;
-  int a_far;  // A has 4 GiB or more: 64-bit row addresses
   // training path only (null otherwise): kept g and u (written by GEMM-1, read by the first backward GEMM) and the
   // weighted h the first backward GEMM writes
   void *aux;

@@ -34,6 +34,7 @@ constexpr int kGemmThreads = 512;
 constexpr int kWaitVmcnt0 = 0x0F70;
 constexpr int kGemmLds = 3 * (kBM / 2 * kBK * 2 + kTileBytes);  // 144 KiB: the ring of the 128-row tiles (two 64 KiB stages
                                                                 // and the epilogues take less)
+constexpr int kGemmLdsBeside = 2 * 65536;  // the same with a ring of two stages there: the two stages of the full tiles
 constexpr int kPatchBytes = 32 * 288;                     // per-wave epilogue patch (fits 8 x in the stages)
 
 // FP8: A and the packed B hold E4M3 codes; a k-step then covers 128 reduction indices in the same 128 bytes per row,
@@ -45,11 +46,10 @@ constexpr int kPatchBytes = 32 * 288;                     // per-wave epilogue p
 //   !GATED : the first GEMM of the backward pass, dh_raw = dy Wd^T (N = f).  With the kept g, u and the gate weight w:
 //            dh = w dh_raw, dg = dh u silu'(g), du = dh silu(g)  ->  g.out = dgu [rows, 2 N] bf16 (dg, then du), and
 //            g.aux2 = w silu(g) u [rows, N] bf16 (the h operand of the down-projection weight gradient, weight folded in).
-template <bool GATED, bool RESIDENT, int NB, int RW, bool FP8 = false, bool TRAIN = false, bool LONE = false,
-          bool FAR = false>
+template <bool GATED, bool RESIDENT, int NB, int RW, bool FP8, bool TRAIN, bool LONE, bool FAR, bool BESIDE>
 __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char *smem, int nt, int le, int m0,
                                                int rows, int poison = 0,
-                                               int32_t *pre_ctr = nullptr, int *pre_slot = nullptr) {
+                                               int32_t *tickets = nullptr, int *pre = nullptr) {
   // RESIDENT (the kernel that loops over items): the thread index goes through an empty asm so that nothing
   // derived from it counts as loop invariant; hoisting those values across items costs more registers than the
   // tile has to spare.
@@ -73,16 +73,14 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
   // read once by one workgroup: requested with the non-temporal hint so that they do not push the operands that other
   // tiles share out of the L2.
   typename std::conditional<(RW > 64), PingPong<FP8, (NB > 0 ? NB : 1), RW, LONE, FAR>,
-                            SlabRing<FP8, NB, (RW > 64 ? 64 : RW), LONE || RW == 32>>::type loop;
+                            SlabRing<FP8, NB, (RW > 64 ? 64 : RW), LONE || RW == 32, BESIDE>>::type loop;
   loop.rows.init(g.A, g.lda);
   loop.rb = lds_load_rsrc(static_cast<const unsigned char *>(g.Bp) + ((size_t)(le * g.n_ntiles + nt) * g.n_ktiles) * kTileBytes,
                           (uint32_t)g.n_ktiles * kTileBytes);
   loop.lds = lds_address(smem);
   loop.smem = smem;
   // LDS -> operand addressing: lane l reads row l & 31 of a 32-row block, k half l >> 5
-  loop.khalf = khalf;
-  loop.sw = (lane >> 1) & 7;
-  loop.a_rd = (wm * RW + l31) * 128;
+  loop.a_rd = row_read_offset(wm * RW + l31, lane);
   loop.b_rd = wn * 8192 + lane * 16;
   loop.b_voff = lane * 16;
   const auto a_row = [&](int row) {  // row of the matrix behind row `row` of the tile (padding: the last valid one)
@@ -126,7 +124,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
   // RESIDENT: the ticket of this workgroup's next item is drawn now, by thread 0, so that the atomic's round trip
   // runs under the epilogue instead of in front of the next item; the value is parked in the LDS at the very end.
   int pre_v = -1;
-  if (RESIDENT && pre_ctr && threadIdx.x == 0) pre_v = atomicAdd(pre_ctr, 1);
+  if (RESIDENT && threadIdx.x == 0) pre_v = atomicAdd(&tickets[(blockIdx.x + pre[1]) & 7], 1);
   unsigned char *patch = smem + w8 * kPatchBytes;
   // GEMM-2: the gate weights and the sole-slot marks of this wave's 128 rows come in once, coalesced, and wait in the
   // LDS behind the patches (1 KiB per wave), instead of 24 scattered loads in front of every 32-row block
@@ -369,16 +367,18 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();  // the patch is reused by the next block
   }
-  if (RESIDENT && pre_ctr && threadIdx.x == 0) *pre_slot = pre_v;
+  if (RESIDENT && threadIdx.x == 0) pre[0] = pre_v;
 }
 
 // One work item on the matrix cores.  Wave-uniform dispatch on the number of valid 32-row blocks: every variant
 // executes the same sequence of barriers.  poison != 0 (GEMM-2 inside the resident kernel, after a wait that gave up):
-// the rows are written as NaN.
-template <bool GATED, bool RESIDENT, bool FP8 = false, bool TRAIN = false>
+// the rows are written as NaN.  FAR (an A matrix of 4 GiB or more): one tile shape with 64-bit addresses for every item,
+// padding rows multiplied and not stored; kernels of its own, because beside the other variants it costs every kernel
+// registers (the resident ones spilled up to 174).  RESIDENT: tickets = the queues' counters, pre = (ticket drawn ahead,
+// queues tried so far).
+template <bool GATED, bool RESIDENT, bool FP8, bool TRAIN, bool FAR, bool BESIDE>
 __device__ __forceinline__ void gemm_bf16_item(const GemmArgs &g, unsigned char *smem, const int4 item,
-                                               int poison = 0, int32_t *pre_ctr = nullptr,
-                                               int *pre_slot = nullptr) {
+                                               int poison = 0, int32_t *tickets = nullptr, int *pre = nullptr) {
   const int le = item.x, m0 = item.y, rows = item.z & kItemRowsMask, nt = item.w & ((1 << kTileShift) - 1);
   // the expert's only M tile (uniform).  Only the resident kernels, which run the layers made of such tiles, have
   // the variants with streaming weight loads: in the per-item kernels they cost six more registers, and those
@@ -388,14 +388,15 @@ __device__ __forceinline__ void gemm_bf16_item(const GemmArgs &g, unsigned char 
   const int wm = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);  // wave row
   const int per_row = (nblk + 1) >> 1;                                   // blocks per wave row
   const int nb = max(0, min(per_row, nblk - per_row * wm));              // those of this wave that hold rows
-#define MOE355_TILE_(NB_, RW_, LONE_) \
-  gemm_bf16_tile<GATED, RESIDENT, NB_, RW_, FP8, TRAIN, LONE_>(g, smem, nt, le, m0, rows, poison, pre_ctr, pre_slot)
+#define MOE355_TILE_(NB_, RW_, LONE_)                                                                                 \
+  gemm_bf16_tile<GATED, RESIDENT, NB_, RW_, FP8, TRAIN, LONE_, FAR, BESIDE>(g, smem, nt, le, m0, rows, poison, tickets, \
+                                                                            pre)
 #define MOE355_TILE(NB_, RW_)                                                                                       \
   do {                                                                                                              \
     if (RESIDENT && RW_ > 32 && lone) MOE355_TILE_(NB_, RW_, (RESIDENT && RW_ > 32)); else MOE355_TILE_(NB_, RW_, false); \
   } while (0)
-  if (g.a_far) {  // (rare: a matrix of 4 GiB or more; padding rows are multiplied, not stored)
-    gemm_bf16_tile<GATED, RESIDENT, 4, 128, FP8, TRAIN, false, true>(g, smem, nt, le, m0, rows, poison, pre_ctr, pre_slot);
+  if constexpr (FAR) {
+    MOE355_TILE_(4, 128, false);
   } else if (nblk <= 2) {
     if (nb == 1) MOE355_TILE(1, 32); else MOE355_TILE(0, 32);
   } else if (nblk <= 4) {
@@ -409,13 +410,15 @@ __device__ __forceinline__ void gemm_bf16_item(const GemmArgs &g, unsigned char 
 #undef MOE355_TILE_
 }
 
-// One workgroup per work item; workgroup -> item by chunked_item.
-template <bool GATED, bool FP8 = false, bool TRAIN = false>
+// One workgroup per work item; workgroup -> item by chunked_item.  BESIDE: the GEMMs of the backward pass, which share
+// their CU with the operand transposes on the side stream: 248 registers (a SIMD has 512: 16 are left beside the two waves
+// of the workgroup) and 128 KiB of LDS.
+template <bool GATED, bool FP8 = false, bool TRAIN = false, bool FAR = false, bool BESIDE = false>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_kernel(const GemmArgs g) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // 2 stages x 64 KiB
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds, BESIDE: kGemmLdsBeside
   const int q = chunked_item(blockIdx.x, *g.n_items);
   if (q < 0) return;
-  gemm_bf16_item<GATED, false, FP8, TRAIN>(g, smem, g.work[q]);
+  gemm_bf16_item<GATED, false, FP8, TRAIN, FAR, BESIDE>(g, smem, g.work[q]);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -459,7 +462,7 @@ constexpr int kMaxPolls = 1 << 22;  // default bound: several seconds
 // tile_done (GEMM-2 only, may be null): counter per M tile that every finished item of the tile is counted in, for
 // the Combine stage that follows in the same launch; s_done: kDoneCap ints of LDS (tiles of the finished items).
 constexpr int kDoneCap = 256;
-template <bool GATED, bool FP8 = false, bool TRAIN = false>
+template <bool GATED, bool FP8, bool TRAIN, bool FAR>
 __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char *smem, int *s_item,
                                                 int32_t *__restrict__ tickets, int32_t *__restrict__ tile_ready,
                                                 int32_t *__restrict__ error, int nt1, int max_polls,
@@ -467,11 +470,12 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
   const int home = blockIdx.x & 7;
   const int n_items = *g.n_items;
   const int n_virtual = (n_items + 8 * kChunk - 1) / (8 * kChunk) * (8 * kChunk);
-  int qsel = 0;  // queues tried so far, in the order home, home + 1, ... (only thread 0's copy is used)
+  // s_item: [0] list position, [1] its wait gave up, [2] ticket drawn ahead (-1: none), [3] queues tried so far, in the
+  // order home, home + 1, ...  Written by thread 0; in the LDS because the tile has no register to spare for them.
   // Next list position for this workgroup, or -1 when every queue is empty (thread 0 only).
   // pre >= 0: a ticket of the queue this workgroup is on, drawn ahead under the previous item's epilogue
-  auto draw = [&](int pre) {
-    int q = -1;
+  auto draw = [&]() {
+    int q = -1, pre = s_item[2], qsel = s_item[3];
     while (qsel < 8) {
       const int queue = (home + qsel) & 7;
       const int v = queue + 8 * (pre >= 0 ? pre : atomicAdd(&tickets[queue], 1));
@@ -496,6 +500,8 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
       }
       qsel = next;
     }
+    s_item[2] = -1;
+    s_item[3] = qsel;
     return q;
   };
   // GEMM-2 items that feed Combine in the same launch: the o rows (and the y rows of sole slots) of all items this
@@ -518,21 +524,24 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
   // (Drawing the next ticket a whole item ahead, to hide the latency of the atomic, was measured slower: a workgroup
   // that holds a long item while it finishes another one keeps that item from an idle workgroup.  What is drawn
   // ahead here is drawn under the epilogue of the item that is being finished, a few microseconds before it is used.)
-  if (threadIdx.x == 0) s_item[2] = -1;
+  if (threadIdx.x == 0) {
+    s_item[2] = -1;
+    s_item[3] = 0;
+  }
   for (;;) {
     __syncthreads();  // the previous item is done with the LDS (and with *s_item)
-    if (threadIdx.x == 0) {
-      *s_item = draw(s_item[2]);
-      s_item[2] = -1;
-    }
+    if (threadIdx.x == 0) *s_item = draw();
     __syncthreads();
-    const int q = *s_item;
+    const int q = __builtin_amdgcn_readfirstlane(*s_item);
     if (q < 0) break;  // nothing left in any queue
-    const int4 item = g.work[q];
+    int4 item = g.work[q];  // (the same in every lane: kept in scalar registers)
+    item.x = __builtin_amdgcn_readfirstlane(item.x);
+    item.y = __builtin_amdgcn_readfirstlane(item.y);
+    item.z = __builtin_amdgcn_readfirstlane(item.z);
+    item.w = __builtin_amdgcn_readfirstlane(item.w);
     const int tile = item.w >> kTileShift;
-    int32_t *pre_ctr = tickets + ((home + qsel) & 7);  // (thread 0's value is the one that is used)
     if (GATED) {
-      gemm_bf16_item<true, true, FP8, TRAIN>(g, smem, item, 0, pre_ctr, s_item + 2);
+      gemm_bf16_item<true, true, FP8, TRAIN, FAR, false>(g, smem, item, 0, tickets, s_item + 2);
       // Release side of the hand-over.  Every wave first waits until its own h stores have been acknowledged, so that
       // the one write-back below cannot overtake any of them (a workgroup barrier alone does not wait for global
       // stores).
@@ -567,7 +576,7 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
         s_item[1] = gave_up;
       }
       __syncthreads();
-      gemm_bf16_item<false, true, FP8>(g, smem, item, s_item[1], pre_ctr, s_item + 2);
+      gemm_bf16_item<false, true, FP8, false, FAR, false>(g, smem, item, s_item[1], tickets, s_item + 2);
       if (tile_done) {
         // remembered, counted later (flush_done): one write-back for all the items of this workgroup
         if (threadIdx.x == 0) s_done[n_pending] = tile;
@@ -627,38 +636,41 @@ __device__ __forceinline__ void resident_combine(const PipelineArgs &p) {
   }
 }
 
+template <bool FAR>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_pipeline_kernel(const PipelineArgs p) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // 2 stages x 64 KiB
-  __shared__ int s_item[3];  // [0] list position drawn by thread 0, [1] its wait gave up, [2] ticket drawn ahead
-  gemm_bf16_drain<true>(p.g1, smem, s_item, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
-  gemm_bf16_drain<false>(p.g2, smem, s_item, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds
+  __shared__ int s_item[4];  // (see gemm_bf16_drain)
+  gemm_bf16_drain<true, false, false, FAR>(p.g1, smem, s_item, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
 }
 
 // The resident kernel with Combine as its third stage: the whole layer after the tile table in one launch.
+template <bool FAR>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_combine_kernel(const PipelineArgs p) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // 2 stages x 64 KiB
-  __shared__ int s_item[3];
-  gemm_bf16_drain<true>(p.g1, smem, s_item, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds
+  __shared__ int s_item[4];
+  gemm_bf16_drain<true, false, false, FAR>(p.g1, smem, s_item, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
   __shared__ int s_done[kDoneCap];
-  gemm_bf16_drain<false>(p.g2, smem, s_item, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls, p.tile_done,
+  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls, p.tile_done,
                          s_done);
   resident_combine(p);
 }
 
 // The same resident kernel for the training forward: GEMM-1 also keeps g and u.
+template <bool FAR>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_train_pipeline_kernel(const PipelineArgs p) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // 2 stages x 64 KiB
-  __shared__ int s_item[3];
-  gemm_bf16_drain<true, false, true>(p.g1, smem, s_item, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
-  gemm_bf16_drain<false>(p.g2, smem, s_item, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds
+  __shared__ int s_item[4];
+  gemm_bf16_drain<true, false, true, FAR>(p.g1, smem, s_item, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
 }
 
-// The same resident kernel on E4M3 operands.
+// The same resident kernel on E4M3 operands (whose rows number less than 2^32 elements, i.e. bytes).
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp8_pipeline_kernel(const PipelineArgs p) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // 2 stages x 64 KiB
-  __shared__ int s_item[3];
-  gemm_bf16_drain<true, true>(p.g1, smem, s_item, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
-  gemm_bf16_drain<false, true>(p.g2, smem, s_item, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds
+  __shared__ int s_item[4];
+  gemm_bf16_drain<true, true, false, false>(p.g1, smem, s_item, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<false, true, false, false>(p.g2, smem, s_item, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
 }
 
 }  // namespace moe355

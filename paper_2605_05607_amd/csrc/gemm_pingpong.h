@@ -68,6 +68,12 @@ __device__ __forceinline__ void slot_barrier() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// Where a lane reads its row of a 32-row block whose rows are 128 bytes with permuted chunks (see RowRequests): chunk
+// 2 kk + lane / 32 of row `row` (row % 32 = lane % 32) is at this offset ^ 32 kk.
+__device__ __forceinline__ int row_read_offset(int row, int lane) {
+  return row * 128 + (((lane >> 5) ^ ((lane >> 1) & 7)) * 16);
+}
+
 // The rows of A as this wave requests them: instruction i of region h moves eight rows (128 bytes each, lane = row by
 // chunk).  The stage image is [row][128 bytes] with the eight 16-byte chunks of a row permuted by (row >> 1) & 7 (gfx950's
 // LDS has 64 banks and serves a 128-bit read 16 lanes at a time); the LDS side of the load is linear in the lane, so the
@@ -80,20 +86,26 @@ struct RowRequests {
   const unsigned char *base;
   uint32_t at[H][I];
   uint32_t pitch;   // bytes of a row of A
-  uint32_t chunks;  // this lane's chunk of instruction i, region h: 4 bits each
+  // FAR: this lane's chunk of instruction i, region h, 4 bits each.  Otherwise (no register to spare) scalar bits: whether
+  // the instruction's first row is an odd multiple of eight, which with the lane gives the chunk.
+  uint32_t chunks;
   __device__ __forceinline__ void init(const void *A, int lda) {
     base = static_cast<const unsigned char *>(A);
     pitch = (uint32_t)lda * (FP8 ? 1 : 2);
     rsrc = lds_load_rsrc(base, 0xFFFFFFFFu);
     chunks = 0;
   }
-  // row = row of the tile (image position), a_row = row of the matrix
+  // row = row of the tile (image position: a multiple of eight plus lane / 8), a_row = row of the matrix
   __device__ __forceinline__ void set(int h, int i, int row, uint32_t a_row, int lane) {
     const uint32_t chunk = (lane & 7) ^ ((row >> 1) & 7);
-    chunks |= chunk << (4 * (h * I + i));
+    chunks |= FAR ? chunk << (4 * (h * I + i)) : (__builtin_amdgcn_readfirstlane(row >> 3) & 1) << (h * I + i);
     at[h][i] = FAR ? a_row : a_row * pitch + chunk * 16;
   }
-  __device__ __forceinline__ uint32_t chunk_of(int h, int i) const { return (chunks >> (4 * (h * I + i))) & 7; }
+  __device__ __forceinline__ uint32_t chunk_of(int h, int i) const {
+    if (FAR) return (chunks >> (4 * (h * I + i))) & 7;
+    uint32_t lane = threadIdx.x & 63;
+    return (lane & 7) ^ (lane >> 4) ^ ((chunks >> (h * I + i)) & 1) << 2;
+  }
   // call before the first request of the last k-step
   __device__ __forceinline__ void clip(int K, int kt_last) {
 #pragma unroll
@@ -149,7 +161,6 @@ struct PingPong {
   uint32_t lds;            // LDS address of the stages
   const unsigned char *smem;
   int a_rd, b_rd;  // this lane's row / operand in a stage
-  int khalf, sw;
   bf16x8 fa[2][2][4], fb[2][4];
   const unsigned char *slab_a, *slab_b;  // GRAD: slab 0 of this workgroup's columns
   size_t step_a, step_b;
@@ -179,15 +190,15 @@ struct PingPong {
     load_to_lds<LONE>(rb, l + 1024, b_voff, s + 1024);
   }
   __device__ __forceinline__ void read_a(int h, int i, int kt) {
-    const unsigned char *s = smem + (kt & 1) * kStage + a_rd + (h * 2 + i) * 4096;
+    const unsigned char *s = smem + (kt & 1) * kStage + (h * 2 + i) * 4096;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) fa[h][i][kk] = *reinterpret_cast<const bf16x8 *>(s + ((kk * 2 + khalf) ^ sw) * 16);
+    for (int kk = 0; kk < 4; ++kk) fa[h][i][kk] = *reinterpret_cast<const bf16x8 *>(s + (a_rd ^ kk * 32));
   }
   __device__ __forceinline__ void read_b(int j, int kt) {
-    const unsigned char *s = smem + (kt & 1) * kStage + b_rd + j * 4096;
+    const unsigned char *s = smem + (kt & 1) * kStage + j * 4096;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
-      fb[j][kk] = *reinterpret_cast<const bf16x8 *>(s + (GRAD ? ((kk * 2 + khalf) ^ sw) * 16 : kk * 1024));
+      fb[j][kk] = *reinterpret_cast<const bf16x8 *>(s + (GRAD ? b_rd ^ kk * 32 : b_rd + kk * 1024));
   }
   template <int H, int J>
   __device__ __forceinline__ void multiply(f32x16 (&acc)[NB][2]) {
@@ -280,18 +291,18 @@ struct PingPong {
 // Tiles of at most 128 rows: bound by the weight stream, so what counts is the bytes a CU keeps in flight.  A ring of
 // three stages (RW = 64: 16 KiB of rows and 32 KiB of weights; RW = 32, at most 64 rows: 8 and 32 KiB); a k-step reads all
 // its operands into registers first, so that the stage is free again and three slabs are on the way while it multiplies.  The wave rows share the rows, RW each, so that all
-// four SIMDs have work.
+// four SIMDs have work.  BESIDE (kernels that leave LDS to others on their CU): two stages for RW = 64.
 // ------------------------------------------------------------------------------------------------
-template <bool FP8, int NB, int RW, bool LONE>
+template <bool FP8, int NB, int RW, bool LONE, bool BESIDE>
 struct SlabRing {
-  static constexpr int kA = RW * 2 * 128, kStage = kA + kTileBytes, kStages = 3;
+  static constexpr int kA = RW * 2 * 128, kStage = kA + kTileBytes, kStages = BESIDE && RW == 64 ? 2 : 3;
   static constexpr int kRowLoads = RW / 32;                  // KiB of rows each wave requests per slab
   static constexpr int kLoads = kRowLoads + 4;
   RowRequests<FP8, 1, kRowLoads, false> rows;
   i32x4 rb;
   uint32_t b_voff, a_lds, b_soff, lds;
   const unsigned char *smem;
-  int a_rd, b_rd, khalf, sw;
+  int a_rd, b_rd;
 
   __device__ __forceinline__ void request(int stage, int kt) const {
     const uint32_t l = lds + stage * kStage;
@@ -312,21 +323,23 @@ struct SlabRing {
     int stage = 0;
     for (int kt = 0; kt < KT; ++kt) {
       // slab kt is here (this wave's part; the barrier: everybody's)
-      if (kt + 2 < KT) wait_loads<2 * kLoads>(); else if (kt + 1 < KT) wait_loads<kLoads>(); else wait_loads<0>();
+      if (kStages > 2 && kt + 2 < KT) wait_loads<2 * kLoads>();
+      else if (kt + 1 < KT) wait_loads<kLoads>();
+      else wait_loads<0>();
       slot_barrier();
       bf16x8 fa[NB > 0 ? NB : 1][4], fb[2][4];
       if constexpr (NB > 0) {
-        const unsigned char *sa = smem + stage * kStage + a_rd, *sb = smem + stage * kStage + kA + b_rd;
+        const unsigned char *sa = smem + stage * kStage, *sb = smem + stage * kStage + kA + b_rd;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
 #pragma unroll
           for (int j = 0; j < 2; ++j) fb[j][kk] = *reinterpret_cast<const bf16x8 *>(sb + j * 4096 + kk * 1024);
 #pragma unroll
           for (int i = 0; i < NB; ++i)
-            fa[i][kk] = *reinterpret_cast<const bf16x8 *>(sa + i * 4096 + ((kk * 2 + khalf) ^ sw) * 16);
+            fa[i][kk] = *reinterpret_cast<const bf16x8 *>(sa + i * 4096 + (a_rd ^ kk * 32));
         }
       }
-      // everybody has read it: its stage takes the slab three steps on
+      // everybody has read it: its stage takes the slab kStages steps on
       wait_lds_reads();
       slot_barrier();
       if (kt + kStages < KT) ask(stage, kt + kStages);
@@ -348,7 +361,7 @@ struct SlabRing {
               for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16(fa[i][kk], fb[j][kk], acc[i][j]);
         }
       }
-      stage = stage == 2 ? 0 : stage + 1;
+      stage = stage == kStages - 1 ? 0 : stage + 1;
     }
   }
 };

@@ -147,10 +147,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void wgrad_bf16_kernel(const Wgrad
   Loop loop;
   loop.lds = lds_address(smem);
   loop.smem = smem;
-  loop.khalf = khalf;
-  loop.sw = (lane >> 1) & 7;
-  loop.a_rd = (wm * 128 + l31) * 128;
-  loop.b_rd = Loop::kB + (wn * 64 + l31) * 128;
+  loop.a_rd = row_read_offset(wm * 128 + l31, lane);
+  loop.b_rd = Loop::kB + row_read_offset(wn * 64 + l31, lane);
   loop.b_soff = (wave >> 1) * 8192 + (wave & 1) * 2048;
   loop.step_a = (size_t)a.lda * 128;
   loop.step_b = (size_t)a.ldb * 128;
