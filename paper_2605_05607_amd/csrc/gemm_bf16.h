@@ -37,6 +37,8 @@ constexpr int kGemmLds = 3 * (kBM / 2 * kBK * 2 + kTileBytes);  // 144 KiB: the 
 constexpr int kGemmLdsBeside = 2 * 65536;  // the same with a ring of two stages there: the two stages of the full tiles
 constexpr int kPatchBytes = 32 * 288;                     // per-wave epilogue patch (fits 8 x in the stages)
 
+__device__ __forceinline__ bool first_thread(int wave) { return wave == 0 && fresh_lane() == 0; }
+
 // FP8: A and the packed B hold E4M3 codes; a k-step then covers 128 reduction indices in the same 128 bytes per row,
 // so the slabs, the LDS image and the fragment reads are byte for byte those of the bf16 tile.  The scales
 // (g.a_scale per token, g.b_scale per expert and output column, g.h_scale per expert) are applied in the epilogues
@@ -48,16 +50,13 @@ constexpr int kPatchBytes = 32 * 288;                     // per-wave epilogue p
 //            g.aux2 = w silu(g) u [rows, N] bf16 (the h operand of the down-projection weight gradient, weight folded in).
 template <bool GATED, bool RESIDENT, int NB, int RW, bool FP8, bool TRAIN, bool LONE, bool FAR, bool BESIDE>
 __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char *smem, int nt, int le, int m0,
-                                               int rows, int poison = 0,
+                                               int rows, int wave, int poison = 0,
                                                int32_t *tickets = nullptr, int *pre = nullptr) {
-  // RESIDENT (the kernel that loops over items): the thread index goes through an empty asm so that nothing
-  // derived from it counts as loop invariant; hoisting those values across items costs more registers than the
+  // wave: number of the wave (scalar).  RESIDENT (the kernel that loops over items): the lane is computed anew, so that
+  // nothing derived from it counts as loop invariant; hoisting those values across items costs more registers than the
   // tile has to spare.
-  int tid = threadIdx.x;
-  if (RESIDENT) asm volatile("" : "+v"(tid));
-  const int lane = tid & 63;
-  const int w8 = tid >> 6;
-  const int wm = w8 >> 2, wn = w8 & 3;
+  const int lane = RESIDENT ? fresh_lane() : threadIdx.x & 63;
+  const int w8 = wave, wm = wave >> 2, wn = wave & 3;
 
   f32x16 acc[NB > 0 ? NB : 1][2];
 #pragma unroll
@@ -68,12 +67,13 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
       for (int r = 0; r < 16; ++r) acc[mi][j][r] = 0.f;
 
   const int l31 = lane & 31, khalf = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(w8);
   // Weight tiles of a streaming item (at most 64 rows), and of any item that is its expert's only M tile (LONE), are
   // read once by one workgroup: requested with the non-temporal hint so that they do not push the operands that other
   // tiles share out of the L2.
-  typename std::conditional<(RW > 64), PingPong<FP8, (NB > 0 ? NB : 1), RW, LONE, FAR>,
-                            SlabRing<FP8, NB, (RW > 64 ? 64 : RW), LONE || RW == 32, BESIDE>>::type loop;
+  typename std::conditional<
+      (RW > 64), PingPong<FP8, (NB > 0 ? NB : 1), RW, LONE, FAR>,
+      typename std::conditional<RW == 64 && !BESIDE, FlowRing<FP8, (NB > 0 ? NB : 1), LONE>,
+                                SlabRing<FP8, NB, (RW > 64 ? 64 : RW), LONE || RW == 32>>::type>::type loop;
   loop.rows.init(g.A, g.lda);
   loop.rb = lds_load_rsrc(static_cast<const unsigned char *>(g.Bp) + ((size_t)(le * g.n_ntiles + nt) * g.n_ktiles) * kTileBytes,
                           (uint32_t)g.n_ktiles * kTileBytes);
@@ -124,7 +124,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
   // RESIDENT: the ticket of this workgroup's next item is drawn now, by thread 0, so that the atomic's round trip
   // runs under the epilogue instead of in front of the next item; the value is parked in the LDS at the very end.
   int pre_v = -1;
-  if (RESIDENT && threadIdx.x == 0) pre_v = atomicAdd(&tickets[(blockIdx.x + pre[1]) & 7], 1);
+  if (RESIDENT && first_thread(wave)) pre_v = atomicAdd(&tickets[(blockIdx.x + pre[1]) & 7], 1);
   unsigned char *patch = smem + w8 * kPatchBytes;
   // GEMM-2: the gate weights and the sole-slot marks of this wave's 128 rows come in once, coalesced, and wait in the
   // LDS behind the patches (1 KiB per wave), instead of 24 scattered loads in front of every 32-row block
@@ -367,7 +367,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();  // the patch is reused by the next block
   }
-  if (RESIDENT && threadIdx.x == 0) pre[0] = pre_v;
+  if (RESIDENT && first_thread(wave)) pre[0] = pre_v;
 }
 
 // One work item on the matrix cores.  Wave-uniform dispatch on the number of valid 32-row blocks: every variant
@@ -377,7 +377,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
 // registers (the resident ones spilled up to 174).  RESIDENT: tickets = the queues' counters, pre = (ticket drawn ahead,
 // queues tried so far).
 template <bool GATED, bool RESIDENT, bool FP8, bool TRAIN, bool FAR, bool BESIDE>
-__device__ __forceinline__ void gemm_bf16_item(const GemmArgs &g, unsigned char *smem, const int4 item,
+__device__ __forceinline__ void gemm_bf16_item(const GemmArgs &g, unsigned char *smem, const int4 item, int wave,
                                                int poison = 0, int32_t *tickets = nullptr, int *pre = nullptr) {
   const int le = item.x, m0 = item.y, rows = item.z & kItemRowsMask, nt = item.w & ((1 << kTileShift) - 1);
   // the expert's only M tile (uniform).  Only the resident kernels, which run the layers made of such tiles, have
@@ -385,12 +385,12 @@ __device__ __forceinline__ void gemm_bf16_item(const GemmArgs &g, unsigned char 
   // kernels leave 16 registers per SIMD to the kernels that run beside them in the backward pass.
   const bool lone = (item.z & kItemLone) != 0;
   const int nblk = (rows + 31) >> 5;                                     // 1..8 blocks of 32 rows
-  const int wm = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);  // wave row
+  const int wm = wave >> 2;                                              // wave row
   const int per_row = (nblk + 1) >> 1;                                   // blocks per wave row
   const int nb = max(0, min(per_row, nblk - per_row * wm));              // those of this wave that hold rows
 #define MOE355_TILE_(NB_, RW_, LONE_)                                                                                 \
-  gemm_bf16_tile<GATED, RESIDENT, NB_, RW_, FP8, TRAIN, LONE_, FAR, BESIDE>(g, smem, nt, le, m0, rows, poison, tickets, \
-                                                                            pre)
+  gemm_bf16_tile<GATED, RESIDENT, NB_, RW_, FP8, TRAIN, LONE_, FAR, BESIDE>(g, smem, nt, le, m0, rows, wave, poison, \
+                                                                            tickets, pre)
 #define MOE355_TILE(NB_, RW_)                                                                                       \
   do {                                                                                                              \
     if (RESIDENT && RW_ > 32 && lone) MOE355_TILE_(NB_, RW_, (RESIDENT && RW_ > 32)); else MOE355_TILE_(NB_, RW_, false); \
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_kernel(const GemmAr
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds, BESIDE: kGemmLdsBeside
   const int q = chunked_item(blockIdx.x, *g.n_items);
   if (q < 0) return;
-  gemm_bf16_item<GATED, false, FP8, TRAIN, FAR, BESIDE>(g, smem, g.work[q]);
+  gemm_bf16_item<GATED, false, FP8, TRAIN, FAR, BESIDE>(g, smem, g.work[q], __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -463,7 +463,7 @@ constexpr int kMaxPolls = 1 << 22;  // default bound: several seconds
 // the Combine stage that follows in the same launch; s_done: kDoneCap ints of LDS (tiles of the finished items).
 constexpr int kDoneCap = 256;
 template <bool GATED, bool FP8, bool TRAIN, bool FAR>
-__device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char *smem, int *s_item,
+__device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char *smem, int *s_item, int wave,
                                                 int32_t *__restrict__ tickets, int32_t *__restrict__ tile_ready,
                                                 int32_t *__restrict__ error, int nt1, int max_polls,
                                                 int32_t *__restrict__ tile_done = nullptr, int *s_done = nullptr) {
@@ -512,7 +512,7 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
   auto flush_done = [&]() {
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);  // this wave's stores have been acknowledged
     __syncthreads();
-    if (threadIdx.x == 0 && n_pending > 0) {
+    if (first_thread(wave) && n_pending > 0) {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);  // the write-back is complete before the counters move
       for (int i = 0; i < n_pending; ++i)
@@ -524,13 +524,13 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
   // (Drawing the next ticket a whole item ahead, to hide the latency of the atomic, was measured slower: a workgroup
   // that holds a long item while it finishes another one keeps that item from an idle workgroup.  What is drawn
   // ahead here is drawn under the epilogue of the item that is being finished, a few microseconds before it is used.)
-  if (threadIdx.x == 0) {
+  if (first_thread(wave)) {
     s_item[2] = -1;
     s_item[3] = 0;
   }
   for (;;) {
     __syncthreads();  // the previous item is done with the LDS (and with *s_item)
-    if (threadIdx.x == 0) *s_item = draw();
+    if (first_thread(wave)) *s_item = draw();
     __syncthreads();
     const int q = __builtin_amdgcn_readfirstlane(*s_item);
     if (q < 0) break;  // nothing left in any queue
@@ -541,13 +541,13 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
     item.w = __builtin_amdgcn_readfirstlane(item.w);
     const int tile = item.w >> kTileShift;
     if (GATED) {
-      gemm_bf16_item<true, true, FP8, TRAIN, FAR, false>(g, smem, item, 0, tickets, s_item + 2);
+      gemm_bf16_item<true, true, FP8, TRAIN, FAR, false>(g, smem, item, wave, 0, tickets, s_item + 2);
       // Release side of the hand-over.  Every wave first waits until its own h stores have been acknowledged, so that
       // the one write-back below cannot overtake any of them (a workgroup barrier alone does not wait for global
       // stores).
       __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
       __syncthreads();  // every thread's h stores happen before thread 0's release ...
-      if (threadIdx.x == 0) {
+      if (first_thread(wave)) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // ... which writes this XCD's L2 back: visible device-wide
         // The write-back has to be complete before the counter moves.  The compiler places no wait between the two
         // here (the wave has just waited for its stores, and the write-back is not counted as outstanding), so the
@@ -561,7 +561,7 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
       // the workgroup.  A wait that gives up (corrupt lists; cannot happen otherwise) raises the error word and the
       // item runs with a NaN in place of the gate weight, so that nothing computed from incomplete h can pass as a
       // result.
-      if (threadIdx.x == 0) {
+      if (first_thread(wave)) {
         int polls = 0, gave_up = 0;
         while (__hip_atomic_load(&tile_ready[tile], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < nt1) {
           __builtin_amdgcn_s_sleep(32);
@@ -576,10 +576,10 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
         s_item[1] = gave_up;
       }
       __syncthreads();
-      gemm_bf16_item<false, true, FP8, false, FAR, false>(g, smem, item, s_item[1], tickets, s_item + 2);
+      gemm_bf16_item<false, true, FP8, false, FAR, false>(g, smem, item, wave, s_item[1], tickets, s_item + 2);
       if (tile_done) {
         // remembered, counted later (flush_done): one write-back for all the items of this workgroup
-        if (threadIdx.x == 0) s_done[n_pending] = tile;
+        if (first_thread(wave)) s_done[n_pending] = tile;
         // (every thread counts: a uniform decision.)  Counting every item at once towards the end of the launch, so
         // that idle workgroups can reduce tokens while the last items run, was measured: no gain, the rows of the
         // last items are what the reduction waits for.
@@ -600,17 +600,15 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
 // Acquire side as in the GEMM-2 wait: relaxed device-scope polls, one acquire fence, then the loads.
 // A wait that gives up raises the error word and the token's row is written as NaN.
 // ------------------------------------------------------------------------------------------------
-__device__ __forceinline__ void resident_combine(const PipelineArgs &p) {
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));
-  const int lane = tid & 63;
+__device__ __forceinline__ void resident_combine(const PipelineArgs &p, int wave) {
+  const int lane = fresh_lane();
   const int n_waves = gridDim.x * (kGemmThreads / 64);
   const int base = p.offsets[p.e_lo];
   const int P = min(p.header[1], p.P_cap);
   const int d = p.g2.N;
   const float *rows = static_cast<const float *>(p.g2.out);
   bf16_t *y = static_cast<bf16_t *>(p.g2.y);
-  for (int t = blockIdx.x * (kGemmThreads / 64) + (tid >> 6); t < p.T; t += n_waves) {  // t is wave-uniform
+  for (int t = blockIdx.x * (kGemmThreads / 64) + wave; t < p.T; t += n_waves) {  // t is wave-uniform
     const int row = combine_slot_row(p.topk_idx, p.inv_perm, t, p.k, lane, p.e_lo, p.E_loc, base, P);
     const int tile = row >= 0 ? min(max(p.row_tile[row], 0), p.n_mtiles_cap - 1) : 0;
     const uint64_t slots = __ballot(row >= 0);
@@ -640,8 +638,9 @@ template <bool FAR>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_pipeline_kernel(const PipelineArgs p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds
   __shared__ int s_item[4];  // (see gemm_bf16_drain)
-  gemm_bf16_drain<true, false, false, FAR>(p.g1, smem, s_item, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
-  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  gemm_bf16_drain<true, false, false, FAR>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
 }
 
 // The resident kernel with Combine as its third stage: the whole layer after the tile table in one launch.
@@ -649,11 +648,12 @@ template <bool FAR>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_combine_kernel(const PipelineArgs p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds
   __shared__ int s_item[4];
-  gemm_bf16_drain<true, false, false, FAR>(p.g1, smem, s_item, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  gemm_bf16_drain<true, false, false, FAR>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
   __shared__ int s_done[kDoneCap];
-  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls, p.tile_done,
+  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls, p.tile_done,
                          s_done);
-  resident_combine(p);
+  resident_combine(p, wave);
 }
 
 // The same resident kernel for the training forward: GEMM-1 also keeps g and u.
@@ -661,16 +661,18 @@ template <bool FAR>
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_train_pipeline_kernel(const PipelineArgs p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds
   __shared__ int s_item[4];
-  gemm_bf16_drain<true, false, true, FAR>(p.g1, smem, s_item, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
-  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  gemm_bf16_drain<true, false, true, FAR>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
 }
 
 // The same resident kernel on E4M3 operands (whose rows number less than 2^32 elements, i.e. bytes).
 __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp8_pipeline_kernel(const PipelineArgs p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds
   __shared__ int s_item[4];
-  gemm_bf16_drain<true, true, false, false>(p.g1, smem, s_item, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
-  gemm_bf16_drain<false, true, false, false>(p.g2, smem, s_item, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  gemm_bf16_drain<true, true, false, false>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<false, true, false, false>(p.g2, smem, s_item, wave, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
 }
 
 }  // namespace moe355

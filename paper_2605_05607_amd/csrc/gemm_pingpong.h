@@ -68,6 +68,14 @@ __device__ __forceinline__ void slot_barrier() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// The lane's number, computed anew at every use: as a value that lives across a main loop (threadIdx is one) it takes a
+// register that the full tiles do not have.
+__device__ __forceinline__ int fresh_lane() {
+  uint32_t zero = 0;
+  asm volatile("" : "+s"(zero));
+  return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+}
+
 // Where a lane reads its row of a 32-row block whose rows are 128 bytes with permuted chunks (see RowRequests): chunk
 // 2 kk + lane / 32 of row `row` (row % 32 = lane % 32) is at this offset ^ 32 kk.
 __device__ __forceinline__ int row_read_offset(int row, int lane) {
@@ -103,7 +111,7 @@ struct RowRequests {
   }
   __device__ __forceinline__ uint32_t chunk_of(int h, int i) const {
     if (FAR) return (chunks >> (4 * (h * I + i))) & 7;
-    uint32_t lane = threadIdx.x & 63;
+    const uint32_t lane = fresh_lane();
     return (lane & 7) ^ (lane >> 4) ^ ((chunks >> (h * I + i)) & 1) << 2;
   }
   // call before the first request of the last k-step
@@ -288,14 +296,15 @@ struct PingPong {
 };
 
 // ------------------------------------------------------------------------------------------------
-// Tiles of at most 128 rows: bound by the weight stream, so what counts is the bytes a CU keeps in flight.  A ring of
-// three stages (RW = 64: 16 KiB of rows and 32 KiB of weights; RW = 32, at most 64 rows: 8 and 32 KiB); a k-step reads all
-// its operands into registers first, so that the stage is free again and three slabs are on the way while it multiplies.  The wave rows share the rows, RW each, so that all
-// four SIMDs have work.  BESIDE (kernels that leave LDS to others on their CU): two stages for RW = 64.
+// Tiles of at most 64 rows: bound by the weight stream, so what counts is the bytes a CU keeps in flight.  A ring of
+// three stages (RW = 32: 8 KiB of rows and 32 KiB of weights); a k-step reads all its operands into registers first, so
+// that the stage is free again and three slabs are on the way while it multiplies.  The wave rows share the rows, RW each,
+// so that all four SIMDs have work.  RW = 64, two stages: tiles of 65 to 128 rows in kernels that leave LDS to others on
+// their CU.
 // ------------------------------------------------------------------------------------------------
-template <bool FP8, int NB, int RW, bool LONE, bool BESIDE>
+template <bool FP8, int NB, int RW, bool LONE>
 struct SlabRing {
-  static constexpr int kA = RW * 2 * 128, kStage = kA + kTileBytes, kStages = BESIDE && RW == 64 ? 2 : 3;
+  static constexpr int kA = RW * 2 * 128, kStage = kA + kTileBytes, kStages = RW == 64 ? 2 : 3;
   static constexpr int kRowLoads = RW / 32;                  // KiB of rows each wave requests per slab
   static constexpr int kLoads = kRowLoads + 4;
   RowRequests<FP8, 1, kRowLoads, false> rows;
@@ -361,6 +370,74 @@ struct SlabRing {
               for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16(fa[i][kk], fb[j][kk], acc[i][j]);
         }
       }
+      stage = stage == kStages - 1 ? 0 : stage + 1;
+    }
+  }
+};
+
+// ------------------------------------------------------------------------------------------------
+// Tiles of 65 to 128 rows: a ring of three stages (16 KiB of rows and 32 KiB of weights), one barrier per k-step.
+// What bounds it: the weight stream, as long as a k-step's 1024 cycles of fragment reads (128 KiB) run under its 1024
+// cycles of matrix instructions: the waves read and multiply in their own time between two barriers.  Slab kt + 2 goes to
+// the stage that everybody has read before the barrier of k-step kt.
+// Measured, about 100 rows per expert, against reading everything, a second barrier, then multiplying (three slabs on the
+// way): 3200 tokens on 8 of 256 experts of 7168 x 2048 195 -> 185 us, 200 tokens on 8 of 16 experts of 2880 x 2880 149 ->
+// 138 us, FP8 140 -> 134 and 104 -> 99 us; at 64 rows and less (SlabRing) the slabs on the way count for more.
+// ------------------------------------------------------------------------------------------------
+template <bool FP8, int NB, bool LONE>
+struct FlowRing {
+  static constexpr int kA = 128 * 128, kStage = kA + kTileBytes, kStages = 3, kRowLoads = 2, kLoads = kRowLoads + 4;
+  RowRequests<FP8, 1, kRowLoads, false> rows;
+  i32x4 rb;
+  uint32_t b_voff, a_lds, b_soff, lds;
+  const unsigned char *smem;
+  int a_rd, b_rd;
+
+  __device__ __forceinline__ void run(f32x16 (&acc)[NB][2], int KT, int K) {
+    const bool tail = K % RowRequests<FP8, 1, kRowLoads, false>::KS != 0;
+    auto ask = [&](int stage, int kt) {
+      if (tail && kt == KT - 1) rows.clip(K, KT - 1);
+      const uint32_t l = lds + stage * kStage;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) load_to_lds<LONE>(rb, l + kA + b_soff + i * 1024, b_voff, kt * kTileBytes + b_soff + i * 1024);
+#pragma unroll
+      for (int i = 0; i < kRowLoads; ++i) rows.request(0, i, l + a_lds + i * 1024, kt);
+    };
+    ask(0, 0);
+    if (KT > 1) ask(1, 1);
+    int stage = 0;
+    for (int kt = 0; kt < KT; ++kt) {
+      wait_lds_reads();
+      if (kt + 1 < KT) wait_loads<kLoads>(); else wait_loads<0>();
+      slot_barrier();
+      if (kt + 2 < KT) ask(stage == 0 ? 2 : stage - 1, kt + 2);
+      bf16x8 fa[NB][4], fb[2][4];
+      const unsigned char *sa = smem + stage * kStage, *sb = smem + stage * kStage + kA + b_rd;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) fb[j][kk] = *reinterpret_cast<const bf16x8 *>(sb + j * 4096 + kk * 1024);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) fa[i][kk] = *reinterpret_cast<const bf16x8 *>(sa + i * 4096 + (a_rd ^ kk * 32));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (FP8) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+          for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              acc[i][j] = mfma_fp8_pair(fa[i][2 * p], fa[i][2 * p + 1], fb[j][2 * p], fb[j][2 * p + 1], acc[i][j]);
+      } else {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+          for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16(fa[i][kk], fb[j][kk], acc[i][j]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
       stage = stage == kStages - 1 ? 0 : stage + 1;
     }
   }

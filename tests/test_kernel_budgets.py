@@ -67,9 +67,8 @@ def test_backward_gemms_leave_room_beside_them(table):
 
 
 def test_gemm_kernels_do_not_spill(table):
-    # the resident kernels on E4M3 operands and those with 64-bit row addresses keep the thread index in scratch between items
+    # the resident kernel on E4M3 operands keeps one value in scratch between items
     for name, k in table.items():
-        if not re.search(r"gemm|wgrad|router_logits", name):
-            continue
-        one = re.search(r"gemm_fp8_pipeline|(pipeline|combine)_kernelILb1E", name)
-        assert k[".vgpr_spill_count"] <= (1 if one else 0), (name, k[".vgpr_spill_count"])
+        if re.search(r"gemm|wgrad|router_logits", name):
+            most = 1 if "gemm_fp8_pipeline" in name else 0
+            assert k[".vgpr_spill_count"] <= most, (name, k[".vgpr_spill_count"])
