@@ -185,9 +185,10 @@ MOE355_API int moe_pack_weights(const moe_shape *shape, const void *W_gate, cons
  * workgroups: a GEMM-2 tile starts as soon as the h rows of its 256-row tile are complete (per-tile readiness
  * counters in the workspace), the one-GPU form of the tile-granular GEMM-1 => GEMM-2 hand-over of the fused
  * kernel (Sec. IV-A, IV-B); otherwise the two GEMMs are two launches.  The result is the same either way.
- * Small batches (bf16, T <= 128, d and f >= 512, few rows per expert) run two weight-streaming kernels instead, which
- * need no tile table and no separate Combine; they split the reduction ranges, so their y can differ from the other
- * forms' in the rounding of the fp32 sums.
+ * Small batches run two weight-streaming kernels instead (and sometimes a third that adds their partial sums), which
+ * need no tile table and no separate Combine: bf16 layers with T <= 128, d and f >= 512 and few rows per expert (at most
+ * 12 on average), or more of them where all local weights together are at most 128 MB.  They split the reduction ranges,
+ * so their y can differ from the other forms' in the rounding of the fp32 sums.
  * A wait inside the resident kernel is bounded; if one gives up (corrupt tables; it cannot happen otherwise) the rows
  * computed from the incomplete tile are written as NaN and moe_forward_status reports 1 for this workspace.
  * `tables` must come from moe_build_dispatch on the same shape and topk_idx.
@@ -202,8 +203,9 @@ MOE355_API int moe_fused_forward(const moe_shape *shape, const void *x, const in
 /*
  * moe_fused_forward with the kernel boundaries marked for measurement: `events` points at five hipEvent_t
  * (created by the caller with timing enabled; a NULL entry is skipped) which are recorded on `stream`
- * [0] before the first kernel, [1] after the tile-table kernel, [2] after GEMM-1, [3] after GEMM-2 (recorded
- * together, after the one launch, when moe_forward_gemm_launches(shape) is 1), [4] after Combine.
+ * [0] before the first kernel, [1] after the tile-table kernel (small batches have none: before GEMM-1), [2] after
+ * GEMM-1, [3] after GEMM-2 (recorded together, after the one launch, when moe_forward_gemm_launches(shape) is 1), [4]
+ * after Combine (small batches: after the sum of GEMM-2's partial results, or with [3]).
  * The kernels and their order are those of moe_fused_forward.
  */
 MOE355_API int moe_fused_forward_timed(const moe_shape *shape, const void *x, const int32_t *topk_idx,
@@ -227,15 +229,17 @@ MOE355_API int moe_fused_forward_bounded(const moe_shape *shape, const void *x, 
                                          const void *packed_down, void *y, void *workspace, size_t workspace_bytes,
                                          void *stream, int max_polls, int wait_extra);
 
-/* 1 or 2: GEMM launches of moe_fused_forward for this shape (host-only; 0 for an invalid shape). */
+/* 1 or 2: GEMM launches of moe_fused_forward for this shape (host-only; 0 for an invalid shape): 1 = the resident kernel,
+ * 2 = one launch per GEMM, of the tile kernels or, for small batches, of the weight-streaming ones. */
 MOE355_API int moe_forward_gemm_launches(const moe_shape *shape);
 
 /*
  * moe_fused_forward with the choice between the two forms of the GEMM-1 => GEMM-2 hand-over made by the caller
  * (comparison of the two, timing of the two GEMMs apart): _two_launch keeps a kernel boundary between the GEMMs,
  * _one_launch runs the resident kernel with per-tile readiness counters (bf16 layers only, MOE_ERR_UNSUPPORTED
- * otherwise).  Same arguments, workspace and result as moe_fused_forward; `events` may be NULL, otherwise five
- * events as in moe_fused_forward_timed.
+ * otherwise).  Both run the tile kernels for every batch: the same y, bit for bit, from either, and from
+ * moe_fused_forward except for small batches (see there).  Same arguments and workspace; `events` may be NULL, otherwise
+ * five events as in moe_fused_forward_timed.
  */
 MOE355_API int moe_fused_forward_two_launch(const moe_shape *shape, const void *x, const int32_t *topk_idx,
                                             const float *topk_w, const moe_dispatch *tables,
@@ -254,9 +258,8 @@ MOE355_API int moe_fused_forward_one_launch(const moe_shape *shape, const void *
  * (Sec. IV-B, IV-C) on one GPU.  A workgroup that finds no GEMM-1 item left takes GEMM-2 items (each waits for the
  * counter of its M tile's GEMM-1 items), and one that finds no GEMM-2 item left reduces tokens, one wave per token:
  * the wave waits for the counters of finished GEMM-2 items of every M tile that holds one of the token's rows, then
- * sums the rows in slot order.  y is bit-identical to the one- and two-launch forms'.  bf16 layers with at most 4091 local experts (the
- * tile table's LDS), MOE_ERR_UNSUPPORTED otherwise.  Arguments as
- * moe_fused_forward_one_launch ([2] and [3] of `events` are recorded together after the launch, [4] right after);
+ * sums the rows in slot order.  y is bit-identical to the one- and two-launch forms'.  bf16 layers with at most 4091
+ * local experts, MOE_ERR_UNSUPPORTED otherwise.  Arguments as moe_fused_forward_one_launch ([2] and [3] of `events` are recorded together after the launch, [4] right after);
  * max_polls: bound on the polls of one wait (0 = the library's default of several seconds); wait_extra: every wait
  * expects that many more finished tiles than exist (0 in normal use; > 0 with a small bound is the test of the
  * give-up path: all kernels still exit, rows computed from incomplete data are NaN, moe_forward_status reports 1).
@@ -312,9 +315,9 @@ MOE355_API int moe_unfused_forward(const moe_shape *shape, const void *x, const 
  * moe_fp8_quantize_rows: the activation quantiser on its own: x [rows, cols] bf16 (16-byte aligned, cols % 8 == 0)
  *   -> codes [rows, cols] (8-byte aligned), scales [rows].  moe_fp8_fused_forward runs it on x internally.
  * moe_fp8_fused_forward: as moe_fused_forward with the packed FP8 weights and h_scale [E_loc] (device);
- *   workspace >= moe_fp8_forward_workspace_bytes(shape), 256-byte aligned; the two GEMMs run as one or two launches
- *   by the rule of moe_forward_gemm_launches.  `events` may be NULL, otherwise five events as in
- *   moe_fused_forward_timed ([1] follows the quantisation of x and the tile table).
+ *   workspace >= moe_fp8_forward_workspace_bytes(shape), 256-byte aligned; the forms are those of moe_fused_forward, by
+ *   the same rules (the 128 MB in bytes of FP8 weights).  `events` may be NULL, otherwise five events as in
+ *   moe_fused_forward_timed ([1] follows the quantisation of x and the tile table, if there is one).
  */
 MOE355_API size_t moe_fp8_packed_weight_bytes(const moe_shape *shape, int which);
 MOE355_API size_t moe_fp8_forward_workspace_bytes(const moe_shape *shape);

@@ -70,12 +70,14 @@ extern "C" size_t moe_workspace_bytes(const moe_shape *shape) {
   return std::max(moe_dispatch_workspace_bytes(shape), moe_forward_workspace_bytes(shape));
 }
 
+int moe355::tile_gemm_launches(const moe_shape *shape) {
+  return shape->dtype == MOE_BF16 && (int64_t)shape->T * shape->k < (int64_t)shape->E * kBM ? 1 : 2;
+}
+
 extern "C" int moe_forward_gemm_launches(const moe_shape *shape) {
   Derived dv;
   if (check_shape(shape, &dv) != MOE_OK) return 0;
-  // one resident launch with the tile-level hand-over when the mean number of rows per expert, T k / E, is below
-  // one M tile; a kernel boundary between the GEMMs otherwise (and always for fp32 layers)
-  return shape->dtype == MOE_BF16 && (int64_t)shape->T * shape->k < (int64_t)shape->E * kBM ? 1 : 2;
+  return stream_form(shape, dv, 2) ? 2 : tile_gemm_launches(shape);
 }
 
 extern "C" size_t moe_unfused_workspace_bytes(const moe_shape *shape) {

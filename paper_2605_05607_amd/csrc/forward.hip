@@ -237,7 +237,7 @@ static int launch_combine(const moe_shape *s, const Derived &dv, const float *ro
 // catches up with the weights (2.8 GB of weights, T = 64 / 96 / 128 at 16 / 24 / 32 rows per expert: 0.99 / 0.91 / 0.81 of
 // the tile kernels' speed; 8 rows: 1.02 to 1.7 x): the line is at 12 rows on average, except where the whole layer is so
 // small (128 MB) that the launches saved outweigh it (50 MB, 16 rows: 1.45 x).
-static bool use_stream(const moe_shape *s, const Derived &dv, int elt) {
+bool stream_form(const moe_shape *s, const Derived &dv, int elt) {
   if (s->dtype != MOE_BF16 || s->T > kStreamTokens || dv.E_loc > kStreamExperts || s->d < 512 || s->f < 512 ||
       stream2_lds_bytes(s->T, (int)dv.P_cap, dv.E_loc) > 160 * 1024)
     return false;
@@ -381,8 +381,8 @@ static int forward_common(const moe_shape *shape, const void *x, const int32_t *
   if ((gemm_launches == 1 || gemm_launches == 3) && shape->dtype != MOE_BF16) return MOE_ERR_UNSUPPORTED;
   const bool with_combine = gemm_launches == 3;
   if (with_combine && (!fused || fp8 || keep)) return MOE_ERR_UNSUPPORTED;
-  if (with_combine && dv.E_loc > 4091) return MOE_ERR_UNSUPPORTED;  // (bound of this form)
-  const bool pipelined = with_combine || (gemm_launches ? gemm_launches : moe_forward_gemm_launches(shape)) == 1;
+  if (with_combine && dv.E_loc > 4091) return MOE_ERR_UNSUPPORTED;  // (documented bound of this form)
+  const bool pipelined = with_combine || (gemm_launches ? gemm_launches : tile_gemm_launches(shape)) == 1;
   // a work item packs its N tile and its M-tile id into one word
   if (std::max(dv.nt1, dv.nt2) >= 1 << kTileShift || dv.max_mtiles >= 1 << (31 - kTileShift)) return MOE_ERR_UNSUPPORTED;
   // the GEMM kernels address A rows with 32-bit element offsets (row * row length)
@@ -425,7 +425,7 @@ static int forward_common(const moe_shape *shape, const void *x, const int32_t *
   }
   // the stream kernels are the form the library picks for a small batch; the forms a caller asks for by name (and the
   // training forward, which keeps its rows) run the tile kernels
-  if (fused && !keep && gemm_launches == 0 && use_stream(shape, dv, fp8 ? 1 : 2))
+  if (fused && !keep && gemm_launches == 0 && stream_form(shape, dv, fp8 ? 1 : 2))
     return launch_stream(shape, dv, x, topk_w, tables, packed_gate_up, packed_down, w, y, st, events, fp8 ? &q : nullptr);
   if ((rc = launch_prep(shape, dv, tables, topk_idx, topk_w, w, sole, st, with_combine)) != MOE_OK) return rc;
   mark(1);

@@ -77,6 +77,11 @@ def test_gemm_launch_rule_follows_rows_per_expert():
     assert lib.moe_forward_gemm_launches(C.byref(good_shape(T=8192, E=256, k=8, R=8))) == 2   # 256
     assert lib.moe_forward_gemm_launches(C.byref(good_shape(T=8, E=8, k=2, R=1, local_rank_end=1, dtype=B.MOE_F32))) == 2
     assert lib.moe_forward_gemm_launches(C.byref(good_shape(E=6, R=4))) == 0                 # invalid shape
+    # small batches: one weight-streaming launch per GEMM instead of the resident kernel (d, f < 512: not these)
+    small = dict(E=64, k=8, R=8, local_rank_begin=0, local_rank_end=1)
+    assert lib.moe_forward_gemm_launches(C.byref(good_shape(T=16, d=2048, f=768, **small))) == 2
+    assert lib.moe_forward_gemm_launches(C.byref(good_shape(T=16, d=504, f=768, **small))) == 1
+    assert lib.moe_forward_gemm_launches(C.byref(good_shape(T=129, d=2048, f=768, **small))) == 1
 
 
 def test_forward_rejects_extents_beyond_32bit_row_offsets():
