@@ -106,7 +106,8 @@ MOE355_API size_t moe_packed_weight_bytes(const moe_shape *shape, int which);
  * reading used is a bias-free linear map).  logits [T,E] fp32 = x [T,d] times the rows of W_r [E,d] (one row per
  * expert, element type of the layer), accumulated in fp32 in a fixed order: the same inputs give the same bits,
  * and so the same routing.  x and W_r must be 16-byte aligned; workspace >= moe_router_workspace_bytes(shape)
- * (partial sums of the parts the reduction range is cut into).  The result feeds moe_route_topk.
+ * (partial sums of the parts the reduction range is cut into; a buffer of that size also serves every smaller T, up to
+ * 131072 tokens).  The result feeds moe_route_topk.
  */
 MOE355_API size_t moe_router_workspace_bytes(const moe_shape *shape);
 MOE355_API int moe_router_logits(const moe_shape *shape, const void *x, const void *W_r, float *logits,
@@ -117,7 +118,7 @@ MOE355_API int moe_router_logits(const moe_shape *shape, const void *x, const vo
  * token rows to the picks): topk_idx / topk_w are those moe_route_topk gives on the logits moe_router_logits gives,
  * bit for bit (the same partial products, added in the same order), but the logits are summed inside the kernel that
  * picks and are written to `logits` [T,E] fp32 only if that pointer is not NULL.  x, W_r as for moe_router_logits;
- * workspace >= moe_route_from_x_workspace_bytes(shape), 16-byte aligned.
+ * workspace >= moe_route_from_x_workspace_bytes(shape) (also of any larger T, as above), 16-byte aligned.
  */
 MOE355_API size_t moe_route_from_x_workspace_bytes(const moe_shape *shape);
 MOE355_API int moe_route_from_x(const moe_shape *shape, const void *x, const void *W_r, float *logits,

@@ -232,8 +232,8 @@ using namespace moe355;
 struct RouterPlan {
   int bm, bn, parts;
 };
-static RouterPlan router_plan(const moe_shape *s) {
-  const int T = s->T > 0 ? s->T : 1, kt = ceil_div(s->d, kBK);
+static RouterPlan router_plan(const moe_shape *s, int T) {
+  const int kt = ceil_div(s->d, kBK);
   const int bn = s->E <= 128 ? 128 : 256;
   RouterPlan best{64, bn, 1};
   double t_best = 1e30;
@@ -253,23 +253,38 @@ static RouterPlan router_plan(const moe_shape *s) {
   return best;
 }
 
-static size_t router_bytes(const moe_shape *s, int parts) {
-  return align_up((size_t)parts * (size_t)(s->T > 0 ? s->T : 1) * s->E * sizeof(float) + 1, 256);
+static RouterPlan router_plan(const moe_shape *s) { return router_plan(s, s->T > 0 ? s->T : 1); }
+
+static size_t router_bytes(const moe_shape *s, int64_t rows) {
+  return align_up((size_t)rows * s->E * sizeof(float) + 1, 256);
+}
+
+// Rows of partial sums (parts times tokens) that this and every smaller batch needs (of at most kRouterSized tokens): a
+// caller sizes its buffer once for its largest batch, and a smaller one may be cut into more parts.  Within 64 tokens the
+// tile counts are the same and the parts do not increase (their sums cost T times as much), so the first batch of
+// each 64 bounds its parts.
+constexpr int kRouterSized = 1 << 17;
+static int64_t router_rows(const moe_shape *s, bool one_part_too) {
+  const int T = s->T > 0 ? s->T : 1;
+  const auto rows = [&](int parts, int t) { return parts > 1 || one_part_too ? (int64_t)parts * t : 0; };
+  int64_t most = rows(router_plan(s).parts, T);
+  for (int t0 = 0; t0 < std::min(T, kRouterSized); t0 += 64)
+    most = std::max(most, rows(router_plan(s, t0 + 1).parts, std::min(t0 + 64, T)));
+  return most;
 }
 
 extern "C" size_t moe_router_workspace_bytes(const moe_shape *shape) {
   Derived dv;
   if (check_shape(shape, &dv) != MOE_OK) return 0;
   if (shape->dtype != MOE_BF16) return 256;
-  const int parts = router_plan(shape).parts;
-  return router_bytes(shape, parts > 1 ? parts : 0);
+  return router_bytes(shape, router_rows(shape, false));
 }
 
 extern "C" size_t moe_route_from_x_workspace_bytes(const moe_shape *shape) {
   Derived dv;
   if (check_shape(shape, &dv) != MOE_OK) return 0;
   // the partial sums of every part (one part at least: the logits need not be stored anywhere else)
-  return router_bytes(shape, shape->dtype == MOE_BF16 ? router_plan(shape).parts : 1);
+  return router_bytes(shape, shape->dtype == MOE_BF16 ? router_rows(shape, true) : shape->T > 0 ? shape->T : 1);
 }
 
 // The product into `partial` (parts > 1) or straight into `direct` (one part).
@@ -313,7 +328,7 @@ extern "C" int moe_router_logits(const moe_shape *shape, const void *x, const vo
   if ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(W_r)) % 16 != 0) return MOE_ERR_INVALID_ARG;
   const RouterPlan plan = shape->dtype == MOE_BF16 ? router_plan(shape) : RouterPlan{0, 0, 1};
   const int parts = plan.parts;
-  if (!workspace || workspace_bytes < router_bytes(shape, parts > 1 ? parts : 0)) return MOE_ERR_WORKSPACE;
+  if (!workspace || workspace_bytes < router_bytes(shape, parts > 1 ? (int64_t)parts * shape->T : 0)) return MOE_ERR_WORKSPACE;
   if (shape->T == 0) return MOE_OK;
   hipStream_t st = (hipStream_t)stream;
   begin_launches();
@@ -345,7 +360,7 @@ extern "C" int moe_route_from_x(const moe_shape *shape, const void *x, const voi
   if ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(W_r)) % 16 != 0) return MOE_ERR_INVALID_ARG;
   const RouterPlan plan = shape->dtype == MOE_BF16 ? router_plan(shape) : RouterPlan{0, 0, 1};
   const int parts = plan.parts;
-  if (!workspace || workspace_bytes < router_bytes(shape, parts)) return MOE_ERR_WORKSPACE;
+  if (!workspace || workspace_bytes < router_bytes(shape, (int64_t)parts * std::max(shape->T, 1))) return MOE_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(workspace) % 16 != 0) return MOE_ERR_INVALID_ARG;
   if (shape->T == 0) return MOE_OK;
   hipStream_t st = (hipStream_t)stream;

@@ -155,6 +155,18 @@ def test_router_logits_arguments():
         assert B.moe_router_workspace_bytes(sh) <= 8 * cfg.T * cfg.E * 4 + 512
 
 
+@pytest.mark.parametrize("E,d,k", [(8, 4096, 2), (32, 2880, 4), (128, 2048, 8), (256, 7168, 8), (600, 512, 8)])
+def test_router_workspaces_serve_every_smaller_batch(E, d, k):
+    # sized once for the largest batch; a smaller one may be cut into more parts (at most 32 of the reduction range)
+    last = (0, 0)
+    for T in list(range(1, 700, 9)) + list(range(700, 20000, 77)):
+        s = good_shape(T=T, d=d, E=E, k=k, R=1, local_rank_begin=0, local_rank_end=1)
+        size = (B.moe_router_workspace_bytes(s), B.moe_route_from_x_workspace_bytes(s))
+        assert size[0] >= last[0] and size[1] >= last[1], T
+        assert max(size) <= 32 * T * E * 4 + 512 and size[1] >= T * E * 4, T
+        last = size
+
+
 def test_fp8_entry_points_arguments():
     lib = B.lib()
     s = good_shape()
