@@ -188,7 +188,8 @@ MOE355_API int moe_pack_weights(const moe_shape *shape, const void *W_gate, cons
  * kernel (Sec. IV-A, IV-B); otherwise the two GEMMs are two launches.  The result is the same either way.
  * Small batches run two weight-streaming kernels instead (and sometimes a third that adds their partial sums), which
  * need no tile table and no separate Combine: bf16 layers with T <= 128, d and f >= 512 and few rows per expert (at most
- * 12 on average), or more of them where all local weights together are at most 128 MB.  They split the reduction ranges,
+ * 12 on average), or more of them where all local weights together are at most 128 MB and, beyond 64 tokens, the
+ * estimated time favours it (moe_forward_gemm_launches tells, for bf16 weights).  They split the reduction ranges,
  * so their y can differ from the other forms' in the rounding of the fp32 sums.
  * A wait inside the resident kernel is bounded; if one gives up (corrupt tables; it cannot happen otherwise) the rows
  * computed from the incomplete tile are written as NaN and moe_forward_status reports 1 for this workspace.

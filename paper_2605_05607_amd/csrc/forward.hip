@@ -233,10 +233,16 @@ static int launch_combine(const moe_shape *s, const Derived &dv, const float *ro
 }
 
 // Small batches: the stream kernels (stream_gemm.h).  The reduction ranges have to give each of the eight waves work
-// (d, f >= 512).  A workgroup reads its expert's rows once per 32 columns, so with many rows per expert that traffic
-// catches up with the weights (2.8 GB of weights, T = 64 / 96 / 128 at 16 / 24 / 32 rows per expert: 0.99 / 0.91 / 0.81 of
-// the tile kernels' speed; 8 rows: 1.02 to 1.7 x): the line is at 12 rows on average, except where the whole layer is so
-// small (128 MB) that the launches saved outweigh it (50 MB, 16 rows: 1.45 x).
+// (d, f >= 512).  A workgroup reads its expert's rows once per 32 columns, and an expert's weights once per 64 rows.
+//   At most 12 rows per expert on average: always (2.3 GB of weights, 8 rows: 1.23 to 1.5 x the tile kernels' speed; 16, 24
+//   and 32 rows of a 2.8 GB layer: 0.99, 0.91 and 0.81 x).
+//   More rows: layers of at most 128 MB, where the launches saved count.  While an expert's rows fit one pass (T <= 64, or
+//   48 rows on average) that holds for all of them (1.2 to 2.5 x at 16 to 64 rows).
+//   Beyond, by estimated time (microseconds): the stream kernels take 4.6 (FP8: 4.0) per million weights of a matrix, the
+//   tile kernels 30 (FP8: 38) and 0.88 per k-step of the two reductions.  Measured at 96 and 128 rows, tile time / stream time: 8
+//   experts of 1024 x 1024 1.32 and 1.21 (FP8 1.45 and 1.30), 1536 x 1024 1.23 and 1.14 (1.31 and 1.20), 2048 x 1024 1.13 and
+//   1.04 (0.93 and 0.83), 1536 x 1536 0.92 and 0.84 (1.04 and 0.91), 2048 x 1280 0.83 and 0.77 (0.94 and 0.85); 4 of 2048 x
+//   2048 1.29 and 1.22 (1.02 and 0.92); 2 of 4096 x 2048 1.25 and 1.17 (1.33 and 1.26).
 bool stream_form(const moe_shape *s, const Derived &dv, int elt) {
   if (s->dtype != MOE_BF16 || s->T > kStreamTokens || dv.E_loc > kStreamExperts || s->d < 512 || s->f < 512 ||
       stream2_lds_bytes(s->T, (int)dv.P_cap, dv.E_loc) > 160 * 1024)
@@ -244,7 +250,12 @@ bool stream_form(const moe_shape *s, const Derived &dv, int elt) {
   // 32-bit offsets into the rows (2 GiB) and into one packed panel of 256 columns (512 bytes per reduction index)
   const int64_t widest = std::max(s->d, s->f);
   if (std::max<int64_t>(s->T, dv.P_cap) * widest * elt >= (int64_t)1 << 31 || widest >= 1 << 22) return false;
-  return (int64_t)s->T * s->k <= 12 * (int64_t)s->E || (int64_t)dv.E_loc * 3 * s->d * s->f * elt <= (int64_t)128 << 20;
+  const int64_t pairs = (int64_t)s->T * s->k, weights = (int64_t)dv.E_loc * s->d * s->f;
+  if (pairs <= 12 * (int64_t)s->E) return true;
+  if (weights * 3 * elt > (int64_t)128 << 20) return false;
+  if (s->T <= 64 || pairs <= 48 * (int64_t)s->E) return true;
+  const double stream = (elt == 1 ? 4.0e-6 : 4.6e-6) * weights;
+  return stream <= (elt == 1 ? 38.0 : 30.0) + 0.88 / 128 * elt * ((double)s->d + s->f);
 }
 
 // Work groups per strip of GEMM-2: one, unless so few strips of 32 columns exist that a second launch (~5 us) costs less

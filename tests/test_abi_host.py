@@ -82,6 +82,11 @@ def test_gemm_launch_rule_follows_rows_per_expert():
     assert lib.moe_forward_gemm_launches(C.byref(good_shape(T=16, d=2048, f=768, **small))) == 2
     assert lib.moe_forward_gemm_launches(C.byref(good_shape(T=16, d=504, f=768, **small))) == 1
     assert lib.moe_forward_gemm_launches(C.byref(good_shape(T=129, d=2048, f=768, **small))) == 1
+    # a small layer with many rows per expert: up to 64 tokens always, beyond only where it is the faster form
+    dense = dict(E=8, k=8, R=1, local_rank_begin=0, local_rank_end=1)
+    for T, d, f, launches in ((64, 1536, 1536, 2), (96, 1536, 1536, 1), (128, 2048, 1280, 1), (96, 1024, 1024, 2),
+                              (128, 1536, 1024, 2), (64, 2048, 2048, 1)):
+        assert lib.moe_forward_gemm_launches(C.byref(good_shape(T=T, d=d, f=f, **dense))) == launches, (T, d, f)
 
 
 def test_forward_rejects_extents_beyond_32bit_row_offsets():
