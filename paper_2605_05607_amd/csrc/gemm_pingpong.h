@@ -28,7 +28,7 @@ __device__ __forceinline__ f32x16 mfma_fp8_pair(bf16x8 a_lo, bf16x8 a_hi, bf16x8
 // ---- loads into the LDS ----
 // 16 bytes per lane from memory to LDS address lds + 16 lane.  Assembler, because the compiler would wait for every such
 // load in front of any LDS read that it cannot tell apart from its target; the waits are placed by hand instead (the main
-// loops have no other vector-memory operation).
+// loops have no other vector-memory operation: nothing is spilled).
 __device__ __forceinline__ i32x4 lds_load_rsrc(const void *base, uint32_t bytes) {
   const uint64_t a = reinterpret_cast<uint64_t>(base);
   i32x4 r;
@@ -152,8 +152,8 @@ struct RowRequests {
 // the requests it has issued since) in a slot before the one in which either row reads the region, and the barrier at
 // that slot's end tells the others.
 // Measured: 16 384 rows x 4096 x 14336 (two GEMMs), dense rows: 1.22 PFLOP/s with slabs staged through registers, one
-// barrier per k-step and all waves in step -> 1.42 PFLOP/s (the vendor library's dense product reaches 1.44 to 1.50 on
-// the box); whole prefill step of that layer 9.73 -> 8.40 ms.
+// barrier per k-step and all waves in step -> 1.38 PFLOP/s (the vendor library's dense product reaches 1.44 to 1.50 on
+// the box); whole prefill step of that layer 9.64 -> 8.84 ms.
 // ------------------------------------------------------------------------------------------------
 // GRAD (weight gradients, wgrad_bf16.h): both operands are slabs of [column][128 bytes], `step` bytes from one k-step to the
 // next, and both are requested and read as A is.
@@ -376,13 +376,16 @@ struct SlabRing {
 };
 
 // ------------------------------------------------------------------------------------------------
-// Tiles of 65 to 128 rows: a ring of three stages (16 KiB of rows and 32 KiB of weights), one barrier per k-step.
+// Tiles of 65 to 128 rows: a ring of three stages (16 KiB of rows and 32 KiB of weights), one barrier per k-step, in the
+// middle of its matrix instructions.
 // What bounds it: the weight stream, as long as a k-step's 1024 cycles of fragment reads (128 KiB) run under its 1024
-// cycles of matrix instructions: the waves read and multiply in their own time between two barriers.  Slab kt + 2 goes to
-// the stage that everybody has read before the barrier of k-step kt.
-// Measured, about 100 rows per expert, against reading everything, a second barrier, then multiplying (three slabs on the
-// way): 3200 tokens on 8 of 256 experts of 7168 x 2048 195 -> 185 us, 200 tokens on 8 of 16 experts of 2880 x 2880 149 ->
-// 138 us, FP8 140 -> 134 and 104 -> 99 us; at 64 rows and less (SlabRing) the slabs on the way count for more.
+// cycles of matrix instructions.  A wave reads slab kt, multiplies the first half as it arrives, and meets the others when
+// everybody has read slab kt and its share of slab kt + 1 is here; slab kt + 3 then goes to the stage of slab kt, and the
+// second half runs under the reads of slab kt + 1.
+// Measured, about 100 rows per expert, against reading everything, a second barrier, then multiplying: 3200 tokens on 8 of
+// 256 experts of 7168 x 2048 195 -> 180 us, 200 tokens on 8 of 16 experts of 2880 x 2880 149 -> 136 us, 100 tokens on 8
+// experts of 4096 x 1536 130 -> 119 us, FP8 140 -> 136, 104 -> 101 and 91 -> 85 us (the barrier in front of the reads: 188,
+// 137 and 122 us).  At 64 rows and less (SlabRing) the slabs on the way count for more.
 // ------------------------------------------------------------------------------------------------
 template <bool FP8, int NB, bool LONE>
 struct FlowRing {
@@ -403,14 +406,13 @@ struct FlowRing {
 #pragma unroll
       for (int i = 0; i < kRowLoads; ++i) rows.request(0, i, l + a_lds + i * 1024, kt);
     };
-    ask(0, 0);
-    if (KT > 1) ask(1, 1);
+#pragma unroll
+    for (int i = 0; i < kStages; ++i)
+      if (i < KT) ask(i, i);
+    if (KT > 2) wait_loads<2 * kLoads>(); else if (KT > 1) wait_loads<kLoads>(); else wait_loads<0>();
+    slot_barrier();
     int stage = 0;
     for (int kt = 0; kt < KT; ++kt) {
-      wait_lds_reads();
-      if (kt + 1 < KT) wait_loads<kLoads>(); else wait_loads<0>();
-      slot_barrier();
-      if (kt + 2 < KT) ask(stage == 0 ? 2 : stage - 1, kt + 2);
       bf16x8 fa[NB][4], fb[2][4];
       const unsigned char *sa = smem + stage * kStage, *sb = smem + stage * kStage + kA + b_rd;
 #pragma unroll
@@ -421,23 +423,29 @@ struct FlowRing {
         for (int i = 0; i < NB; ++i) fa[i][kk] = *reinterpret_cast<const bf16x8 *>(sa + i * 4096 + (a_rd ^ kk * 32));
       }
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (FP8) {
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
+      auto multiply = [&](int half) {
+        if constexpr (FP8) {
 #pragma unroll
           for (int i = 0; i < NB; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j)
-              acc[i][j] = mfma_fp8_pair(fa[i][2 * p], fa[i][2 * p + 1], fb[j][2 * p], fb[j][2 * p + 1], acc[i][j]);
-      } else {
+              acc[i][j] = mfma_fp8_pair(fa[i][2 * half], fa[i][2 * half + 1], fb[j][2 * half], fb[j][2 * half + 1], acc[i][j]);
+        } else {
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
+          for (int kk = 2 * half; kk < 2 * half + 2; ++kk)
 #pragma unroll
-          for (int i = 0; i < NB; ++i)
+            for (int i = 0; i < NB; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16(fa[i][kk], fb[j][kk], acc[i][j]);
-      }
+              for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16(fa[i][kk], fb[j][kk], acc[i][j]);
+        }
+      };
+      multiply(0);
       __builtin_amdgcn_sched_barrier(0);
+      wait_lds_reads();
+      if (kt + 2 < KT) wait_loads<kLoads>(); else wait_loads<0>();
+      slot_barrier();
+      if (kt + kStages < KT) ask(stage, kt + kStages);
+      multiply(1);
       stage = stage == kStages - 1 ? 0 : stage + 1;
     }
   }
