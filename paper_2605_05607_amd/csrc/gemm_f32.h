@@ -17,7 +17,7 @@ namespace moe355 {
 // loads ends at 63: a second group in flight would not fit it).  The waves of the workgroup share the reduction range (the layers have few tiles: what fills the chip is
 // cutting the sum) and meet in the LDS in wave order.
 // Measured on 8 experts of 512 x 1024, GEMM-1 + GEMM-2 of 256 tokens: 76 + 95 us with 64 x 64 tiles on the vector ALU ->
-// 29 + 17 us; step 191 -> 62 us, 8 tokens 185 -> 39 us, 2048 tokens 315 -> 226 us.
+// 29 + 17 us; step 192 -> 58 us, 8 tokens 189 -> 39 us, 2048 tokens 318 -> 195 us.
 // ------------------------------------------------------------------------------------------------
 template <int COLS>
 __device__ __forceinline__ void f32_fetch(float (&v)[COLS], rsrc_t r, uint32_t voff, uint32_t soff) {

@@ -7,9 +7,9 @@
 // (GEMM-1) or 32 output columns (GEMM-2), its waves share the reduction range, and the weights go from memory straight
 // into the registers the matrix instructions read: the packed tile stores an operand as one contiguous KiB, so there is
 // nothing for the LDS to rearrange.  The waves' partial sums meet in the LDS, in wave order.
-// Measured, forward step, before (tile table + tile kernels + Combine) -> here: 0.7 GB of weights for one token 262 ->
-// 133 us (5.3 TB/s), 34 MB for 16 tokens 67 -> 28 us, 2.3 GB for 96 tokens 417 -> 357 us (6.5 TB/s), 0.24 GB of FP8
-// weights for 48 tokens 115 -> 76 us.
+// Measured, whole step with route and tables, before (tile table + tile kernels + Combine) -> here: 0.7 GB of weights for
+// one token 262 -> 126 us, 34 MB for 16 tokens 67.7 -> 28.8 us, 2.3 GB for 96 tokens 399 -> 335 us, 0.24 GB of FP8
+// weights for 48 tokens 121 -> 85.6 us.
 #pragma once
 #include "gemm_bf16.h"
 
