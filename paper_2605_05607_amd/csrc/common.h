@@ -77,11 +77,18 @@ struct FwdLayout {
   size_t tile_ready;  // int32[max_mtiles] GEMM-1 items finished per M tile (hand-over inside the resident kernel)
   size_t row_tile;    // int32[P_cap]      M tile of each local row        } resident kernel that also runs
   size_t tile_done;   // int32[max_mtiles] GEMM-2 items finished per M tile } Combine
-  size_t h;         // elt  [P_cap, f]
+  size_t h;         // elt  [P_cap, h_pitch]
   size_t o;         // float[P_cap, d]
   size_t total;
 };
 FwdLayout forward_layout(const moe_shape *s, const Derived &dv);
+
+// Elements from one row of h to the next (elt = bytes of one).  The tile kernels of bf16 layers start every row on a
+// 128-byte line: the resident kernels hand rows over between XCDs without invalidating L2s, so a line must not hold rows of
+// two M tiles.
+inline int h_pitch(const moe_shape *s, int elt) {
+  return s->dtype == MOE_BF16 ? (int)align_up((size_t)s->f * elt, 128) / elt : s->f;
+}
 
 // ---- packed weight geometry ----
 // bf16: gate/up as [E_loc][ceil(f/128)][ceil(d/64)] tiles of 256 x 64 elements (128 gate + 128 up columns

@@ -133,15 +133,20 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
   g1.A = a1; g1.row_map = a1_map; g1.Bp = packed_gu; g1.out = w.h; g1.row_w = nullptr;
   g1.row_sole = nullptr; g1.y = nullptr;
   g1.n_items = w.header + 0; g1.work = w.work1;
-  g1.K = s->d; g1.N = s->f; g1.lda = a1_ld; g1.ldo = s->f;
+  int ldh = h_pitch(s, q ? 1 : dv.elt);
+  if (q && dv.P_cap * ldh >= (int64_t)1 << 32) {  // (padding the rows would take them out of reach of 32-bit offsets)
+    ldh = s->f;
+    pipelined = false;
+  }
+  g1.K = s->d; g1.N = s->f; g1.lda = a1_ld; g1.ldo = ldh;
   GemmArgs g2 = g1;
   g2.A = w.h; g2.row_map = nullptr; g2.Bp = packed_down; g2.out = w.o; g2.row_w = w.row_w;
   g2.row_sole = sole; g2.y = y;
-  g2.K = s->f; g2.N = s->d; g2.lda = s->f; g2.ldo = s->d;
+  g2.K = s->f; g2.N = s->d; g2.lda = ldh; g2.ldo = s->d;
   g2.n_items = w.header + 3; g2.work = w.work2;
   // (bf16 only: an operand has less than 2^32 elements, see forward_common)
   const bool far1 = (a1_map ? (int64_t)s->T : dv.P_cap) * a1_ld * 2 >= (int64_t)1 << 32;
-  const bool far2 = dv.P_cap * s->f * 2 >= (int64_t)1 << 32;
+  const bool far2 = dv.P_cap * ldh * 2 >= (int64_t)1 << 32;
   if (keep_gu) {  // training forward: g and u are kept, and every weighted row goes to the kept o
     g1.aux = keep_gu;
     g2.out = keep_o;

@@ -37,6 +37,13 @@ constexpr int kGemmLds = 3 * (kBM / 2 * kBK * 2 + kTileBytes);  // 144 KiB: the 
 constexpr int kGemmLdsBeside = 2 * 65536;  // the same with a ring of two stages there: the two stages of the full tiles
 constexpr int kPatchBytes = 32 * 288;                     // per-wave epilogue patch (fits 8 x in the stages)
 
+// Eight bytes of h, past the L2 of this XCD (a relaxed store of device scope): visible to the other XCDs as soon as it is
+// acknowledged.
+__device__ __forceinline__ void store_h_through(void *at, const unsigned char *from) {
+  __hip_atomic_store(static_cast<uint64_t *>(at), *reinterpret_cast<const uint64_t *>(from), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ bool first_thread(int wave) { return wave == 0 && fresh_lane() == 0; }
 
 // FP8: A and the packed B hold E4M3 codes; a k-step then covers 128 reduction indices in the same 128 bytes per row,
@@ -74,7 +81,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
       (RW > 64), PingPong<FP8, (NB > 0 ? NB : 1), RW, LONE, FAR>,
       typename std::conditional<RW == 64 && !BESIDE, FlowRing<FP8, (NB > 0 ? NB : 1), LONE>,
                                 SlabRing<FP8, NB, (RW > 64 ? 64 : RW), LONE || RW == 32>>::type>::type loop;
-  loop.rows.init(g.A, g.lda);
+  loop.rows.init(g.A, g.lda, (uint32_t)poison - 1u);  // (a wait that gave up: nothing of an incomplete h is read)
   loop.rb = lds_load_rsrc(static_cast<const unsigned char *>(g.Bp) + ((size_t)(le * g.n_ntiles + nt) * g.n_ktiles) * kTileBytes,
                           (uint32_t)g.n_ktiles * kTileBytes);
   loop.lds = lds_address(smem);
@@ -279,7 +286,15 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      {
+      if constexpr (RESIDENT) {
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+          const int c = it * 64 + fresh_lane(), rl = c >> 2, cc = c & 3;  // 8-byte chunk: 4 chunks per row
+          const int row_l = blk_row0 + rl, col = nt * (kBN / 2) + wn * 32 + cc * 8;
+          if (row_l < rows && col < g.N)
+            store_h_through(static_cast<uint8_t *>(g.out) + (size_t)(m0 + row_l) * g.ldo + col, patch + rl * 48 + cc * 8);
+        }
+      } else {
         const int rl = lane >> 1, cc = lane & 1;  // 16-byte chunk: 2 chunks per row
         const int row_l = blk_row0 + rl;
         const int col = nt * (kBN / 2) + wn * 32 + cc * 16;
@@ -305,15 +320,25 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if constexpr (RESIDENT && !FAR) {
 #pragma unroll
-      for (int it = 0; it < 2; ++it) {
+        for (int it = 0; it < 4; ++it) {
+          const int c = it * 64 + fresh_lane(), rl = c >> 3, cc = c & 7;  // 8-byte chunk: 8 chunks per row
+          const int row_l = blk_row0 + rl, col = nt * (kBN / 2) + wn * 32 + cc * 4;
+          if (row_l < rows && col < g.N)
+            store_h_through(static_cast<bf16_t *>(g.out) + (size_t)(m0 + row_l) * g.ldo + col, patch + rl * 80 + cc * 8);
+        }
+      }
+#pragma unroll
+      for (int it = 0; it < (RESIDENT && !FAR && !TRAIN ? 0 : 2); ++it) {
         const int c = it * 64 + lane;        // 16-byte chunk: 4 chunks per row
         const int rl = c >> 2, cc = c & 3;
         const int row_l = blk_row0 + rl;
         const int col = nt * (kBN / 2) + wn * 32 + cc * 8;
-        const u32x4 v = *reinterpret_cast<const u32x4 *>(patch + rl * 80 + cc * 16);
         if (row_l < rows && col < g.N) {
-          *reinterpret_cast<u32x4 *>(static_cast<bf16_t *>(g.out) + (size_t)(m0 + row_l) * g.ldo + col) = v;
+          if (!RESIDENT || FAR)
+            *reinterpret_cast<u32x4 *>(static_cast<bf16_t *>(g.out) + (size_t)(m0 + row_l) * g.ldo + col) =
+                *reinterpret_cast<const u32x4 *>(patch + rl * 80 + cc * 16);
           if (TRAIN) {
             bf16_t *gu = static_cast<bf16_t *>(g.aux) + (size_t)(m0 + row_l) * 2 * g.N + col;
             *reinterpret_cast<u32x4 *>(gu) = *reinterpret_cast<const u32x4 *>(patch + 2560 + rl * 80 + cc * 16);
@@ -371,7 +396,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
 }
 
 // One work item on the matrix cores.  Wave-uniform dispatch on the number of valid 32-row blocks: every variant
-// executes the same sequence of barriers.  poison != 0 (GEMM-2 inside the resident kernel, after a wait that gave up):
+// executes the same sequence of barriers.  poison = 1 (GEMM-2 inside the resident kernel, after a wait that gave up):
 // the rows are written as NaN.  FAR (an A matrix of 4 GiB or more): one tile shape with 64-bit addresses for every item,
 // padding rows multiplied and not stored; kernels of its own, because beside the other variants it costs every kernel
 // registers (the resident ones spilled up to 174).  RESIDENT: tickets = the queues' counters, pre = (ticket drawn ahead,
@@ -438,9 +463,14 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_kernel(const GemmAr
 // it has seen every GEMM-1 queue empty, i.e. when every GEMM-1 item is already in the hands of a running
 // workgroup; GEMM-1 items never wait, so the counter a GEMM-2 item polls is always completed by workgroups that
 // make progress: no deadlock for any number of resident workgroups and any placement.
-// Hand-over: the producers of an M tile store h, fence at device scope, and count themselves in tile_ready;
-// the consumer polls the counter, then fences before it loads h (the L2s of the XCDs are not coherent with
-// each other, the device-scope fences write back / invalidate them).
+// Hand-over: the producers of an M tile store h past their L2 (device-scope stores), wait for the acknowledgement and
+// count themselves in tile_ready; the consumer polls the counter and loads.  The L2s of the XCDs are not coherent with each
+// other, but neither a write-back nor an invalidate is needed: an XCD loads a line of h only after the line's M tile has been
+// counted in full (rows start on a line of their own, see h_pitch, so no line belongs to two M tiles; a wait that gave up
+// loads nothing), and lines of an earlier launch went at the start of this one.  Against one L2 write-back per GEMM-1 item and
+// an invalidate per GEMM-2 item: about 5 us per item, forward of 4096 tokens on the skewed 7168 x 2048 layer 715 -> 683 us
+// (two launches on the same boxes: 752, 738), 5003 tokens on 32 experts of 2880 x 2880 374 -> 352 us (364, 361).  FAR (h of
+// 4 GiB and more) keeps both.
 // ------------------------------------------------------------------------------------------------
 struct PipelineArgs {
   GemmArgs g1, g2;
@@ -542,23 +572,23 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
     const int tile = item.w >> kTileShift;
     if (GATED) {
       gemm_bf16_item<true, true, FP8, TRAIN, FAR, false>(g, smem, item, wave, 0, tickets, s_item + 2);
-      // Release side of the hand-over.  Every wave first waits until its own h stores have been acknowledged, so that
-      // the one write-back below cannot overtake any of them (a workgroup barrier alone does not wait for global
-      // stores).
+      // Release side of the hand-over.  Every wave waits until its own h stores have been acknowledged (a workgroup
+      // barrier alone does not wait for global stores); they went past the L2 (store_h_through), so there is nothing to write back.
       __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-      __syncthreads();  // every thread's h stores happen before thread 0's release ...
+      __syncthreads();  // every thread's h stores happen before thread 0's count
       if (first_thread(wave)) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // ... which writes this XCD's L2 back: visible device-wide
-        // The write-back has to be complete before the counter moves.  The compiler places no wait between the two
-        // here (the wave has just waited for its stores, and the write-back is not counted as outstanding), so the
-        // wait is spelled out.
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+        if constexpr (FAR) {
+          // h through the L2: written back with one release.  The write-back has to be complete before the counter moves.
+          // The compiler places no wait between the two here (the wave has just waited for its stores, and the write-back
+          // is not counted as outstanding), so the wait is spelled out.
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+          __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+        }
         __hip_atomic_fetch_add(&tile_ready[tile], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ... then counted
       }
     } else {
-      // Acquire side: thread 0 polls with relaxed device-scope loads (an acquire per poll would invalidate the L2
-      // every time), then one acquire fence orders the loads of h after the counter; the barrier hands the result to
-      // the workgroup.  A wait that gives up (corrupt lists; cannot happen otherwise) raises the error word and the
+      // Acquire side: thread 0 polls with relaxed device-scope loads; the barrier hands the result to the workgroup.  A wait
+      // that gives up (corrupt lists; cannot happen otherwise) raises the error word and the
       // item runs with a NaN in place of the gate weight, so that nothing computed from incomplete h can pass as a
       // result.
       if (first_thread(wave)) {
@@ -571,12 +601,15 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
             break;
           }
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);  // the invalidate is complete before the barrier lets the others load
+        if constexpr (FAR) {
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+          __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);  // the invalidate is complete before the barrier lets the others load
+        }
         s_item[1] = gave_up;
       }
       __syncthreads();
-      gemm_bf16_item<false, true, FP8, false, FAR, false>(g, smem, item, wave, s_item[1], tickets, s_item + 2);
+      gemm_bf16_item<false, true, FP8, false, FAR, false>(g, smem, item, wave, __builtin_amdgcn_readfirstlane(s_item[1]),
+                                                          tickets, s_item + 2);
       if (tile_done) {
         // remembered, counted later (flush_done): one write-back for all the items of this workgroup
         if (first_thread(wave)) s_done[n_pending] = tile;

@@ -97,10 +97,11 @@ struct RowRequests {
   // FAR: this lane's chunk of instruction i, region h, 4 bits each.  Otherwise (no register to spare) scalar bits: whether
   // the instruction's first row is an odd multiple of eight, which with the lane gives the chunk.
   uint32_t chunks;
-  __device__ __forceinline__ void init(const void *A, int lda) {
+  // bytes: bound of the descriptor (0: every request is answered with zeros; FAR has no descriptor)
+  __device__ __forceinline__ void init(const void *A, int lda, uint32_t bytes = 0xFFFFFFFFu) {
     base = static_cast<const unsigned char *>(A);
     pitch = (uint32_t)lda * (FP8 ? 1 : 2);
-    rsrc = lds_load_rsrc(base, 0xFFFFFFFFu);
+    rsrc = lds_load_rsrc(base, bytes);
     chunks = 0;
   }
   // row = row of the tile (image position: a multiple of eight plus lane / 8), a_row = row of the matrix
