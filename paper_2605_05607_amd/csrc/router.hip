@@ -18,7 +18,7 @@ constexpr int router_stage_bytes(int BM, int BN) { return (BM + BN) * kBK * 2; }
 // One workgroup owns BM tokens (64, 128, or 256) x BN experts (128 or 256) x one contiguous part of the reduction range: the
 // product is skinny (a few hundred experts), so its cost is reading x once, and cutting the reduction range is
 // what gives the chip enough workgroups.  What bounds it: every workgroup pulls its whole W_r part through its CU's L2
-// port next to its rows of x, (BM + BN) x 128 bytes per k-step at some 50 GB/s, and the partial sums are written and read
+// port next to its rows of x, (BM + BN) x 128 bytes per k-step at some 60 GB/s, and the partial sums are written and read
 // back; router_plan weighs the two.  Both operands have the reduction index contiguous in memory and go straight into the LDS (chunks
 // permuted as in the expert GEMMs), a ring of three stages.  A part's block is written as fp32
 // to partial[part][T][E]; the kernels below add the parts in the order 0, 1, 2, ... so that the logits, and the routing
@@ -56,16 +56,22 @@ __global__ __launch_bounds__(kRouterThreads) void router_logits_bf16_kernel(cons
   }
   const uint32_t lds = lds_address(smem);
   const bool tail = d % kBK != 0;
-  auto request = [&](int stage, int kt) {
+  auto clip = [&](int kt) {  // before the first request of slab kt
     if (tail && kt == KT - 1) {
       xr.clip(d, KT - 1);
       wr.clip(d, KT - 1);
     }
+  };
+  // Requests of half a slab: those of x first, then those of W_r (the second half starts with request kFirst).
+  constexpr int kFirst = (kLoads + 1) / 2;
+  auto ask_one = [&](int n, int stage, int kt) {
     const uint32_t l = lds + stage * kStage;
+    if (n < MB) xr.request(0, n, l + (wave * MB + n) * 1024, kt);
+    else wr.request(0, n - MB, l + kA + (wave * NW + n - MB) * 1024, kt);
+  };
+  auto ask_half = [&](int half, int stage, int kt) {
 #pragma unroll
-    for (int i = 0; i < MB; ++i) xr.request(0, i, l + (wave * MB + i) * 1024, kt);
-#pragma unroll
-    for (int i = 0; i < NW; ++i) wr.request(0, i, l + kA + (wave * NW + i) * 1024, kt);
+    for (int n = half == 0 ? 0 : kFirst; n < (half == 0 ? kFirst : kLoads); ++n) ask_one(n, stage, kt);
   };
   f32x16 acc[MB][NJ];
 #pragma unroll
@@ -74,45 +80,86 @@ __global__ __launch_bounds__(kRouterThreads) void router_logits_bf16_kernel(cons
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[mi][j][r] = 0.f;
-#pragma unroll
-  for (int i = 0; i < kRouterStages; ++i)
-    if (kt_begin + i < kt_end) request(i, kt_begin + i);
-  int stage = 0;
-  for (int kt = kt_begin; kt < kt_end; ++kt) {
-    // slab kt is here (this wave's part; the barrier: everybody's)
-    if (kt + 2 < kt_end) wait_loads<2 * kLoads>(); else if (kt + 1 < kt_end) wait_loads<kLoads>(); else wait_loads<0>();
-    slot_barrier();
+  // A k-step is two halves of two substeps: the next half is read while one is multiplied, the requests go out one by one
+  // between the matrix instructions (in one burst they keep the waves from reading and multiplying while the CU accepts
+  // them), and one barrier between the halves says that slab kt has been read and slab kt + 1 is here.
+  // Measured, 4096 tokens, 256 experts, d = 7168, with the pick: 31.1 us with everything read first, two barriers and the
+  // requests in a burst -> 29.5 us (28 k-steps of 40 KiB per workgroup; twice the tokens 50.4 us).
+  bf16x8 fa[2][MB][2], fb[2][NJ][2];
+  auto read = [&](int h, int stage, int kt) {
     const unsigned char *sA = smem + stage * kStage + (wm * (BM / 2) + l31) * 128;
     const unsigned char *sB = smem + stage * kStage + kA + (wn * 32 * NJ + l31) * 128;
-    bf16x8 fa[MB][4], fb[NJ][4];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const int slot = ((kk * 2 + khalf) ^ sw) * 16;
+    for (int q = 0; q < 2; ++q) {
+      const int slot = (((2 * h + q) * 2 + khalf) ^ sw) * 16;
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) fb[j][kk] = *reinterpret_cast<const bf16x8 *>(sB + j * 4096 + slot);
+      for (int j = 0; j < NJ; ++j) fb[h][j][q] = *reinterpret_cast<const bf16x8 *>(sB + j * 4096 + slot);
 #pragma unroll
-      for (int mi = 0; mi < MB; ++mi) fa[mi][kk] = *reinterpret_cast<const bf16x8 *>(sA + mi * 4096 + slot);
+      for (int mi = 0; mi < MB; ++mi) fa[h][mi][q] = *reinterpret_cast<const bf16x8 *>(sA + mi * 4096 + slot);
     }
-    // everybody has read it: its stage takes the slab three steps on, so that three are on the way while this one is
-    // multiplied
-    wait_lds_reads();
-    slot_barrier();
-    if (kt + kRouterStages < kt_end) request(stage, kt + kRouterStages);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // products of half h of slab kt; ASK: with the requests of half `half` of slab kt_ask between them
+  auto multiply = [&](int h, int kt, auto ask, int half, int stage, int kt_ask) {
     if (tail && kt == KT - 1) {  // chunks past d repeat another chunk in both operands: zero those of x
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        if (kt * kBK + kk * 16 + khalf * 8 >= d) {
+      for (int q = 0; q < 2; ++q)
+        if (kt * kBK + (2 * h + q) * 16 + khalf * 8 >= d) {
 #pragma unroll
-          for (int mi = 0; mi < MB; ++mi) fa[mi][kk] = bf16x8{};
+          for (int mi = 0; mi < MB; ++mi) fa[h][mi][q] = bf16x8{};
         }
     }
+    constexpr int N = 2 * MB * NJ;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
+    for (int m = 0; m < N; ++m) {
+      const int q = m / (MB * NJ), mi = m % (MB * NJ) / NJ, j = m % NJ;
+      acc[mi][j] = mfma_bf16(fa[h][mi][q], fb[h][j][q], acc[mi][j]);
+      if constexpr (decltype(ask)::value) {
+        const int n0 = half == 0 ? 0 : kFirst, n = half == 0 ? kFirst : kLoads - kFirst;
 #pragma unroll
-      for (int mi = 0; mi < MB; ++mi)
+        for (int a = 0; a < kLoads; ++a)
+          if (a < n && (a + 1) * N / (n + 1) == m) ask_one(n0 + a, stage, kt_ask);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  constexpr int S = kRouterStages;
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[mi][j] = mfma_bf16(fa[mi][kk], fb[j][kk], acc[mi][j]);
-    stage = stage == 2 ? 0 : stage + 1;
+  for (int i = 0; i < S - 1; ++i)
+    if (kt_begin + i < kt_end) {
+      clip(kt_begin + i);
+      ask_half(0, i, kt_begin + i);
+      ask_half(1, i, kt_begin + i);
+    }
+  int stage = 0;
+  // SECOND: the second half of slab kt + S - 1 is still to be requested; FIRST: the first half of the slab behind it is
+  auto k_step = [&](int kt, auto second, auto first) {
+    read(1, stage, kt);
+    multiply(0, kt, second, 1, stage == 0 ? S - 1 : stage - 1, kt + S - 1);
+    wait_lds_reads();
+    if (decltype(first)::value || kt + S <= kt_end) wait_loads<(S - 2) * kLoads>(); else wait_loads<0>();
+    slot_barrier();  // slab kt has been read, slab kt + 1 is here
+    const int old = stage;
+    stage = stage == S - 1 ? 0 : stage + 1;
+    if (decltype(first)::value || kt + 1 < kt_end) read(0, stage, kt + 1);
+    if (decltype(first)::value) clip(kt + S);
+    multiply(1, kt, first, 0, old, kt + S);
+  };
+  static_assert(S == 3, "the waits count two slabs on the way");
+  if (kt_begin < kt_end) {
+    if (kt_begin + S - 1 <= kt_end) wait_loads<(S - 2) * kLoads>(); else wait_loads<0>();
+    slot_barrier();
+    read(0, 0, kt_begin);
+    if (kt_begin + S - 1 < kt_end) {
+      clip(kt_begin + S - 1);
+      ask_half(0, S - 1, kt_begin + S - 1);
+    }
+    const std::true_type yes;
+    const std::false_type no;
+    int kt = kt_begin;
+    for (; kt + S < kt_end; ++kt) k_step(kt, yes, yes);
+    if (kt + S == kt_end) k_step(kt++, yes, no);
+    for (; kt < kt_end; ++kt) k_step(kt, no, no);
   }
   // accumulator register r of lane l is C[8 * (r / 4) + 4 * (l / 32) + r % 4][l % 32] of its 32 x 32 block
   float *out = partial + (size_t)part * T * E;
