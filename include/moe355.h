@@ -352,12 +352,13 @@ MOE355_API int moe_fp8_fused_forward(const moe_shape *shape, const void *x, cons
  *   are written in full.  dW_gate, dW_up [E_loc,d,f] and dW_down [E_loc,f,d] (bf16, 16-byte aligned, written in full, zero for
  *   an expert without rows) are computed when all three pointers are non-NULL and skipped when all three are NULL.
  *   workspace >= moe_backward_workspace_bytes(shape), 256-byte aligned.  Sums run in a fixed order: same inputs,
- *   same bits.  With weight gradients, the transposed copies of the operands are made on a stream of the library's
- *   own (one per device, default priority, created by the first such call and kept) beside the two GEMMs: it waits
- *   for an event recorded on `stream` and `stream` waits for its last kernel before the products start, so the call's
- *   work is ordered in `stream` like any other call's, also inside a stream capture (later calls only: see above).
- *   Calls from several host threads on one device share that side stream: the library serialises their enqueueing
- *   (a mutex held for the duration of the call) and their side work runs in turn; they still need separate workspaces.
+ *   same bits.  Where x, dy or [dg | du] has 4 GiB and more, the weight gradients are computed from transposed copies of
+ *   the operands, made on a stream of the library's own (one per device, default priority, created by the first such call
+ *   and kept) beside the two GEMMs: it waits for an event recorded on `stream` and `stream` waits for its last kernel before
+ *   the products start, so the call's work is ordered in `stream` like any other call's, also inside a stream capture
+ *   (later calls only: see above).  Such calls from several host threads on one device share that side stream: the library
+ *   serialises their enqueueing (a mutex held for the duration of the call) and their side work runs in turn; they still
+ *   need separate workspaces.
  */
 MOE355_API size_t moe_train_kept_bytes(const moe_shape *shape);
 MOE355_API size_t moe_backward_workspace_bytes(const moe_shape *shape);

@@ -749,9 +749,9 @@ extern "C" int moe_fused_forward_train(const moe_shape *shape, const void *x, co
                         workspace_bytes, stream, true, nullptr, 0, nullptr, kept);
 }
 
-// The backward pass runs its memory-bound preparation for the weight gradients (zero gradients of experts without
-// rows, transposed operands) beside its compute-bound GEMMs: those kernels need at most 16 registers and little or no
-// LDS, so their waves fit on a CU next to a GEMM workgroup.  They go to a stream of the library's own (one per device,
+// Where the weight gradients need transposed operands (4 GiB and more), the backward pass makes them beside its
+// compute-bound GEMMs: those kernels need at most 16 registers and little or no LDS, so their waves fit on a CU next to a
+// GEMM workgroup.  They go to a stream of the library's own (one per device,
 // default priority, created on first use and kept), forked from and joined to the caller's stream by events.
 struct SideStream {
   hipStream_t stream;
@@ -831,7 +831,7 @@ extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const v
   const float *kept_o = reinterpret_cast<const float *>(static_cast<const unsigned char *>(kept) +
                                                         align_up(rows * 2 * shape->f * 2, 256));
   if ((rc = launch_prep(shape, dvb, tables, topk_idx, topk_w, w, w.row_sole, st)) != MOE_OK) return rc;
-  // side stream: what the weight gradients need besides the products (nothing of it reads a GEMM's output before `mid`)
+  // side stream (transposed operands): nothing on it reads a GEMM's output before `mid`
   SideStream *side = nullptr;
   std::unique_lock<std::mutex> side_lock;  // (released when the call returns)
   int32_t *kb = reinterpret_cast<int32_t *>(b + L.kb);
@@ -849,8 +849,11 @@ extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const v
       return code != MOE_OK ? code : (int)MOE_ERR_HIP;
     return code;
   };
-  if (wgrad) {
-    if (kblocks > 65535) return MOE_ERR_UNSUPPORTED;
+  // weight gradients straight from the operands, where 32-bit offsets reach their rows; else from transposed copies
+  const int64_t reach = ((int64_t)1 << 32) - (1 << 16);
+  const bool direct = std::max((int64_t)shape->T * shape->d, dv.P_cap * 2 * shape->f) * 2 < reach;
+  if (wgrad && kblocks > 65535) return MOE_ERR_UNSUPPORTED;
+  if (wgrad && !direct) {
     if (!(side = side_stream())) return MOE_ERR_HIP;
     side_lock = std::unique_lock<std::mutex>(side->enqueue);
     if (hipEventRecord(side->fork, st) != hipSuccess || hipStreamWaitEvent(side->stream, side->fork, 0) != hipSuccess) {
@@ -863,12 +866,9 @@ extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const v
     transpose(static_cast<const bf16_t *>(dy), w.row_tok, shape->d, shape->d, dyT);
     if ((rc = launch_status()) != MOE_OK) return join(rc);
   }
-  // gradient of the gate weights (zero for the slots whose expert is not local)
-  hipLaunchKernelGGL(fill_f32_kernel, dim3((unsigned)std::min<size_t>(1024, (n_pairs + 255) / 256)), dim3(256), 0, st,
-                     d_topk_w, n_pairs, 0.0f);
   hipLaunchKernelGGL(gate_weight_grad_kernel, dim3((unsigned)std::min<size_t>(4096, (rows + 3) / 4)), dim3(256), 0, st,
-                     kept_o, static_cast<const bf16_t *>(dy), w.header, w.row_tok, w.row_w, tables->perm, shape->d,
-                     d_topk_w);
+                     kept_o, static_cast<const bf16_t *>(dy), w.header, w.row_tok, w.row_w, tables->perm, tables->inv_perm,
+                     (int)n_pairs, shape->d, d_topk_w);
   if ((rc = launch_status()) != MOE_OK) return join(rc);
   const auto grid_of = [&](int nt) { return dim3((unsigned)(((size_t)dvb.max_mtiles * nt + 255) / 256 * 256)); };
   // dh_raw = dy[token of the row] Wd^T, then the SwiGLU derivative with the kept g and u
@@ -879,8 +879,10 @@ extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const v
   g1.K = shape->d; g1.N = shape->f; g1.lda = shape->d; g1.ldo = 2 * shape->f;
   g1.n_ntiles = dvb.nt1; g1.n_ktiles = ceil_div(shape->d, kBK);
   const bool far1 = (int64_t)shape->T * shape->d * 2 >= (int64_t)1 << 32;
-  if ((rc = launch_items<false, false, true, true>(g1, far1, grid_of(dvb.nt1), st)) != MOE_OK) return join(rc);
-  if (wgrad) {  // dg, du and w h are there: their transposes run beside the second GEMM
+  rc = side ? launch_items<false, false, true, true>(g1, far1, grid_of(dvb.nt1), st)
+            : launch_items<false, false, true, false>(g1, far1, grid_of(dvb.nt1), st);
+  if (rc != MOE_OK) return join(rc);
+  if (side) {  // dg, du and w h are there: their transposes run beside the second GEMM
     if (hipEventRecord(side->mid, st) != hipSuccess || hipStreamWaitEvent(side->stream, side->mid, 0) != hipSuccess)
       return join(MOE_ERR_HIP);
     transpose(hw, nullptr, shape->f, shape->f, hwT);
@@ -895,26 +897,49 @@ extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const v
   g2.K = 2 * shape->f; g2.N = shape->d; g2.lda = 2 * shape->f; g2.ldo = shape->d;
   g2.n_ntiles = dvb.nt2; g2.n_ktiles = 2 * (shape->f / kBK);
   const bool far2 = dv.P_cap * 2 * shape->f * 2 >= (int64_t)1 << 32;
-  if ((rc = launch_items<false, false, false, true>(g2, far2, grid_of(dvb.nt2), st)) != MOE_OK) return join(rc);
+  rc = side ? launch_items<false, false, false, true>(g2, far2, grid_of(dvb.nt2), st)
+            : launch_items<false, false, false, false>(g2, far2, grid_of(dvb.nt2), st);
+  if (rc != MOE_OK) return join(rc);
   if ((rc = launch_combine(shape, dv, dxr, topk_idx, tables, dx, true, st)) != MOE_OK || !wgrad) return join(rc);
-  // weight gradients: one grouped product per weight matrix, over the transposed operands
-  static std::atomic<uint64_t> done_w{0};
-  if (!allow_dynamic_lds(reinterpret_cast<const void *>(&wgrad_bf16_kernel), 2 * kStageBytes, done_w))
-    return join(MOE_ERR_HIP);
   if ((rc = join(MOE_OK)) != MOE_OK) return rc;
   const size_t units = (size_t)shape->d * shape->f / 8;  // 16-byte units of one expert's gradient
   hipLaunchKernelGGL(wgrad_zero_empty_kernel,
                      dim3((unsigned)std::min<size_t>(1024, ceil_div(units, (size_t)8192)), dv.E_loc, 3), dim3(256), 0,
-                     st, kb, static_cast<u32x4 *>(dW_gate), static_cast<u32x4 *>(dW_up), static_cast<u32x4 *>(dW_down),
-                     units);
+                     st, tables->offsets, w.header, dv.e_lo, static_cast<u32x4 *>(dW_gate), static_cast<u32x4 *>(dW_up),
+                     static_cast<u32x4 *>(dW_down), units);
+  if (direct) {
+    WgradDirectArgs a;
+    a.x = static_cast<const bf16_t *>(x); a.dy = static_cast<const bf16_t *>(dy); a.dgu = dgu; a.hw = hw;
+    a.dW_gate = static_cast<bf16_t *>(dW_gate); a.dW_up = static_cast<bf16_t *>(dW_up);
+    a.dW_down = static_cast<bf16_t *>(dW_down);
+    a.offsets = tables->offsets; a.header = w.header; a.row_tok = w.row_tok;
+    a.e_lo = dv.e_lo; a.E_loc = dv.E_loc; a.T = shape->T; a.d = shape->d; a.f = shape->f;
+    const auto tiles = [&](int edge) {
+      const int64_t td = ceil_div(shape->d, edge);
+      return td * ceil_div(2 * shape->f, edge) + td * ceil_div(shape->f, edge);
+    };
+    if (tiles(kBM) * dv.E_loc >= (int64_t)1 << 30) return MOE_ERR_UNSUPPORTED;
+    a.n_items = (int)(tiles(kBM) * dv.E_loc);
+    static std::atomic<uint64_t> done_d{0};
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(&wgrad_bf16_kernel), kWgradLds, done_d)) return MOE_ERR_HIP;
+    hipLaunchKernelGGL(wgrad_bf16_kernel, dim3((unsigned)align_up(a.n_items, 8 * kChunk)), dim3(kGemmThreads), kWgradLds, st,
+                       a);
+    if ((rc = launch_status()) != MOE_OK) return rc;
+    hipLaunchKernelGGL(wgrad_thin_bf16_kernel, dim3((unsigned)(tiles(128) + kThinTiles - 1) / kThinTiles, dv.E_loc), dim3(256), 0,
+                       st, a);
+    return launch_status();
+  }
+  // one grouped product per weight matrix, over the transposed operands
+  static std::atomic<uint64_t> done_w{0};
+  if (!allow_dynamic_lds(reinterpret_cast<const void *>(&wgrad_slab_kernel), 2 * kStageBytes, done_w)) return MOE_ERR_HIP;
   const auto product = [&](const bf16_t *AT, int lda, const bf16_t *BT, int ldb, int b0, int M, int N, void *C) {
     WgradArgs a;
     a.AT = AT; a.BT = BT; a.C = static_cast<bf16_t *>(C); a.kb = kb;
     a.lda = lda; a.ldb = ldb; a.a0 = 0; a.b0 = b0;
     a.M = M; a.N = N; a.n_mt = ceil_div(M, kBM); a.n_nt = ceil_div(N, kBN);
-    hipLaunchKernelGGL(wgrad_bf16_kernel, dim3(a.n_mt * a.n_nt, dv.E_loc), dim3(kGemmThreads), 2 * kStageBytes, st, a);
+    hipLaunchKernelGGL(wgrad_slab_kernel, dim3(a.n_mt * a.n_nt, dv.E_loc), dim3(kGemmThreads), 2 * kStageBytes, st, a);
     a.n_mt = ceil_div(M, 128); a.n_nt = ceil_div(N, 128);  // experts with few or no rows: small tiles
-    hipLaunchKernelGGL(wgrad_thin_bf16_kernel, dim3(ceil_div(a.n_mt * a.n_nt, kThinTiles), dv.E_loc), dim3(256), 0, st,
+    hipLaunchKernelGGL(wgrad_thin_slab_kernel, dim3(ceil_div(a.n_mt * a.n_nt, kThinTiles), dv.E_loc), dim3(256), 0, st,
                        a);
   };
   product(xT, shape->d, dguT, 2 * shape->f, 0, shape->d, shape->f, dW_gate);         // x^T dg

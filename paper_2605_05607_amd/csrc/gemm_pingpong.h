@@ -156,9 +156,34 @@ struct RowRequests {
 // barrier per k-step and all waves in step -> 1.38 PFLOP/s (the vendor library's dense product reaches 1.44 to 1.50 on
 // the box); whole prefill step of that layer 9.64 -> 8.84 ms.
 // ------------------------------------------------------------------------------------------------
-// GRAD (weight gradients, wgrad_bf16.h): both operands are slabs of [column][128 bytes], `step` bytes from one k-step to the
-// next, and both are requested and read as A is.
-template <bool FP8, int NB, int RW, bool LONE, bool FAR, bool GRAD = false>
+// GRAD (weight gradients, wgrad_bf16.h), kGradSlabs: both operands are slabs of [column][128 bytes], `step` bytes from one
+// k-step to the next, and both are requested and read as A is.
+// kGradGatherA, kGradGatherB: the reduction index is the row of both operands and they are requested as they lie in memory,
+// 64 rows per k-step; one operand's rows are gathered (byte offsets of the rows in the LDS table `tab`), the other's follow
+// one another.  The stage holds blocks of [64 rows][64 columns] (B: [64 rows][32 columns] per region) and the reads
+// transpose: a 16-lane group of ds_read_b64_tr_b16 turns four rows of sixteen columns into sixteen lanes of four reduction
+// indices.  The halves of an A row swap where bit 1 of the row is set, so that four rows lie in different banks.  Rows past
+// the last are offsets past the descriptor's end, i.e. zeros.
+// ------------------------------------------------------------------------------------------------
+constexpr int kGradSlabs = 1, kGradGatherA = 2, kGradGatherB = 3;
+constexpr uint32_t kNoRow = 0xFFFFFF00u;  // beyond every descriptor (less than 2^32 - 2^16 bytes), and no wrap behind it
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ s16x4 lds_read_transposed(uint32_t at) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(uintptr_t)at);
+}
+// Eight reduction indices of a lane's column: two such reads, four rows (`four` bytes) apart.
+__device__ __forceinline__ bf16x8 transposed_fragment(uint32_t at, int four) {
+  const s16x4 lo = lds_read_transposed(at), hi = lds_read_transposed(at + four);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+// Where a lane's address for such a read lies in a block of 64-column rows (sub-block i of 32 columns: ^ 64 i), from the
+// first of eight rows: lane group of 16 = 16 columns and half of the eight rows' pairs, lane in it = row by 4 columns.
+__device__ __forceinline__ uint32_t transposed_read_offset(int lane) {
+  const uint32_t row = (lane >> 5) * 8 + ((lane & 15) >> 2);
+  return row * 128 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8 + ((row >> 1) & 1) * 64;
+}
+
+template <bool FP8, int NB, int RW, bool LONE, bool FAR, int GRAD = 0>
 struct PingPong {
   static constexpr int kStage = 65536, kB = 32768;
   static constexpr int NB0 = NB < 2 ? NB : 2, NB1 = NB > 2 ? NB - 2 : 0;  // row blocks with valid rows in A0, A1
@@ -171,9 +196,33 @@ struct PingPong {
   const unsigned char *smem;
   int a_rd, b_rd;  // this lane's row / operand in a stage
   bf16x8 fa[2][2][4], fb[2][4];
-  const unsigned char *slab_a, *slab_b;  // GRAD: slab 0 of this workgroup's columns
+  const unsigned char *slab_a, *slab_b;  // kGradSlabs: slab 0 of this workgroup's columns
   size_t step_a, step_b;
   uint32_t va[2][2], vb[2][2];           // this lane's offsets in them, by region and instruction
+  // kGradGather*
+  i32x4 gathered;              // the gathered matrix
+  const unsigned char *next;   // the other operand: row 0, and the bytes from there to the end of its last row
+  uint32_t next_bytes, pitch;
+  uint32_t tab;                // LDS address of the table at this lane's row of instruction 0
+  uint32_t col, col_next;      // gathered operand: this lane's byte in a row; the other: in a slab (region 0, instruction 0)
+  uint32_t row[2];             // gathered operand: offsets of this lane's rows of the slab being requested
+
+  __device__ __forceinline__ void find_rows(int kt) {  // instruction 1: 8 (B: 16) rows further
+    const uint32_t at = tab + kt * 256;
+    row[0] = *(const __attribute__((address_space(3))) uint32_t *)(uintptr_t)at;
+    row[1] = *(const __attribute__((address_space(3))) uint32_t *)(uintptr_t)(at + (GRAD == kGradGatherA ? 32 : 64));
+  }
+  // region h of A or j of B, `wide` bytes of a row
+  __device__ __forceinline__ void request_gathered(int region, int wide, uint32_t l) const {
+    load_to_lds(gathered, l, row[0] + col + region * wide, 0);
+    load_to_lds(gathered, l + 1024, row[1] + col + region * wide, 0);
+  }
+  __device__ __forceinline__ void request_next(int region, int wide, int rows_on, uint32_t l, int kt) const {
+    const uint64_t skip = (uint64_t)kt * 64 * pitch;
+    const i32x4 r = lds_load_rsrc(next + skip, skip < next_bytes ? next_bytes - (uint32_t)skip : 0u);
+    load_to_lds(r, l, col_next + region * wide, 0);
+    load_to_lds(r, l + 1024, col_next + region * wide + rows_on * pitch, 0);
+  }
 
   __device__ __forceinline__ void request_slab(const unsigned char *slab, const uint32_t (&v)[2], uint32_t l) const {
     const i32x4 r = lds_load_rsrc(slab, 0xFFFFFFFFu);
@@ -182,8 +231,16 @@ struct PingPong {
   }
   __device__ __forceinline__ void request_a(int h, int kt) const {
     const uint32_t l = lds + (kt & 1) * kStage + a_lds[h];
-    if constexpr (GRAD) {
+    if constexpr (GRAD == kGradSlabs) {
       request_slab(slab_a + kt * step_a, va[h], l);
+      return;
+    }
+    if constexpr (GRAD == kGradGatherA) {
+      request_gathered(h, 128, l);
+      return;
+    }
+    if constexpr (GRAD == kGradGatherB) {
+      request_next(h, 128, 8, l, kt);
       return;
     }
     rows.request(h, 0, l, kt);
@@ -191,19 +248,39 @@ struct PingPong {
   }
   __device__ __forceinline__ void request_b(int j, int kt) const {
     const uint32_t l = lds + (kt & 1) * kStage + kB + b_soff + j * 4096, s = kt * kTileBytes + b_soff + j * 4096;
-    if constexpr (GRAD) {
+    if constexpr (GRAD == kGradSlabs) {
       request_slab(slab_b + kt * step_b, vb[j], l);
+      return;
+    }
+    if constexpr (GRAD == kGradGatherA) {
+      request_next(j, 64, 16, l, kt);
+      return;
+    }
+    if constexpr (GRAD == kGradGatherB) {
+      request_gathered(j, 64, l);
       return;
     }
     load_to_lds<LONE>(rb, l, b_voff, s);
     load_to_lds<LONE>(rb, l + 1024, b_voff, s + 1024);
   }
   __device__ __forceinline__ void read_a(int h, int i, int kt) {
+    if constexpr (GRAD >= kGradGatherA) {
+      const uint32_t s = lds + (kt & 1) * kStage + h * 8192 + (a_rd ^ i * 64);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) fa[h][i][kk] = transposed_fragment(s + kk * 2048, 512);
+      return;
+    }
     const unsigned char *s = smem + (kt & 1) * kStage + (h * 2 + i) * 4096;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) fa[h][i][kk] = *reinterpret_cast<const bf16x8 *>(s + (a_rd ^ kk * 32));
   }
   __device__ __forceinline__ void read_b(int j, int kt) {
+    if constexpr (GRAD >= kGradGatherA) {
+      const uint32_t s = lds + (kt & 1) * kStage + j * 4096 + b_rd;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) fb[j][kk] = transposed_fragment(s + kk * 1024, 256);
+      return;
+    }
     const unsigned char *s = smem + (kt & 1) * kStage + j * 4096;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
@@ -235,6 +312,7 @@ struct PingPong {
   template <int LEFT>
   __device__ __forceinline__ void k_step(f32x16 (&acc)[NB][2], int kt) {
     read_b(0, kt);
+    if (LEFT == 2 && GRAD == kGradGatherA) find_rows(kt + 2);
     if (LEFT == 2) request_a(0, kt + 2);
     wait_loads<LEFT == 2 ? 8 + I1 : LEFT == 1 ? 6 + I1 : 0>();
     wait_lds_reads();
@@ -242,6 +320,7 @@ struct PingPong {
     multiply<0, 0>(acc);
     read_b(1, kt);
     if (NB > 2) read_a(1, 0, kt);
+    if (LEFT == 2 && GRAD == kGradGatherB) find_rows(kt + 2);
     if (LEFT == 2) request_b(0, kt + 2);
     wait_lds_reads();
     slot_barrier();
@@ -267,6 +346,7 @@ struct PingPong {
     const bool tail = !GRAD && K % RowRequests<FP8, 2, 2, FAR>::KS != 0;
     auto slab = [&](int kt) {
       if (tail && kt == KT - 1) rows.clip(K, KT - 1);
+      if (GRAD >= kGradGatherA) find_rows(kt);
       request_a(0, kt);
       request_b(0, kt);
       request_b(1, kt);
