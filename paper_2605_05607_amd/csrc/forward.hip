@@ -263,16 +263,17 @@ bool stream_form(const moe_shape *s, const Derived &dv, int elt) {
   return stream <= (elt == 1 ? 38.0 : 30.0) + 0.88 / 128 * elt * ((double)s->d + s->f);
 }
 
-// Work groups per strip of GEMM-2: one, unless so few strips of 32 columns exist that a second launch (~5 us) costs less
-// than what the missing CUs would have pulled (a CU pulls ~36 GB/s here, the chip ~6.5 TB/s, i.e. what ~180 CUs pull).
+// Work groups per strip of GEMM-2: one, unless so few strips of 32 columns exist that handing the sums over (~1.5 us) costs
+// less than what the missing CUs would have pulled (a CU pulls ~36 GB/s here, the chip ~6.5 TB/s, i.e. what ~180 CUs pull).
 static int stream_groups(const moe_shape *s, const Derived &dv, int elt) {
   const int strips = ceil_div(s->d, 32);
   const double busy = std::min<double>(dv.E_loc, (double)s->T * s->k * dv.E_loc / s->E);
   const double us = busy * s->f * s->d * elt / 36e3;  // one CU, microseconds
   int best = 1;
   double t_best = us / std::min(strips, 180);
-  for (int g = 2; g <= std::min(8, std::min(s->k, dv.E_loc)); ++g) {  // (the partial sums live in the o rows)
-    const double t = us / std::min(strips * g, 180) + 5.0;
+  const int slots = std::min(s->k, dv.E_loc);  // (the partial sums, strips of 32 columns, live in the rows of o)
+  for (int g = 2; g <= std::min(8, slots) && (int64_t)g * strips * 32 <= (int64_t)slots * s->d; ++g) {
+    const double t = us / std::min(strips * g, 180) + 1.5;
     if (t < t_best) {
       t_best = t;
       best = g;
@@ -296,7 +297,11 @@ static int launch_stream(const moe_shape *s, const Derived &dv, const void *x, c
   g1.K = s->d; g1.N = s->f; g1.n_ntiles = ceil_div(s->f, kBN / 2); g1.n_ktiles = ceil_div(s->d, step);
   StreamArgs g2 = g1;
   const int groups = stream_groups(s, dv, q ? 1 : 2);
-  g2.A = w.h; g2.Bp = packed_down; g2.out = groups > 1 ? static_cast<void *>(w.o) : y;
+  g2.A = w.h; g2.Bp = packed_down; g2.out = y;
+  // (the counters in GEMM-2's work list, which this form does not use: 32 bytes per 256 columns and M tile, at least two)
+  g1.arrived = g2.arrived = reinterpret_cast<int32_t *>(w.work2);
+  g1.n_arrived = groups > 1 ? ceil_div(s->d, 32) : 0;
+  g2.partial = w.o;
   g2.K = s->f; g2.N = s->d; g2.n_ntiles = ceil_div(s->d, kBN); g2.n_ktiles = ceil_div(s->f, step);
   if (q) {
     g1.a_scale = q->x_scale; g1.b_scale = q->gu_scale; g1.h_scale = q->h_scale;
@@ -321,11 +326,6 @@ static int launch_stream(const moe_shape *s, const Derived &dv, const void *x, c
   }
 #undef MOE355_STREAM
   mark(3);
-  if (groups > 1) {
-    const int n4 = s->T * (s->d / 4);
-    hipLaunchKernelGGL(stream_reduce_kernel, dim3((unsigned)ceil_div(n4, 256)), dim3(256), 0, st, w.o,
-                       static_cast<bf16_t *>(y), n4, groups);
-  }
   mark(4);
   return launch_status();
 }

@@ -22,7 +22,10 @@ constexpr int kStreamWaves = 8;
 struct StreamArgs {
   const void *A;    // GEMM-1: x [T, K] (bf16, or codes); GEMM-2: h [rows, K]
   const void *Bp;   // packed tiles
-  void *out;        // GEMM-1: h [rows, N]; GEMM-2: y [T, N] bf16 (one group) or partial sums [groups][T][N] fp32
+  void *out;        // GEMM-1: h [rows, N]; GEMM-2: y [T, N] bf16
+  float *partial;   // GEMM-2 with several groups: their sums, [group][strip][T][32]
+  int32_t *arrived; // groups that have stored theirs, per strip (cleared by GEMM-1: n_arrived of them, none for one group)
+  int n_arrived;
   const int32_t *offsets, *perm;
   const float *topk_w;
   int32_t *error;   // status word of the workspace (cleared by GEMM-1: no wait can give up here)
@@ -174,7 +177,10 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void stream_gemm1_kernel(cons
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l31 = lane & 31, khalf = lane >> 5;
   const int c = blockIdx.x, le = blockIdx.y;
-  if (c == 0 && le == 0 && tid == 0) *g.error = 0;
+  if (c == 0 && le == 0) {
+    if (tid == 0) *g.error = 0;
+    for (int i = tid; i < g.n_arrived; i += kStreamWaves * 64) g.arrived[i] = 0;
+  }
   const int base = g.offsets[g.e_lo];
   const int start = min(max(g.offsets[g.e_lo + le] - base, 0), g.P_cap);
   const int rows_all = min(max(g.offsets[g.e_lo + le + 1] - base, 0), g.P_cap) - start;
@@ -242,7 +248,8 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void stream_gemm1_kernel(cons
 // of all busy experts of the strip form one list, cut into equal runs over the waves (and groups).  When a wave leaves an
 // expert it adds weight * sum to its own fp32 row of each token in the LDS; at the end the waves' rows are added in wave order and written once: tokens without
 // a local slot come out as zeros, and no row of o ever exists.  groups > 1 (strips too few to pull the weights at the
-// chip's rate): the groups' sums go to partial[group] and stream_reduce_kernel adds them in group order.
+// chip's rate): every group stores its sums past the L2s (device-scope stores, as the resident kernels store h), counts itself
+// for the strip, and the one that comes last adds them all in group order.  A launch of its own for that sum took 4 to 5 us.
 // ------------------------------------------------------------------------------------------------
 // LDS: the waves' token rows | the busy list | token and weight of every local row
 constexpr int stream_row_blocks(int T) { return T <= 32 ? 1 : 2; }  // NB: 32-row blocks per pass
@@ -355,42 +362,59 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void stream_gemm2_kernel(cons
   }
   __syncthreads();
   const int tot = g.T * 8;  // four columns per thread
-  for (int i = tid; i < tot; i += kStreamWaves * 64) {
-    const int t = i >> 3, col = c * 32 + (i & 7) * 4;
+  const auto column_sum = [&](int i) {  // of this workgroup
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int q = 0; q < kStreamWaves; ++q) {
-      const f32x4 o = *reinterpret_cast<const f32x4 *>(ysum + ((size_t)q * g.T + t) * 32 + (i & 7) * 4);
+      const f32x4 o = *reinterpret_cast<const f32x4 *>(ysum + ((size_t)q * g.T + (i >> 3)) * 32 + (i & 7) * 4);
 #pragma unroll
       for (int u = 0; u < 4; ++u) v[u] += o[u];
     }
-    if (col >= g.N) continue;
-    if (gridDim.y == 1) {
-      bf16x4 o;
+    return v;
+  };
+  const auto store_y = [&](int i, const f32x4 &v) {
+    const int col = c * 32 + (i & 7) * 4;
+    if (col >= g.N) return;
+    bf16x4 o;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) o[u] = (bf16_t)v[u];
-      *reinterpret_cast<bf16x4 *>(static_cast<bf16_t *>(g.out) + (size_t)t * g.N + col) = o;
-    } else {
-      *reinterpret_cast<f32x4 *>(static_cast<float *>(g.out) + ((size_t)blockIdx.y * g.T + t) * g.N + col) = v;
+    for (int u = 0; u < 4; ++u) o[u] = (bf16_t)v[u];
+    *reinterpret_cast<bf16x4 *>(static_cast<bf16_t *>(g.out) + (size_t)(i >> 3) * g.N + col) = o;
+  };
+  if (gridDim.y == 1) {
+    for (int i = tid; i < tot; i += kStreamWaves * 64) store_y(i, column_sum(i));
+    return;
+  }
+  uint64_t *partial = reinterpret_cast<uint64_t *>(g.partial);  // two columns each
+  const auto place = [&](int group, int i) { return ((size_t)(group * (int)gridDim.x + c) * tot + i) * 2; };
+  for (int i = tid; i < tot; i += kStreamWaves * 64) {
+    const f32x4 v = column_sum(i);
+    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+    const u64x2 w = __builtin_bit_cast(u64x2, v);
+    __hip_atomic_store(&partial[place(blockIdx.y, i)], w[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&partial[place(blockIdx.y, i) + 1], w[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);  // acknowledged, every wave's, before the workgroup counts itself
+  __syncthreads();
+  if (tid == 0)
+    *n_seg_s = __hip_atomic_fetch_add(&g.arrived[c], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.y - 1;
+  __syncthreads();
+  if (!*n_seg_s) return;  // whole workgroup
+  for (int i = tid; i < tot; i += kStreamWaves * 64) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < (int)gridDim.y; ++q) {
+      typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+      u64x2 w;
+      w[0] = __hip_atomic_load(&partial[place(q, i)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      w[1] = __hip_atomic_load(&partial[place(q, i) + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const f32x4 o = __builtin_bit_cast(f32x4, w);
+      if (q == 0) v = o;
+      else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] += o[u];
+      }
     }
+    store_y(i, v);
   }
-}
-
-// y = partial[0] + partial[1] + ... in that order, rounded once.
-__global__ __launch_bounds__(256) void stream_reduce_kernel(const float *__restrict__ partial, bf16_t *__restrict__ y,
-                                                            int n4, int groups) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n4) return;
-  f32x4 v = reinterpret_cast<const f32x4 *>(partial)[i];
-  for (int q = 1; q < groups; ++q) {
-    const f32x4 o = reinterpret_cast<const f32x4 *>(partial)[(size_t)q * n4 + i];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] += o[u];
-  }
-  bf16x4 o;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) o[u] = (bf16_t)v[u];
-  reinterpret_cast<bf16x4 *>(y)[i] = o;
 }
 
 }  // namespace moe355
