@@ -231,6 +231,16 @@ MOE355_API int moe_fused_forward_bounded(const moe_shape *shape, const void *x, 
                                          const void *packed_down, void *y, void *workspace, size_t workspace_bytes,
                                          void *stream, int max_polls, int wait_extra);
 
+/*
+ * moe_route_topk, moe_build_dispatch and moe_fused_forward in one call (their arguments, results and statuses, in that
+ * order; the first that fails ends it).  Small batches (at most 32 tokens, 512 experts) route and build the tables in one
+ * launch.
+ */
+MOE355_API int moe_step(const moe_shape *shape, const float *logits, const void *x, int32_t *topk_idx, float *topk_w,
+                        const moe_dispatch *tables, void *dispatch_workspace, size_t dispatch_workspace_bytes,
+                        const void *packed_gate_up, const void *packed_down, void *y, void *workspace,
+                        size_t workspace_bytes, void *stream);
+
 /* 1 or 2: GEMM launches of moe_fused_forward for this shape (host-only; 0 for an invalid shape): 1 = the resident kernel,
  * 2 = one launch per GEMM, of the tile kernels or, for small batches, of the weight-streaming ones. */
 MOE355_API int moe_forward_gemm_launches(const moe_shape *shape);

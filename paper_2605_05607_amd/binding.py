@@ -82,6 +82,8 @@ def lib() -> C.CDLL:
         L.moe_fused_forward_bounded.argtypes = [sp, vp, vp, vp, dp, vp, vp, vp, vp, sz, vp, i32, i32]
         L.moe_pack_weights.restype = i32
         L.moe_pack_weights.argtypes = [sp, vp, vp, vp, vp, vp, vp]
+        L.moe_step.restype = i32
+        L.moe_step.argtypes = [sp, vp, vp, vp, vp, dp, vp, sz, vp, vp, vp, vp, sz, vp]
         for name in ("moe_fused_forward", "moe_unfused_forward"):
             fn = getattr(L, name)
             fn.restype = i32
@@ -275,6 +277,14 @@ def moe_fused_forward(shape, x, topk_idx, topk_w, tables, packed_gate_up, packed
                       workspace_bytes=None, stream=None) -> None:
     _forward("moe_fused_forward", shape, x, topk_idx, topk_w, tables, packed_gate_up, packed_down, y, workspace,
              workspace_bytes, stream)
+
+
+def moe_step(shape, logits, x, topk_idx, topk_w, tables, dispatch_ws, packed_gate_up, packed_down, y, workspace,
+             stream=None) -> None:
+    """moe_route_topk, moe_build_dispatch and moe_fused_forward in one call."""
+    _check(lib().moe_step(C.byref(shape), _ptr(logits), _ptr(x), _ptr(topk_idx), _ptr(topk_w), C.byref(tables.struct),
+                          _ptr(dispatch_ws), _nbytes(dispatch_ws), _ptr(packed_gate_up), _ptr(packed_down), _ptr(y),
+                          _ptr(workspace), _nbytes(workspace), _stream(stream)), "moe_step")
 
 
 def moe_fused_forward_timed(shape, x, topk_idx, topk_w, tables, packed_gate_up, packed_down, y, workspace, events,

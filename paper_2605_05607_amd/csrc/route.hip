@@ -15,25 +15,8 @@ __global__ __launch_bounds__(256) void route_topk_reg_kernel(const float *__rest
   const int lane = lane_id();
   const int t = blockIdx.x * (blockDim.x >> 6) + wave;
   if (t >= T) return;  // whole wave leaves together
-  const float *row = logits + (size_t)t * E;
   RowPicker<PER> pick;
-  if (PER % 4 == 0 && (E & 3) == 0) {
-#pragma unroll
-    for (int q = 0; q < PER / 4; ++q) {
-      const int e0 = lane * PER + q * 4;
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (e0 < E) v = *reinterpret_cast<const float4 *>(row + e0);  // E % 4 == 0: the four are inside together
-      const float vv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int u = 0; u < 4; ++u) pick.key[q * 4 + u] = e0 < E ? ordered_key(vv[u]) : 0u;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int e = lane * PER + i;
-      pick.key[i] = e < E ? ordered_key(row[e]) : 0u;
-    }
-  }
+  route_load_row(pick, logits + (size_t)t * E, E);
   route_pick_registers<PER>(pick, E, k, t, topk_idx, topk_w);
 }
 

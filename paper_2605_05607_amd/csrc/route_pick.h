@@ -72,11 +72,35 @@ struct RowPicker {
   }
 };
 
+// The keys of a token's logits, lane l owning experts [l * PER, l * PER + PER).
+template <int PER>
+__device__ __forceinline__ void route_load_row(RowPicker<PER> &pick, const float *__restrict__ row, int E) {
+  const int lane = lane_id();
+  if (PER % 4 == 0 && (E & 3) == 0) {
+#pragma unroll
+    for (int q = 0; q < PER / 4; ++q) {
+      const int e0 = lane * PER + q * 4;
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (e0 < E) v = *reinterpret_cast<const float4 *>(row + e0);  // E % 4 == 0: the four are inside together
+      const float vv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) pick.key[q * 4 + u] = e0 < E ? ordered_key(vv[u]) : 0u;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int e = lane * PER + i;
+      pick.key[i] = e < E ? ordered_key(row[e]) : 0u;
+    }
+  }
+}
+
 // The k picks of one token whose logits' keys sit in `row`.  Lanes 0..k-1 write the picks (slot order = pick order) and
 // their softmax weights renormalised over the picks.
 template <int PER>
 __device__ __forceinline__ void route_pick_registers(RowPicker<PER> &row, int E, int k, int t,
-                                                     int32_t *__restrict__ topk_idx, float *__restrict__ topk_w) {
+                                                     int32_t *__restrict__ topk_idx, float *__restrict__ topk_w,
+                                                     int *also = nullptr) {  // also: a second place for the picks (LDS)
   const int lane = lane_id();
   row.sort();
   int my_e = 0;
@@ -95,6 +119,7 @@ __device__ __forceinline__ void route_pick_registers(RowPicker<PER> &row, int E,
   for (int j = 0; j < k; ++j) sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j));  // slot order
   if (lane < k) {
     topk_idx[(size_t)t * k + lane] = my_e;
+    if (also) also[t * k + lane] = my_e;
     topk_w[(size_t)t * k + lane] = x / sum;
   }
 }

@@ -130,9 +130,8 @@ class MoELayer:
 
     def step(self, logits, x) -> None:
         """One pass of the whole hot path."""
-        self.route(logits)
-        self.build_dispatch()
-        self.forward(x)
+        B.moe_step(self.shape, logits, x, self.topk_idx, self.topk_w, self.tables, self.dispatch_ws, self.packed_gate_up,
+                   self.packed_down, self.y, self.forward_ws)
 
     def y_host(self) -> np.ndarray:
         """y as float64 on the host (bf16 values widened exactly)."""

@@ -1,0 +1,47 @@
+"""moe_step (routing and tables of a small batch in one launch) against the three calls it stands for: the same tables and
+the same y, bit for bit, at the edges of the one-launch form (two tokens per wave, 1024 pairs, 512 experts)."""
+import pytest
+
+from paper_2605_05607_amd import layer as L
+from paper_2605_05607_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+TABLES = ("counts", "offsets", "perm", "inv_perm", "rank_counts", "rank_offsets", "pair_to_dedup")
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F32])
+@pytest.mark.parametrize("T,E,k,R", [(1, 8, 2, 1), (16, 64, 8, 8), (17, 60, 5, 4), (31, 128, 8, 8), (32, 256, 32, 4),
+                                     (32, 512, 6, 64), (33, 64, 8, 8), (5, 520, 4, 8), (2, 1, 1, 1)])
+def test_step_equals_the_three_calls(T, E, k, R, dtype):
+    import torch
+    d, f = 512, 512
+    print(f"step T={T} E={E} k={k} R={R} dtype={dtype}", flush=True)
+    cfg = wl.MoEConfig("step", T=T, d=d, f=f, E=E, k=k, R=R, local_rank_begin=0, local_rank_end=1, dtype=dtype,
+                       router="normal", seed=1)
+    gen = torch.Generator(device="cuda").manual_seed(T * E + k)
+    elt = torch.bfloat16 if dtype == wl.BF16 else torch.float32
+    randn = lambda *s: torch.randn(s, generator=gen, device="cuda")  # noqa: E731
+    W = [(randn(cfg.E_loc, a, b) * a ** -0.5).to(elt) for a, b in ((d, f), (d, f), (f, d))]
+    host = [L.from_device_bf16_bits(w) if dtype == wl.BF16 else w.cpu().numpy() for w in W]
+    logits, x = randn(T, E).round(decimals=1), randn(T, d).to(elt)  # (rounded: ties between experts)
+    lays = [L.MoELayer(cfg) for _ in range(2)]
+    for lay in lays:
+        lay.load_weights(*host)
+        for t in (lay.topk_idx, lay.topk_w, lay.y, lay.forward_ws, *(getattr(lay.tables, n) for n in TABLES)):
+            t.fill_(7)
+    a, b = lays
+    a.route(logits)
+    a.build_dispatch()
+    a.forward(x)
+    for _ in range(3):
+        b.y.fill_(float("nan"))
+        b.step(logits, x)
+        torch.cuda.synchronize()
+        assert torch.equal(a.topk_idx, b.topk_idx) and torch.equal(a.topk_w, b.topk_w)
+        for n in TABLES:
+            assert torch.equal(getattr(a.tables, n), getattr(b.tables, n)), n
+        n = int(a.tables.rank_offsets[-1])
+        for t in ("dedup_tok", "dedup_mask"):
+            assert torch.equal(getattr(a.tables, t)[:n], getattr(b.tables, t)[:n]), t
+        assert torch.equal(a.y, b.y)
