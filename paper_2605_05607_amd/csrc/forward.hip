@@ -849,9 +849,10 @@ extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const v
       return code != MOE_OK ? code : (int)MOE_ERR_HIP;
     return code;
   };
-  // weight gradients straight from the operands, where 32-bit offsets reach their rows; else from transposed copies
+  // weight gradients straight from the operands, where 32-bit offsets reach their rows and one behind the last token (row T:
+  // the zeros behind an expert's rows); else from transposed copies
   const int64_t reach = ((int64_t)1 << 32) - (1 << 16);
-  const bool direct = std::max((int64_t)shape->T * shape->d, dv.P_cap * 2 * shape->f) * 2 < reach;
+  const bool direct = std::max(((int64_t)shape->T + 1) * shape->d, dv.P_cap * 2 * shape->f) * 2 < reach;
   if (wgrad && kblocks > 65535) return MOE_ERR_UNSUPPORTED;
   if (wgrad && !direct) {
     if (!(side = side_stream())) return MOE_ERR_HIP;

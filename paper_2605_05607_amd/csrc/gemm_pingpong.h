@@ -166,7 +166,6 @@ struct RowRequests {
 // the last are offsets past the descriptor's end, i.e. zeros.
 // ------------------------------------------------------------------------------------------------
 constexpr int kGradSlabs = 1, kGradGatherA = 2, kGradGatherB = 3;
-constexpr uint32_t kNoRow = 0xFFFFFF00u;  // beyond every descriptor (less than 2^32 - 2^16 bytes), and no wrap behind it
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ s16x4 lds_read_transposed(uint32_t at) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(uintptr_t)at);

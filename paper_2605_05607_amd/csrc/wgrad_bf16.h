@@ -406,7 +406,7 @@ __device__ __forceinline__ void wgrad_direct_tile(const WgradDirectArgs &a, unsi
     const int n = min(cnt - c0, kWgradTable), KT = (n + 63) >> 6;
     if (c0 > 0) __syncthreads();  // every wave is done with the table and the stages
     for (int r = tid; r < KT * 64; r += kGemmThreads)
-      tab[r] = r < n ? (uint32_t)min(max(a.row_tok[start + c0 + r], 0), a.T - 1) * (a.d * 2) : kNoRow;
+      tab[r] = (uint32_t)(r < n ? min(max(a.row_tok[start + c0 + r], 0), a.T - 1) : a.T) * (a.d * 2);
     __syncthreads();
     loop.next = reinterpret_cast<const unsigned char *>(GU ? a.dgu : a.hw) + (size_t)(start + c0) * loop.pitch;
     loop.next_bytes = (uint32_t)n * loop.pitch;
@@ -487,7 +487,7 @@ __device__ __forceinline__ void wgrad_thin_tile(const WgradDirectArgs &a, unsign
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int r = kt * 64 + row0 + 32 * i;
-      const uint32_t og = r < cnt ? (uint32_t)min(max(a.row_tok[start + r], 0), a.T - 1) * gpitch + col_g : kNoRow;
+      const uint32_t og = (uint32_t)(r < cnt ? min(max(a.row_tok[start + r], 0), a.T - 1) : a.T) * gpitch + col_g;
       const uint32_t on = r * npitch + col_n;
 #pragma unroll
       for (int b = 0; b < 2; ++b) {

@@ -54,3 +54,37 @@ def test_weight_gradients_match_autograd(rows, d, f):
             # kept g and u, dg and du (or w h) and the result rounded to bf16: twice the forward's mean
             assert err.max() <= G.BF16_MAX_REL * max(r.max().item(), 1e-30)
             assert err.mean() <= 2 * G.BF16_MEAN_REL * max(r.mean().item(), 1e-30)
+
+
+@pytest.mark.parametrize("rows,d,f", [((129, 300, 65), 520, 320), ((1, 7681), 328, 64)])
+def test_a_token_of_nans_stays_with_its_expert(rows, d, f):
+    """What pads an expert's rows to whole steps is zero in both operands, whatever the first and the last token hold."""
+    import torch
+    E, T = len(rows), sum(rows)
+    print(f"weight gradients beside NaN rows={rows} d={d} f={f}", flush=True)
+    cfg = wl.MoEConfig("wgrad", T=T, d=d, f=f, E=E, k=1, R=1, local_rank_begin=0, local_rank_end=1, dtype=wl.BF16,
+                       router="normal", seed=3)
+    gen = torch.Generator(device="cuda").manual_seed(d + f)
+    randn = lambda *s: torch.randn(s, generator=gen, device="cuda")  # noqa: E731
+    bits = [L.from_device_bf16_bits((randn(E, a, b) * a ** -0.5).bfloat16()) for a, b in ((d, f), (d, f), (f, d))]
+    x, dy = randn(T, d).bfloat16(), randn(T, d).bfloat16()
+    lay = L.MoELayer(cfg)
+    lay.topk_idx.copy_(torch.from_numpy(np.repeat(np.arange(E), rows).astype(np.int32)).cuda())
+    lay.topk_w.fill_(1.0)
+    lay.build_dispatch()
+    lay.load_weights(*bits)
+    lay.enable_training(*bits)
+    for token in (0, T - 1):
+        owner = int(lay.topk_idx[token])
+        grads = []
+        for value in (None, float("nan"), float("inf")):
+            a, b = x.clone(), dy.clone()
+            if value is not None:
+                a[token], b[token] = value, value
+            lay.forward_train(a)
+            lay.backward(a, b)
+            torch.cuda.synchronize()
+            grads.append([g.clone() for g in (lay.dW_gate, lay.dW_up, lay.dW_down)])
+        for other in (e for e in range(E) if e != owner):
+            for g in grads[1:]:
+                assert all(torch.equal(p[other], q[other]) for p, q in zip(grads[0], g)), (token, other)
