@@ -310,11 +310,11 @@ __global__ __launch_bounds__(kSmallThreads) void dispatch_hist_pairs_kernel(cons
 // hand the picks over in the LDS (16 tokens of 64 experts, k = 8: 3.0 + 5.3 us as two launches).
 template <int ITERS, bool CHUNKED, int PER = 0>
 __global__ __launch_bounds__(kSmallThreads) void dispatch_pairs_kernel(
-    const float *__restrict__ logits, float *__restrict__ topk_w, int32_t *__restrict__ topk_idx, int T, int E, int k, int R, int tpc, int nch, int ebits, int rbits,
-    const int32_t *__restrict__ chunk_cnt, const int32_t *__restrict__ chunk_rcnt, int32_t *__restrict__ counts,
-    int32_t *__restrict__ offsets, int32_t *__restrict__ rank_counts, int32_t *__restrict__ rank_offsets,
-    int32_t *__restrict__ perm, int32_t *__restrict__ inv_perm, int32_t *__restrict__ dedup_tok,
-    uint32_t *__restrict__ dedup_mask, int32_t *__restrict__ pair_to_dedup) {
+    const float *__restrict__ logits, float *__restrict__ topk_w, int32_t *__restrict__ topk_idx, int T, int E, int k, int R,
+    int tpc, int nch, int ebits, int rbits, const int32_t *__restrict__ chunk_cnt, const int32_t *__restrict__ chunk_rcnt,
+    int32_t *__restrict__ counts, int32_t *__restrict__ offsets, int32_t *__restrict__ rank_counts,
+    int32_t *__restrict__ rank_offsets, int32_t *__restrict__ perm, int32_t *__restrict__ inv_perm,
+    int32_t *__restrict__ dedup_tok, uint32_t *__restrict__ dedup_mask, int32_t *__restrict__ pair_to_dedup) {
   extern __shared__ int sm[];
   constexpr int kWaves = kSmallThreads / kWave, NV = ITERS * kWaves;
   int *s_e = sm;                           // expert of every pair of this workgroup
@@ -500,9 +500,10 @@ static int build_dispatch_launches(const moe_shape *shape, const int32_t *topk_i
                            done))                                                                                   \
       return MOE_ERR_HIP;                                                                                           \
     hipLaunchKernelGGL((dispatch_pairs_kernel<ITERS_, CHUNKED_>), dim3(GRID_), dim3(kSmallThreads),                 \
-                       small_lds_bytes(ITERS_, E, R), st, nullptr, nullptr, const_cast<int32_t *>(topk_idx), T, E, k, R, TPC_, NCH_, ebits, rbits, CNT_,     \
-                       RCNT_, out->counts, out->offsets, out->rank_counts, out->rank_offsets, out->perm,            \
-                       out->inv_perm, out->dedup_tok, out->dedup_mask, out->pair_to_dedup);                         \
+                       small_lds_bytes(ITERS_, E, R), st, nullptr, nullptr, const_cast<int32_t *>(topk_idx), T, E,  \
+                       k, R, TPC_, NCH_, ebits, rbits, CNT_, RCNT_, out->counts, out->offsets, out->rank_counts,    \
+                       out->rank_offsets, out->perm, out->inv_perm, out->dedup_tok, out->dedup_mask,                \
+                       out->pair_to_dedup);                                                                         \
   } while (0)
   // Small batches (up to kSmallPairs pairs whose counters fit the LDS): one launch of one workgroup.
   const auto iters_of = [](int64_t pairs) { return pairs <= 1024 ? 1 : pairs <= 2048 ? 2 : pairs <= 4096 ? 4 : 8; };
