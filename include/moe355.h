@@ -369,6 +369,8 @@ MOE355_API int moe_fp8_fused_forward(const moe_shape *shape, const void *x, cons
  *   (later calls only: see above).  Such calls from several host threads on one device share that side stream: the library
  *   serialises their enqueueing (a mutex held for the duration of the call) and their side work runs in turn; they still
  *   need separate workspaces.
+ * moe_fused_backward_copies: moe_fused_backward that computes the weight gradients from transposed copies whatever the sizes
+ *   (same arguments, workspace and results, bit for bit), for comparing the two forms.
  */
 MOE355_API size_t moe_train_kept_bytes(const moe_shape *shape);
 MOE355_API size_t moe_backward_workspace_bytes(const moe_shape *shape);
@@ -385,6 +387,11 @@ MOE355_API int moe_fused_backward(const moe_shape *shape, const void *x, const v
                                   const void *packed_gate_up_t, const void *kept, size_t kept_bytes, void *dx,
                                   float *d_topk_w, void *dW_gate, void *dW_up, void *dW_down, void *workspace,
                                   size_t workspace_bytes, void *stream);
+MOE355_API int moe_fused_backward_copies(const moe_shape *shape, const void *x, const void *dy, const int32_t *topk_idx,
+                                         const float *topk_w, const moe_dispatch *tables, const void *packed_down_t,
+                                         const void *packed_gate_up_t, const void *kept, size_t kept_bytes, void *dx,
+                                         float *d_topk_w, void *dW_gate, void *dW_up, void *dW_down, void *workspace,
+                                         size_t workspace_bytes, void *stream);
 
 /*
  * Backward of moe_route_topk's weights (a softmax over the k picked logits; the selection is piecewise constant):

@@ -119,8 +119,9 @@ def lib() -> C.CDLL:
         L.moe_pack_weights_backward.argtypes = [sp, vp, vp, vp, vp, vp, vp]
         L.moe_fused_forward_train.restype = i32
         L.moe_fused_forward_train.argtypes = [sp, vp, vp, vp, dp, vp, vp, vp, vp, sz, vp, sz, vp]
-        L.moe_fused_backward.restype = i32
-        L.moe_fused_backward.argtypes = [sp, vp, vp, vp, vp, dp, vp, vp, vp, sz, vp, vp, vp, vp, vp, vp, sz, vp]
+        for name in ("moe_fused_backward", "moe_fused_backward_copies"):
+            getattr(L, name).restype = i32
+            getattr(L, name).argtypes = [sp, vp, vp, vp, vp, dp, vp, vp, vp, sz, vp, vp, vp, vp, vp, vp, sz, vp]
         L.moe_dispatch_gather.restype = i32
         L.moe_dispatch_gather.argtypes = [sp, vp, dp, vp, vp]
         L.moe_combine_reduce.restype = i32
@@ -422,13 +423,25 @@ def moe_fused_forward_train(shape, x, topk_idx, topk_w, tables, packed_gate_up, 
                                          _stream(stream)), "moe_fused_forward_train")
 
 
+def _backward(name, shape, x, dy, topk_idx, topk_w, tables, packed_down_t, packed_gate_up_t, kept, dx, d_topk_w, dW_gate,
+              dW_up, dW_down, workspace, stream):
+    _check(getattr(lib(), name)(C.byref(shape), _ptr(x), _ptr(dy), _ptr(topk_idx), _ptr(topk_w), C.byref(tables.struct),
+                                _ptr(packed_down_t), _ptr(packed_gate_up_t), _ptr(kept), _nbytes(kept), _ptr(dx),
+                                _ptr(d_topk_w), _ptr(dW_gate), _ptr(dW_up), _ptr(dW_down), _ptr(workspace),
+                                _nbytes(workspace), _stream(stream)), name)
+
+
 def moe_fused_backward(shape, x, dy, topk_idx, topk_w, tables, packed_down_t, packed_gate_up_t, kept, dx, d_topk_w,
                        dW_gate, dW_up, dW_down, workspace, stream=None) -> None:
-    _check(lib().moe_fused_backward(C.byref(shape), _ptr(x), _ptr(dy), _ptr(topk_idx), _ptr(topk_w),
-                                    C.byref(tables.struct), _ptr(packed_down_t), _ptr(packed_gate_up_t), _ptr(kept),
-                                    _nbytes(kept), _ptr(dx), _ptr(d_topk_w), _ptr(dW_gate), _ptr(dW_up),
-                                    _ptr(dW_down), _ptr(workspace), _nbytes(workspace), _stream(stream)),
-           "moe_fused_backward")
+    _backward("moe_fused_backward", shape, x, dy, topk_idx, topk_w, tables, packed_down_t, packed_gate_up_t, kept, dx,
+              d_topk_w, dW_gate, dW_up, dW_down, workspace, stream)
+
+
+def moe_fused_backward_copies(shape, x, dy, topk_idx, topk_w, tables, packed_down_t, packed_gate_up_t, kept, dx, d_topk_w,
+                              dW_gate, dW_up, dW_down, workspace, stream=None) -> None:
+    """moe_fused_backward with the weight gradients from transposed copies of the operands, whatever the sizes."""
+    _backward("moe_fused_backward_copies", shape, x, dy, topk_idx, topk_w, tables, packed_down_t, packed_gate_up_t, kept, dx,
+              d_topk_w, dW_gate, dW_up, dW_down, workspace, stream)
 
 
 def moe_dispatch_gather(shape, x, tables, xs, stream=None) -> None:

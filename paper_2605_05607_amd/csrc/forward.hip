@@ -782,11 +782,11 @@ static SideStream *side_stream() {
   return state[dev].load(std::memory_order_acquire) == 2 ? &made[dev] : nullptr;
 }
 
-extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const void *dy, const int32_t *topk_idx,
-                                  const float *topk_w, const moe_dispatch *tables, const void *packed_down_t,
-                                  const void *packed_gate_up_t, const void *kept, size_t kept_bytes, void *dx,
-                                  float *d_topk_w, void *dW_gate, void *dW_up, void *dW_down, void *workspace,
-                                  size_t workspace_bytes, void *stream) {
+static int backward_common(const moe_shape *shape, const void *x, const void *dy, const int32_t *topk_idx,
+                           const float *topk_w, const moe_dispatch *tables, const void *packed_down_t,
+                           const void *packed_gate_up_t, const void *kept, size_t kept_bytes, void *dx, float *d_topk_w,
+                           void *dW_gate, void *dW_up, void *dW_down, void *workspace, size_t workspace_bytes, void *stream,
+                           bool copies) {
   Derived dv;
   int rc = check_shape(shape, &dv);
   if (rc != MOE_OK) return rc;
@@ -850,9 +850,9 @@ extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const v
     return code;
   };
   // weight gradients straight from the operands, where 32-bit offsets reach their rows and one behind the last token (row T:
-  // the zeros behind an expert's rows); else from transposed copies
+  // the zeros behind an expert's rows); else, or where the caller asks for them, from transposed copies
   const int64_t reach = ((int64_t)1 << 32) - (1 << 16);
-  const bool direct = std::max(((int64_t)shape->T + 1) * shape->d, dv.P_cap * 2 * shape->f) * 2 < reach;
+  const bool direct = !copies && std::max(((int64_t)shape->T + 1) * shape->d, dv.P_cap * 2 * shape->f) * 2 < reach;
   if (wgrad && kblocks > 65535) return MOE_ERR_UNSUPPORTED;
   if (wgrad && !direct) {
     if (!(side = side_stream())) return MOE_ERR_HIP;
@@ -947,6 +947,24 @@ extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const v
   product(xT, shape->d, dguT, 2 * shape->f, shape->f, shape->d, shape->f, dW_up);    // x^T du
   product(hwT, shape->f, dyT, shape->d, 0, shape->f, shape->d, dW_down);             // (w h)^T dy
   return launch_status();
+}
+
+extern "C" int moe_fused_backward(const moe_shape *shape, const void *x, const void *dy, const int32_t *topk_idx,
+                                  const float *topk_w, const moe_dispatch *tables, const void *packed_down_t,
+                                  const void *packed_gate_up_t, const void *kept, size_t kept_bytes, void *dx,
+                                  float *d_topk_w, void *dW_gate, void *dW_up, void *dW_down, void *workspace,
+                                  size_t workspace_bytes, void *stream) {
+  return backward_common(shape, x, dy, topk_idx, topk_w, tables, packed_down_t, packed_gate_up_t, kept, kept_bytes, dx,
+                         d_topk_w, dW_gate, dW_up, dW_down, workspace, workspace_bytes, stream, false);
+}
+
+extern "C" int moe_fused_backward_copies(const moe_shape *shape, const void *x, const void *dy, const int32_t *topk_idx,
+                                         const float *topk_w, const moe_dispatch *tables, const void *packed_down_t,
+                                         const void *packed_gate_up_t, const void *kept, size_t kept_bytes, void *dx,
+                                         float *d_topk_w, void *dW_gate, void *dW_up, void *dW_down, void *workspace,
+                                         size_t workspace_bytes, void *stream) {
+  return backward_common(shape, x, dy, topk_idx, topk_w, tables, packed_down_t, packed_gate_up_t, kept, kept_bytes, dx,
+                         d_topk_w, dW_gate, dW_up, dW_down, workspace, workspace_bytes, stream, true);
 }
 
 extern "C" int moe_dispatch_gather(const moe_shape *shape, const void *x, const moe_dispatch *tables, void *xs,

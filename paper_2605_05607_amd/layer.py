@@ -101,6 +101,12 @@ class MoELayer:
                              self.packed_gate_up_t, self.kept, self.dx, self.d_topk_w, self.dW_gate, self.dW_up,
                              self.dW_down, self.backward_ws)
 
+    def backward_copies(self, x, dy) -> None:
+        """The same with the weight gradients from transposed copies of the operands."""
+        B.moe_fused_backward_copies(self.shape, x, dy, self.topk_idx, self.topk_w, self.tables, self.packed_down_t,
+                                    self.packed_gate_up_t, self.kept, self.dx, self.d_topk_w, self.dW_gate, self.dW_up,
+                                    self.dW_down, self.backward_ws)
+
     def route(self, logits) -> None:
         B.moe_route_topk(self.shape, logits, self.topk_idx, self.topk_w)
 

@@ -58,7 +58,7 @@ def test_router_tokens_beyond_4_gib():
 T_FAR, E_FAR = 524300, 4
 
 
-def far_layer(d, f):
+def far_layer(d, f, T_FAR=T_FAR):
     import torch
     cfg = wl.MoEConfig("far", T=T_FAR, d=d, f=f, E=E_FAR, k=1, R=1, local_rank_begin=0, local_rank_end=1, dtype=wl.BF16,
                        router="normal", seed=5)
@@ -129,3 +129,36 @@ def test_training_beyond_4_gib(d, f):
     got = sampled(lay.dx, toks)
     assert abs(got - ref_dx).max() <= G.BF16_MAX_REL * abs(ref_dx).max()
     assert abs(got - ref_dx).mean() <= 2 * G.BF16_MEAN_REL * abs(ref_dx).mean()
+
+
+# x and dy, then [dg | du], of the last size whose weight gradients come straight from the operands (a row behind the last
+# one within 4 GiB - 64 KiB), and one step of the size further: the transposed copies
+@pytest.mark.parametrize("T,d,f,direct", [(525304, 4088, 64, True), (525305, 4088, 64, False), (524276, 64, 2048, True),
+                                          (524280, 64, 2048, False)])
+def test_weight_gradients_around_4_gib(T, d, f, direct):
+    import torch
+    assert (max((T + 1) * d, T * 2 * f) * 2 < GIB4 - (1 << 16)) == direct
+    lay, W, bits, x, _ = far_layer(d, f, T)
+    dy = randn((T, d), 1.0, 6)
+    lay.enable_training(*bits)
+    lay.forward_train(x)
+    got = (lay.dW_gate, lay.dW_up, lay.dW_down)
+    for g in got:
+        g.fill_(float("nan"))
+    print(f"weight gradients T={T} d={d} f={f} direct={direct}", flush=True)
+    lay.backward(x, dy)
+    torch.cuda.synchronize()
+    for e in range(E_FAR):
+        wg, wu, wd = (w[e].double() for w in W)
+        ref = [torch.zeros_like(w) for w in (wg, wu, wd)]
+        for toks in (lay.topk_idx == e).nonzero()[:, 0].split(1 << 14):  # k = 1: the gate weight is 1
+            xt, dyt = x[toks].double(), dy[toks].double()
+            g, u, dh = xt @ wg, xt @ wu, dyt @ wd.T
+            sg = torch.sigmoid(g)
+            ref[0] += xt.T @ (dh * u * sg * (1 + g * (1 - sg)))
+            ref[1] += xt.T @ (dh * g * sg)
+            ref[2] += (g * sg * u).T @ dyt
+        for a, r in zip(got, ref):
+            err, r = (a[e].double() - r).abs(), r.abs()
+            # kept g and u, dg and du (or w h) and the result rounded to bf16: twice the forward's mean
+            assert err.max() <= G.BF16_MAX_REL * r.max() and err.mean() <= 2 * G.BF16_MEAN_REL * r.mean()

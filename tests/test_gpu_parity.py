@@ -920,20 +920,29 @@ def test_backward_full_size_whole_output(oracle, name):
         assert torch.isfinite(t.float()).all()
 
 
+# how the backward call gets its weight gradients: straight from the operands, or from transposed copies that the library
+# makes on a stream of its own
+FORMS = ["backward", "backward_copies"]
+
+
+@pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("name", ["ragged", "empty_experts"])
-def test_backward_replays_from_a_hip_graph(oracle, name):
-    """The backward call forks part of its work to a stream of the library's own and joins it before it returns, so
-    a capture of the caller's stream takes in all of it.  Replays alternate with eager calls and synchronisations and
+def test_backward_replays_from_a_hip_graph(oracle, name, form):
+    """A capture of the caller's stream takes in all of the call, also the part that the form with transposed copies forks to
+    a stream of the library's own and joins before it returns.  Replays alternate with eager calls and synchronisations and
     must give the eager call's bits every time."""
     import torch
     cfg = BWD_SMALL[name]
-    say(f"backward graph replay {name}")
+    say(f"{form} graph replay {name}")
     w, lay, x, dy, dy_bits, idx, tw = run_backward(cfg, oracle, wgrad=True)   # eager; also the one-off set-up calls
+    backward = getattr(lay, form)
     outs = lambda: (lay.dx, lay.d_topk_w, lay.dW_gate, lay.dW_up, lay.dW_down)
     want = [t.clone() for t in outs()]
+    backward(x, dy)
+    torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
-        lay.backward(x, dy)
+        backward(x, dy)
     for rep in range(3):
         for t in outs():
             t.fill_(float("nan"))
@@ -941,23 +950,27 @@ def test_backward_replays_from_a_hip_graph(oracle, name):
         graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(want, outs())), f"replay {rep} differs from the eager call"
-        lay.backward(x, dy)   # eager work between the replays
+        backward(x, dy)   # eager work between the replays
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(want, outs()))
 
 
-def test_backward_from_two_host_threads(oracle):
-    """Two host threads, each with its own layer, workspace and stream, call the backward at the same time.  The
-    library's side stream and its events are shared per device, so it serialises the two callers' enqueueing; each
-    must get the bits of its own single-threaded call."""
+@pytest.mark.parametrize("form", FORMS)
+def test_backward_from_two_host_threads(oracle, form):
+    """Two host threads, each with its own layer, workspace and stream, call the backward at the same time; each must get the
+    bits of its own single-threaded call.  With transposed copies they share the library's side stream and its events (one
+    set per device), so it serialises their enqueueing."""
     import threading
 
     import torch
     names = ["ragged", "deepseek_like"]
-    say(f"backward from two host threads: {names}")
+    say(f"{form} from two host threads: {names}")
     runs = [run_backward(BWD_SMALL[n], oracle, wgrad=True) for n in names]   # eager, one after the other
     outs = lambda lay: (lay.dx, lay.d_topk_w, lay.dW_gate, lay.dW_up, lay.dW_down)
     want = [[t.clone() for t in outs(r[1])] for r in runs]
+    for r in runs:
+        for t in outs(r[1]):
+            t.fill_(float("nan"))
     torch.cuda.synchronize()
     errors = []
 
@@ -967,7 +980,7 @@ def test_backward_from_two_host_threads(oracle):
             stream = torch.cuda.Stream()
             with torch.cuda.stream(stream):
                 for _ in range(25):
-                    lay.backward(x, dy)
+                    getattr(lay, form)(x, dy)
             stream.synchronize()
         except Exception as exc:   # reported by the main thread
             errors.append(exc)

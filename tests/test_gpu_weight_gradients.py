@@ -88,3 +88,35 @@ def test_a_token_of_nans_stays_with_its_expert(rows, d, f):
         for other in (e for e in range(E) if e != owner):
             for g in grads[1:]:
                 assert all(torch.equal(p[other], q[other]) for p, q in zip(grads[0], g)), (token, other)
+
+
+@pytest.mark.parametrize("rows,d,f", CASES + [((700, 0, 65, 1, 300, 64), 1032, 576)])
+def test_transposed_copies_give_the_same_bits(rows, d, f):
+    """The form that operands of 4 GiB and more take, on the sizes above: every output equal to the direct form's."""
+    import torch
+    E, T = len(rows), sum(rows)
+    print(f"weight gradients, both forms rows={rows} d={d} f={f}", flush=True)
+    cfg = wl.MoEConfig("wgrad", T=T, d=d, f=f, E=E, k=1, R=1, local_rank_begin=0, local_rank_end=1, dtype=wl.BF16,
+                       router="normal", seed=3)
+    gen = torch.Generator(device="cuda").manual_seed(d + f)
+    randn = lambda *s: torch.randn(s, generator=gen, device="cuda")  # noqa: E731
+    bits = [L.from_device_bf16_bits((randn(E, a, b) * a ** -0.5).bfloat16()) for a, b in ((d, f), (d, f), (f, d))]
+    x, dy = randn(T, d).bfloat16(), randn(T, d).bfloat16()
+    lay = L.MoELayer(cfg)
+    lay.topk_idx.copy_(torch.from_numpy(np.random.default_rng(f).permutation(np.repeat(np.arange(E), rows)).astype(np.int32)))
+    lay.topk_w.uniform_(0.1, 1.0, generator=gen)
+    lay.build_dispatch()
+    lay.load_weights(*bits)
+    lay.enable_training(*bits)
+    lay.forward_train(x)
+    out = []
+    for form in (lay.backward, lay.backward_copies, lay.backward_copies):
+        lay.backward_ws.fill_(0xFF)
+        tensors = (lay.dx, lay.d_topk_w, lay.dW_gate, lay.dW_up, lay.dW_down)
+        for t in tensors:
+            t.fill_(float("nan"))
+        form(x, dy)
+        torch.cuda.synchronize()
+        out.append([t.clone() for t in tensors])
+    for other in out[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(out[0], other))
