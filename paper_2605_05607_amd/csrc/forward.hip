@@ -271,8 +271,7 @@ static int stream_groups(const moe_shape *s, const Derived &dv, int elt) {
   const double us = busy * s->f * s->d * elt / 36e3;  // one CU, microseconds
   int best = 1;
   double t_best = us / std::min(strips, 180);
-  const int slots = std::min(s->k, dv.E_loc);  // (the partial sums, strips of 32 columns, live in the rows of o)
-  for (int g = 2; g <= std::min(8, slots) && (int64_t)g * strips * 32 <= (int64_t)slots * s->d; ++g) {
+  for (int g = 2; g <= std::min(8, std::min(s->k, dv.E_loc)); ++g) {  // (the partial sums live in the rows of o)
     const double t = us / std::min(strips * g, 180) + 1.5;
     if (t < t_best) {
       t_best = t;

@@ -23,7 +23,7 @@ struct StreamArgs {
   const void *A;    // GEMM-1: x [T, K] (bf16, or codes); GEMM-2: h [rows, K]
   const void *Bp;   // packed tiles
   void *out;        // GEMM-1: h [rows, N]; GEMM-2: y [T, N] bf16
-  float *partial;   // GEMM-2 with several groups: their sums, [group][strip][T][32]
+  float *partial;   // GEMM-2 with several groups: their sums, [group][strip][T][columns of the strip]
   int32_t *arrived; // groups that have stored theirs, per strip (cleared by GEMM-1: n_arrived of them, none for one group)
   int n_arrived;
   const int32_t *offsets, *perm;
@@ -384,9 +384,14 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void stream_gemm2_kernel(cons
     for (int i = tid; i < tot; i += kStreamWaves * 64) store_y(i, column_sum(i));
     return;
   }
-  uint64_t *partial = reinterpret_cast<uint64_t *>(g.partial);  // two columns each
-  const auto place = [&](int group, int i) { return ((size_t)(group * (int)gridDim.x + c) * tot + i) * 2; };
+  // two columns each; the last strip may have fewer than 32 columns, and no place is left for those it does not have
+  uint64_t *partial = reinterpret_cast<uint64_t *>(g.partial);
+  const int wide = min(32, g.N - c * 32);
+  const auto place = [&](int group, int i) {
+    return ((size_t)group * g.T * g.N + (size_t)c * 32 * g.T + (i >> 3) * wide + (i & 7) * 4) / 2;
+  };
   for (int i = tid; i < tot; i += kStreamWaves * 64) {
+    if ((i & 7) * 4 >= wide) continue;
     const f32x4 v = column_sum(i);
     typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
     const u64x2 w = __builtin_bit_cast(u64x2, v);
@@ -400,6 +405,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void stream_gemm2_kernel(cons
   __syncthreads();
   if (!*n_seg_s) return;  // whole workgroup
   for (int i = tid; i < tot; i += kStreamWaves * 64) {
+    if ((i & 7) * 4 >= wide) continue;
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
     for (int q = 0; q < (int)gridDim.y; ++q) {
       typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));

@@ -66,3 +66,24 @@ def check_y(y, ref, dtype):
         return err.max() / scale, mean_rel
     assert err.max() <= F32_MAX_REL * scale, f"max err {err.max():.3e} vs scale {scale:.3e}"
     return err.max() / scale, err.mean() / np.abs(ref).mean()
+
+
+def device_us(call, calls=20, replays=10):
+    """Microseconds of one call on the device, without the host: the fastest of several runs of a captured graph."""
+    import torch
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(calls):
+            call()
+    best = float("inf")
+    for _ in range(6):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(replays):
+            graph.replay()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / (calls * replays))
+    return best

@@ -53,6 +53,10 @@ EDGES = {
     "no_local_row": dict(T=3, E=64, k=1, R=64, local_rank_begin=5, local_rank_end=6),
     "many_experts": dict(T=100, E=512, k=6, R=1, local_rank_begin=0, local_rank_end=1),
     "groups": dict(T=24, d=512, f=2048, E=32, k=16, R=1, local_rank_begin=0, local_rank_end=1),
+    # several groups and a last strip of 8 or 16 columns: the groups' sums fill the rows of o to the last element
+    "groups_last_strip_8": dict(T=33, d=520, f=1512, E=8, k=2, R=1, local_rank_begin=0, local_rank_end=1),
+    "groups_last_strip_16": dict(T=128, d=1008, f=1504, E=8, k=2, R=1, local_rank_begin=0, local_rank_end=1),
+    "groups_last_strip_8_one_token": dict(T=1, d=1000, f=2048, E=16, k=16, R=1, local_rank_begin=0, local_rank_end=1),
 }
 
 
@@ -80,7 +84,7 @@ def test_small_batch_forward(oracle, name):
         assert B.moe_forward_status(lay.forward_ws) == 0
 
 
-@pytest.mark.parametrize("name", ["one_token", "rows_33", "rows_128_two_passes", "groups"])
+@pytest.mark.parametrize("name", ["one_token", "rows_33", "rows_128_two_passes", "groups", "groups_last_strip_16"])
 def test_small_batch_fp8_forward(oracle, name):
     import torch
     kw = dict(EDGES[name])
@@ -102,6 +106,27 @@ def test_small_batch_fp8_forward(oracle, name):
     ref = oracle.forward_fp8(w.x, idx, tw, w.W_gate, w.W_up, w.W_down, hs, cfg.E, cfg.R, cfg.local_rank_begin,
                              cfg.local_rank_end)
     G.check_y(lay.y_host(), ref, cfg.dtype)
+
+
+# A layer whose last strip of 32 columns is short shares its strips among as many work groups as the next larger one (with
+# one group per strip it takes 1.2 times as long here; runs of one side differ by 2 %).
+@pytest.mark.parametrize("T", [16, 64])
+def test_short_last_strip_costs_no_groups(T):
+    import torch
+    us = []
+    for d in (1000, 1024):
+        cfg = cfg_of(T=T, d=d, f=1512, E=8, k=2, R=1, local_rank_begin=0, local_rank_end=1)
+        gen = torch.Generator(device="cuda").manual_seed(T)
+        randn = lambda *s: torch.randn(s, generator=gen, device="cuda")  # noqa: E731
+        lay = L.MoELayer(cfg)
+        lay.load_weights(*(L.from_device_bf16_bits((randn(8, a, b) * a ** -0.5).bfloat16())
+                           for a, b in ((d, 1512), (d, 1512), (1512, d))))
+        lay.route(randn(T, 8))
+        lay.build_dispatch()
+        x = randn(T, d).bfloat16()
+        us.append(G.device_us(lambda: lay.forward(x)))
+        print(f"small-batch forward T={T} d={d}: {us[-1]:.1f} us", flush=True)
+    assert us[0] <= 1.1 * us[1]
 
 
 # fp32 reductions that end inside a load group: the padding must not meet an infinity of the row (0 * inf)
