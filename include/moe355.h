@@ -233,8 +233,8 @@ MOE355_API int moe_fused_forward_bounded(const moe_shape *shape, const void *x, 
 
 /*
  * moe_route_topk, moe_build_dispatch and moe_fused_forward in one call (their arguments, results and statuses, in that
- * order; the first that fails ends it).  Small batches (at most 32 tokens, 512 experts) route and build the tables in one
- * launch.
+ * order; the first that fails ends it).  The smallest batches (up to 32 tokens with few experts and picks) route and build
+ * the tables in one launch.
  */
 MOE355_API int moe_step(const moe_shape *shape, const float *logits, const void *x, int32_t *topk_idx, float *topk_w,
                         const moe_dispatch *tables, void *dispatch_workspace, size_t dispatch_workspace_bytes,

@@ -569,11 +569,19 @@ static int build_dispatch_launches(const moe_shape *shape, const int32_t *topk_i
   return launch_status();
 }
 
-// Routing and tables of a small batch in one launch: at most two tokens per wave (more and the picks, one after the other,
-// take longer than the launch they save) and 1024 pairs.
+// Routing and tables of a small batch in one launch, where its one workgroup routes the tokens in less time than the launch it
+// saves.  A wave's tokens come one after the other and the waves of a SIMD share it: time in proportion to the tokens, to the
+// picks plus what loading and sorting a row take (about eight picks) and, more slowly, to the experts per lane.  Gain over two
+// launches, microseconds of a step:
+//   tokens               8      16      24      32    |  64 experts, k = 2:   1.6   1.3   1.1   0.6
+//   64 experts, k = 8    1.5    1.0     0.2    -0.8   |  64 experts, k = 32:  0.9  -1.2  -3.6  -7.2
+//   128 experts, k = 8   1.3    0.6    -0.2    -1.4   |  128 experts, k = 4:  1.5   1.1   0.3  -0.4
+//   256 experts, k = 8   1.1    0.2    -0.6    -2.3   |  256 experts, k = 2:  1.2   1.0   0.5  -0.2
+//   512 experts, k = 8   0.7   -0.9    -2.5    -5.0   |  512 experts, k = 1:  0.8   0.3  -0.5  -1.4
 constexpr int kRoutedTokens = 32;
 static bool routed_form(const moe_shape *s) {
-  return s->T > 0 && s->T <= kRoutedTokens && s->E <= 512 && s->T * s->k <= kSmallThreads &&
+  const int most = s->E <= 64 ? 384 : s->E <= 128 ? 320 : s->E <= 256 ? 264 : 160;
+  return s->T > 0 && s->T <= kRoutedTokens && s->E <= 512 && s->T * (s->k + 8) <= most &&
          small_lds_bytes(1, s->E, s->R) <= kSmallLds;
 }
 static int launch_routed(const moe_shape *s, const float *logits, int32_t *topk_idx, float *topk_w, const moe_dispatch *out,
