@@ -271,7 +271,7 @@ static int stream_groups(const moe_shape *s, const Derived &dv, int elt) {
   const double us = busy * s->f * s->d * elt / 36e3;  // one CU, microseconds
   int best = 1;
   double t_best = us / std::min(strips, 180);
-  for (int g = 2; g <= std::min(8, std::min(s->k, dv.E_loc)); ++g) {  // (the partial sums live in the rows of o)
+  for (int g = 2; g <= std::min(kStreamGroups, std::min(s->k, dv.E_loc)); ++g) {  // (the partial sums live in the rows of o)
     const double t = us / std::min(strips * g, 180) + 1.5;
     if (t < t_best) {
       t_best = t;

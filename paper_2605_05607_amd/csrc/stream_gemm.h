@@ -18,6 +18,7 @@ namespace moe355 {
 constexpr int kStreamTokens = 128;   // largest batch (GEMM-2 keeps one fp32 row of 32 columns per token and wave)
 constexpr int kStreamExperts = 512;  // most local experts (GEMM-2 lists the busy ones in the LDS)
 constexpr int kStreamWaves = 8;
+constexpr int kStreamGroups = 8;  // most work groups per strip of GEMM-2
 
 struct StreamArgs {
   const void *A;    // GEMM-1: x [T, K] (bf16, or codes); GEMM-2: h [rows, K]
@@ -249,7 +250,9 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void stream_gemm1_kernel(cons
 // expert it adds weight * sum to its own fp32 row of each token in the LDS; at the end the waves' rows are added in wave order and written once: tokens without
 // a local slot come out as zeros, and no row of o ever exists.  groups > 1 (strips too few to pull the weights at the
 // chip's rate): every group stores its sums past the L2s (device-scope stores, as the resident kernels store h), counts itself
-// for the strip, and the one that comes last adds them all in group order.  A launch of its own for that sum took 4 to 5 us.
+// for the strip, and the one that comes last adds them all in group order, every group's requested before the first is added
+// (one after the other, the loads past the L2s took 0.8 us of six groups and one token, 2 us of eight groups and 128 tokens).
+// A launch of its own for that sum took 4 to 5 us.
 // ------------------------------------------------------------------------------------------------
 // LDS: the waves' token rows | the busy list | token and weight of every local row
 constexpr int stream_row_blocks(int T) { return T <= 32 ? 1 : 2; }  // NB: 32-row blocks per pass
@@ -380,7 +383,8 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void stream_gemm2_kernel(cons
     for (int u = 0; u < 4; ++u) o[u] = (bf16_t)v[u];
     *reinterpret_cast<bf16x4 *>(static_cast<bf16_t *>(g.out) + (size_t)(i >> 3) * g.N + col) = o;
   };
-  if (gridDim.y == 1) {
+  if (gridDim.y == 1 || total == 0) {  // (no local row: y is zero, nothing to hand over)
+    if (blockIdx.y > 0) return;
     for (int i = tid; i < tot; i += kStreamWaves * 64) store_y(i, column_sum(i));
     return;
   }
@@ -406,18 +410,23 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void stream_gemm2_kernel(cons
   if (!*n_seg_s) return;  // whole workgroup
   for (int i = tid; i < tot; i += kStreamWaves * 64) {
     if ((i & 7) * 4 >= wide) continue;
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    for (int q = 0; q < (int)gridDim.y; ++q) {
+    // every group's sum is requested before the first is added
+    f32x4 sums[kStreamGroups];
+#pragma unroll
+    for (int q = 0; q < kStreamGroups; ++q) {
+      if (q >= (int)gridDim.y) break;
       typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
       u64x2 w;
       w[0] = __hip_atomic_load(&partial[place(q, i)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       w[1] = __hip_atomic_load(&partial[place(q, i) + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const f32x4 o = __builtin_bit_cast(f32x4, w);
-      if (q == 0) v = o;
-      else {
+      sums[q] = __builtin_bit_cast(f32x4, w);
+    }
+    f32x4 v = sums[0];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] += o[u];
-      }
+    for (int q = 1; q < kStreamGroups; ++q) {
+      if (q >= (int)gridDim.y) break;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] += sums[q][u];
     }
     store_y(i, v);
   }

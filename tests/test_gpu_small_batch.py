@@ -129,6 +129,26 @@ def test_short_last_strip_costs_no_groups(T):
     assert us[0] <= 1.1 * us[1]
 
 
+# several groups per strip, and no pick on a local expert: zeros, whatever the rows of o held
+@pytest.mark.parametrize("T", [1, 40])
+def test_groups_without_a_local_row(T):
+    import torch
+    cfg = cfg_of(T=T, d=520, f=8192, E=16, k=8, R=2, local_rank_begin=1, local_rank_end=2)
+    print(f"groups without a local row T={T}", flush=True)
+    w = wl.make_workload(cfg)
+    lay = L.MoELayer(cfg)
+    lay.load_weights(w.W_gate, w.W_up, w.W_down)
+    lay.topk_idx.copy_(torch.arange(8, dtype=torch.int32).repeat(T).reshape(lay.topk_idx.shape))
+    lay.topk_w.fill_(0.125)
+    lay.build_dispatch()
+    lay.forward_ws.fill_(0xFF)
+    for _ in range(2):
+        lay.y.fill_(float("nan"))
+        lay.forward(L.to_device(w.x))
+        torch.cuda.synchronize()
+        assert not lay.y[:T].any()
+
+
 # fp32 reductions that end inside a load group: the padding must not meet an infinity of the row (0 * inf)
 @pytest.mark.parametrize("T,d,f", [(4, 264, 40), (200, 264, 264), (4, 24, 8)])
 def test_f32_reduction_tail_beside_an_infinity(T, d, f):
