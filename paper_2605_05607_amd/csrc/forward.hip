@@ -821,6 +821,16 @@ static int backward_common(const moe_shape *shape, const void *x, const void *dy
     return launch_status();
   }
   const BwdLayout L = backward_layout(shape, dvb);
+  // weight gradients straight from the operands, where 32-bit offsets reach their rows and one behind the last token (row T:
+  // the zeros behind an expert's rows); else, or where the caller asks for them, from transposed copies
+  const int64_t reach = ((int64_t)1 << 32) - (1 << 16);
+  const bool direct = !copies && std::max(((int64_t)shape->T + 1) * shape->d, dv.P_cap * 2 * shape->f) * 2 < reach;
+  const auto tiles = [&](int edge) {  // of all three gradients of an expert
+    const int64_t td = ceil_div(shape->d, edge);
+    return td * ceil_div(2 * shape->f, edge) + td * ceil_div(shape->f, edge);
+  };
+  const int kblocks = (int)(L.kpad / 64);
+  if (wgrad && (kblocks > 65535 || (direct && tiles(kBM) * dv.E_loc >= (int64_t)1 << 30))) return MOE_ERR_UNSUPPORTED;
   const Ws w = carve(workspace, L.t);
   unsigned char *b = static_cast<unsigned char *>(workspace);
   bf16_t *dgu = reinterpret_cast<bf16_t *>(b + L.dgu), *hw = reinterpret_cast<bf16_t *>(b + L.hw);
@@ -836,7 +846,6 @@ static int backward_common(const moe_shape *shape, const void *x, const void *dy
   int32_t *kb = reinterpret_cast<int32_t *>(b + L.kb);
   bf16_t *xT = reinterpret_cast<bf16_t *>(b + L.xT), *dyT = reinterpret_cast<bf16_t *>(b + L.dyT);
   bf16_t *hwT = reinterpret_cast<bf16_t *>(b + L.hwT), *dguT = reinterpret_cast<bf16_t *>(b + L.dguT);
-  const int kblocks = (int)(L.kpad / 64);
   const auto transpose = [&](const bf16_t *src, const int32_t *map, int ld, int C, bf16_t *dst) {
     hipLaunchKernelGGL(gather_transpose_kernel, dim3(ceil_div(C, 64), kblocks), dim3(256), 0, side->stream, src, map,
                        ld, 0, C, tables->offsets, w.header, kb, dv.e_lo, dv.E_loc, dst);
@@ -848,11 +857,6 @@ static int backward_common(const moe_shape *shape, const void *x, const void *dy
       return code != MOE_OK ? code : (int)MOE_ERR_HIP;
     return code;
   };
-  // weight gradients straight from the operands, where 32-bit offsets reach their rows and one behind the last token (row T:
-  // the zeros behind an expert's rows); else, or where the caller asks for them, from transposed copies
-  const int64_t reach = ((int64_t)1 << 32) - (1 << 16);
-  const bool direct = !copies && std::max(((int64_t)shape->T + 1) * shape->d, dv.P_cap * 2 * shape->f) * 2 < reach;
-  if (wgrad && kblocks > 65535) return MOE_ERR_UNSUPPORTED;
   if (wgrad && !direct) {
     if (!(side = side_stream())) return MOE_ERR_HIP;
     side_lock = std::unique_lock<std::mutex>(side->enqueue);
@@ -914,11 +918,6 @@ static int backward_common(const moe_shape *shape, const void *x, const void *dy
     a.dW_down = static_cast<bf16_t *>(dW_down);
     a.offsets = tables->offsets; a.header = w.header; a.row_tok = w.row_tok;
     a.e_lo = dv.e_lo; a.E_loc = dv.E_loc; a.T = shape->T; a.d = shape->d; a.f = shape->f;
-    const auto tiles = [&](int edge) {
-      const int64_t td = ceil_div(shape->d, edge);
-      return td * ceil_div(2 * shape->f, edge) + td * ceil_div(shape->f, edge);
-    };
-    if (tiles(kBM) * dv.E_loc >= (int64_t)1 << 30) return MOE_ERR_UNSUPPORTED;
     a.n_items = (int)(tiles(kBM) * dv.E_loc);
     static std::atomic<uint64_t> done_d{0};
     if (!allow_dynamic_lds(reinterpret_cast<const void *>(&wgrad_bf16_kernel), kWgradLds, done_d)) return MOE_ERR_HIP;

@@ -249,6 +249,21 @@ def test_training_entry_points_arguments():
     # (T = 0 launches a fill for the weight gradients, or nothing without them: exercised on the GPU)
 
 
+def test_backward_refuses_before_its_first_launch():
+    """Weight gradients of more tiles or rows than the grids hold: refused with nothing enqueued (here a launch would fail with
+    another status)."""
+    lib = B.lib()
+    fake, big = 4096, 1 << 62
+    tb = B.moe_dispatch(*([fake] * 9))
+    many_tiles = good_shape(T=1, d=80000, f=80000, E=4096, R=1, k=1, local_rank_begin=0, local_rank_end=1)
+    many_rows = good_shape(T=1 << 23, d=64, f=64, E=1, R=1, k=1, local_rank_begin=0, local_rank_end=1)
+    for s, names in ((many_tiles, ["moe_fused_backward"]), (many_rows, ["moe_fused_backward", "moe_fused_backward_copies"])):
+        for name in names:
+            call = lambda *grads: getattr(lib, name)(C.byref(s), fake, fake, fake, fake, C.byref(tb), fake, fake, fake, big,
+                                                     fake, fake, *grads, fake, big, None)
+            assert call(fake, fake, fake) == B.MOE_ERR_UNSUPPORTED, name
+
+
 def test_route_backward_arguments():
     lib = B.lib()
     s = good_shape()
