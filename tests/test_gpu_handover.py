@@ -3,16 +3,19 @@ whose rows are no whole number of 128-byte lines, inputs that change from call t
 would show."""
 import pytest
 
+import gpu_util as G
+from paper_2605_05607_amd import binding as B
 from paper_2605_05607_amd import layer as L
 from paper_2605_05607_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 
 
-# rows per expert: a few, some tiles of every height, several M tiles that start inside a line of the unpadded matrix
-@pytest.mark.parametrize("T", [40, 600, 2100])
+# rows per expert: a few, some tiles of every height, several M tiles that start inside a line of the unpadded matrix (just
+# below the mean from which calls that choose by shape take two launches, and a quarter of the experts with half of the rows)
+@pytest.mark.parametrize("T", [40, 600, 2040])
 @pytest.mark.parametrize("form,f", [("bf16", 72), ("bf16", 200), ("bf16", 1000), ("train", 192), ("fp8", 80), ("fp8", 336)])
-def test_handover_follows_changing_inputs(form, f, T):
+def test_handover_follows_changing_inputs(oracle, form, f, T):
     import numpy as np
     import torch
     d, E, k = 256, 32, 4
@@ -25,10 +28,14 @@ def test_handover_follows_changing_inputs(form, f, T):
     W = [(randn(cfg.E_loc, a, b) * a ** -0.5).bfloat16() for a, b in ((d, f), (d, f), (f, d))]
     bits = [L.from_device_bf16_bits(w) for w in W]
     xs = [randn(T, d).bfloat16() for _ in range(3)]
-    lay.route(randn(T, E))
+    lay.route(randn(T, E) + 1.5 * (torch.arange(E, device="cuda") % 4 == 0))
     lay.build_dispatch()
+    assert B.moe_forward_gemm_launches(lay.shape) == 1  # (train and fp8 choose by shape)
+    rows = lay.tables.counts[cfg.local_rank_begin * cfg.epr:][:cfg.E_loc]
+    assert T < 2000 or (rows > 2 * 256).any()
     if form == "fp8":
-        lay.load_weights_fp8(*bits, np.full(cfg.E_loc, 0.02, dtype=np.float32))
+        h_scale = np.full(cfg.E_loc, 0.02, dtype=np.float32)
+        lay.load_weights_fp8(*bits, h_scale)
         run, first = lay.forward_fp8, lay.forward_fp8  # (one form: later calls have to repeat the first ones)
     else:
         lay.load_weights(*bits)
@@ -36,30 +43,22 @@ def test_handover_follows_changing_inputs(form, f, T):
         if form == "train":
             lay.enable_training(*bits, wgrad=False)
             run = lay.forward_train
+    ws = lay.fp8_ws if form == "fp8" else lay.forward_ws
     want = []
     for x in xs:
+        ws.fill_(0xFF)  # (NaN as bf16 and as a code: a row read before it was handed over would show in the first calls)
         first(x)
         want.append(lay.y.clone())
     assert not torch.equal(want[0], want[1])
-    if form == "fp8":  # the codes' own error is a few per cent: wrong rows are not
+    if form == "fp8":
+        idx, tw = lay.topk_idx.cpu().numpy().reshape(T, k), lay.topk_w.cpu().numpy().reshape(T, k)
         for x, w in zip(xs, want):
-            ref = reference(lay, cfg, W, x)
-            assert (w.double() - ref).norm() <= 0.1 * ref.norm()
+            G.check_y(w.double().cpu().numpy(),
+                      oracle.forward_fp8(L.from_device_bf16_bits(x), idx, tw, *bits, h_scale, E, cfg.R, 0, 1), wl.BF16)
     for n in range(24):
-        (lay.fp8_ws if form == "fp8" else lay.forward_ws).fill_(0xFF) if n % 4 == 0 else None
+        if n % 4 == 0:
+            ws.fill_(0xFF)
         lay.y.fill_(float("nan"))
         run(xs[n % 3])
         torch.cuda.synchronize()
         assert torch.equal(lay.y, want[n % 3]), (form, f, T, n)
-
-
-def reference(lay, cfg, W, x):
-    import torch
-    y = torch.zeros(cfg.T, cfg.d, dtype=torch.float64, device="cuda")
-    idx, w = lay.topk_idx.view(cfg.T, cfg.k), lay.topk_w.view(cfg.T, cfg.k).double()
-    for e in range(cfg.E_loc):
-        t, j = (idx == e).nonzero(as_tuple=True)
-        xt = x[t].double()
-        h = torch.nn.functional.silu(xt @ W[0][e].double()) * (xt @ W[1][e].double())
-        y.index_add_(0, t, (h @ W[2][e].double()) * w[t, j][:, None])
-    return y
