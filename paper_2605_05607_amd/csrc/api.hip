@@ -49,6 +49,7 @@ FwdLayout forward_layout(const moe_shape *s, const Derived &dv) {
   L.tile_ready = take((size_t)dv.max_mtiles * sizeof(int32_t));
   L.row_tile = take(rows * sizeof(int32_t));
   L.tile_done = take((size_t)dv.max_mtiles * sizeof(int32_t));
+  L.arrived = take((size_t)ceil_div(s->d, 32) * sizeof(int32_t));
   L.h = take(rows * (size_t)h_pitch(s, dv.elt) * dv.elt);
   L.o = take(rows * (size_t)s->d * sizeof(float));
   L.total = off;

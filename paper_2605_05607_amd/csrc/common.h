@@ -77,6 +77,7 @@ struct FwdLayout {
   size_t tile_ready;  // int32[max_mtiles] GEMM-1 items finished per M tile (hand-over inside the resident kernel)
   size_t row_tile;    // int32[P_cap]      M tile of each local row        } resident kernel that also runs
   size_t tile_done;   // int32[max_mtiles] GEMM-2 items finished per M tile } Combine
+  size_t arrived;   // int32[ceil(d / 32)] small batches: work groups of a strip of GEMM-2 that have stored their sums
   size_t h;         // elt  [P_cap, h_pitch]
   size_t o;         // float[P_cap, d]
   size_t total;

@@ -22,7 +22,7 @@ namespace moe355 {
 // Host-side launch helpers
 // ------------------------------------------------------------------------------------------------
 struct Ws {
-  int32_t *header, *row_tok, *row_sole, *tile_ready, *row_tile, *tile_done;
+  int32_t *header, *row_tok, *row_sole, *tile_ready, *row_tile, *tile_done, *arrived;
   int4 *work1, *work2;
   float *row_w;
   void *h;
@@ -41,6 +41,7 @@ static Ws carve(void *workspace, const FwdLayout &L) {
   w.tile_ready = reinterpret_cast<int32_t *>(b + L.tile_ready);
   w.row_tile = reinterpret_cast<int32_t *>(b + L.row_tile);
   w.tile_done = reinterpret_cast<int32_t *>(b + L.tile_done);
+  w.arrived = reinterpret_cast<int32_t *>(b + L.arrived);
   w.h = b + L.h;
   w.o = reinterpret_cast<float *>(b + L.o);
   return w;
@@ -297,8 +298,7 @@ static int launch_stream(const moe_shape *s, const Derived &dv, const void *x, c
   StreamArgs g2 = g1;
   const int groups = stream_groups(s, dv, q ? 1 : 2);
   g2.A = w.h; g2.Bp = packed_down; g2.out = y;
-  // (the counters in GEMM-2's work list, which this form does not use: 32 bytes per 256 columns and M tile, at least two)
-  g1.arrived = g2.arrived = reinterpret_cast<int32_t *>(w.work2);
+  g1.arrived = g2.arrived = w.arrived;
   g1.n_arrived = groups > 1 ? ceil_div(s->d, 32) : 0;
   g2.partial = w.o;
   g2.K = s->f; g2.N = s->d; g2.n_ntiles = ceil_div(s->d, kBN); g2.n_ktiles = ceil_div(s->f, step);
@@ -670,7 +670,7 @@ static BwdLayout backward_layout(const moe_shape *s, const Derived &dvb) {
   L.t.row_w = take(rows * sizeof(float));
   L.t.row_sole = take(rows * sizeof(int32_t));
   L.t.tile_ready = take((size_t)dvb.max_mtiles * sizeof(int32_t));
-  L.t.row_tile = L.t.tile_done = 0;  // forward only
+  L.t.row_tile = L.t.tile_done = L.t.arrived = 0;  // forward only
   L.t.h = L.t.o = 0;
   L.dgu = take(rows * 2 * (size_t)s->f * 2);
   L.hw = take(rows * (size_t)s->f * 2);
