@@ -370,7 +370,8 @@ MOE355_API int moe_fp8_fused_forward(const moe_shape *shape, const void *x, cons
  *   serialises their enqueueing (a mutex held for the duration of the call) and their side work runs in turn; they still
  *   need separate workspaces.
  * moe_fused_backward_copies: moe_fused_backward that computes the weight gradients from transposed copies whatever the sizes
- *   (same arguments, workspace and results, bit for bit), for comparing the two forms.
+ *   (same arguments, workspace and results, bit for bit), for comparing the two forms.  The workspace has room for the copies
+ *   at every size.
  */
 MOE355_API size_t moe_train_kept_bytes(const moe_shape *shape);
 MOE355_API size_t moe_backward_workspace_bytes(const moe_shape *shape);

@@ -266,6 +266,8 @@ bool stream_form(const moe_shape *s, const Derived &dv, int elt) {
 
 // Work groups per strip of GEMM-2: one, unless so few strips of 32 columns exist that handing the sums over (~1.5 us) costs
 // less than what the missing CUs would have pulled (a CU pulls ~36 GB/s here, the chip ~6.5 TB/s, i.e. what ~180 CUs pull).
+// Within 6 % of the best count at 1 to 128 tokens on 8 experts of 512 x 2048, 1024 x 1024 and 2048 x 512, 16 of 2048 x 2048 and
+// 32 of 2880 x 2880 (one group instead: up to 2.6 x as long, 128 tokens of the first).
 static int stream_groups(const moe_shape *s, const Derived &dv, int elt) {
   const int strips = ceil_div(s->d, 32);
   const double busy = std::min<double>(dv.E_loc, (double)s->T * s->k * dv.E_loc / s->E);
@@ -748,10 +750,10 @@ extern "C" int moe_fused_forward_train(const moe_shape *shape, const void *x, co
                         workspace_bytes, stream, true, nullptr, 0, nullptr, kept);
 }
 
-// Where the weight gradients need transposed operands (4 GiB and more), the backward pass makes them beside its
-// compute-bound GEMMs: those kernels need at most 16 registers and little or no LDS, so their waves fit on a CU next to a
-// GEMM workgroup.  They go to a stream of the library's own (one per device,
-// default priority, created on first use and kept), forked from and joined to the caller's stream by events.
+// Where the weight gradients come from transposed operands (4 GiB and more, or where a caller asks for it), the backward pass
+// makes them beside its compute-bound GEMMs: those kernels need at most 16 registers and little or no LDS, so their waves fit
+// on a CU next to a GEMM workgroup.  They go to a stream of the library's own (one per device, default priority, created on
+// first use and kept), forked from and joined to the caller's stream by events.
 struct SideStream {
   hipStream_t stream;
   hipEvent_t fork, mid, join;

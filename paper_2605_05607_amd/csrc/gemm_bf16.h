@@ -406,8 +406,8 @@ __device__ __forceinline__ void gemm_bf16_item(const GemmArgs &g, unsigned char 
                                                int poison = 0, int32_t *tickets = nullptr, int *pre = nullptr) {
   const int le = item.x, m0 = item.y, rows = item.z & kItemRowsMask, nt = item.w & ((1 << kTileShift) - 1);
   // the expert's only M tile (uniform).  Only the resident kernels, which run the layers made of such tiles, have
-  // the variants with streaming weight loads: in the per-item kernels they cost six more registers, and those
-  // kernels leave 16 registers per SIMD to the kernels that run beside them in the backward pass.
+  // the variants with streaming weight loads: in the per-item kernels they cost six more registers, which the BESIDE ones
+  // do not have.
   const bool lone = (item.z & kItemLone) != 0;
   const int nblk = (rows + 31) >> 5;                                     // 1..8 blocks of 32 rows
   const int wm = wave >> 2;                                              // wave row
@@ -452,10 +452,16 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_kernel(const GemmAr
 // as the h rows of its M tile are complete, so the CUs that run out of GEMM-1 work (a launch of a few hundred
 // tiles of ~100 us ends with many CUs idle) continue with GEMM-2 instead of waiting for a kernel boundary.
 // moe_fused_forward uses it for bf16 layers whose experts get less than one full M tile of rows on average: the
-// launches are then dominated by partial tiles and, under skewed routing, by the tail of the few large experts
-// (measured 5 % faster than two launches on the DeepSeek-shaped skewed load, 1 % slower on the same shape with
-// uniform routing).  With fuller experts a whole step is 1-3 % slower than with two launches (7-9 % on layers of
-// 0.1-0.2 ms), and the kernel boundary of moe_fused_forward_two_launch is used instead.
+// launches are then dominated by partial tiles and, under skewed routing, by the tail of the few large experts.  With fuller
+// experts the kernel boundary of moe_fused_forward_two_launch is used instead: a line that dates from a hand-over with an L2
+// write-back and an invalidate per item.  Time of the forward call in one launch over two, now, by rows per expert:
+//                                        even load:  50   100   200  |  300   600  2000   skewed:  50   100   200  |  300   600  2000
+//   8 of 64 experts of 2048 x 512                   1.19  1.22  1.19 | 1.07  1.11  1.03           1.14  1.11  1.10 | 1.00  1.02  0.97
+//   16 of 128 experts of 4096 x 1536                1.20  0.97  0.95 | 0.87  0.94  0.97           1.11  0.99  0.86 | 0.90  0.95  0.96
+//   32 of 128 experts of 2880 x 2880                1.06  1.00  0.97 | 0.98  0.99  1.02           1.04  0.96  0.94 | 0.94  1.00  1.00
+//   8 experts of 4096 x 14336                       1.00  0.96  1.00 | 1.01  1.00  1.00           0.95  0.89  0.96 | 0.95  0.98  1.00
+//   32 of 256 experts of 7168 x 2048                1.01  0.92  0.93 | 0.95  0.98  0.98           0.91  0.92  0.93 | 0.93  0.99  0.98
+// i.e. what loses is a launch of less than about 0.1 ms, on either side of the line.
 //
 // Work distribution: both lists are cut into 8 queues exactly as a plain launch would spread them over the XCDs
 // (queue x = virtual blocks x, x + 8, ...; see chunked_item); a workgroup draws tickets from its home queue

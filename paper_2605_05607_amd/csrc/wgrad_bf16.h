@@ -110,8 +110,8 @@ constexpr int kThinSteps = 2;
 constexpr int kThinTiles = 4;  // output tiles per workgroup of wgrad_thin_slab_kernel
 
 // Zero gradients of the local experts without rows: grid (shares, E_loc, 3 matrices), each workgroup clears one
-// contiguous share of `units` 16-byte units.  Few registers and no LDS on purpose: its waves fit beside a GEMM
-// workgroup on the same CU.
+// contiguous share of `units` 16-byte units.  A launch of its own, ahead of the products: run beside them its writers cost the
+// matrix-core workgroups more than they hide.
 __global__ __launch_bounds__(256) void wgrad_zero_empty_kernel(const int32_t *__restrict__ offsets,
                                                                const int32_t *__restrict__ header, int e_lo, u32x4 *c0,
                                                                u32x4 *c1, u32x4 *c2, size_t units) {
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256) void wgrad_zero_empty_kernel(const int32_t *__
   for (size_t u = u0 + threadIdx.x; u < u1; u += 256) __builtin_nontemporal_store(zero, &C[u]);
 }
 
-// The gradients are written once and not read again by this library: all three kernels below store them with the
+// The gradients are written once and not read again by this library: all kernels below store them with the
 // non-temporal hint, so that 0.9 GB of output per product does not push the operands, which every tile of an expert
 // shares, out of the L2s (measured: -9 % of the weight-gradient time on the GPT-OSS-shaped layer, -6.5 % on the
 // Mixtral-shaped one, -9 % on the Qwen3-shaped one, -2 % on the DeepSeek-shaped one).
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(256) void wgrad_zero_empty_kernel(const int32_t *__
 // LDS: two stages of (A 256 x 64, B 256 x 64), rows of 128 bytes with the forward tile's chunk swizzle; main loop of the
 // forward's full tiles (slabs straight into the LDS, wave rows half a step apart) instead of slabs staged through registers
 // with all waves in step.  What bounds it is the short reduction (8 k-steps for 512 rows) between a two-slab prologue and the
-// store of 128 KiB: training step of 8192 tokens on 16 experts of 4096 x 1536 about 1277 -> 1267 us.
+// store of 128 KiB: training step of 8192 tokens on 16 experts of 4096 x 1536, when every size took this form, 1277 -> 1267 us.
 __global__ __launch_bounds__(kGemmThreads, 1) void wgrad_slab_kernel(const WgradArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, w8 = tid >> 6;
