@@ -4,6 +4,7 @@
 // with a single write-back (Combine; the one-GPU form of the in-switch reduction of Sec. II-C).
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <mutex>
 
 #include "backward_kernels.h"
@@ -219,6 +220,57 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
   if (mtiles * dv.nt2 >= kF32Tiles) launch(gemm_f32_kernel<false, 2, 2, 4>, dv.nt2, f32_parts(2, 2), 4, g2);
   else if (mtiles * dv.nt2 >= kF32Tiles / 4) launch(gemm_f32_kernel<false, 1, 2, 4>, dv.nt2, f32_parts(1, 2), 4, g2);
   else launch(gemm_f32_kernel<false, 1, 1, 8>, dv.nt2, f32_parts(1, 1), 8, g2);
+  mark(3);
+  return launch_status();
+}
+
+// fp32 layers of small batches: the kernels without a tile table (gemm_f32_direct_kernel); 32-row blocks per workgroup of
+// GEMM-1, 0 = the tile kernels.  By rows per expert and workgroups of GEMM-1, time of the tile kernels' step / of this one:
+//   up to 24 rows, one block: 1.1 to 1.7 (table at the kernel; 64 tokens on 4 experts of 1024 x 512 33.7 / 31.3 us);
+//   more rows, one block each while that leaves CUs idle: 256 tokens on 4 experts of 1024 x 512 41.4 / 37.9 us (more
+//   workgroups: 64 rows on 4 of 1504 x 1000 54 / 57);
+//   three blocks, 192 to 1024 workgroups in nearly full rounds of one per CU: 256 tokens on 8 of 512 x 1024 1.09, of 2048 x
+//   2048 1.1, 1000 on 4 of 2048 x 2048 1.21, 2048 1.08 (a round and a half: 256 tokens on 4 of 1504 x 1000, k = 4, 139 / 157 us;
+//   short reductions are all prologue and sum: 256 tokens on 16 of 264 x 2000 90 / 101; beyond, the tile kernels' larger
+//   tiles: 2048 tokens on 8 of 512 x 1024 190 / 219).
+static int f32_direct_blocks(const moe_shape *s, const Derived &dv) {
+  const int64_t strips = (int64_t)dv.E_loc * ceil_div(s->f, 32);
+  if (strips > 1 << 14) return 0;
+  const double rows = (double)s->T * s->k / s->E;
+  if (rows <= 24.0 || strips * std::ceil(rows / 32) < 256) return 1;
+  const double wgs = strips * std::ceil(1.1 * rows / 96);
+  return s->d >= 512 && wgs >= 192 && wgs <= 1024 && (wgs <= 256 || wgs >= 0.9 * 256 * std::ceil(wgs / 256)) ? 3 : 0;
+}
+
+static int launch_f32_direct(const moe_shape *s, const Derived &dv, int blocks, const void *x, const float *topk_w,
+                             const moe_dispatch *tb, const void *packed_gu, const void *packed_down, const Ws &w,
+                             hipStream_t st, void *const *events) {
+  auto mark = [&](int i) {
+    if (events && events[i]) (void)hipEventRecord((hipEvent_t)events[i], st);
+  };
+  F32Args g1{};
+  g1.A = static_cast<const float *>(x); g1.W = static_cast<const float *>(packed_gu); g1.out = static_cast<float *>(w.h);
+  g1.offsets = tb->offsets; g1.perm = tb->perm; g1.topk_w = topk_w; g1.error = w.header + 24;
+  g1.T = s->T; g1.k = s->k; g1.e_lo = dv.e_lo; g1.E_loc = dv.E_loc; g1.P_cap = (int)dv.P_cap;
+  g1.K = s->d; g1.N = s->f;
+  F32Args g2 = g1;
+  g2.A = static_cast<const float *>(w.h); g2.W = static_cast<const float *>(packed_down); g2.out = w.o;
+  g2.K = s->f; g2.N = s->d;
+  const double rows = (double)s->T * s->k / s->E;
+  const auto launch = [&](auto kernel, int mb, const F32Args &g) {
+    // (an expert with more rows than its blocks hold takes several turns)
+    const int z = (int)std::min(std::max(1.0, std::ceil((mb == 1 ? 1.25 : 1.1) * rows / (32 * mb))), 64.0);
+    hipLaunchKernelGGL(kernel, dim3(ceil_div(g.N, 32), dv.E_loc, z), dim3(kF32Waves * 64), 0, st, g);
+  };
+  mark(1);
+  // one block: four groups in flight, or two and twice the workgroups per CU where those are many and short
+  if (blocks == 3) launch(gemm_f32_direct_kernel<true, 3, 2, 2>, 3, g1);
+  else if (s->d < 512 && (int64_t)dv.E_loc * ceil_div(s->f, 32) >= 768) launch(gemm_f32_direct_kernel<true, 1, 2, 4>, 1, g1);
+  else launch(gemm_f32_direct_kernel<true, 1, 4, 2>, 1, g1);
+  const int rc = launch_status();
+  mark(2);
+  if (rc != MOE_OK) return rc;
+  launch(gemm_f32_direct_kernel<false, 1, 4, 4>, 1, g2);
   mark(3);
   return launch_status();
 }
@@ -444,6 +496,14 @@ static int forward_common(const moe_shape *shape, const void *x, const int32_t *
   // training forward, which keeps its rows) run the tile kernels
   if (fused && !keep && gemm_launches == 0 && stream_form(shape, dv, fp8 ? 1 : 2))
     return launch_stream(shape, dv, x, topk_w, tables, packed_gate_up, packed_down, w, y, st, events, fp8 ? &q : nullptr);
+  if (const int blocks = fused && shape->dtype == MOE_F32 && gemm_launches == 0 ? f32_direct_blocks(shape, dv) : 0) {
+    if ((rc = launch_f32_direct(shape, dv, blocks, x, topk_w, tables, packed_gate_up, packed_down, w, st, events)) !=
+        MOE_OK)
+      return rc;
+    rc = launch_combine(shape, dv, w.o, topk_idx, tables, y, false, st);
+    mark(4);
+    return rc;
+  }
   if ((rc = launch_prep(shape, dv, tables, topk_idx, topk_w, w, sole, st, with_combine)) != MOE_OK) return rc;
   mark(1);
   if (fused) {

@@ -163,4 +163,166 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_kernel(const GemmArgs g) 
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// The same products where the batch is small: no tile table (an expert's rows come from the dispatch tables), one workgroup of
+// eight waves per (32 columns, local expert, block of 32 MB rows), each wave with an eighth of the reduction range.  What
+// bounds it is the latency of the weight stream, so a wave has D groups of 16 reduction indices in flight: with D = 4 all of a
+// range of 512 at once.  MB = 3: experts of 32 to 96 rows in one pass over their weights; such experts are hardly ever empty, so
+// the weights are requested before the tables have been read.
+// Measured, step, against the kernels above with their tile table: 8 tokens on 8 experts of 512 x 1024 35.7 -> 27.2 us, 32 on 8
+// of 2048 x 2048 178 -> 105 (402 MB of weights), 64 on 16 of 264 x 2000 84 -> 54; MB = 3: 256 tokens on 8 experts of 512 x 1024
+// 57.9 -> 52 us, on 8 of 2048 x 2048 250 -> 222.
+// ------------------------------------------------------------------------------------------------
+struct F32Args {
+  const float *A, *W;  // GEMM-1: x [T, K] and the gate, then the up matrices; GEMM-2: h [rows, K] and the down matrices
+  float *out;          // h [rows, N]; weighted rows o [rows, N]
+  const int32_t *offsets, *perm;
+  const float *topk_w;
+  int32_t *error;      // status word of the workspace (cleared by GEMM-1: no wait can give up here)
+  int T, k, e_lo, E_loc, P_cap, K, N;
+};
+
+constexpr int kF32Waves = 8;
+// OCC: waves per SIMD that the registers are cut for.
+template <bool GATED, int MB, int D, int OCC>
+__global__ __launch_bounds__(kF32Waves * 64, OCC) void gemm_f32_direct_kernel(const F32Args g) {
+  constexpr int NM = GATED ? 2 : 1, G = 16, NW = kF32Waves;
+  constexpr bool EARLY = MB > 1;  // the first weights ahead of the tables
+  __shared__ float red[NW][NM][32][32];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l31 = lane & 31, khalf = lane >> 5;
+  const int n0 = blockIdx.x * 32, le = blockIdx.y;
+  if (GATED && tid == 0 && blockIdx.x == 0 && le == 0 && blockIdx.z == 0) *g.error = 0;
+  const int n_groups = (g.K + G - 1) / G;
+  const int k0 = w * n_groups / NW, n_mine = (w + 1) * n_groups / NW - k0;  // this wave's groups
+  const size_t wsz = (size_t)g.K * g.N;
+  const float *W0 = g.W + (size_t)le * wsz + (size_t)k0 * G * g.N;
+  const int k_len = max(0, min(n_mine * G, g.K - k0 * G)), n_whole = k_len / G;
+  const uint32_t pitch = (uint32_t)g.N * 4;
+  const uint32_t b_off = khalf * (G / 2) * pitch + min(n0 + l31, g.N - 1) * 4;  // (columns past the end: not stored)
+  const float *a_row[MB];
+  F32Group<MB, NM, G, 1> s[D];
+  const std::true_type whole;
+  auto load_b = [&](F32Group<MB, NM, G, 1> &s, int kg, auto whole) {
+    // a descriptor per group: its offsets fit 32 bits whatever the size of the matrix
+    const uint32_t bytes = (uint32_t)min(G, k_len - kg * G) * pitch;
+    rsrc_t b[NM];
+#pragma unroll
+    for (int m = 0; m < NM; ++m) b[m] = stream_rsrc(W0 + m * g.E_loc * wsz + (size_t)kg * G * g.N, bytes);
+#pragma unroll
+    for (int i = 0; i < G / 2; ++i)
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        if constexpr (decltype(whole)::value) {
+          f32_fetch(s.b[m][i], b[m], b_off, (uint32_t)i * pitch);
+        } else {  // indices past K: zeros, from offsets that the descriptor's bound rejects
+          f32_fetch(s.b[m][i], b[m], b_off + (uint32_t)i * pitch, 0);
+        }
+      }
+  };
+  auto load_a = [&](F32Group<MB, NM, G, 1> &s, int kg, auto whole) {
+#pragma unroll
+    for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+      for (int i = 0; i < G / 8; ++i) {
+        const int kk = kg * G + khalf * (G / 2) + i * 4;
+        s.a[mi][i] = *reinterpret_cast<const f32x4 *>(a_row[mi] + (decltype(whole)::value || kk < k_len ? kk : 0));
+        if (!decltype(whole)::value && kk >= k_len) s.a[mi][i] = f32x4{0.f, 0.f, 0.f, 0.f};  // (an infinity times 0)
+      }
+  };
+  if (EARLY) {
+#pragma unroll
+    for (int i = 0; i < D; ++i)
+      if (i < n_whole) load_b(s[i], i, whole);
+  }
+  const int base = g.offsets[g.e_lo];
+  const int start = min(max(g.offsets[g.e_lo + le] - base, 0), g.P_cap);
+  const int rows_all = min(max(g.offsets[g.e_lo + le + 1] - base, 0), g.P_cap) - start;
+  const int z0 = blockIdx.z * MB * 32;
+  for (int m0 = z0; m0 < rows_all; m0 += gridDim.z * MB * 32) {
+    const int rows = min(MB * 32, rows_all - m0), nb = (rows + 31) >> 5;
+#pragma unroll
+    for (int mi = 0; mi < MB; ++mi) {
+      const int r = start + m0 + min(mi * 32 + l31, rows - 1);
+      a_row[mi] = g.A + (size_t)(GATED ? min(max(g.perm[base + r], 0), g.T * g.k - 1) / g.k : r) * g.K + k0 * G;
+    }
+    f32x16 acc[MB][NM];
+    stream_clear(acc);
+    auto load = [&](F32Group<MB, NM, G, 1> &s, int kg, auto whole) {
+      load_b(s, kg, whole);
+      load_a(s, kg, whole);
+    };
+    auto multiply = [&](const F32Group<MB, NM, G, 1> &s) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int mi = 0; mi < MB; ++mi)
+        if (mi < nb) {
+#pragma unroll
+          for (int i = 0; i < G / 2; ++i)
+#pragma unroll
+            for (int m = 0; m < NM; ++m)
+              acc[mi][m] = __builtin_amdgcn_mfma_f32_32x32x2f32(s.a[mi][i >> 2][i & 3], s.b[m][i][0], acc[mi][m], 0, 0, 0);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int i = 0; i < D; ++i)
+      if (i < n_whole) {
+        if (!EARLY || m0 > z0) load_b(s[i], i, whole);
+        load_a(s[i], i, whole);
+      }
+    int kg = 0;
+    for (; kg + 2 * D <= n_whole; kg += D) {
+#pragma unroll
+      for (int i = 0; i < D; ++i) {
+        multiply(s[i]);
+        load(s[i], kg + D + i, whole);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < D; ++i)
+      if (kg + i < n_whole) {
+        multiply(s[i]);
+        if (kg + D + i < n_whole) load(s[i], kg + D + i, whole);
+      }
+#pragma unroll
+    for (int i = 0; i < D - 1; ++i)
+      if (kg + D + i < n_whole) multiply(s[i]);
+    if (n_whole * G < k_len) {
+      load(s[0], n_whole, std::false_type());
+      multiply(s[0]);
+    }
+    // the waves' parts of one 32-row block at a time, in wave order
+#pragma unroll
+    for (int mi = 0; mi < MB; ++mi) {
+      if (mi >= nb) break;  // (uniform)
+      const int live = min(32, rows - mi * 32);
+      if (mi > 0 || m0 > z0) __syncthreads();  // (the block before is done with the LDS)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int rl = (r >> 2) * 8 + khalf * 4 + (r & 3);
+        if (rl < live) {
+#pragma unroll
+          for (int m = 0; m < NM; ++m) red[w][m][rl][l31] = acc[mi][m][r];
+        }
+      }
+      __syncthreads();
+      for (int i = tid; i < live * 32; i += NW * 64) {
+        const int rl = i >> 5, cl = i & 31;
+        float v[NM];
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+          v[m] = 0.f;
+#pragma unroll
+          for (int p = 0; p < NW; ++p) v[m] += red[p][m][rl][cl];
+        }
+        const int row = start + m0 + mi * 32 + rl, col = n0 + cl;
+        if (col >= g.N) continue;
+        g.out[(size_t)row * g.N + col] = GATED ? (v[0] / (1.0f + expf(-v[0]))) * v[NM - 1]
+                                               : v[0] * g.topk_w[min(max(g.perm[base + row], 0), g.T * g.k - 1)];
+      }
+    }
+  }
+}
+
 }  // namespace moe355
