@@ -41,12 +41,13 @@ FwdLayout forward_layout(const moe_shape *s, const Derived &dv) {
   };
   const size_t rows = (size_t)(dv.P_cap > 0 ? dv.P_cap : 1);
   L.header = take(32 * sizeof(int32_t));
+  L.tickets = take(16 * kTicketStride * sizeof(int32_t));
   L.work1 = take((size_t)dv.max_mtiles * dv.nt1 * 4 * sizeof(int32_t));
   L.work2 = take((size_t)dv.max_mtiles * dv.nt2 * 4 * sizeof(int32_t));
   L.row_tok = take(rows * sizeof(int32_t));
   L.row_w = take(rows * sizeof(float));
   L.row_sole = take(rows * sizeof(int32_t));
-  L.tile_ready = take((size_t)dv.max_mtiles * sizeof(int32_t));
+  L.tile_ready = take((size_t)dv.max_mtiles * kReadyStride * sizeof(int32_t));
   L.row_tile = take(rows * sizeof(int32_t));
   L.tile_done = take((size_t)dv.max_mtiles * sizeof(int32_t));
   L.arrived = take((size_t)ceil_div(s->d, 32) * sizeof(int32_t));

@@ -64,17 +64,22 @@ inline bool allow_dynamic_lds(const void *kernel, int bytes, std::atomic<uint64_
   return true;
 }
 
+// Ticket counters of the resident kernels: ints from one to the next.  Each has a line of its own: 256 workgroups draw from
+// eight of them at once, and draws from one line are served one after the other, whichever counter they name.
+constexpr int kTicketStride = 64;
+constexpr int kReadyStride = 32;  // the same for the counters of finished GEMM-1 items
+
 // ---- layout of the forward workspace (offsets in bytes, 256-byte aligned) ----
 struct FwdLayout {
   size_t header;    // int32[32]: [0] work items of GEMM-1, [1] P, [2] first layout row of the local segment,
-                    //            [3] work items of GEMM-2, [4] M tiles, [8..23] queue tickets and [24] error flag
-                    //            of the resident GEMM kernel
+                    //            [3] work items of GEMM-2, [4] M tiles, [24] error flag of the resident GEMM kernel
+  size_t tickets;   // int32[16 * kTicketStride]: ticket counters of the resident kernel's queues, GEMM-1, then GEMM-2
   size_t work1;     // int4[max_mtiles * nt1]  (local expert, first local row, valid rows, N tile) per work item
   size_t work2;     // int4[max_mtiles * nt2]
   size_t row_tok;   // int32[P_cap]       token of each local row
   size_t row_w;     // float[P_cap]       gate weight of each local row
   size_t row_sole;  // int32[P_cap]       the row's token if it is that token's only local slot, else -1
-  size_t tile_ready;  // int32[max_mtiles] GEMM-1 items finished per M tile (hand-over inside the resident kernel)
+  size_t tile_ready;  // int32[max_mtiles * kReadyStride] GEMM-1 items finished per M tile (hand-over inside the resident kernel)
   size_t row_tile;    // int32[P_cap]      M tile of each local row        } resident kernel that also runs
   size_t tile_done;   // int32[max_mtiles] GEMM-2 items finished per M tile } Combine
   size_t arrived;   // int32[ceil(d / 32)] small batches: work groups of a strip of GEMM-2 that have stored their sums

@@ -23,7 +23,7 @@ namespace moe355 {
 // Host-side launch helpers
 // ------------------------------------------------------------------------------------------------
 struct Ws {
-  int32_t *header, *row_tok, *row_sole, *tile_ready, *row_tile, *tile_done, *arrived;
+  int32_t *header, *tickets, *row_tok, *row_sole, *tile_ready, *row_tile, *tile_done, *arrived;
   int4 *work1, *work2;
   float *row_w;
   void *h;
@@ -34,6 +34,7 @@ static Ws carve(void *workspace, const FwdLayout &L) {
   unsigned char *b = static_cast<unsigned char *>(workspace);
   Ws w;
   w.header = reinterpret_cast<int32_t *>(b + L.header);
+  w.tickets = reinterpret_cast<int32_t *>(b + L.tickets);
   w.work1 = reinterpret_cast<int4 *>(b + L.work1);
   w.work2 = reinterpret_cast<int4 *>(b + L.work2);
   w.row_tok = reinterpret_cast<int32_t *>(b + L.row_tok);
@@ -64,7 +65,7 @@ static int launch_prep(const moe_shape *s, const Derived &dv, const moe_dispatch
   const int blocks = (int)std::min<int64_t>(512, std::max<int64_t>(1, (dv.P_cap + 255) / 256));
   hipLaunchKernelGGL(fwd_prep_kernel, dim3(2 * blocks), dim3(256), prep_lds_bytes(dv, combine_tables), st,
                      tb->offsets, tb->perm, topk_w, s->T, s->k, dv.e_lo, dv.E_loc, dv.bm, (int)dv.P_cap, dv.max_mtiles,
-                     dv.nt1, dv.nt2, blocks, w.header, w.work1, w.work2, w.row_tok, w.row_w, topk_idx, sole, w.tile_ready,
+                     dv.nt1, dv.nt2, blocks, w.header, w.tickets, w.work1, w.work2, w.row_tok, w.row_w, topk_idx, sole, w.tile_ready,
                      combine_tables ? w.row_tile : nullptr, combine_tables ? w.tile_done : nullptr);
   return launch_status();
 }
@@ -166,7 +167,7 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
     if (pipelined) {
       PipelineArgs pa{};
       pa.g1 = g1; pa.g2 = g2;
-      pa.tickets = w.header + 8; pa.tile_ready = w.tile_ready; pa.error = w.header + 24; pa.nt1 = dv.nt1 + wait_extra;
+      pa.tickets = w.tickets; pa.tile_ready = w.tile_ready; pa.error = w.header + 24; pa.nt1 = dv.nt1 + wait_extra;
       pa.max_polls = max_polls;
       const bool far = far1 || far2;
 #define MOE355_RESIDENT(KERNEL_) (far ? launch_resident<KERNEL_<true>>(pa, st) : launch_resident<KERNEL_<false>>(pa, st))
@@ -726,12 +727,13 @@ static BwdLayout backward_layout(const moe_shape *s, const Derived &dvb) {
   };
   const size_t rows = (size_t)(dvb.P_cap > 0 ? dvb.P_cap : 1);
   L.t.header = take(32 * sizeof(int32_t));
+  L.t.tickets = take(16 * kTicketStride * sizeof(int32_t));
   L.t.work1 = take((size_t)dvb.max_mtiles * dvb.nt1 * 4 * sizeof(int32_t));
   L.t.work2 = take((size_t)dvb.max_mtiles * dvb.nt2 * 4 * sizeof(int32_t));
   L.t.row_tok = take(rows * sizeof(int32_t));
   L.t.row_w = take(rows * sizeof(float));
   L.t.row_sole = take(rows * sizeof(int32_t));
-  L.t.tile_ready = take((size_t)dvb.max_mtiles * sizeof(int32_t));
+  L.t.tile_ready = take((size_t)dvb.max_mtiles * kReadyStride * sizeof(int32_t));
   L.t.row_tile = L.t.tile_done = L.t.arrived = 0;  // forward only
   L.t.h = L.t.o = 0;
   L.dgu = take(rows * 2 * (size_t)s->f * 2);

@@ -131,7 +131,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
   // RESIDENT: the ticket of this workgroup's next item is drawn now, by thread 0, so that the atomic's round trip
   // runs under the epilogue instead of in front of the next item; the value is parked in the LDS at the very end.
   int pre_v = -1;
-  if (RESIDENT && first_thread(wave)) pre_v = atomicAdd(&tickets[(blockIdx.x + pre[1]) & 7], 1);
+  if (RESIDENT && first_thread(wave)) pre_v = atomicAdd(&tickets[((blockIdx.x + pre[1]) & 7) * kTicketStride], 1);
   unsigned char *patch = smem + w8 * kPatchBytes;
   // GEMM-2: the gate weights and the sole-slot marks of this wave's 128 rows come in once, coalesced, and wait in the
   // LDS behind the patches (1 KiB per wave), instead of 24 scattered loads in front of every 32-row block
@@ -480,7 +480,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_kernel(const GemmAr
 // ------------------------------------------------------------------------------------------------
 struct PipelineArgs {
   GemmArgs g1, g2;
-  int32_t *tickets;     // [16]: queues of GEMM-1, then of GEMM-2
+  int32_t *tickets;     // [16] x kTicketStride: queues of GEMM-1, then of GEMM-2
   int32_t *tile_ready;  // [M tiles] GEMM-1 items finished per M tile
   int32_t *error;       // set if a wait gave up (cannot happen unless the lists are corrupt)
   int nt1;              // GEMM-1 items per M tile a GEMM-2 item waits for
@@ -514,7 +514,7 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
     int q = -1, pre = s_item[2], qsel = s_item[3];
     while (qsel < 8) {
       const int queue = (home + qsel) & 7;
-      const int v = queue + 8 * (pre >= 0 ? pre : atomicAdd(&tickets[queue], 1));
+      const int v = queue + 8 * (pre >= 0 ? pre : atomicAdd(&tickets[queue * kTicketStride], 1));
       pre = -1;
       if (v < n_virtual) {
         if ((q = chunked_item(v, n_items)) >= 0) break;
@@ -525,7 +525,7 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
       unsigned open_queues = 0;  // bit i: queue i still has positions
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int t = __hip_atomic_load(&tickets[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int t = __hip_atomic_load(&tickets[i * kTicketStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         open_queues |= (unsigned)(i + 8 * t < n_virtual) << i;
       }
       int next = 8;
@@ -590,7 +590,7 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
           __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
           __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
         }
-        __hip_atomic_fetch_add(&tile_ready[tile], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ... then counted
+        __hip_atomic_fetch_add(&tile_ready[(size_t)tile * kReadyStride], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ... then counted
       }
     } else {
       // Acquire side: thread 0 polls with relaxed device-scope loads; the barrier hands the result to the workgroup.  A wait
@@ -599,7 +599,7 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
       // result.
       if (first_thread(wave)) {
         int polls = 0, gave_up = 0;
-        while (__hip_atomic_load(&tile_ready[tile], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < nt1) {
+        while (__hip_atomic_load(&tile_ready[(size_t)tile * kReadyStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < nt1) {
           __builtin_amdgcn_s_sleep(32);
           if (++polls > max_polls) {
             __hip_atomic_store(error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -679,7 +679,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_pipeline_kernel(con
   __shared__ int s_item[4];  // (see gemm_bf16_drain)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   gemm_bf16_drain<true, false, false, FAR>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
-  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8 * kTicketStride, p.tile_ready, p.error, p.nt1, p.max_polls);
 }
 
 // The resident kernel with Combine as its third stage: the whole layer after the tile table in one launch.
@@ -690,7 +690,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_combine_kernel(cons
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   gemm_bf16_drain<true, false, false, FAR>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
   __shared__ int s_done[kDoneCap];
-  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls, p.tile_done,
+  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8 * kTicketStride, p.tile_ready, p.error, p.nt1, p.max_polls, p.tile_done,
                          s_done);
   resident_combine(p, wave);
 }
@@ -702,7 +702,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_train_pipeline_kernel(co
   __shared__ int s_item[4];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   gemm_bf16_drain<true, false, true, FAR>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
-  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8 * kTicketStride, p.tile_ready, p.error, p.nt1, p.max_polls);
 }
 
 // The same resident kernel on E4M3 operands (whose rows number less than 2^32 elements, i.e. bytes).
@@ -711,7 +711,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp8_pipeline_kernel(cons
   __shared__ int s_item[4];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   gemm_bf16_drain<true, true, false, false>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
-  gemm_bf16_drain<false, true, false, false>(p.g2, smem, s_item, wave, p.tickets + 8, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<false, true, false, false>(p.g2, smem, s_item, wave, p.tickets + 8 * kTicketStride, p.tile_ready, p.error, p.nt1, p.max_polls);
 }
 
 }  // namespace moe355

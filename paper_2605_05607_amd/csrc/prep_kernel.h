@@ -7,8 +7,8 @@ namespace moe355 {
 // ------------------------------------------------------------------------------------------------
 // Work lists and per-row metadata of the local layout segment.
 // header[0] = work items of GEMM-1, header[1] = P (local rows), header[2] = first layout row of the segment,
-// header[3] = work items of GEMM-2, header[4] = M tiles; header[8..15] / [16..23] = ticket counters of the GEMM-1 /
-// GEMM-2 queues and header[24] = error flag of the resident GEMM kernel (all cleared here).  row_tile / tile_done
+// header[3] = work items of GEMM-2, header[4] = M tiles; header[24] = error flag of the resident GEMM kernel
+// and tickets[0 .. 7] / [8 .. 15] x kTicketStride = ticket counters of its GEMM-1 / GEMM-2 queues (all cleared here).  row_tile / tile_done
 // (both may be null): M tile of every local row and the per-tile counter of finished GEMM-2 items, for the resident
 // kernel that also runs Combine.
 //
@@ -39,6 +39,7 @@ __global__ __launch_bounds__(256) void fwd_prep_kernel(const int32_t *__restrict
                                                        const float *__restrict__ topk_w, int T, int k, int e_lo,
                                                        int E_loc, int bm, int P_cap, int max_mtiles, int nt1, int nt2,
                                                        int list_blocks, int32_t *__restrict__ header,
+                                                       int32_t *__restrict__ tickets,
                                                        int4 *__restrict__ work1, int4 *__restrict__ work2,
                                                        int32_t *__restrict__ row_tok, float *__restrict__ row_w,
                                                        const int32_t *__restrict__ topk_idx,
@@ -136,10 +137,11 @@ __global__ __launch_bounds__(256) void fwd_prep_kernel(const int32_t *__restrict
     header[2] = base;
     header[3] = n2;
     header[4] = n_tiles;
-    for (int i = 8; i <= 24; ++i) header[i] = 0;
+    header[24] = 0;
   }
+  if (me < 16) tickets[me * kTicketStride] = 0;
   for (int i = me; i < n_tiles; i += nthr) {
-    tile_ready[i] = 0;
+    tile_ready[(size_t)i * kReadyStride] = 0;
     if (tile_done) tile_done[i] = 0;
   }
   // M tile of every local row (the resident kernel's Combine stage looks up the tile whose GEMM-2 items it waits for)
