@@ -182,10 +182,11 @@ MOE355_API int moe_pack_weights(const moe_shape *shape, const void *W_gate, cons
  * topk_w[t,j] * FFN_{e(t,j)}(x[t]); rows of tokens without a local slot are written as zeros.
  * Token rows are gathered straight into the GEMM-1 tiles (no dispatched copy of x is materialised);
  * each y row is written exactly once, without atomics.  When moe_forward_gemm_launches(shape) is 1 (bf16 layers
- * with fewer than 256 rows per expert on average, T*k < 256*E), GEMM-1 and GEMM-2 run in ONE launch of resident
- * workgroups: a GEMM-2 tile starts as soon as the h rows of its 256-row tile are complete (per-tile readiness
- * counters in the workspace), the one-GPU form of the tile-granular GEMM-1 => GEMM-2 hand-over of the fused
- * kernel (Sec. IV-A, IV-B); otherwise the two GEMMs are two launches.  The result is the same either way.
+ * with fewer than 256 rows per expert on average, T*k < 256*E, or whose GEMMs take more than about 60 us), GEMM-1 and
+ * GEMM-2 run in ONE launch of resident workgroups: a GEMM-2 tile starts as soon as the h rows of its 256-row tile are
+ * complete (per-tile readiness counters in the workspace), the one-GPU form of the tile-granular GEMM-1 => GEMM-2
+ * hand-over of the fused kernel (Sec. IV-A, IV-B); otherwise the two GEMMs are two launches.  The result is the same
+ * either way.
  * Small batches run two weight-streaming kernels instead (and sometimes a third that adds their partial sums), which
  * need no tile table and no separate Combine: bf16 layers with T <= 128, d and f >= 512 and few rows per expert (at most
  * 12 on average), or more of them where all local weights together are at most 128 MB and, beyond 64 tokens, the

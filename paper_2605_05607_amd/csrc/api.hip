@@ -72,14 +72,25 @@ extern "C" size_t moe_workspace_bytes(const moe_shape *shape) {
   return std::max(moe_dispatch_workspace_bytes(shape), moe_forward_workspace_bytes(shape));
 }
 
-int moe355::tile_gemm_launches(const moe_shape *shape) {
-  return shape->dtype == MOE_BF16 && (int64_t)shape->T * shape->k < (int64_t)shape->E * kBM ? 1 : 2;
+// With fuller experts by the time both GEMMs take, estimated from their flops: below about 60 us (time of the forward call in
+// one launch over two: 8 experts of 2048 x 512 with 300 and 1000 rows each 1.05 and 1.01) what a workgroup pays for its queues
+// and the hand-over is more than the kernel boundary, beyond it one launch is level or up to 13 % faster (table at
+// gemm_bf16_pipeline_kernel).  Not for matrices of 4 GiB and more, whose hand-over writes back and invalidates L2s.
+int moe355::tile_gemm_launches(const moe_shape *shape, int elt) {
+  if (shape->dtype != MOE_BF16) return 2;
+  if ((int64_t)shape->T * shape->k < (int64_t)shape->E * kBM) return 1;
+  Derived dv;
+  if (check_shape(shape, &dv) != MOE_OK) return 2;
+  const int64_t widest = std::max(shape->T * (int64_t)shape->d, dv.P_cap * (int64_t)h_pitch(shape, elt)) * elt;
+  if (widest >= (int64_t)1 << 32) return 2;
+  const double flops = 6.0 * shape->T * shape->k * dv.E_loc / shape->E * shape->d * shape->f;
+  return flops >= 60e-6 * (elt == 1 ? 1.8e15 : 1.1e15) ? 1 : 2;
 }
 
 extern "C" int moe_forward_gemm_launches(const moe_shape *shape) {
   Derived dv;
   if (check_shape(shape, &dv) != MOE_OK) return 0;
-  return stream_form(shape, dv, 2) ? 2 : tile_gemm_launches(shape);
+  return stream_form(shape, dv, 2) ? 2 : tile_gemm_launches(shape, 2);
 }
 
 extern "C" size_t moe_unfused_workspace_bytes(const moe_shape *shape) {

@@ -42,9 +42,10 @@ int check_shape(const moe_shape *s, Derived *out);
 
 // Forms of the forward pass.  stream_form: a small batch runs the weight-streaming kernels (elt: bytes of a weight).
 // tile_gemm_launches, for the others: 1 = one resident launch with the tile-level hand-over, where the mean number of
-// rows per expert, T k / E, is below one M tile; 2 = a kernel boundary between the GEMMs (always for fp32 layers).
+// rows per expert, T k / E, is below one M tile or the launch takes long enough; 2 = a kernel boundary between the GEMMs
+// (always for fp32 layers).
 bool stream_form(const moe_shape *s, const Derived &dv, int elt);
-int tile_gemm_launches(const moe_shape *s);
+int tile_gemm_launches(const moe_shape *s, int elt);
 
 // hipGetLastError() reports (and clears) the last error of ANY earlier runtime call on this thread, including
 // the caller's own; every entry point therefore drops a stale error before its first launch and reads the

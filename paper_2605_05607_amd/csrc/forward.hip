@@ -452,7 +452,7 @@ static int forward_common(const moe_shape *shape, const void *x, const int32_t *
   const bool with_combine = gemm_launches == 3;
   if (with_combine && (!fused || fp8 || keep)) return MOE_ERR_UNSUPPORTED;
   if (with_combine && dv.E_loc > 4091) return MOE_ERR_UNSUPPORTED;  // (documented bound of this form)
-  const bool pipelined = with_combine || (gemm_launches ? gemm_launches : tile_gemm_launches(shape)) == 1;
+  const bool pipelined = with_combine || (gemm_launches ? gemm_launches : tile_gemm_launches(shape, fp8 ? 1 : 2)) == 1;
   // a work item packs its N tile and its M-tile id into one word
   if (std::max(dv.nt1, dv.nt2) >= 1 << kTileShift || dv.max_mtiles >= 1 << (31 - kTileShift)) return MOE_ERR_UNSUPPORTED;
   // the GEMM kernels address A rows with 32-bit element offsets (row * row length)

@@ -453,15 +453,17 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_kernel(const GemmAr
 // tiles of ~100 us ends with many CUs idle) continue with GEMM-2 instead of waiting for a kernel boundary.
 // moe_fused_forward uses it for bf16 layers whose experts get less than one full M tile of rows on average: the
 // launches are then dominated by partial tiles and, under skewed routing, by the tail of the few large experts.  With fuller
-// experts the kernel boundary of moe_fused_forward_two_launch is used instead: a line that dates from a hand-over with an L2
-// write-back and an invalidate per item.  Time of the forward call in one launch over two, now, by rows per expert:
+// experts it depends on the time the launch takes (tile_gemm_launches).  Time of the forward call in one launch over two, by
+// rows per expert:
 //                                        even load:  50   100   200  |  300   600  2000   skewed:  50   100   200  |  300   600  2000
-//   8 of 64 experts of 2048 x 512                   1.19  1.22  1.19 | 1.07  1.11  1.03           1.14  1.11  1.10 | 1.00  1.02  0.97
-//   16 of 128 experts of 4096 x 1536                1.20  0.97  0.95 | 0.87  0.94  0.97           1.11  0.99  0.86 | 0.90  0.95  0.96
-//   32 of 128 experts of 2880 x 2880                1.06  1.00  0.97 | 0.98  0.99  1.02           1.04  0.96  0.94 | 0.94  1.00  1.00
-//   8 experts of 4096 x 14336                       1.00  0.96  1.00 | 1.01  1.00  1.00           0.95  0.89  0.96 | 0.95  0.98  1.00
-//   32 of 256 experts of 7168 x 2048                1.01  0.92  0.93 | 0.95  0.98  0.98           0.91  0.92  0.93 | 0.93  0.99  0.98
-// i.e. what loses is a launch of less than about 0.1 ms, on either side of the line.
+//   8 of 64 experts of 2048 x 512                   1.10  1.15  1.15 | 1.05  1.05  0.95           1.07  1.08  1.06 | 0.97  0.99  0.98
+//   16 of 128 experts of 4096 x 1536                1.03  0.92  0.90 | 0.88  0.94  0.97           1.03  0.97  0.84 | 0.88  0.93  0.96
+//   32 of 128 experts of 2880 x 2880                1.00  0.94  0.97 | 0.97  0.99  1.00           1.03  0.95  0.93 | 0.92  0.99  1.01
+//   8 experts of 4096 x 14336                       0.98  0.93  0.99 | 0.99  1.01  1.00           0.93  0.90  0.95 | 0.95  0.98  0.99
+//   32 of 256 experts of 7168 x 2048                1.00  0.91  0.95 | 0.93  0.99  0.99           0.89  0.91  0.93 | 0.94  0.97  0.98
+// and the same for FP8 and for the training forward.  What it owes to counters on lines of their own (kTicketStride,
+// kReadyStride): 4096 FP8 tokens on 32 of 256 experts of 7168 x 2048 391 -> 352 us, 5003 tokens on 32 experts of 2880 x 2880
+// 380 -> 362.
 //
 // Work distribution: both lists are cut into 8 queues exactly as a plain launch would spread them over the XCDs
 // (queue x = virtual blocks x, x + 8, ...; see chunked_item); a workgroup draws tickets from its home queue
