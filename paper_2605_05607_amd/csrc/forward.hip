@@ -749,6 +749,22 @@ static BwdLayout backward_layout(const moe_shape *s, const Derived &dvb) {
   return L;
 }
 
+// The two backward GEMMs as one resident launch.  Time of the backward pass without weight gradients in one launch over two, by
+// rows per expert (even load / skewed):
+//                                     8 to 50              90           200 to 400   500          750   2000
+//   8 of 64 experts of 2048 x 512     1.10 / 1.12          1.10 / 1.07                            1.05  -
+//   16 of 128 of 4096 x 1536          1.00-1.07 / 1.0-1.15 0.91 / 0.89  0.94 / 0.91  1.00 / 0.96  -     -
+//   32 of 128 of 2880 x 2880          0.95 / 1.0-1.15      0.89 / 0.88  0.90 / 1.0   -            -     -
+//   8 of 4096 x 14336                 1.00 / 0.91          0.97 / 0.90  0.89 / 1.03  -            1.04  1.02
+//   32 of 256 of 7168 x 2048          1.0 / 0.86-1.16      0.96 / 0.98  0.90 / 0.97  -            -     -
+// i.e. it pays from some 64 rows, where a skewed load leaves few experts busy below that, to 600, where the rows of [dg | du]
+// past the L2s cost more than the last round of the first GEMM, and in launches of 0.1 ms and more (estimated from the weights'
+// bytes and from the flops).
+static bool backward_one_launch(const moe_shape *s, const Derived &dv) {
+  const double rows = (double)s->T * s->k / s->E, work = 3.0 * dv.E_loc * s->d * s->f;
+  return rows >= 64 && rows < 600 && std::max(work * 2 / 6e12, 2 * rows * work / 1.1e15) >= 100e-6;
+}
+
 static bool backward_supported(const moe_shape *s) { return s->dtype == MOE_BF16 && s->f % kBK == 0; }
 
 }  // namespace moe355
@@ -947,9 +963,13 @@ static int backward_common(const moe_shape *shape, const void *x, const void *dy
   g1.K = shape->d; g1.N = shape->f; g1.lda = shape->d; g1.ldo = 2 * shape->f;
   g1.n_ntiles = dvb.nt1; g1.n_ktiles = ceil_div(shape->d, kBK);
   const bool far1 = (int64_t)shape->T * shape->d * 2 >= (int64_t)1 << 32;
-  rc = side ? launch_items<false, false, true, true>(g1, far1, grid_of(dvb.nt1), st)
-            : launch_items<false, false, true, false>(g1, far1, grid_of(dvb.nt1), st);
-  if (rc != MOE_OK) return join(rc);
+  const bool far2 = dv.P_cap * 2 * shape->f * 2 >= (int64_t)1 << 32;
+  const bool one_launch = !side && !far1 && !far2 && backward_one_launch(shape, dv);
+  if (!one_launch) {
+    rc = side ? launch_items<false, false, true, true>(g1, far1, grid_of(dvb.nt1), st)
+              : launch_items<false, false, true, false>(g1, far1, grid_of(dvb.nt1), st);
+    if (rc != MOE_OK) return join(rc);
+  }
   if (side) {  // dg, du and w h are there: their transposes run beside the second GEMM
     if (hipEventRecord(side->mid, st) != hipSuccess || hipStreamWaitEvent(side->stream, side->mid, 0) != hipSuccess)
       return join(MOE_ERR_HIP);
@@ -964,9 +984,15 @@ static int backward_common(const moe_shape *shape, const void *x, const void *dy
   g2.n_items = w.header + 3; g2.work = w.work2;
   g2.K = 2 * shape->f; g2.N = shape->d; g2.lda = 2 * shape->f; g2.ldo = shape->d;
   g2.n_ntiles = dvb.nt2; g2.n_ktiles = 2 * (shape->f / kBK);
-  const bool far2 = dv.P_cap * 2 * shape->f * 2 >= (int64_t)1 << 32;
-  rc = side ? launch_items<false, false, false, true>(g2, far2, grid_of(dvb.nt2), st)
-            : launch_items<false, false, false, false>(g2, far2, grid_of(dvb.nt2), st);
+  if (one_launch) {
+    PipelineArgs pa{};
+    pa.g1 = g1; pa.g2 = g2;
+    pa.tickets = w.tickets; pa.tile_ready = w.tile_ready; pa.error = w.header + 24; pa.nt1 = dvb.nt1; pa.max_polls = kMaxPolls;
+    rc = launch_resident<gemm_backward_pipeline_kernel>(pa, st);
+  } else {
+    rc = side ? launch_items<false, false, false, true>(g2, far2, grid_of(dvb.nt2), st)
+              : launch_items<false, false, false, false>(g2, far2, grid_of(dvb.nt2), st);
+  }
   if (rc != MOE_OK) return join(rc);
   if ((rc = launch_combine(shape, dv, dxr, topk_idx, tables, dx, true, st)) != MOE_OK || !wgrad) return join(rc);
   if ((rc = join(MOE_OK)) != MOE_OK) return rc;

@@ -37,11 +37,12 @@ constexpr int kGemmLds = 3 * (kBM / 2 * kBK * 2 + kTileBytes);  // 144 KiB: the 
 constexpr int kGemmLdsBeside = 2 * 65536;  // the same with a ring of two stages there: the two stages of the full tiles
 constexpr int kPatchBytes = 32 * 288;                     // per-wave epilogue patch (fits 8 x in the stages)
 
-// Eight bytes of h, past the L2 of this XCD (a relaxed store of device scope): visible to the other XCDs as soon as it is
-// acknowledged.
-__device__ __forceinline__ void store_h_through(void *at, const unsigned char *from) {
-  __hip_atomic_store(static_cast<uint64_t *>(at), *reinterpret_cast<const uint64_t *>(from), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_AGENT);
+// Sixteen bytes past the L2 of this XCD, at a byte offset from `base` (a store of device scope, sc1): visible to the other
+// XCDs as soon as it is acknowledged.
+constexpr int kDeviceScope = 16;  // the sc1 bit in the cache policy of a buffer instruction
+__device__ __forceinline__ void store_through(void *base, uint32_t at, const unsigned char *from) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(base, 0, 0xFFFFFFFFu, 0x00027000);
+  __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4 *>(from), r, at, 0, kDeviceScope);
 }
 
 __device__ __forceinline__ bool first_thread(int wave) { return wave == 0 && fresh_lane() == 0; }
@@ -263,8 +264,14 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
         const int row_l = blk_row0 + rl, col = col0 + cc * 8;
         if (row_l < rows && col < g.N) {
           bf16_t *dst = dgu + (size_t)(m0 + row_l) * 2 * g.N + col;
-          *reinterpret_cast<u32x4 *>(dst) = *reinterpret_cast<const u32x4 *>(blk + rl * 144 + cc * 16);
-          *reinterpret_cast<u32x4 *>(dst + g.N) = *reinterpret_cast<const u32x4 *>(blk + 4608 + rl * 144 + cc * 16);
+          if (RESIDENT && !FAR) {  // other workgroups' second GEMM reads them in this launch
+            const uint32_t at = ((uint32_t)(m0 + row_l) * 2 * g.N + col) * 2;
+            store_through(dgu, at, blk + rl * 144 + cc * 16);
+            store_through(dgu, at + g.N * 2, blk + 4608 + rl * 144 + cc * 16);
+          } else {
+            *reinterpret_cast<u32x4 *>(dst) = *reinterpret_cast<const u32x4 *>(blk + rl * 144 + cc * 16);
+            *reinterpret_cast<u32x4 *>(dst + g.N) = *reinterpret_cast<const u32x4 *>(blk + 4608 + rl * 144 + cc * 16);
+          }
           *reinterpret_cast<u32x4 *>(hw + (size_t)(m0 + row_l) * g.N + col) =
               *reinterpret_cast<const u32x4 *>(blk + 9216 + rl * 144 + cc * 16);
         }
@@ -286,21 +293,16 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      if constexpr (RESIDENT) {
-#pragma unroll
-        for (int it = 0; it < 2; ++it) {
-          const int c = it * 64 + fresh_lane(), rl = c >> 2, cc = c & 3;  // 8-byte chunk: 4 chunks per row
-          const int row_l = blk_row0 + rl, col = nt * (kBN / 2) + wn * 32 + cc * 8;
-          if (row_l < rows && col < g.N)
-            store_h_through(static_cast<uint8_t *>(g.out) + (size_t)(m0 + row_l) * g.ldo + col, patch + rl * 48 + cc * 8);
-        }
-      } else {
-        const int rl = lane >> 1, cc = lane & 1;  // 16-byte chunk: 2 chunks per row
-        const int row_l = blk_row0 + rl;
-        const int col = nt * (kBN / 2) + wn * 32 + cc * 16;
-        const u32x4 v = *reinterpret_cast<const u32x4 *>(patch + rl * 48 + cc * 16);
-        if (row_l < rows && col < g.N)
-          *reinterpret_cast<u32x4 *>(static_cast<uint8_t *>(g.out) + (size_t)(m0 + row_l) * g.ldo + col) = v;
+      const int ln = RESIDENT ? fresh_lane() : lane;
+      const int rl = ln >> 1, cc = ln & 1;  // 16-byte chunk: 2 chunks per row
+      const int row_l = blk_row0 + rl;
+      const int col = nt * (kBN / 2) + wn * 32 + cc * 16;
+      if (row_l < rows && col < g.N) {
+        if (RESIDENT)
+          store_through(g.out, (uint32_t)(m0 + row_l) * g.ldo + col, patch + rl * 48 + cc * 16);
+        else
+          *reinterpret_cast<u32x4 *>(static_cast<uint8_t *>(g.out) + (size_t)(m0 + row_l) * g.ldo + col) =
+              *reinterpret_cast<const u32x4 *>(patch + rl * 48 + cc * 16);
       }
     } else if (GATED) {
       // h block: 32 rows x 32 columns bf16, row pitch 80 bytes (keeps the two half-waves on different banks);
@@ -320,23 +322,16 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      if constexpr (RESIDENT && !FAR) {
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
-          const int c = it * 64 + fresh_lane(), rl = c >> 3, cc = c & 7;  // 8-byte chunk: 8 chunks per row
-          const int row_l = blk_row0 + rl, col = nt * (kBN / 2) + wn * 32 + cc * 4;
-          if (row_l < rows && col < g.N)
-            store_h_through(static_cast<bf16_t *>(g.out) + (size_t)(m0 + row_l) * g.ldo + col, patch + rl * 80 + cc * 8);
-        }
-      }
-#pragma unroll
-      for (int it = 0; it < (RESIDENT && !FAR && !TRAIN ? 0 : 2); ++it) {
-        const int c = it * 64 + lane;        // 16-byte chunk: 4 chunks per row
+      for (int it = 0; it < 2; ++it) {
+        const int c = it * 64 + (RESIDENT ? fresh_lane() : lane);  // 16-byte chunk: 4 chunks per row
         const int rl = c >> 2, cc = c & 3;
         const int row_l = blk_row0 + rl;
         const int col = nt * (kBN / 2) + wn * 32 + cc * 8;
         if (row_l < rows && col < g.N) {
-          if (!RESIDENT || FAR)
+          if (RESIDENT && !FAR)
+            store_through(g.out, ((uint32_t)(m0 + row_l) * g.ldo + col) * 2, patch + rl * 80 + cc * 16);
+          else
             *reinterpret_cast<u32x4 *>(static_cast<bf16_t *>(g.out) + (size_t)(m0 + row_l) * g.ldo + col) =
                 *reinterpret_cast<const u32x4 *>(patch + rl * 80 + cc * 16);
           if (TRAIN) {
@@ -500,7 +495,8 @@ constexpr int kMaxPolls = 1 << 22;  // default bound: several seconds
 // tile_done (GEMM-2 only, may be null): counter per M tile that every finished item of the tile is counted in, for
 // the Combine stage that follows in the same launch; s_done: kDoneCap ints of LDS (tiles of the finished items).
 constexpr int kDoneCap = 256;
-template <bool GATED, bool FP8, bool TRAIN, bool FAR>
+// FIRST: the GEMM whose items are counted (else: the one that waits for them).
+template <bool FIRST, bool GATED, bool FP8, bool TRAIN, bool FAR>
 __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char *smem, int *s_item, int wave,
                                                 int32_t *__restrict__ tickets, int32_t *__restrict__ tile_ready,
                                                 int32_t *__restrict__ error, int nt1, int max_polls,
@@ -578,10 +574,10 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
     item.z = __builtin_amdgcn_readfirstlane(item.z);
     item.w = __builtin_amdgcn_readfirstlane(item.w);
     const int tile = item.w >> kTileShift;
-    if (GATED) {
-      gemm_bf16_item<true, true, FP8, TRAIN, FAR, false>(g, smem, item, wave, 0, tickets, s_item + 2);
+    if (FIRST) {
+      gemm_bf16_item<GATED, true, FP8, TRAIN, FAR, false>(g, smem, item, wave, 0, tickets, s_item + 2);
       // Release side of the hand-over.  Every wave waits until its own h stores have been acknowledged (a workgroup
-      // barrier alone does not wait for global stores); they went past the L2 (store_h_through), so there is nothing to write back.
+      // barrier alone does not wait for global stores); they went past the L2 (store_through), so there is nothing to write back.
       __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
       __syncthreads();  // every thread's h stores happen before thread 0's count
       if (first_thread(wave)) {
@@ -628,7 +624,7 @@ __device__ __forceinline__ void gemm_bf16_drain(const GemmArgs &g, unsigned char
       }
     }
   }
-  if (!GATED && tile_done) flush_done();
+  if (!FIRST && tile_done) flush_done();
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -680,8 +676,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_pipeline_kernel(con
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds
   __shared__ int s_item[4];  // (see gemm_bf16_drain)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  gemm_bf16_drain<true, false, false, FAR>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
-  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8 * kTicketStride, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<true, true, false, false, FAR>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<false, false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8 * kTicketStride, p.tile_ready, p.error, p.nt1, p.max_polls);
 }
 
 // The resident kernel with Combine as its third stage: the whole layer after the tile table in one launch.
@@ -690,9 +686,9 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_combine_kernel(cons
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds
   __shared__ int s_item[4];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  gemm_bf16_drain<true, false, false, FAR>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<true, true, false, false, FAR>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
   __shared__ int s_done[kDoneCap];
-  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8 * kTicketStride, p.tile_ready, p.error, p.nt1, p.max_polls, p.tile_done,
+  gemm_bf16_drain<false, false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8 * kTicketStride, p.tile_ready, p.error, p.nt1, p.max_polls, p.tile_done,
                          s_done);
   resident_combine(p, wave);
 }
@@ -703,8 +699,18 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_train_pipeline_kernel(co
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds
   __shared__ int s_item[4];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  gemm_bf16_drain<true, false, true, FAR>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
-  gemm_bf16_drain<false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8 * kTicketStride, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<true, true, false, true, FAR>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<false, false, false, false, FAR>(p.g2, smem, s_item, wave, p.tickets + 8 * kTicketStride, p.tile_ready, p.error, p.nt1, p.max_polls);
+}
+
+// The two GEMMs of the backward pass as one resident launch: the rows [dg | du] of the first (which also writes w h) are what
+// the second one reads.  Where it is taken, with both forms' times: backward_one_launch.
+__global__ __launch_bounds__(kGemmThreads, 1) void gemm_backward_pipeline_kernel(const PipelineArgs p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds
+  __shared__ int s_item[4];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  gemm_bf16_drain<true, false, false, true, false>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<false, false, false, false, false>(p.g2, smem, s_item, wave, p.tickets + 8 * kTicketStride, p.tile_ready, p.error, p.nt1, p.max_polls);
 }
 
 // The same resident kernel on E4M3 operands (whose rows number less than 2^32 elements, i.e. bytes).
@@ -712,8 +718,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_fp8_pipeline_kernel(cons
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // kGemmLds
   __shared__ int s_item[4];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  gemm_bf16_drain<true, true, false, false>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
-  gemm_bf16_drain<false, true, false, false>(p.g2, smem, s_item, wave, p.tickets + 8 * kTicketStride, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<true, true, true, false, false>(p.g1, smem, s_item, wave, p.tickets, p.tile_ready, p.error, p.nt1, p.max_polls);
+  gemm_bf16_drain<false, false, true, false, false>(p.g2, smem, s_item, wave, p.tickets + 8 * kTicketStride, p.tile_ready, p.error, p.nt1, p.max_polls);
 }
 
 }  // namespace moe355
