@@ -50,6 +50,9 @@ EDGES = {
     "rows_64": dict(T=64, E=3, k=2, R=3, local_rank_begin=0, local_rank_end=3, d=1032, f=512),
     "rows_65": dict(T=65, E=2, k=2, R=2, local_rank_begin=0, local_rank_end=2, d=512, f=776),
     "rows_128_two_passes": dict(T=128, E=4, k=4, R=1, local_rank_begin=0, local_rank_end=1, d=544, f=552),
+    # more than one pass over an expert that is not the first: it goes first
+    "large_expert_last": dict(T=100, E=5, k=1, R=1, local_rank_begin=0, local_rank_end=1, router="zipf", seed=4),
+    "large_expert_of_many": dict(T=128, E=256, k=8, R=4, local_rank_begin=0, local_rank_end=1, router="zipf", d=520, f=536),
     "no_local_row": dict(T=3, E=64, k=1, R=64, local_rank_begin=5, local_rank_end=6),
     "many_experts": dict(T=100, E=512, k=6, R=1, local_rank_begin=0, local_rank_end=1),
     "groups": dict(T=24, d=512, f=2048, E=32, k=16, R=1, local_rank_begin=0, local_rank_end=1),
