@@ -54,20 +54,31 @@ static size_t prep_lds_bytes(const Derived &dv, bool combine_tables) {
   return (size_t)((combine_tables ? 5 : 4) * dv.E_loc + 2 + 1 + 17) * sizeof(int);
 }
 
+// Whether the tile-table kernel also makes the FP8 codes: not where its tables take so much LDS that few workgroups fit a CU.
+constexpr size_t kTokenCodesLds = 16 * 1024;
+static bool codes_with_table(const moe_shape *s, const Derived &dv) {
+  return s->T <= 1 << 22 && prep_lds_bytes(dv, false) <= kTokenCodesLds;
+}
+
 // sole != nullptr: also mark the rows GEMM-2 may write straight to y (see the GEMM-2 epilogue);
-// combine_tables: also the row -> M tile map and the cleared GEMM-2 counters of the resident kernel's Combine stage
+// combine_tables: also the row -> M tile map and the cleared GEMM-2 counters of the resident kernel's Combine stage;
+// tokens.codes != nullptr: also the FP8 codes of the tokens that have a local slot
 static int launch_prep(const moe_shape *s, const Derived &dv, const moe_dispatch *tb, const int32_t *topk_idx,
-                       const float *topk_w, const Ws &w, int32_t *sole, hipStream_t st,
-                       bool combine_tables = false) {
-  static std::atomic<uint64_t> done{0};
+                       const float *topk_w, const Ws &w, int32_t *sole, hipStream_t st, bool combine_tables = false,
+                       const TokenCodes &tokens = TokenCodes{}) {
   static_assert((5 * kMaxExperts + 20) * sizeof(int) <= 96 * 1024, "per-expert tables fit the LDS");
-  if (!allow_dynamic_lds(reinterpret_cast<const void *>(&fwd_prep_kernel), 96 * 1024, done)) return MOE_ERR_HIP;
   const int blocks = (int)std::min<int64_t>(512, std::max<int64_t>(1, (dv.P_cap + 255) / 256));
-  hipLaunchKernelGGL(fwd_prep_kernel, dim3(2 * blocks), dim3(256), prep_lds_bytes(dv, combine_tables), st,
-                     tb->offsets, tb->perm, topk_w, s->T, s->k, dv.e_lo, dv.E_loc, dv.bm, (int)dv.P_cap, dv.max_mtiles,
-                     dv.nt1, dv.nt2, blocks, w.header, w.tickets, w.work1, w.work2, w.row_tok, w.row_w, topk_idx, sole, w.tile_ready,
-                     combine_tables ? w.row_tile : nullptr, combine_tables ? w.tile_done : nullptr);
-  return launch_status();
+  const int token_blocks = tokens.codes ? s->T : 0;
+  const auto launch = [&](auto kernel, std::atomic<uint64_t> &done) {
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(kernel), 96 * 1024, done)) return (int)MOE_ERR_HIP;
+    hipLaunchKernelGGL(kernel, dim3(2 * blocks + token_blocks), dim3(256), prep_lds_bytes(dv, combine_tables), st,
+                       tb->offsets, tb->perm, topk_w, s->T, s->k, dv.e_lo, dv.E_loc, dv.bm, (int)dv.P_cap, dv.max_mtiles,
+                       dv.nt1, dv.nt2, blocks, w.header, w.tickets, w.work1, w.work2, w.row_tok, w.row_w, topk_idx, sole,
+                       w.tile_ready, combine_tables ? w.row_tile : nullptr, combine_tables ? w.tile_done : nullptr, tokens);
+    return launch_status();
+  };
+  static std::atomic<uint64_t> done{0}, done_q{0};
+  return tokens.codes ? launch(&fwd_prep_kernel<true>, done_q) : launch(&fwd_prep_kernel<false>, done);
 }
 
 // Compute units of the current device, looked up once per device (0 on failure).
@@ -477,14 +488,24 @@ static int forward_common(const moe_shape *shape, const void *x, const int32_t *
   }
   mark(0);
   Fp8Operands q{};
+  const bool streams = fused && !keep && gemm_launches == 0 && stream_form(shape, dv, fp8 ? 1 : 2);
+  TokenCodes tokens{};
   if (fp8) {
     // x as codes with one scale per token, behind the tile-table part of the workspace
     unsigned char *b = static_cast<unsigned char *>(workspace);
     uint8_t *xq = b + L.total;
     float *x_scale = reinterpret_cast<float *>(b + L.total + align_up((size_t)shape->T * shape->d, 256));
-    hipLaunchKernelGGL(fp8_quantize_rows_kernel, dim3((unsigned)shape->T), dim3(256), 0, st,
-                       static_cast<const uint4 *>(x), shape->d, xq, x_scale);
-    if ((rc = launch_status()) != MOE_OK) return rc;
+    if (!streams && codes_with_table(shape, dv)) {
+      tokens.x = static_cast<const uint4 *>(x);
+      tokens.cols = shape->d;
+      tokens.codes = xq;
+      tokens.scales = x_scale;
+      tokens.inv_perm = tables->inv_perm;
+    } else {
+      hipLaunchKernelGGL(fp8_quantize_rows_kernel, dim3((unsigned)shape->T), dim3(256), 0, st,
+                         static_cast<const uint4 *>(x), shape->d, xq, x_scale);
+      if ((rc = launch_status()) != MOE_OK) return rc;
+    }
     q.xq = xq;
     q.x_scale = x_scale;
     q.gu_scale = reinterpret_cast<const float *>(static_cast<const unsigned char *>(packed_gate_up) +
@@ -495,7 +516,7 @@ static int forward_common(const moe_shape *shape, const void *x, const int32_t *
   }
   // the stream kernels are the form the library picks for a small batch; the forms a caller asks for by name (and the
   // training forward, which keeps its rows) run the tile kernels
-  if (fused && !keep && gemm_launches == 0 && stream_form(shape, dv, fp8 ? 1 : 2))
+  if (streams)
     return launch_stream(shape, dv, x, topk_w, tables, packed_gate_up, packed_down, w, y, st, events, fp8 ? &q : nullptr);
   if (const int blocks = fused && shape->dtype == MOE_F32 && gemm_launches == 0 ? f32_direct_blocks(shape, dv) : 0) {
     if ((rc = launch_f32_direct(shape, dv, blocks, x, topk_w, tables, packed_gate_up, packed_down, w, st, events)) !=
@@ -505,7 +526,7 @@ static int forward_common(const moe_shape *shape, const void *x, const int32_t *
     mark(4);
     return rc;
   }
-  if ((rc = launch_prep(shape, dv, tables, topk_idx, topk_w, w, sole, st, with_combine)) != MOE_OK) return rc;
+  if ((rc = launch_prep(shape, dv, tables, topk_idx, topk_w, w, sole, st, with_combine, tokens)) != MOE_OK) return rc;
   mark(1);
   if (fused) {
     if ((rc = launch_gemms(shape, dv, x, w.row_tok, shape->d, packed_gate_up, packed_down, w, sole, y, st,

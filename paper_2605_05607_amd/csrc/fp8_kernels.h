@@ -44,11 +44,9 @@ __device__ __forceinline__ uint2 codes_of(uint4 v, float scale, float rcp) {
 }
 
 constexpr int kQuantChunks = 4;
-__global__ __launch_bounds__(256) void fp8_quantize_rows_kernel(const uint4 *__restrict__ x, int cols,
-                                                                uint8_t *__restrict__ codes,
-                                                                float *__restrict__ scales) {
+__device__ __forceinline__ void fp8_quantize_row(const uint4 *__restrict__ x, size_t row, int cols, uint8_t *__restrict__ codes,
+                                                 float *__restrict__ scales) {
   __shared__ float wave_max[4];
-  const size_t row = blockIdx.x;
   const int chunks = cols / 8, tid = threadIdx.x;
   const uint4 *src = x + row * chunks;
   uint4 v[kQuantChunks];
@@ -73,6 +71,11 @@ __global__ __launch_bounds__(256) void fp8_quantize_rows_kernel(const uint4 *__r
   for (int i = 0; i < kQuantChunks; ++i)
     if (tid + i * 256 < chunks) dst[tid + i * 256] = codes_of(v[i], scale, rcp);
   for (int c = tid + kQuantChunks * 256; c < chunks; c += 256) dst[c] = codes_of(src[c], scale, rcp);
+}
+__global__ __launch_bounds__(256) void fp8_quantize_rows_kernel(const uint4 *__restrict__ x, int cols,
+                                                                uint8_t *__restrict__ codes,
+                                                                float *__restrict__ scales) {
+  fp8_quantize_row(x, blockIdx.x, cols, codes, scales);
 }
 
 // Largest magnitude of every output column of W [E_loc][K][N] (bf16) over one slice of the reduction index

@@ -1,6 +1,8 @@
 // Tile table: work lists of the two GEMMs and per-row metadata of the local layout segment.
 #pragma once
+#include "combine_kernels.h"
 #include "forward_types.h"
+#include "fp8_kernels.h"
 
 namespace moe355 {
 
@@ -30,10 +32,22 @@ namespace moe355 {
 // the matrix cores.
 constexpr int kStreamRows = 64;
 
+// The FP8 form's codes of x, made by the same launch: the tile table is a chain of latencies on a few hundred workgroups, the
+// codes are bound by HBM, and a row that no local slot names is not read (4096 tokens, k = 8, 32 of 256 experts of 7168: a
+// third of the rows; 17.1 + 5.2 us as two launches, step 372 -> 359).
+struct TokenCodes {
+  const uint4 *x;
+  int cols;
+  uint8_t *codes;
+  float *scales;
+  const int32_t *inv_perm;
+};
+
 // Two kinds of blocks run side by side, since each is a short chain of dependent reads and together they made one twice as
 // long: the first list_blocks blocks write the work lists (each rebuilds the small per-expert tables in its LDS), the others
 // the per-row metadata.  (8192 tokens, k = 8, 128 experts: 9.6 us with every block doing both, one after the other, and
-// looking each item's expert up in `offsets`; 6.3 us.)
+// looking each item's expert up in `offsets`; 6.3 us.)  QUANT: behind them a block per token.
+template <bool QUANT>
 __global__ __launch_bounds__(256) void fwd_prep_kernel(const int32_t *__restrict__ offsets,
                                                        const int32_t *__restrict__ perm,
                                                        const float *__restrict__ topk_w, int T, int k, int e_lo,
@@ -46,12 +60,19 @@ __global__ __launch_bounds__(256) void fwd_prep_kernel(const int32_t *__restrict
                                                        int32_t *__restrict__ row_sole,
                                                        int32_t *__restrict__ tile_ready,
                                                        int32_t *__restrict__ row_tile,
-                                                       int32_t *__restrict__ tile_done) {
+                                                       int32_t *__restrict__ tile_done, const TokenCodes tokens) {
   const int base = offsets[e_lo], end = offsets[e_lo + E_loc];
   const int P = max(0, min(P_cap, end - base));
+  if (QUANT && (int)blockIdx.x >= 2 * list_blocks) {
+    const int t = blockIdx.x - 2 * list_blocks;
+    const int row = combine_slot_row(topk_idx, tokens.inv_perm, t, k, threadIdx.x & 63, e_lo, E_loc, base, P_cap);
+    if (__ballot(row >= 0) == 0) return;  // (the same in all four waves)
+    fp8_quantize_row(tokens.x, t, tokens.cols, tokens.codes, tokens.scales);
+    return;
+  }
   if ((int)blockIdx.x >= list_blocks) {
     const long long npairs = (long long)T * k;
-    const int stride = (gridDim.x - list_blocks) * blockDim.x;
+    const int stride = list_blocks * blockDim.x;
     for (int r = (blockIdx.x - list_blocks) * blockDim.x + threadIdx.x; r < P; r += stride) {
       int p = perm[base + r];
       p = p < 0 ? 0 : (p >= npairs ? (int)(npairs - 1) : p);
