@@ -1017,11 +1017,6 @@ static int backward_common(const moe_shape *shape, const void *x, const void *dy
   if (rc != MOE_OK) return join(rc);
   if ((rc = launch_combine(shape, dv, dxr, topk_idx, tables, dx, true, st)) != MOE_OK || !wgrad) return join(rc);
   if ((rc = join(MOE_OK)) != MOE_OK) return rc;
-  const size_t units = (size_t)shape->d * shape->f / 8;  // 16-byte units of one expert's gradient
-  hipLaunchKernelGGL(wgrad_zero_empty_kernel,
-                     dim3((unsigned)std::min<size_t>(1024, ceil_div(units, (size_t)8192)), dv.E_loc, 3), dim3(256), 0,
-                     st, tables->offsets, w.header, dv.e_lo, static_cast<u32x4 *>(dW_gate), static_cast<u32x4 *>(dW_up),
-                     static_cast<u32x4 *>(dW_down), units);
   if (direct) {
     WgradDirectArgs a;
     a.x = static_cast<const bf16_t *>(x); a.dy = static_cast<const bf16_t *>(dy); a.dgu = dgu; a.hw = hw;
@@ -1039,6 +1034,11 @@ static int backward_common(const moe_shape *shape, const void *x, const void *dy
                        st, a);
     return launch_status();
   }
+  const size_t units = (size_t)shape->d * shape->f / 8;  // 16-byte units of one expert's gradient
+  hipLaunchKernelGGL(wgrad_zero_empty_kernel,
+                     dim3((unsigned)std::min<size_t>(1024, ceil_div(units, (size_t)8192)), dv.E_loc, 3), dim3(256), 0,
+                     st, tables->offsets, w.header, dv.e_lo, static_cast<u32x4 *>(dW_gate), static_cast<u32x4 *>(dW_up),
+                     static_cast<u32x4 *>(dW_down), units);
   // one grouped product per weight matrix, over the transposed operands
   static std::atomic<uint64_t> done_w{0};
   if (!allow_dynamic_lds(reinterpret_cast<const void *>(&wgrad_slab_kernel), 2 * kStageBytes, done_w)) return MOE_ERR_HIP;

@@ -102,8 +102,8 @@ struct WgradArgs {
   int M, N, n_mt, n_nt;
 };
 
-// Experts with at most kThinSteps blocks of 64 rows are left to wgrad_thin_slab_kernel (those without rows to
-// wgrad_zero_empty_kernel): their cost is writing the output, and that kernel's small workgroups overlap the stores of
+// Experts with at most kThinSteps blocks of 64 rows are left to the thin kernels (those without rows to
+// wgrad_zero_empty_kernel where the operands are transposed copies): their cost is writing the output, and that kernel's small workgroups overlap the stores of
 // one tile with the loads of the next on the same CU.
 constexpr int kStageBytes = 2 * kBM * kBK * 2;  // 64 KiB: A slab then B slab
 constexpr int kThinSteps = 2;
@@ -541,13 +541,30 @@ __device__ __forceinline__ void wgrad_thin_tile(const WgradDirectArgs &a, unsign
   }
 }
 
-// grid (ceil(tiles of 128 x 128 of all three matrices / kThinTiles), E_loc)
+// Zero gradients of an expert without rows: workgroup `share` of `shares` clears a contiguous share of its three matrices.
+__device__ __forceinline__ void wgrad_zero_share(const WgradDirectArgs &a, int le, uint32_t share, uint32_t shares) {
+  const uint64_t units = (uint64_t)a.d * a.f / 8, all = 3 * units, per = (all + shares - 1) / shares;  // of 16 bytes
+  const uint64_t end = per * (share + 1) < all ? per * (share + 1) : all;
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  for (uint64_t u = per * share + threadIdx.x; u < end; u += 256) {
+    const uint32_t m = (u >= units) + (u >= 2 * units);
+    bf16_t *C = m == 0 ? a.dW_gate : m == 1 ? a.dW_up : a.dW_down;
+    __builtin_nontemporal_store(zero, reinterpret_cast<u32x4 *>(C) + (size_t)le * units + (u - m * units));
+  }
+}
+
+// grid (ceil(tiles of 128 x 128 of all three matrices / kThinTiles), E_loc).  Experts without rows as well: what either takes
+// is the time of its stores, and a launch that finds no such expert still costs 5 us.
 __global__ __launch_bounds__(256, 4) void wgrad_thin_bf16_kernel(const WgradDirectArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[4 * kPatchBytes];  // 36 KiB >= one 32 KiB stage
   const int le = blockIdx.y;
   int start;
   const int cnt = expert_rows(a.offsets, a.header, a.e_lo, le, start);
-  if (cnt > 64 * kThinSteps || cnt == 0) return;  // whole workgroup: wgrad_bf16_kernel / wgrad_zero_empty_kernel own it
+  if (cnt > 64 * kThinSteps) return;  // whole workgroup: wgrad_bf16_kernel owns it
+  if (cnt == 0) {
+    wgrad_zero_share(a, le, blockIdx.x, gridDim.x);
+    return;
+  }
   const int td = (a.d + 127) / 128, tf = (a.f + 127) / 128, tg = (2 * a.f + 127) / 128, gu = td * tg;
   for (int rep = 0; rep < kThinTiles; ++rep) {
     int id = blockIdx.x * kThinTiles + rep;
