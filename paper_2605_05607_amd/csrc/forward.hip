@@ -164,6 +164,7 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
   if (keep_gu) {  // training forward: g and u are kept, and every weighted row goes to the kept o
     g1.aux = keep_gu;
     g2.out = keep_o;
+    g2.keep_rows = 1;
   }
   const auto grid_of = [&](int nt) { return dim3((unsigned)(((size_t)dv.max_mtiles * nt + 255) / 256 * 256)); };
   if (s->dtype == MOE_BF16) {
@@ -476,9 +477,10 @@ static int forward_common(const moe_shape *shape, const void *x, const int32_t *
   auto mark = [&](int i) {
     if (events && events[i]) (void)hipEventRecord((hipEvent_t)events[i], st);
   };
-  // fused bf16 layers: GEMM-2 writes the rows that need no reduction straight to y and Combine skips them
-  // (not in the training forward, which keeps every weighted row for the backward pass)
-  int32_t *sole = fused && shape->dtype == MOE_BF16 && !keep ? w.row_sole : nullptr;
+  // fused bf16 layers: GEMM-2 writes the rows that need no reduction straight to y and Combine skips them.  The training
+  // forward, which keeps every weighted row for the backward pass, does both: two more bytes written per element instead of
+  // four read back.
+  int32_t *sole = fused && shape->dtype == MOE_BF16 ? w.row_sole : nullptr;
   void *keep_gu = nullptr;
   float *keep_o = nullptr;
   if (keep) {

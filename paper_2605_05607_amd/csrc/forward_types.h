@@ -51,6 +51,7 @@ struct GemmArgs {
   const float *row_w;
   const int32_t *row_sole;  // GEMM-2 only, may be null: token of a row that is the token's only local slot, else -1
   void *y;                  // GEMM-2 only: layer output, target of the sole rows
+  int keep_rows;            // GEMM-2 only: the sole rows go to `out` as well
   const int32_t *n_items;  // device: number of work items of this GEMM
   const int4 *work;        // device: work list
   int K, N, lda, ldo, n_ntiles, n_ktiles;

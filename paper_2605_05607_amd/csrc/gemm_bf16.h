@@ -378,7 +378,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs &g, unsigned char 
             // (y is not read again by this launch: streamed past the L2, which the operands need)
             __builtin_nontemporal_store(
                 b, reinterpret_cast<bf16x4 *>(static_cast<bf16_t *>(g.y) + (size_t)sole[it] * g.ldo + col));
-          } else {
+          }
+          if (sole[it] < 0 || g.keep_rows) {
             *reinterpret_cast<f32x4 *>(static_cast<float *>(g.out) + (size_t)(m0 + row_l) * g.ldo + col) = v;
           }
         }
