@@ -238,21 +238,27 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
 }
 
 // fp32 layers of small batches: the kernels without a tile table (gemm_f32_direct_kernel); 32-row blocks per workgroup of
-// GEMM-1, 0 = the tile kernels.  By rows per expert and workgroups of GEMM-1, time of the tile kernels' step / of this one:
+// GEMM-1, 0 = the tile kernels.  By rows per expert and strips of GEMM-1, time of the tile kernels' step / of this one:
 //   up to 24 rows, one block: 1.1 to 1.7 (table at the kernel; 64 tokens on 4 experts of 1024 x 512 33.7 / 31.3 us);
 //   more rows, one block each while that leaves CUs idle: 256 tokens on 4 experts of 1024 x 512 41.4 / 37.9 us (more
 //   workgroups: 64 rows on 4 of 1504 x 1000 54 / 57);
-//   three blocks, 192 to 1024 workgroups in nearly full rounds of one per CU: 256 tokens on 8 of 512 x 1024 1.09, of 2048 x
-//   2048 1.1, 1000 on 4 of 2048 x 2048 1.21, 2048 1.08 (a round and a half: 256 tokens on 4 of 1504 x 1000, k = 4, 139 / 157 us;
-//   short reductions are all prologue and sum: 256 tokens on 16 of 264 x 2000 90 / 101; beyond, the tile kernels' larger
-//   tiles: 2048 tokens on 8 of 512 x 1024 190 / 219).
+//   three blocks, where an even load takes one pass of a workgroup per strip in nearly full rounds of one per CU: 256 tokens on
+//   8 of 512 x 1024 1.09 (short reductions are all prologue and sum: 256 tokens on 16 of 264 x 2000 90 / 101; a round and
+//   a half: 256 tokens on 4 of 1504 x 1000, k = 4, 139 / 157 us; two passes, of which the second is nearly empty: 188 tokens
+//   on 8 of 2032 x 368, k = 4, 97 / 110).
+// The last two up to 384 tokens, i.e. four passes for an expert that all of them pick: a skewed load cannot be seen here, and
+// with its large expert in the passes of few workgroups 614 tokens on 4 of 16 of 1088 x 1872 took 115 / 125 us, 498 on 1 of 4 of
+// 952 x 1296 65 / 68.
+constexpr int kF32SkewTokens = 384;
 static int f32_direct_blocks(const moe_shape *s, const Derived &dv) {
   const int64_t strips = (int64_t)dv.E_loc * ceil_div(s->f, 32);
   if (strips > 1 << 14) return 0;
   const double rows = (double)s->T * s->k / s->E;
-  if (rows <= 24.0 || strips * std::ceil(rows / 32) < 256) return 1;
-  const double wgs = strips * std::ceil(1.1 * rows / 96);
-  return s->d >= 512 && wgs >= 192 && wgs <= 1024 && (wgs <= 256 || wgs >= 0.9 * 256 * std::ceil(wgs / 256)) ? 3 : 0;
+  if (rows <= 24.0) return 1;
+  if (s->T > kF32SkewTokens) return 0;
+  if (strips * std::ceil(rows / 32) < 256) return 1;
+  const bool full_rounds = strips >= 192 && strips <= 1024 && (strips <= 256 || strips >= 0.9 * 256 * std::ceil(strips / 256.0));
+  return s->d >= 512 && 1.1 * rows <= 96 && full_rounds ? 3 : 0;
 }
 
 static int launch_f32_direct(const moe_shape *s, const Derived &dv, int blocks, const void *x, const float *topk_w,
@@ -270,9 +276,13 @@ static int launch_f32_direct(const moe_shape *s, const Derived &dv, int blocks, 
   g2.A = static_cast<const float *>(w.h); g2.W = static_cast<const float *>(packed_down); g2.out = w.o;
   g2.K = s->f; g2.N = s->d;
   const double rows = (double)s->T * s->k / s->E;
-  const auto launch = [&](auto kernel, int mb, const F32Args &g) {
-    // (an expert with more rows than its blocks hold takes several turns)
-    const int z = (int)std::min(std::max(1.0, std::ceil((mb == 1 ? 1.25 : 1.1) * rows / (32 * mb))), 64.0);
+  const auto launch = [&](auto kernel, int mb, F32Args g) {
+    // an even load's workgroups, and under a skewed one more of them for the large experts (those without rows leave at once),
+    // up to some four per CU; an expert with more rows still takes several turns.  (184 tokens on 4 of 16 experts of 408 x 536,
+    // one of which gets 95, 54.7 us with the even load's; 376, k = 4, on 2 of 8 of 1096 x 1024 118.)
+    const int strips = ceil_div(g.N, 32) * dv.E_loc;
+    g.mean_z = (int)std::min(std::max(1.0, std::ceil((mb == 1 ? 1.25 : 1.1) * rows / (32 * mb))), 64.0);
+    const int z = std::max(g.mean_z, std::min(ceil_div((int)std::min<int64_t>(s->T, dv.P_cap), 32 * mb), 1024 / strips));
     hipLaunchKernelGGL(kernel, dim3(ceil_div(g.N, 32), dv.E_loc, z), dim3(kF32Waves * 64), 0, st, g);
   };
   mark(1);

@@ -180,6 +180,7 @@ struct F32Args {
   const float *topk_w;
   int32_t *error;      // status word of the workspace (cleared by GEMM-1: no wait can give up here)
   int T, k, e_lo, E_loc, P_cap, K, N;
+  int mean_z;          // workgroups of a strip that an even load fills
 };
 
 constexpr int kF32Waves = 8;
@@ -187,11 +188,11 @@ constexpr int kF32Waves = 8;
 template <bool GATED, int MB, int D, int OCC>
 __global__ __launch_bounds__(kF32Waves * 64, OCC) void gemm_f32_direct_kernel(const F32Args g) {
   constexpr int NM = GATED ? 2 : 1, G = 16, NW = kF32Waves;
-  constexpr bool EARLY = MB > 1;  // the first weights ahead of the tables
   __shared__ float red[NW][NM][32][32];
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l31 = lane & 31, khalf = lane >> 5;
   const int n0 = blockIdx.x * 32, le = blockIdx.y;
+  const bool early = MB > 1 && (int)blockIdx.z < g.mean_z;  // the first weights ahead of the tables
   if (GATED && tid == 0 && blockIdx.x == 0 && le == 0 && blockIdx.z == 0) *g.error = 0;
   const int n_groups = (g.K + G - 1) / G;
   const int k0 = w * n_groups / NW, n_mine = (w + 1) * n_groups / NW - k0;  // this wave's groups
@@ -230,7 +231,7 @@ __global__ __launch_bounds__(kF32Waves * 64, OCC) void gemm_f32_direct_kernel(co
         if (!decltype(whole)::value && kk >= k_len) s.a[mi][i] = f32x4{0.f, 0.f, 0.f, 0.f};  // (an infinity times 0)
       }
   };
-  if (EARLY) {
+  if (early) {
 #pragma unroll
     for (int i = 0; i < D; ++i)
       if (i < n_whole) load_b(s[i], i, whole);
@@ -268,7 +269,7 @@ __global__ __launch_bounds__(kF32Waves * 64, OCC) void gemm_f32_direct_kernel(co
 #pragma unroll
     for (int i = 0; i < D; ++i)
       if (i < n_whole) {
-        if (!EARLY || m0 > z0) load_b(s[i], i, whole);
+        if (!early || m0 > z0) load_b(s[i], i, whole);
         load_a(s[i], i, whole);
       }
     int kg = 0;

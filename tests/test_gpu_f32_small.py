@@ -20,6 +20,8 @@ CASES = {
     "skew": ((200, 0, 1, 0, 0, 0, 0, 0), 520, 160),                        # several turns of a workgroup
     "three_blocks": ((64, 65, 96, 97, 33, 1, 0, 90), 520, 1048),
     "three_blocks_skew": ((300, 0, 0, 0, 0, 2, 130, 64), 600, 1048),
+    "three_blocks_one_round": ((64, 65, 96, 97, 33, 1, 0, 20), 520, 1000),
+    "three_blocks_large_expert": ((300, 0, 0, 0, 0, 2, 30, 44), 600, 1000),  # in the workgroups an even load leaves empty
 }
 
 
