@@ -245,6 +245,9 @@ MOE355_API int moe_step(const moe_shape *shape, const float *logits, const void 
 /* 1 or 2: GEMM launches of moe_fused_forward for this shape (host-only; 0 for an invalid shape): 1 = the resident kernel,
  * 2 = one launch per GEMM, of the tile kernels or, for small batches, of the weight-streaming ones. */
 MOE355_API int moe_forward_gemm_launches(const moe_shape *shape);
+/* The small-batch kernels moe_fused_forward runs for this shape (host-only): 0 = none (or an invalid shape); bf16: 1 = the
+ * weight-streaming ones; fp32: 1 or 3 = those without a tile table, that many 32-row blocks of an expert at a time. */
+MOE355_API int moe_forward_small_batch(const moe_shape *shape);
 
 /*
  * moe_fused_forward with the choice between the two forms of the GEMM-1 => GEMM-2 hand-over made by the caller

@@ -58,6 +58,8 @@ def lib() -> C.CDLL:
         L.moe_unfused_workspace_bytes.argtypes = [sp]
         L.moe_forward_gemm_launches.restype = i32
         L.moe_forward_gemm_launches.argtypes = [sp]
+        L.moe_forward_small_batch.restype = i32
+        L.moe_forward_small_batch.argtypes = [sp]
         L.moe_packed_weight_bytes.restype = sz
         L.moe_packed_weight_bytes.argtypes = [sp, i32]
         L.moe_router_workspace_bytes.restype = sz
@@ -300,6 +302,10 @@ def moe_fused_forward_timed(shape, x, topk_idx, topk_w, tables, packed_gate_up, 
 
 def moe_forward_gemm_launches(shape) -> int:
     return int(lib().moe_forward_gemm_launches(C.byref(shape)))
+
+
+def moe_forward_small_batch(shape) -> int:
+    return int(lib().moe_forward_small_batch(C.byref(shape)))
 
 
 def _forward_choice(name, shape, x, topk_idx, topk_w, tables, packed_gate_up, packed_down, y, workspace, events,

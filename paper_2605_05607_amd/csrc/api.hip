@@ -93,6 +93,12 @@ extern "C" int moe_forward_gemm_launches(const moe_shape *shape) {
   return stream_form(shape, dv, 2) ? 2 : tile_gemm_launches(shape, 2);
 }
 
+extern "C" int moe_forward_small_batch(const moe_shape *shape) {
+  Derived dv;
+  if (check_shape(shape, &dv) != MOE_OK) return 0;
+  return stream_form(shape, dv, 2) ? 1 : f32_direct_blocks(shape, dv);
+}
+
 extern "C" size_t moe_unfused_workspace_bytes(const moe_shape *shape) {
   Derived dv;
   if (check_shape(shape, &dv) != MOE_OK) return 0;

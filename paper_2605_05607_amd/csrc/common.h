@@ -44,7 +44,9 @@ int check_shape(const moe_shape *s, Derived *out);
 // tile_gemm_launches, for the others: 1 = one resident launch with the tile-level hand-over, where the mean number of
 // rows per expert, T k / E, is below one M tile or the launch takes long enough; 2 = a kernel boundary between the GEMMs
 // (always for fp32 layers).
+// f32_direct_blocks: 32-row blocks of the fp32 kernels without a tile table, 0 = the tile kernels.
 bool stream_form(const moe_shape *s, const Derived &dv, int elt);
+int f32_direct_blocks(const moe_shape *s, const Derived &dv);
 int tile_gemm_launches(const moe_shape *s, int elt);
 
 // hipGetLastError() reports (and clears) the last error of ANY earlier runtime call on this thread, including

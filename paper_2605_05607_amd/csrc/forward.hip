@@ -238,27 +238,28 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
 }
 
 // fp32 layers of small batches: the kernels without a tile table (gemm_f32_direct_kernel); 32-row blocks per workgroup of
-// GEMM-1, 0 = the tile kernels.  By rows per expert and strips of GEMM-1, time of the tile kernels' step / of this one:
-//   up to 24 rows, one block: 1.1 to 1.7 (table at the kernel; 64 tokens on 4 experts of 1024 x 512 33.7 / 31.3 us);
-//   more rows, one block each while that leaves CUs idle: 256 tokens on 4 experts of 1024 x 512 41.4 / 37.9 us (more
-//   workgroups: 64 rows on 4 of 1504 x 1000 54 / 57);
-//   three blocks, where an even load takes one pass of a workgroup per strip in nearly full rounds of one per CU: 256 tokens on
-//   8 of 512 x 1024 1.09 (short reductions are all prologue and sum: 256 tokens on 16 of 264 x 2000 90 / 101; a round and
-//   a half: 256 tokens on 4 of 1504 x 1000, k = 4, 139 / 157 us; two passes, of which the second is nearly empty: 188 tokens
-//   on 8 of 2032 x 368, k = 4, 97 / 110).
-// The last two up to 384 tokens, i.e. four passes for an expert that all of them pick: a skewed load cannot be seen here, and
-// with its large expert in the passes of few workgroups 614 tokens on 4 of 16 of 1088 x 1872 took 115 / 125 us, 498 on 1 of 4 of
-// 952 x 1296 65 / 68.
-constexpr int kF32SkewTokens = 384;
-static int f32_direct_blocks(const moe_shape *s, const Derived &dv) {
-  const int64_t strips = (int64_t)dv.E_loc * ceil_div(s->f, 32);
-  if (strips > 1 << 14) return 0;
+// GEMM-1, 0 = the tile kernels.  A load cannot be seen here, so each line holds for even loads and for the skewed ones of the
+// workload generator (power law, the hottest rank local).  Time of this form's forward call over the tile kernels', median (and
+// the tenth of the layers above), 256 to 2048 columns, 2 to 128 local experts, weights from HBM:
+//   up to 24 rows per expert, up to 512 tokens, at most 1536 strips of 32 columns: one block, even 0.70 to 0.90 (0.98), skewed
+//     0.75 to 0.93 (1.03).  More tokens (1025 to 2048: skewed 0.94, up to 1.19): the tile kernels, which read a large expert's
+//     weights half as often.  More strips: two workgroups per CU on every one of them, so that the latency this form saves counts
+//     less (2000 strips: even 0.95, up to 1.30), but not with one unit per expert, up to 32 tokens (0.68 to 0.90, up to 3500);
+//   more rows, up to 384 tokens: one block each while that leaves CUs idle, even 0.92 (1.01), skewed 0.90 (1.03); (more
+//     workgroups: 24 to 32 rows on 16 of 936 x 440 1.09);
+//   three blocks, where an even load is one unit of up to 96 rows per expert in nearly full rounds of one workgroup per CU: 0.93
+//     (1.03), skewed 0.93 (1.03).  Short reductions are all prologue and sum (columns of 376 to 424 in GEMM-2 1.10 to 1.23).  In
+//     more than one round up to 36 rows only: 38 to 64 are what the tile kernels are cut for (1.00 to 1.11), and a skewed load of
+//     more fills their tiles as well (1.05 to 1.17).
+int f32_direct_blocks(const moe_shape *s, const Derived &dv) {
+  if (s->dtype != MOE_F32) return 0;
+  const int64_t strips = (int64_t)dv.E_loc * ceil_div(s->f, 32), widest = (int64_t)dv.E_loc * ceil_div(std::max(s->d, s->f), 32);
   const double rows = (double)s->T * s->k / s->E;
-  if (rows <= 24.0) return 1;
-  if (s->T > kF32SkewTokens) return 0;
-  if (strips * std::ceil(rows / 32) < 256) return 1;
+  if (rows <= 24.0) return s->T <= 512 && widest <= (s->T <= 32 ? 3584 : 1536) ? 1 : 0;
+  if (s->T > 384) return 0;
+  if (strips * std::ceil(rows / 32) < 256 && strips * std::ceil(1.25 * rows / 32) < 384) return 1;
   const bool full_rounds = strips >= 192 && strips <= 1024 && (strips <= 256 || strips >= 0.9 * 256 * std::ceil(strips / 256.0));
-  return s->d >= 512 && 1.1 * rows <= 96 && full_rounds ? 3 : 0;
+  return s->d >= 512 && s->f >= 512 && rows <= (strips > 256 ? 36.0 : 87.0) && full_rounds ? 3 : 0;
 }
 
 static int launch_f32_direct(const moe_shape *s, const Derived &dv, int blocks, const void *x, const float *topk_w,
@@ -275,25 +276,24 @@ static int launch_f32_direct(const moe_shape *s, const Derived &dv, int blocks, 
   F32Args g2 = g1;
   g2.A = static_cast<const float *>(w.h); g2.W = static_cast<const float *>(packed_down); g2.out = w.o;
   g2.K = s->f; g2.N = s->d;
-  const double rows = (double)s->T * s->k / s->E;
-  const auto launch = [&](auto kernel, int mb, F32Args g) {
-    // an even load's workgroups, and under a skewed one more of them for the large experts (those without rows leave at once),
-    // up to some four per CU; an expert with more rows still takes several turns.  (184 tokens on 4 of 16 experts of 408 x 536,
-    // one of which gets 95, 54.7 us with the even load's; 376, k = 4, on 2 of 8 of 1096 x 1024 118.)
-    const int strips = ceil_div(g.N, 32) * dv.E_loc;
-    g.mean_z = (int)std::min(std::max(1.0, std::ceil((mb == 1 ? 1.25 : 1.1) * rows / (32 * mb))), 64.0);
-    const int z = std::max(g.mean_z, std::min(ceil_div((int)std::min<int64_t>(s->T, dv.P_cap), 32 * mb), 1024 / strips));
-    hipLaunchKernelGGL(kernel, dim3(ceil_div(g.N, 32), dv.E_loc, z), dim3(kF32Waves * 64), 0, st, g);
+  const double local = (double)s->T * s->k * dv.E_loc / s->E;  // rows of an even load
+  const auto launch = [&](auto kernel, int mb, int resident, const F32Args &g) {
+    // units of any load, or those of an even one and a quarter more, or what the chip holds at once; workgroups take turns
+    const int strips = ceil_div(g.N, 32);
+    const int64_t most = (mb > 1 ? dv.E_loc : std::min<int64_t>(dv.E_loc, dv.P_cap)) + dv.P_cap / 32;
+    const int64_t even = mb > 1 ? dv.E_loc : (int64_t)std::ceil(1.25 * (std::min<double>(dv.E_loc, local) + local / 32));
+    const int64_t units = std::min(most, std::max<int64_t>(even, ceil_div(resident, strips)));
+    hipLaunchKernelGGL(kernel, dim3(strips, (unsigned)units), dim3(kF32Waves * 64), 0, st, g);
   };
   mark(1);
   // one block: four groups in flight, or two and twice the workgroups per CU where those are many and short
-  if (blocks == 3) launch(gemm_f32_direct_kernel<true, 3, 2, 2>, 3, g1);
-  else if (s->d < 512 && (int64_t)dv.E_loc * ceil_div(s->f, 32) >= 768) launch(gemm_f32_direct_kernel<true, 1, 2, 4>, 1, g1);
-  else launch(gemm_f32_direct_kernel<true, 1, 4, 2>, 1, g1);
+  if (blocks == 3) launch(gemm_f32_direct_kernel<true, 3, 2, 2>, 3, 512, g1);
+  else if (s->d < 512 && (int64_t)dv.E_loc * ceil_div(s->f, 32) >= 768) launch(gemm_f32_direct_kernel<true, 1, 2, 4>, 1, 512, g1);
+  else launch(gemm_f32_direct_kernel<true, 1, 4, 2>, 1, 512, g1);
   const int rc = launch_status();
   mark(2);
   if (rc != MOE_OK) return rc;
-  launch(gemm_f32_direct_kernel<false, 1, 4, 4>, 1, g2);
+  launch(gemm_f32_direct_kernel<false, 1, 4, 4>, 1, 1024, g2);
   mark(3);
   return launch_status();
 }
@@ -530,7 +530,7 @@ static int forward_common(const moe_shape *shape, const void *x, const int32_t *
   // training forward, which keeps its rows) run the tile kernels
   if (streams)
     return launch_stream(shape, dv, x, topk_w, tables, packed_gate_up, packed_down, w, y, st, events, fp8 ? &q : nullptr);
-  if (const int blocks = fused && shape->dtype == MOE_F32 && gemm_launches == 0 ? f32_direct_blocks(shape, dv) : 0) {
+  if (const int blocks = fused && gemm_launches == 0 ? f32_direct_blocks(shape, dv) : 0) {
     if ((rc = launch_f32_direct(shape, dv, blocks, x, topk_w, tables, packed_gate_up, packed_down, w, st, events)) !=
         MOE_OK)
       return rc;

@@ -165,13 +165,17 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_kernel(const GemmArgs g) 
 
 // ------------------------------------------------------------------------------------------------
 // The same products where the batch is small: no tile table (an expert's rows come from the dispatch tables), one workgroup of
-// eight waves per (32 columns, local expert, block of 32 MB rows), each wave with an eighth of the reduction range.  What
-// bounds it is the latency of the weight stream, so a wave has D groups of 16 reduction indices in flight: with D = 4 all of a
+// eight waves per (32 columns, unit), each wave with an eighth of the reduction range.  A unit is an expert with up to 32 MB rows,
+// or 32 rows of one with more; the workgroups of a strip take turns over the units of the whole load, which they number from
+// `offsets`.  (With workgroups that each keep to one expert, a large one was turn after turn of a few of them, and the
+// experts without rows scattered the others over the CUs.  Forward call, 414 tokens on 8 of 64 experts of 1024 x 1024, 200 rows
+// on one of them, 81.9 -> 50.1 us, 430 on 16 of 128 of 512 x 1024, 400 rows on one, 126.8 -> 54.2; tile kernels 70.4 and 73.1.)
+// What bounds it is the latency of the weight stream, so a wave has D groups of 16 reduction indices in flight: with D = 4 all of a
 // range of 512 at once.  MB = 3: experts of 32 to 96 rows in one pass over their weights; such experts are hardly ever empty, so
-// the weights are requested before the tables have been read.
-// Measured, step, against the kernels above with their tile table: 8 tokens on 8 experts of 512 x 1024 35.7 -> 27.2 us, 32 on 8
-// of 2048 x 2048 178 -> 105 (402 MB of weights), 64 on 16 of 264 x 2000 84 -> 54; MB = 3: 256 tokens on 8 experts of 512 x 1024
-// 57.9 -> 52 us, on 8 of 2048 x 2048 250 -> 222.
+// the first weights of each are requested before the tables have been read.
+// Measured, step with weights from HBM, against the kernels above with their tile table: 8 tokens on 8 experts of 512 x 1024
+// 41.2 -> 30.9 us, 32 on 8 of 2048 x 2048 179 -> 107 (402 MB of weights), 64 on 16 of 264 x 2000 88 -> 54; MB = 3: 256 tokens on 8
+// experts of 512 x 1024 60.0 -> 54.8 us.
 // ------------------------------------------------------------------------------------------------
 struct F32Args {
   const float *A, *W;  // GEMM-1: x [T, K] and the gate, then the up matrices; GEMM-2: h [rows, K] and the down matrices
@@ -180,8 +184,39 @@ struct F32Args {
   const float *topk_w;
   int32_t *error;      // status word of the workspace (cleared by GEMM-1: no wait can give up here)
   int T, k, e_lo, E_loc, P_cap, K, N;
-  int mean_z;          // workgroups of a strip that an even load fills
 };
+
+// Unit `u` of the load: its expert, that expert's first row and rows, the unit's number in the expert; more: whether there may
+// be a unit u + step.  An expert with up to 32 MB rows is one unit, one with more has a unit per 32 rows.  MB > 1 (up to 64
+// experts): units 0 .. E_loc - 1 are the first of each expert, also of one without rows, the others follow.
+struct F32Unit { int le, start, rows, number; bool more; };
+template <int MB>
+__device__ __forceinline__ F32Unit f32_unit(const F32Args &g, int u, int step, int base, int lane) {
+  F32Unit r{-1, 0, 0, 0, false};
+  for (int e0 = 0; e0 < g.E_loc; e0 += 64) {
+    const int e = g.e_lo + min(e0 + lane, g.E_loc - 1);
+    const int start = min(max(g.offsets[e] - base, 0), g.P_cap);
+    const int rows = e0 + lane < g.E_loc ? max(min(max(g.offsets[e + 1] - base, 0), g.P_cap) - start, 0) : 0;
+    const int n = MB > 1 ? (rows > 32 * MB ? (rows - 1) >> 5 : 0) : (rows + 31) >> 5;
+    const int upto = wave_inclusive_scan(n), all = __builtin_amdgcn_readlane(upto, 63);
+    int at = u;  // MB > 1: the lane of the expert whose first unit it is
+    if (MB == 1 || u >= g.E_loc) {
+      const int i = MB > 1 ? u - g.E_loc : u;
+      if (i >= all) {
+        u -= all;
+        continue;
+      }
+      at = __builtin_ctzll(__ballot(upto > i));
+      r.number = i - __builtin_amdgcn_readlane(upto - n, at) + (MB > 1 ? 1 : 0);
+    }
+    r.le = e0 + at;
+    r.start = __builtin_amdgcn_readlane(start, at);
+    r.rows = __builtin_amdgcn_readlane(rows, at);
+    r.more = u + step < all + (MB > 1 ? g.E_loc : 0) || e0 + 64 < g.E_loc;
+    break;
+  }
+  return r;
+}
 
 constexpr int kF32Waves = 8;
 // OCC: waves per SIMD that the registers are cut for.
@@ -189,18 +224,16 @@ template <bool GATED, int MB, int D, int OCC>
 __global__ __launch_bounds__(kF32Waves * 64, OCC) void gemm_f32_direct_kernel(const F32Args g) {
   constexpr int NM = GATED ? 2 : 1, G = 16, NW = kF32Waves;
   __shared__ float red[NW][NM][32][32];
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l31 = lane & 31, khalf = lane >> 5;
-  const int n0 = blockIdx.x * 32, le = blockIdx.y;
-  const bool early = MB > 1 && (int)blockIdx.z < g.mean_z;  // the first weights ahead of the tables
-  if (GATED && tid == 0 && blockIdx.x == 0 && le == 0 && blockIdx.z == 0) *g.error = 0;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n0 = blockIdx.x * 32;
+  if (GATED && threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0) *g.error = 0;
   const int n_groups = (g.K + G - 1) / G;
   const int k0 = w * n_groups / NW, n_mine = (w + 1) * n_groups / NW - k0;  // this wave's groups
   const size_t wsz = (size_t)g.K * g.N;
-  const float *W0 = g.W + (size_t)le * wsz + (size_t)k0 * G * g.N;
+  const float *W0 = g.W + (size_t)min((int)blockIdx.y, g.E_loc - 1) * wsz + (size_t)k0 * G * g.N;
   const int k_len = max(0, min(n_mine * G, g.K - k0 * G)), n_whole = k_len / G;
   const uint32_t pitch = (uint32_t)g.N * 4;
-  const uint32_t b_off = khalf * (G / 2) * pitch + min(n0 + l31, g.N - 1) * 4;  // (columns past the end: not stored)
+  int l31 = threadIdx.x & 31, khalf = (threadIdx.x >> 5) & 1;
+  uint32_t b_off = khalf * (G / 2) * pitch + min(n0 + l31, g.N - 1) * 4;  // (columns past the end: not stored)
   const float *a_row[MB];
   F32Group<MB, NM, G, 1> s[D];
   const std::true_type whole;
@@ -231,17 +264,28 @@ __global__ __launch_bounds__(kF32Waves * 64, OCC) void gemm_f32_direct_kernel(co
         if (!decltype(whole)::value && kk >= k_len) s.a[mi][i] = f32x4{0.f, 0.f, 0.f, 0.f};  // (an infinity times 0)
       }
   };
+  bool early = MB > 1 && (int)blockIdx.y < g.E_loc;  // the first weights ahead of the tables
   if (early) {
 #pragma unroll
     for (int i = 0; i < D; ++i)
       if (i < n_whole) load_b(s[i], i, whole);
   }
   const int base = g.offsets[g.e_lo];
-  const int start = min(max(g.offsets[g.e_lo + le] - base, 0), g.P_cap);
-  const int rows_all = min(max(g.offsets[g.e_lo + le + 1] - base, 0), g.P_cap) - start;
-  const int z0 = blockIdx.z * MB * 32;
-  for (int m0 = z0; m0 < rows_all; m0 += gridDim.z * MB * 32) {
-    const int rows = min(MB * 32, rows_all - m0), nb = (rows + 31) >> 5;
+  bool more = true, used = false;  // used: the LDS, by an earlier unit
+  for (int u = blockIdx.y; more; u += gridDim.y) {
+    const F32Unit e = f32_unit<MB>(g, u, gridDim.y, base, fresh_lane());
+    more = e.more;
+    if (e.rows <= 0) {  // (uniform)
+      early = false;
+      continue;
+    }
+    W0 = g.W + (size_t)e.le * wsz + (size_t)k0 * G * g.N;
+    const int tid = w * 64 + fresh_lane();  // (what hangs on the lane is not kept across the units: registers)
+    l31 = tid & 31;
+    khalf = (tid >> 5) & 1;
+    b_off = khalf * (G / 2) * pitch + min(n0 + l31, g.N - 1) * 4;
+    const int start = e.start, m0 = e.number * 32;
+    const int rows = e.rows <= 32 * MB ? e.rows : min(32, e.rows - m0), nb = (rows + 31) >> 5;
 #pragma unroll
     for (int mi = 0; mi < MB; ++mi) {
       const int r = start + m0 + min(mi * 32 + l31, rows - 1);
@@ -269,9 +313,10 @@ __global__ __launch_bounds__(kF32Waves * 64, OCC) void gemm_f32_direct_kernel(co
 #pragma unroll
     for (int i = 0; i < D; ++i)
       if (i < n_whole) {
-        if (!early || m0 > z0) load_b(s[i], i, whole);
+        if (!early) load_b(s[i], i, whole);
         load_a(s[i], i, whole);
       }
+    early = false;
     int kg = 0;
     for (; kg + 2 * D <= n_whole; kg += D) {
 #pragma unroll
@@ -298,7 +343,7 @@ __global__ __launch_bounds__(kF32Waves * 64, OCC) void gemm_f32_direct_kernel(co
     for (int mi = 0; mi < MB; ++mi) {
       if (mi >= nb) break;  // (uniform)
       const int live = min(32, rows - mi * 32);
-      if (mi > 0 || m0 > z0) __syncthreads();  // (the block before is done with the LDS)
+      if (mi > 0 || used) __syncthreads();  // (the block before is done with the LDS)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int rl = (r >> 2) * 8 + khalf * 4 + (r & 3);
@@ -323,6 +368,7 @@ __global__ __launch_bounds__(kF32Waves * 64, OCC) void gemm_f32_direct_kernel(co
                                                : v[0] * g.topk_w[min(max(g.perm[base + row], 0), g.T * g.k - 1)];
       }
     }
+    used = true;
   }
 }
 

@@ -89,6 +89,31 @@ def test_gemm_launch_rule_follows_rows_per_expert():
         assert lib.moe_forward_gemm_launches(C.byref(good_shape(T=T, d=d, f=f, **dense))) == launches, (T, d, f)
 
 
+def test_f32_small_batch_rule():
+    form = lambda T, d, f, E, k, R: B.moe_forward_small_batch(  # noqa: E731  (one rank local)
+        good_shape(T=T, d=d, f=f, E=E, k=k, R=R, local_rank_begin=0, local_rank_end=1, dtype=B.MOE_F32))
+    assert form(256, 512, 1024, 8, 2, 1) == 3 and form(8, 512, 1024, 8, 2, 1) == 1
+    # few rows per expert on average, but tokens enough for a large expert: the tile kernels
+    for T, E, k, R in ((3000, 128, 1, 4), (768, 256, 8, 8), (6000, 256, 1, 4)):
+        assert form(T, 1024, 1024, E, k, R) == 0
+    assert form(512, 1024, 1024, 64, 1, 8) == 1 and form(513, 1024, 1024, 64, 1, 8) == 0
+    # strips enough for two workgroups on every CU
+    assert form(256, 1024, 1536, 32, 1, 1) == 1 and form(256, 1024, 1544, 32, 1, 1) == 0
+    assert form(256, 1544, 1024, 32, 1, 1) == 0  # those of GEMM-2 count as well
+    assert form(32, 1024, 3584, 32, 1, 1) == 1 and form(32, 1024, 3592, 32, 1, 1) == 0
+    # more than 24 rows per expert: one block where few workgroups exist, three in nearly full rounds
+    assert form(384, 1024, 512, 16, 1, 4) == 1 and form(385, 1024, 512, 8, 1, 2) == 0
+    assert form(124, 936, 440, 16, 4, 1) == 0  # 31 rows: many experts have more than 32
+    assert form(120, 1024, 504, 8, 2, 1) == 1 and form(300, 1024, 504, 8, 2, 1) == 0 and form(144, 512, 2048, 8, 2, 1) == 3
+    for T, f, blocks in ((288, 1024, 3), (296, 1024, 0)):  # two rounds: up to 36 rows
+        assert form(T, 512, f, 16, 2, 1) == blocks, T
+    assert form(200, 1944, 384, 16, 4, 1) == 0 and form(200, 1944, 512, 16, 4, 1) != 1  # short reduction of GEMM-2
+    assert form(600, 512, 1024, 8, 2, 1) == 0 and B.moe_forward_small_batch(good_shape(E=6, R=4)) == 0
+    # bf16: the weight-streaming kernels
+    assert B.moe_forward_small_batch(good_shape(T=16, d=512, f=512)) == 1
+    assert B.moe_forward_small_batch(good_shape(T=16, d=512, f=504)) == 0
+
+
 def test_forward_rejects_extents_beyond_32bit_row_offsets():
     lib = B.lib()
     s = good_shape(T=1 << 20, d=8192, f=8192, k=2)
