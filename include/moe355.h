@@ -378,6 +378,9 @@ MOE355_API int moe_fp8_fused_forward(const moe_shape *shape, const void *x, cons
  *   at every size.
  */
 MOE355_API size_t moe_train_kept_bytes(const moe_shape *shape);
+/* 1 or 2: launches that moe_fused_backward runs its two GEMMs in for this shape (host-only; 0 for an invalid or unsupported
+ * shape): 1 = resident workgroups that hand [dg | du] over tile by tile.  moe_fused_backward_copies: 2 with weight gradients. */
+MOE355_API int moe_backward_gemm_launches(const moe_shape *shape);
 MOE355_API size_t moe_backward_workspace_bytes(const moe_shape *shape);
 MOE355_API size_t moe_backward_packed_weight_bytes(const moe_shape *shape, int which);
 MOE355_API int moe_pack_weights_backward(const moe_shape *shape, const void *W_gate, const void *W_up,

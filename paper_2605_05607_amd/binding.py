@@ -58,8 +58,9 @@ def lib() -> C.CDLL:
         L.moe_unfused_workspace_bytes.argtypes = [sp]
         L.moe_forward_gemm_launches.restype = i32
         L.moe_forward_gemm_launches.argtypes = [sp]
-        L.moe_forward_small_batch.restype = i32
-        L.moe_forward_small_batch.argtypes = [sp]
+        for name in ("moe_forward_small_batch", "moe_backward_gemm_launches"):
+            getattr(L, name).restype = i32
+            getattr(L, name).argtypes = [sp]
         L.moe_packed_weight_bytes.restype = sz
         L.moe_packed_weight_bytes.argtypes = [sp, i32]
         L.moe_router_workspace_bytes.restype = sz
@@ -306,6 +307,10 @@ def moe_forward_gemm_launches(shape) -> int:
 
 def moe_forward_small_batch(shape) -> int:
     return int(lib().moe_forward_small_batch(C.byref(shape)))
+
+
+def moe_backward_gemm_launches(shape) -> int:
+    return int(lib().moe_backward_gemm_launches(C.byref(shape)))
 
 
 def _forward_choice(name, shape, x, topk_idx, topk_w, tables, packed_gate_up, packed_down, y, workspace, events,

@@ -782,25 +782,50 @@ static BwdLayout backward_layout(const moe_shape *s, const Derived &dvb) {
   return L;
 }
 
-// The two backward GEMMs as one resident launch.  Time of the backward pass without weight gradients in one launch over two, by
-// rows per expert (even load / skewed):
-//                                     8 to 50              90           200 to 400   500          750   2000
-//   8 of 64 experts of 2048 x 512     1.10 / 1.12          1.10 / 1.07                            1.05  -
-//   16 of 128 of 4096 x 1536          1.00-1.07 / 1.0-1.15 0.91 / 0.89  0.94 / 0.91  1.00 / 0.96  -     -
-//   32 of 128 of 2880 x 2880          0.95 / 1.0-1.15      0.89 / 0.88  0.90 / 1.0   -            -     -
-//   8 of 4096 x 14336                 1.00 / 0.91          0.97 / 0.90  0.89 / 1.03  -            1.04  1.02
-//   32 of 256 of 7168 x 2048          1.0 / 0.86-1.16      0.96 / 0.98  0.90 / 0.97  -            -     -
-// i.e. it pays from some 64 rows, where a skewed load leaves few experts busy below that, to 600, where the rows of [dg | du]
-// past the L2s cost more than the last round of the first GEMM, and in launches of 0.1 ms and more (estimated from the weights'
-// bytes and from the flops).
+// The two backward GEMMs as one resident launch, where they take 0.1 ms and more (estimated from the weights' bytes and from the
+// flops).  Time of the backward pass without weight gradients in one launch over two, by rows per expert (even load / training
+// load spread / power law):
+//                               64              76 to 120       150 to 260      300 to 450      500 to 575
+//   16 of 128 of 4096 x 1536    1.10 1.08 1.02  0.94 0.98 0.93  0.96 0.91 0.99  1.01 0.99 0.91  0.94 0.98 0.90
+//   16 of 128 of 4096 x 1024    < 0.1 ms        < 0.1 ms        < 0.1 ms        1.02 1.00 1.00  1.02 1.00 0.99
+//   16 of 128 of 7168 x 1024    1.02 1.00 0.93  0.96 0.95 0.95  0.97 0.91 0.96  0.97 0.96 0.96  0.99 0.98 0.91
+//   16 of 32 of 4096 x 2048     0.98 1.10 0.89  0.93 0.96 0.89  0.97 0.91 0.92  1.02 0.93 0.88  0.89 0.90 0.97
+//   32 of 128 of 2880 x 2880    0.93 0.96 0.89  0.91 0.90 0.92  0.90 0.94 0.95  1.01 0.94 0.99  0.99 1.00 1.00
+//   32 of 256 of 7168 x 2048    0.96 0.96 0.96  0.91 0.92 0.94  0.96 0.89 0.93  1.00 0.95 0.95  0.97 0.96 0.97
+//   64 of 2048 x 1024           0.94 0.93 0.93  0.90 0.91 0.93  0.94 0.90 0.90  0.98 0.92 0.93  0.97 0.95 0.96
+//   8 of 64 of 8192 x 2048      0.98 0.97 0.92  0.95 0.96 0.95  0.95 0.90 1.00  1.01 0.95 0.94  1.02 0.99 0.92
+//   8 of 64 of 4096 x 4096      -               0.99 0.98 1.03  0.96 0.94 0.99  1.02 0.98 0.89  0.90 0.88 1.02
+//   8 of 4096 x 14336           0.97 0.96 0.94  1.02 1.00 0.97  1.03 1.00 0.96  1.01 1.01 0.99  0.99 0.99 0.96
+//   4 of 8 of 4096 x 14336      -               0.97 0.98 0.95  0.99 0.99 1.03  1.03 1.01 1.02  1.04 1.01 0.97
+//   8 of 32 of 2048 x 4096      < 0.1 ms        < 0.1 ms        < 0.1 ms        1.05 0.99 1.03  1.01 1.04 0.96
+// Around 64 rows, where some experts have a tile of 64 rows and others one of 128, it pays from 32 experts on.  The second GEMM needs an item
+// per CU in every M tile's share of experts: with fewer its last round is nearly empty in either form and the rows of [dg | du] past
+// the L2s are all that differs (4096 x 14336, 2048 x 4096); half as many do where an expert has three M tiles.  From 600 rows on
+// (750: 1.04, 2000: 1.02) those rows cost more than the last round of the first GEMM.  Below 0.1 ms: 8 of 64 of 2048 x 512 1.05 to 1.15.
 static bool backward_one_launch(const moe_shape *s, const Derived &dv) {
   const double rows = (double)s->T * s->k / s->E, work = 3.0 * dv.E_loc * s->d * s->f;
-  return rows >= 64 && rows < 600 && std::max(work * 2 / 6e12, 2 * rows * work / 1.1e15) >= 100e-6;
+  const int64_t items = (int64_t)dv.E_loc * ceil_div(s->d, kBN);  // of the second GEMM, per M tile of an expert
+  return rows >= (dv.E_loc >= 32 ? 64 : 76) && rows < 600 && items >= (rows >= 512 ? 128 : 256) &&
+         std::max(work * 2 / 6e12, 2 * rows * work / 1.1e15) >= 100e-6;
+}
+
+// Whether 32-bit offsets reach the operands of the two backward GEMMs (else: 64-bit ones, and two launches).
+struct BwdFar { bool dy, dgu; };
+static BwdFar backward_far(const moe_shape *s, const Derived &dv) {
+  const int64_t end = (int64_t)1 << 32;
+  return {(int64_t)s->T * s->d * 2 >= end, dv.P_cap * 2 * s->f * 2 >= end};
 }
 
 static bool backward_supported(const moe_shape *s) { return s->dtype == MOE_BF16 && s->f % kBK == 0; }
 
 }  // namespace moe355
+
+extern "C" int moe_backward_gemm_launches(const moe_shape *shape) {
+  Derived dv;
+  if (check_shape(shape, &dv) != MOE_OK || !backward_supported(shape)) return 0;
+  const BwdFar far = backward_far(shape, dv);
+  return !far.dy && !far.dgu && backward_one_launch(shape, dv) ? 1 : 2;
+}
 
 extern "C" size_t moe_train_kept_bytes(const moe_shape *shape) {
   Derived dv;
@@ -995,12 +1020,11 @@ static int backward_common(const moe_shape *shape, const void *x, const void *dy
   g1.n_items = w.header + 0; g1.work = w.work1;
   g1.K = shape->d; g1.N = shape->f; g1.lda = shape->d; g1.ldo = 2 * shape->f;
   g1.n_ntiles = dvb.nt1; g1.n_ktiles = ceil_div(shape->d, kBK);
-  const bool far1 = (int64_t)shape->T * shape->d * 2 >= (int64_t)1 << 32;
-  const bool far2 = dv.P_cap * 2 * shape->f * 2 >= (int64_t)1 << 32;
-  const bool one_launch = !side && !far1 && !far2 && backward_one_launch(shape, dv);
+  const BwdFar far = backward_far(shape, dv);
+  const bool one_launch = !side && !far.dy && !far.dgu && backward_one_launch(shape, dv);
   if (!one_launch) {
-    rc = side ? launch_items<false, false, true, true>(g1, far1, grid_of(dvb.nt1), st)
-              : launch_items<false, false, true, false>(g1, far1, grid_of(dvb.nt1), st);
+    rc = side ? launch_items<false, false, true, true>(g1, far.dy, grid_of(dvb.nt1), st)
+              : launch_items<false, false, true, false>(g1, far.dy, grid_of(dvb.nt1), st);
     if (rc != MOE_OK) return join(rc);
   }
   if (side) {  // dg, du and w h are there: their transposes run beside the second GEMM
@@ -1023,8 +1047,8 @@ static int backward_common(const moe_shape *shape, const void *x, const void *dy
     pa.tickets = w.tickets; pa.tile_ready = w.tile_ready; pa.error = w.header + 24; pa.nt1 = dvb.nt1; pa.max_polls = kMaxPolls;
     rc = launch_resident<gemm_backward_pipeline_kernel>(pa, st);
   } else {
-    rc = side ? launch_items<false, false, false, true>(g2, far2, grid_of(dvb.nt2), st)
-              : launch_items<false, false, false, false>(g2, far2, grid_of(dvb.nt2), st);
+    rc = side ? launch_items<false, false, false, true>(g2, far.dgu, grid_of(dvb.nt2), st)
+              : launch_items<false, false, false, false>(g2, far.dgu, grid_of(dvb.nt2), st);
   }
   if (rc != MOE_OK) return join(rc);
   if ((rc = launch_combine(shape, dv, dxr, topk_idx, tables, dx, true, st)) != MOE_OK || !wgrad) return join(rc);

@@ -114,6 +114,27 @@ def test_f32_small_batch_rule():
     assert B.moe_forward_small_batch(good_shape(T=16, d=512, f=504)) == 0
 
 
+def test_backward_gemm_launch_rule():
+    def launches(rows, El, R, d, f, k=8, **kw):
+        E = El * R
+        assert rows * E % k == 0
+        return B.moe_backward_gemm_launches(good_shape(T=rows * E // k, d=d, f=f, E=E, k=k, R=R, local_rank_begin=0,
+                                                       local_rank_end=1, **kw))
+    # rows per expert, by the number of experts
+    assert [launches(r, 16, 8, 4096, 1536) for r in (64, 75, 76, 256, 512, 599, 600)] == [2, 2, 1, 1, 1, 1, 2]
+    assert [launches(r, 32, 4, 2880, 2880) for r in (63, 64, 599, 600)] == [2, 1, 1, 2]
+    # an item of the second GEMM for every CU, half of them with three M tiles per expert
+    assert [launches(r, 8, 1, 4096, 14336) for r in (90, 300, 511, 512)] == [2, 2, 2, 1]
+    assert [launches(r, 8, 1, 8192, 2048) for r in (90, 300)] == [1, 1] and launches(90, 8, 1, 7936, 2048) == 2
+    assert launches(550, 8, 4, 2048, 4096) == 2
+    # launches of less than 0.1 ms; operands of 4 GiB; shapes the backward pass does not take
+    assert launches(300, 8, 8, 2048, 512) == 2
+    assert launches(500, 32, 4, 4096, 16704) == 1 and launches(500, 32, 4, 4096, 16832) == 2   # 64000 rows of [dg | du]
+    assert launches(500, 32, 64, 2096, 1024, k=1) == 1 and launches(500, 32, 64, 2104, 1024, k=1) == 2  # 1024000 of dy
+    assert launches(300, 32, 4, 4096, 2024) == 0 and launches(300, 32, 4, 4096, 2048, dtype=B.MOE_F32) == 0
+    assert B.moe_backward_gemm_launches(good_shape(E=6, R=4)) == 0
+
+
 def test_forward_rejects_extents_beyond_32bit_row_offsets():
     lib = B.lib()
     s = good_shape(T=1 << 20, d=8192, f=8192, k=2)

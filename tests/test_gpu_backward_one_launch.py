@@ -4,20 +4,23 @@ that a row handed over too early, or a line of an earlier call, would show.  Loa
 of every height and experts of several tiles; a hidden size that is no multiple of a tile."""
 import pytest
 
+from paper_2605_05607_amd import binding as B
 from paper_2605_05607_amd import layer as L
 from paper_2605_05607_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 
 
-# (64, 600) rows per expert, weights that take 0.1 ms and more: the range of the form
-@pytest.mark.parametrize("T,d,f,E,k,skew", [(1100, 2048, 1600, 32, 2, 0.0), (2100, 2048, 1600, 32, 2, 2.0),
-                                            (600, 3080, 4032, 8, 1, 0.0), (2300, 3080, 4032, 8, 2, 1.0)])
+# the range of the form: rows per expert around 64 and 76, even and skewed, ragged tiles in every direction, three M tiles
+@pytest.mark.parametrize("T,d,f,E,k,skew", [(1100, 2048, 1792, 32, 2, 0.0), (2100, 2048, 1792, 32, 2, 2.0),
+                                            (1250, 4104, 1728, 16, 1, 0.0), (2300, 4104, 1728, 16, 2, 1.0),
+                                            (2200, 4104, 2112, 8, 2, 0.0)])
 def test_backward_one_launch_matches_two(T, d, f, E, k, skew):
     import torch
     print(f"backward in one launch T={T} d={d} f={f} E={E} k={k} skew={skew}", flush=True)
     cfg = wl.MoEConfig("bwd", T=T, d=d, f=f, E=E, k=k, R=1, local_rank_begin=0, local_rank_end=1, dtype=wl.BF16,
                        router="normal", seed=3)
+    assert B.moe_backward_gemm_launches(B.shape_of(cfg)) == 1
     gen = torch.Generator(device="cuda").manual_seed(T + d)
     randn = lambda *s: torch.randn(s, generator=gen, device="cuda")  # noqa: E731
     W = [(randn(E, a, b) * a ** -0.5).bfloat16() for a, b in ((d, f), (d, f), (f, d))]
