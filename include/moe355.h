@@ -217,8 +217,8 @@ MOE355_API int moe_fused_forward_timed(const moe_shape *shape, const void *x, co
                                        void *stream, void *const *events);
 
 /*
- * *flag (host) = 0, or 1 if a wait inside the resident GEMM kernel of the last forward call that used `workspace`
- * gave up.  The one call of this library that copies to the host and synchronises with `stream`; for diagnostics.
+ * *flag (host) = 0, or 1 if a wait inside the resident GEMM kernel of the last forward (or moe_fused_backward) call that
+ * used `workspace` gave up.  The one call of this library that copies to the host and synchronises with `stream`; for diagnostics.
  *
  * moe_fused_forward_bounded: moe_fused_forward_one_launch with the bound on the polls of one wait given by the caller
  * (max_polls >= 1, each poll about a microsecond; the library's default is several seconds) and with every GEMM-2 tile
@@ -373,6 +373,13 @@ MOE355_API int moe_fp8_fused_forward(const moe_shape *shape, const void *x, cons
  *   (later calls only: see above).  Such calls from several host threads on one device share that side stream: the library
  *   serialises their enqueueing (a mutex held for the duration of the call) and their side work runs in turn; they still
  *   need separate workspaces.
+ *   The two GEMMs run as one or two launches (moe_backward_gemm_launches).  In one launch, a wait of the second GEMM for the
+ *   rows of the first is bounded as in moe_fused_forward: if one gives up, the rows of dx computed from the incomplete tile
+ *   are NaN (d_topk_w and the weight gradients do not depend on it) and moe_forward_status, given the backward workspace,
+ *   reports 1.
+ * moe_fused_backward_bounded: moe_fused_backward with its two GEMMs in one launch whatever the sizes (MOE_ERR_UNSUPPORTED where
+ *   an operand has 4 GiB and more), the bound on the polls of one wait given by the caller and every tile of the second GEMM
+ *   waiting for wait_extra more tiles than exist, as in moe_fused_forward_bounded: the way the give-up path is tested.
  * moe_fused_backward_copies: moe_fused_backward that computes the weight gradients from transposed copies whatever the sizes
  *   (same arguments, workspace and results, bit for bit), for comparing the two forms.  The workspace has room for the copies
  *   at every size.
@@ -400,6 +407,11 @@ MOE355_API int moe_fused_backward_copies(const moe_shape *shape, const void *x, 
                                          const void *packed_gate_up_t, const void *kept, size_t kept_bytes, void *dx,
                                          float *d_topk_w, void *dW_gate, void *dW_up, void *dW_down, void *workspace,
                                          size_t workspace_bytes, void *stream);
+MOE355_API int moe_fused_backward_bounded(const moe_shape *shape, const void *x, const void *dy, const int32_t *topk_idx,
+                                          const float *topk_w, const moe_dispatch *tables, const void *packed_down_t,
+                                          const void *packed_gate_up_t, const void *kept, size_t kept_bytes, void *dx,
+                                          float *d_topk_w, void *dW_gate, void *dW_up, void *dW_down, void *workspace,
+                                          size_t workspace_bytes, void *stream, int max_polls, int wait_extra);
 
 /*
  * Backward of moe_route_topk's weights (a softmax over the k picked logits; the selection is piecewise constant):

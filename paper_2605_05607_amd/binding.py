@@ -125,6 +125,8 @@ def lib() -> C.CDLL:
         for name in ("moe_fused_backward", "moe_fused_backward_copies"):
             getattr(L, name).restype = i32
             getattr(L, name).argtypes = [sp, vp, vp, vp, vp, dp, vp, vp, vp, sz, vp, vp, vp, vp, vp, vp, sz, vp]
+        L.moe_fused_backward_bounded.restype = i32
+        L.moe_fused_backward_bounded.argtypes = [sp, vp, vp, vp, vp, dp, vp, vp, vp, sz, vp, vp, vp, vp, vp, vp, sz, vp, i32, i32]
         L.moe_dispatch_gather.restype = i32
         L.moe_dispatch_gather.argtypes = [sp, vp, dp, vp, vp]
         L.moe_combine_reduce.restype = i32
@@ -435,11 +437,11 @@ def moe_fused_forward_train(shape, x, topk_idx, topk_w, tables, packed_gate_up, 
 
 
 def _backward(name, shape, x, dy, topk_idx, topk_w, tables, packed_down_t, packed_gate_up_t, kept, dx, d_topk_w, dW_gate,
-              dW_up, dW_down, workspace, stream):
+              dW_up, dW_down, workspace, stream, *more):
     _check(getattr(lib(), name)(C.byref(shape), _ptr(x), _ptr(dy), _ptr(topk_idx), _ptr(topk_w), C.byref(tables.struct),
                                 _ptr(packed_down_t), _ptr(packed_gate_up_t), _ptr(kept), _nbytes(kept), _ptr(dx),
                                 _ptr(d_topk_w), _ptr(dW_gate), _ptr(dW_up), _ptr(dW_down), _ptr(workspace),
-                                _nbytes(workspace), _stream(stream)), name)
+                                _nbytes(workspace), _stream(stream), *more), name)
 
 
 def moe_fused_backward(shape, x, dy, topk_idx, topk_w, tables, packed_down_t, packed_gate_up_t, kept, dx, d_topk_w,
@@ -453,6 +455,13 @@ def moe_fused_backward_copies(shape, x, dy, topk_idx, topk_w, tables, packed_dow
     """moe_fused_backward with the weight gradients from transposed copies of the operands, whatever the sizes."""
     _backward("moe_fused_backward_copies", shape, x, dy, topk_idx, topk_w, tables, packed_down_t, packed_gate_up_t, kept, dx,
               d_topk_w, dW_gate, dW_up, dW_down, workspace, stream)
+
+
+def moe_fused_backward_bounded(shape, x, dy, topk_idx, topk_w, tables, packed_down_t, packed_gate_up_t, kept, dx, d_topk_w,
+                               dW_gate, dW_up, dW_down, workspace, max_polls: int, wait_extra: int = 0, stream=None) -> None:
+    """moe_fused_backward with its two GEMMs in one launch and a bound on its waits, whatever the sizes."""
+    _backward("moe_fused_backward_bounded", shape, x, dy, topk_idx, topk_w, tables, packed_down_t, packed_gate_up_t, kept, dx,
+              d_topk_w, dW_gate, dW_up, dW_down, workspace, stream, int(max_polls), int(wait_extra))
 
 
 def moe_dispatch_gather(shape, x, tables, xs, stream=None) -> None:

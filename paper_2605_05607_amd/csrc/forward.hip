@@ -923,7 +923,7 @@ static int backward_common(const moe_shape *shape, const void *x, const void *dy
                            const float *topk_w, const moe_dispatch *tables, const void *packed_down_t,
                            const void *packed_gate_up_t, const void *kept, size_t kept_bytes, void *dx, float *d_topk_w,
                            void *dW_gate, void *dW_up, void *dW_down, void *workspace, size_t workspace_bytes, void *stream,
-                           bool copies) {
+                           bool copies, bool force_one_launch = false, int max_polls = kMaxPolls, int wait_extra = 0) {
   Derived dv;
   int rc = check_shape(shape, &dv);
   if (rc != MOE_OK) return rc;
@@ -967,6 +967,8 @@ static int backward_common(const moe_shape *shape, const void *x, const void *dy
     const int64_t td = ceil_div(shape->d, edge);
     return td * ceil_div(2 * shape->f, edge) + td * ceil_div(shape->f, edge);
   };
+  const BwdFar far = backward_far(shape, dv);
+  if (force_one_launch && (far.dy || far.dgu || (wgrad && !direct))) return MOE_ERR_UNSUPPORTED;
   const int kblocks = (int)(L.kpad / 64);
   if (wgrad && (kblocks > 65535 || (direct && tiles(kBM) * dv.E_loc >= (int64_t)1 << 30))) return MOE_ERR_UNSUPPORTED;
   const Ws w = carve(workspace, L.t);
@@ -1020,8 +1022,7 @@ static int backward_common(const moe_shape *shape, const void *x, const void *dy
   g1.n_items = w.header + 0; g1.work = w.work1;
   g1.K = shape->d; g1.N = shape->f; g1.lda = shape->d; g1.ldo = 2 * shape->f;
   g1.n_ntiles = dvb.nt1; g1.n_ktiles = ceil_div(shape->d, kBK);
-  const BwdFar far = backward_far(shape, dv);
-  const bool one_launch = !side && !far.dy && !far.dgu && backward_one_launch(shape, dv);
+  const bool one_launch = force_one_launch || (!side && !far.dy && !far.dgu && backward_one_launch(shape, dv));
   if (!one_launch) {
     rc = side ? launch_items<false, false, true, true>(g1, far.dy, grid_of(dvb.nt1), st)
               : launch_items<false, false, true, false>(g1, far.dy, grid_of(dvb.nt1), st);
@@ -1044,7 +1045,8 @@ static int backward_common(const moe_shape *shape, const void *x, const void *dy
   if (one_launch) {
     PipelineArgs pa{};
     pa.g1 = g1; pa.g2 = g2;
-    pa.tickets = w.tickets; pa.tile_ready = w.tile_ready; pa.error = w.header + 24; pa.nt1 = dvb.nt1; pa.max_polls = kMaxPolls;
+    pa.tickets = w.tickets; pa.tile_ready = w.tile_ready; pa.error = w.header + 24;
+    pa.nt1 = dvb.nt1 + wait_extra; pa.max_polls = max_polls;
     rc = launch_resident<gemm_backward_pipeline_kernel>(pa, st);
   } else {
     rc = side ? launch_items<false, false, false, true>(g2, far.dgu, grid_of(dvb.nt2), st)
@@ -1110,6 +1112,17 @@ extern "C" int moe_fused_backward_copies(const moe_shape *shape, const void *x, 
                                          size_t workspace_bytes, void *stream) {
   return backward_common(shape, x, dy, topk_idx, topk_w, tables, packed_down_t, packed_gate_up_t, kept, kept_bytes, dx,
                          d_topk_w, dW_gate, dW_up, dW_down, workspace, workspace_bytes, stream, true);
+}
+
+extern "C" int moe_fused_backward_bounded(const moe_shape *shape, const void *x, const void *dy, const int32_t *topk_idx,
+                                          const float *topk_w, const moe_dispatch *tables, const void *packed_down_t,
+                                          const void *packed_gate_up_t, const void *kept, size_t kept_bytes, void *dx,
+                                          float *d_topk_w, void *dW_gate, void *dW_up, void *dW_down, void *workspace,
+                                          size_t workspace_bytes, void *stream, int max_polls, int wait_extra) {
+  if (max_polls < 1 || wait_extra < 0) return MOE_ERR_INVALID_ARG;
+  return backward_common(shape, x, dy, topk_idx, topk_w, tables, packed_down_t, packed_gate_up_t, kept, kept_bytes, dx,
+                         d_topk_w, dW_gate, dW_up, dW_down, workspace, workspace_bytes, stream, false, true, max_polls,
+                         wait_extra);
 }
 
 extern "C" int moe_dispatch_gather(const moe_shape *shape, const void *x, const moe_dispatch *tables, void *xs,

@@ -310,6 +310,23 @@ def test_backward_refuses_before_its_first_launch():
             assert call(fake, fake, fake) == B.MOE_ERR_UNSUPPORTED, name
 
 
+def test_bounded_backward_arguments():
+    lib = B.lib()
+    fake, big = 4096, 1 << 62
+    tb = B.moe_dispatch(*([fake] * 9))
+    call = lambda s, grad, polls, extra: lib.moe_fused_backward_bounded(  # noqa: E731
+        C.byref(s), fake, fake, fake, fake, C.byref(tb), fake, fake, fake, big, fake, fake, grad, grad, grad, fake, big, None,
+        polls, extra)
+    assert call(good_shape(), fake, 0, 0) == B.MOE_ERR_INVALID_ARG
+    assert call(good_shape(), fake, 4, -1) == B.MOE_ERR_INVALID_ARG
+    assert call(good_shape(f=72), None, 4, 0) == B.MOE_ERR_UNSUPPORTED
+    # an operand of 4 GiB and more, and weight gradients that would come from transposed copies: refused before any launch
+    rows = dict(E=8, R=1, k=1, local_rank_begin=0, local_rank_end=1)
+    assert call(good_shape(T=1 << 18, d=8192, f=64, **rows), None, 4, 0) == B.MOE_ERR_UNSUPPORTED
+    assert call(good_shape(T=1 << 18, d=64, f=4096, **rows), None, 4, 0) == B.MOE_ERR_UNSUPPORTED
+    assert call(good_shape(T=(1 << 18) - 1, d=8192, f=64, **rows), fake, 4, 0) == B.MOE_ERR_UNSUPPORTED
+
+
 def test_route_backward_arguments():
     lib = B.lib()
     s = good_shape()
