@@ -337,6 +337,8 @@ MOE355_API int moe_unfused_forward(const moe_shape *shape, const void *x, const 
  */
 MOE355_API size_t moe_fp8_packed_weight_bytes(const moe_shape *shape, int which);
 MOE355_API size_t moe_fp8_forward_workspace_bytes(const moe_shape *shape);
+/* The counterpart of moe_forward_gemm_launches (0 for an invalid or unsupported shape). */
+MOE355_API int moe_fp8_forward_gemm_launches(const moe_shape *shape);
 MOE355_API int moe_fp8_pack_weights(const moe_shape *shape, const void *W_gate, const void *W_up, const void *W_down,
                                     void *packed_gate_up, void *packed_down, void *stream);
 MOE355_API int moe_fp8_quantize_rows(int64_t rows, int cols, const void *x, void *codes, float *scales, void *stream);

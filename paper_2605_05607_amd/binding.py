@@ -58,7 +58,7 @@ def lib() -> C.CDLL:
         L.moe_unfused_workspace_bytes.argtypes = [sp]
         L.moe_forward_gemm_launches.restype = i32
         L.moe_forward_gemm_launches.argtypes = [sp]
-        for name in ("moe_forward_small_batch", "moe_backward_gemm_launches"):
+        for name in ("moe_forward_small_batch", "moe_fp8_forward_gemm_launches", "moe_backward_gemm_launches"):
             getattr(L, name).restype = i32
             getattr(L, name).argtypes = [sp]
         L.moe_packed_weight_bytes.restype = sz
@@ -305,6 +305,10 @@ def moe_fused_forward_timed(shape, x, topk_idx, topk_w, tables, packed_gate_up, 
 
 def moe_forward_gemm_launches(shape) -> int:
     return int(lib().moe_forward_gemm_launches(C.byref(shape)))
+
+
+def moe_fp8_forward_gemm_launches(shape) -> int:
+    return int(lib().moe_fp8_forward_gemm_launches(C.byref(shape)))
 
 
 def moe_forward_small_batch(shape) -> int:

@@ -72,9 +72,10 @@ extern "C" size_t moe_workspace_bytes(const moe_shape *shape) {
   return std::max(moe_dispatch_workspace_bytes(shape), moe_forward_workspace_bytes(shape));
 }
 
-// With fuller experts by the time both GEMMs take, estimated from their flops: below about 60 us (time of the forward call in
+// Below one M tile of rows per expert one launch, whatever its time (8 of 64 experts of 2048 x 512, 100 rows, would be the faster in
+// two: 58 and 49 us).  With fuller experts by the time both GEMMs take, estimated from their flops: below about 60 us (time of the forward call in
 // one launch over two: 8 experts of 2048 x 512 with 300 and 1000 rows each 1.05 and 1.01) what a workgroup pays for its queues
-// and the hand-over is more than the kernel boundary, beyond it one launch is level or up to 13 % faster (table at
+// and the hand-over is more than the kernel boundary, beyond it one launch is 3 % slower to 17 % faster (table at
 // gemm_bf16_pipeline_kernel).  Not for matrices of 4 GiB and more, whose hand-over writes back and invalidates L2s.
 int moe355::tile_gemm_launches(const moe_shape *shape, int elt) {
   if (shape->dtype != MOE_BF16) return 2;
@@ -91,6 +92,12 @@ extern "C" int moe_forward_gemm_launches(const moe_shape *shape) {
   Derived dv;
   if (check_shape(shape, &dv) != MOE_OK) return 0;
   return stream_form(shape, dv, 2) ? 2 : tile_gemm_launches(shape, 2);
+}
+
+extern "C" int moe_fp8_forward_gemm_launches(const moe_shape *shape) {
+  Derived dv;
+  if (check_shape(shape, &dv) != MOE_OK || shape->dtype != MOE_BF16 || shape->d % 16 != 0 || shape->f % 16 != 0) return 0;
+  return stream_form(shape, dv, 1) ? 2 : tile_gemm_launches(shape, 1);
 }
 
 extern "C" int moe_forward_small_batch(const moe_shape *shape) {

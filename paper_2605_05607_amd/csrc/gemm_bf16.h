@@ -38,7 +38,8 @@ constexpr int kGemmLdsBeside = 2 * 65536;  // the same with a ring of two stages
 constexpr int kPatchBytes = 32 * 288;                     // per-wave epilogue patch (fits 8 x in the stages)
 
 // Sixteen bytes past the L2 of this XCD, at a byte offset from `base` (a store of device scope, sc1): visible to the other
-// XCDs as soon as it is acknowledged.
+// XCDs as soon as it is acknowledged.  (Against two 8-byte stores the forward call is level: 328.6 and 329.8 us for 8192 tokens on
+// 16 of 128 experts of 4096 x 1536, 685.5 and 686.0 for 4096 with a skewed load on 32 of 256 of 7168 x 2048.)
 constexpr int kDeviceScope = 16;  // the sc1 bit in the cache policy of a buffer instruction
 __device__ __forceinline__ void store_through(void *base, uint32_t at, const unsigned char *from) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(base, 0, 0xFFFFFFFFu, 0x00027000);
@@ -457,9 +458,11 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16_kernel(const GemmAr
 //   32 of 128 experts of 2880 x 2880                1.00  0.94  0.97 | 0.97  0.99  1.00           1.03  0.95  0.93 | 0.92  0.99  1.01
 //   8 experts of 4096 x 14336                       0.98  0.93  0.99 | 0.99  1.01  1.00           0.93  0.90  0.95 | 0.95  0.98  0.99
 //   32 of 256 experts of 7168 x 2048                1.00  0.91  0.95 | 0.93  0.99  0.99           0.89  0.91  0.93 | 0.94  0.97  0.98
-// and the same for FP8 and for the training forward.  What it owes to counters on lines of their own (kTicketStride,
-// kReadyStride): 4096 FP8 tokens on 32 of 256 experts of 7168 x 2048 391 -> 352 us, 5003 tokens on 32 experts of 2880 x 2880
-// 380 -> 362.
+// Where the rule takes one launch from 256 rows on, eight layers of 256 to 2000 rows, even and skewed: bf16 0.83 to 1.03 (median
+// 0.97), FP8 0.88 to 1.03 (0.98), the training forward 0.84 to 1.04 (0.97); where it takes two, one launch would be 0.88 to 1.10
+// (1.03).  What one launch owes to counters on lines of their own (kTicketStride, kReadyStride): 4096 FP8 tokens on 32 of 256 experts
+// of 7168 x 2048 355 -> 331 us, 5003 tokens on 32 of 128 experts of 2880 x 2880 358 -> 339, 8192 on 16 of 128 of 4096 x 1536
+// 334 -> 328.
 //
 // Work distribution: both lists are cut into 8 queues exactly as a plain launch would spread them over the XCDs
 // (queue x = virtual blocks x, x + 8, ...; see chunked_item); a workgroup draws tickets from its home queue

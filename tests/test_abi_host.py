@@ -89,6 +89,27 @@ def test_gemm_launch_rule_follows_rows_per_expert():
         assert lib.moe_forward_gemm_launches(C.byref(good_shape(T=T, d=d, f=f, **dense))) == launches, (T, d, f)
 
 
+def test_gemm_launch_rule_follows_the_time_of_fuller_experts():
+    def launches(rows, El, R, d, f, k=8):
+        E = El * R
+        s = good_shape(T=rows * E // k, d=d, f=f, E=E, k=k, R=R, local_rank_begin=0, local_rank_end=1)
+        return B.moe_forward_gemm_launches(s), B.moe_fp8_forward_gemm_launches(s)
+    # from 256 rows per expert on by the flops: 66 GFLOP in bf16, 108 in FP8
+    assert launches(255, 8, 8, 2048, 512) == (1, 1) and launches(256, 8, 8, 2048, 512) == (2, 2)
+    assert [launches(r, 8, 8, 2048, 512) for r in (1311, 1312, 2145, 2146)] == [(2, 2), (1, 2), (1, 2), (1, 1)]
+    assert launches(256, 32, 4, 2880, 2880) == (1, 1)
+    # x, or h with its rows on lines of their own, of 4 GiB: two launches (262144 tokens of 8192; 524288 rows of 4096 and 4032)
+    assert [launches(1 << 18, 1, 1, d, 512, k=1) for d in (8176, 8192, 16368, 16384)] == [(1, 1), (2, 1), (2, 1), (2, 2)]
+    assert [launches(1 << 19, 1, 1, 512, f, k=1) for f in (4032, 4048, 4096)] == [(1, 1), (2, 1), (2, 1)]
+    # below 256 rows the resident kernel has a form for such operands
+    s = good_shape(T=1 << 18, d=8192, f=512, E=2048, k=1, R=64, local_rank_begin=0, local_rank_end=1)
+    assert B.moe_forward_gemm_launches(s) == 1
+    # FP8: weight-streaming kernels for small batches, nothing for shapes it does not take
+    assert B.moe_fp8_forward_gemm_launches(good_shape(T=16, d=512, f=512)) == 2
+    assert B.moe_fp8_forward_gemm_launches(good_shape(f=72)) == 0
+    assert B.moe_fp8_forward_gemm_launches(good_shape(dtype=B.MOE_F32)) == 0
+
+
 def test_f32_small_batch_rule():
     form = lambda T, d, f, E, k, R: B.moe_forward_small_batch(  # noqa: E731  (one rank local)
         good_shape(T=T, d=d, f=f, E=E, k=k, R=R, local_rank_begin=0, local_rank_end=1, dtype=B.MOE_F32))
