@@ -182,16 +182,18 @@ MOE355_API int moe_pack_weights(const moe_shape *shape, const void *W_gate, cons
  * topk_w[t,j] * FFN_{e(t,j)}(x[t]); rows of tokens without a local slot are written as zeros.
  * Token rows are gathered straight into the GEMM-1 tiles (no dispatched copy of x is materialised);
  * each y row is written exactly once, without atomics.  When moe_forward_gemm_launches(shape) is 1 (bf16 layers
- * with fewer than 256 rows per expert on average, T*k < 256*E, or whose GEMMs take more than about 60 us), GEMM-1 and
- * GEMM-2 run in ONE launch of resident workgroups: a GEMM-2 tile starts as soon as the h rows of its 256-row tile are
- * complete (per-tile readiness counters in the workspace), the one-GPU form of the tile-granular GEMM-1 => GEMM-2
- * hand-over of the fused kernel (Sec. IV-A, IV-B); otherwise the two GEMMs are two launches.  The result is the same
- * either way.
- * Small batches run two weight-streaming kernels instead (and sometimes a third that adds their partial sums), which
- * need no tile table and no separate Combine: bf16 layers with T <= 128, d and f >= 512 and few rows per expert (at most
- * 12 on average), or more of them where all local weights together are at most 128 MB and, beyond 64 tokens, the
- * estimated time favours it (moe_forward_gemm_launches tells, for bf16 weights).  They split the reduction ranges,
- * so their y can differ from the other forms' in the rounding of the fp32 sums.
+ * with fewer than 256 rows per expert on average, T*k < 256*E, or whose GEMMs take more than about 60 us by their flops and
+ * whose x and h have less than 4 GiB each), GEMM-1 and GEMM-2 run in ONE launch of resident workgroups: a GEMM-2 tile
+ * starts as soon as the h rows of its 256-row tile are complete (per-tile readiness counters in the workspace), the
+ * one-GPU form of the tile-granular GEMM-1 => GEMM-2 hand-over of the fused kernel (Sec. IV-A, IV-B); otherwise the two
+ * GEMMs are two launches.  The result is the same either way.
+ * Small batches (moe_forward_small_batch) run kernels that need no tile table and split the reduction ranges, so their y can
+ * differ from the other forms' in the rounding of the fp32 sums (the same inputs still give the same bits).
+ *   bf16 layers: two weight-streaming kernels, the second with the reduction over a token's slots in it, for T <= 128, d and
+ *   f >= 512 and few rows per expert (at most 12 on average), or more of them where all local weights together are at most
+ *   128 MB and, beyond 64 tokens, the estimated time favours it.
+ *   fp32 layers: a launch per GEMM, then Combine, for T <= 512 with at most 24 rows per expert on average and layers that are
+ *   not too wide for them (E_loc * max(d, f) of about 49000, for T <= 32 115000), and for some of more rows up to T = 384.
  * A wait inside the resident kernel is bounded; if one gives up (corrupt tables; it cannot happen otherwise) the rows
  * computed from the incomplete tile are written as NaN and moe_forward_status reports 1 for this workspace.
  * `tables` must come from moe_build_dispatch on the same shape and topk_idx.
@@ -208,7 +210,7 @@ MOE355_API int moe_fused_forward(const moe_shape *shape, const void *x, const in
  * (created by the caller with timing enabled; a NULL entry is skipped) which are recorded on `stream`
  * [0] before the first kernel, [1] after the tile-table kernel (small batches have none: before GEMM-1), [2] after
  * GEMM-1, [3] after GEMM-2 (recorded together, after the one launch, when moe_forward_gemm_launches(shape) is 1), [4]
- * after Combine (small batches: after the sum of GEMM-2's partial results, or with [3]).
+ * after Combine (small batches in bf16, whose GEMM-2 ends with it: with [3]).
  * The kernels and their order are those of moe_fused_forward.
  */
 MOE355_API int moe_fused_forward_timed(const moe_shape *shape, const void *x, const int32_t *topk_idx,
@@ -243,7 +245,7 @@ MOE355_API int moe_step(const moe_shape *shape, const float *logits, const void 
                         size_t workspace_bytes, void *stream);
 
 /* 1 or 2: GEMM launches of moe_fused_forward for this shape (host-only; 0 for an invalid shape): 1 = the resident kernel,
- * 2 = one launch per GEMM, of the tile kernels or, for small batches, of the weight-streaming ones. */
+ * 2 = one launch per GEMM, of the tile kernels or, for small batches, of those without a tile table. */
 MOE355_API int moe_forward_gemm_launches(const moe_shape *shape);
 /* The small-batch kernels moe_fused_forward runs for this shape (host-only): 0 = none (or an invalid shape); bf16: 1 = the
  * weight-streaming ones; fp32: 1 or 3 = those without a tile table, that many 32-row blocks of an expert at a time. */
@@ -254,7 +256,7 @@ MOE355_API int moe_forward_small_batch(const moe_shape *shape);
  * (comparison of the two, timing of the two GEMMs apart): _two_launch keeps a kernel boundary between the GEMMs,
  * _one_launch runs the resident kernel with per-tile readiness counters (bf16 layers only, MOE_ERR_UNSUPPORTED
  * otherwise).  Both run the tile kernels for every batch: the same y, bit for bit, from either, and from
- * moe_fused_forward except for small batches (see there).  Same arguments and workspace; `events` may be NULL, otherwise
+ * moe_fused_forward except where moe_forward_small_batch is not 0.  Same arguments and workspace; `events` may be NULL, otherwise
  * five events as in moe_fused_forward_timed.
  */
 MOE355_API int moe_fused_forward_two_launch(const moe_shape *shape, const void *x, const int32_t *topk_idx,
