@@ -240,22 +240,25 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
 // fp32 layers of small batches: the kernels without a tile table (gemm_f32_direct_kernel); 32-row blocks per workgroup of
 // GEMM-1, 0 = the tile kernels.  A load cannot be seen here, so each line holds for even loads and for the skewed ones of the
 // workload generator (power law, the hottest rank local).  Time of this form's forward call over the tile kernels', median (and
-// the tenth of the layers above), 256 to 2048 columns, 2 to 128 local experts, weights from HBM:
-//   up to 24 rows per expert, up to 512 tokens, at most 1536 strips of 32 columns: one block, even 0.70 to 0.90 (0.98), skewed
-//     0.75 to 0.93 (1.03).  More tokens (1025 to 2048: skewed 0.94, up to 1.19): the tile kernels, which read a large expert's
-//     weights half as often.  More strips: two workgroups per CU on every one of them, so that the latency this form saves counts
-//     less (2000 strips: even 0.95, up to 1.30), but not with one unit per expert, up to 32 tokens (0.68 to 0.90, up to 3500);
-//   more rows, up to 384 tokens: one block each while that leaves CUs idle, even 0.92 (1.01), skewed 0.90 (1.03); (more
-//     workgroups: 24 to 32 rows on 16 of 936 x 440 1.09);
-//   three blocks, where an even load is one unit of up to 96 rows per expert in nearly full rounds of one workgroup per CU: 0.93
-//     (1.03), skewed 0.93 (1.03).  Short reductions are all prologue and sum (columns of 376 to 424 in GEMM-2 1.10 to 1.23).  In
-//     more than one round up to 36 rows only: 38 to 64 are what the tile kernels are cut for (1.00 to 1.11), and a skewed load of
-//     more fills their tiles as well (1.05 to 1.17).
+// the tenth of the layers above), 7800 random layers of 256 to 2048 columns and 1 to 128 local experts, weights from HBM:
+//                                                                    even          skewed
+//   up to 24 rows per expert, 1 to 32 tokens, up to 3584 strips       0.83 (0.91)   0.84 (0.92)
+//     33 to 256 tokens, up to 1536 strips of 32 columns               0.75 (0.92)   0.85 (0.96)
+//     257 to 768                                                      0.71 (0.85)   0.87 (1.00)
+//     769 to 1536 (beyond: up to 1.25 under skew)                     0.70 (0.79)   0.92 (1.02)
+//     more strips: two workgroups per CU on every one of them, so that the latency this form saves counts less;
+//     33 to 512 tokens                                                0.84 (1.15)   0.89 (1.12)   tile kernels
+//   more than 24 rows, up to 384 tokens, few workgroups: one block    0.92 (0.99)   0.90 (1.00)
+//   three blocks, an even load is one unit of up to 96 rows per
+//   expert in nearly full rounds of one workgroup per CU              0.90 (1.03)   0.91 (1.03)
+// Three blocks: short reductions are all prologue and sum (columns of 376 to 424 in GEMM-2 1.10 to 1.23); in more than one round
+// up to 36 rows only: 38 to 64 are what the tile kernels are cut for (1.00 to 1.11), and a skewed load of more fills their tiles
+// as well (1.05 to 1.17).  One block: 24 to 32 rows on 16 of 936 x 440, where many experts have more than 32, 1.09.
 int f32_direct_blocks(const moe_shape *s, const Derived &dv) {
   if (s->dtype != MOE_F32) return 0;
   const int64_t strips = (int64_t)dv.E_loc * ceil_div(s->f, 32), widest = (int64_t)dv.E_loc * ceil_div(std::max(s->d, s->f), 32);
   const double rows = (double)s->T * s->k / s->E;
-  if (rows <= 24.0) return s->T <= 512 && widest <= (s->T <= 32 ? 3584 : 1536) ? 1 : 0;
+  if (rows <= 24.0) return s->T <= 1536 && widest <= (s->T <= 32 ? 3584 : 1536) ? 1 : 0;
   if (s->T > 384) return 0;
   if (strips * std::ceil(rows / 32) < 256 && strips * std::ceil(1.25 * rows / 32) < 384) return 1;
   const bool full_rounds = strips >= 192 && strips <= 1024 && (strips <= 256 || strips >= 0.9 * 256 * std::ceil(strips / 256.0));
