@@ -246,8 +246,8 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
 //     33 to 256 tokens, up to 1536 strips of 32 columns               0.75 (0.92)   0.85 (0.96)
 //     257 to 768                                                      0.71 (0.85)   0.87 (1.00)
 //     769 to 1536 (beyond: up to 1.25 under skew)                     0.70 (0.79)   0.92 (1.02)
-//     more strips: two workgroups per CU on every one of them, so that the latency this form saves counts less;
-//     33 to 512 tokens                                                0.84 (1.15)   0.89 (1.12)   tile kernels
+//     more strips (tile kernels), 33 to 512 tokens: the weights come
+//     from enough workgroups in either form, latency counts less      0.84 (1.15)   0.89 (1.12)
 //   more than 24 rows, up to 384 tokens, few workgroups: one block    0.92 (0.99)   0.90 (1.00)
 //   three blocks, an even load is one unit of up to 96 rows per
 //   expert in nearly full rounds of one workgroup per CU              0.90 (1.03)   0.91 (1.03)
