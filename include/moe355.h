@@ -193,7 +193,7 @@ MOE355_API int moe_pack_weights(const moe_shape *shape, const void *W_gate, cons
  *   f >= 512 and few rows per expert (at most 12 on average), or more of them where all local weights together are at most
  *   128 MB and, beyond 64 tokens, the estimated time favours it.
  *   fp32 layers: a launch per GEMM, then Combine, for T <= 1536 with at most 24 rows per expert on average and layers that are
- *   not too wide for them (E_loc * max(d, f) of about 49000, for T <= 32 115000), and for some of more rows up to T = 384.
+ *   not too wide for them (E_loc * max(d, f) of about 49000, for T <= 32 98000), and for some of more rows up to T = 384.
  * A wait inside the resident kernel is bounded; if one gives up (corrupt tables; it cannot happen otherwise) the rows
  * computed from the incomplete tile are written as NaN and moe_forward_status reports 1 for this workspace.
  * `tables` must come from moe_build_dispatch on the same shape and topk_idx.

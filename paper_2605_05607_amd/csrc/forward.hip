@@ -240,29 +240,34 @@ static int launch_gemms(const moe_shape *s, const Derived &dv, const void *a1, c
 // fp32 layers of small batches: the kernels without a tile table (gemm_f32_direct_kernel); 32-row blocks per workgroup of
 // GEMM-1, 0 = the tile kernels.  A load cannot be seen here, so each line holds for even loads and for the skewed ones of the
 // workload generator (power law, the hottest rank local).  Time of this form's forward call over the tile kernels', median (and
-// the tenth of the layers above), 7800 random layers of 256 to 2048 columns and 1 to 128 local experts, weights from HBM:
+// the tenth of the layers above), 5200 random layers of 256 to 2048 columns and 1 to 128 local experts, weights from HBM:
 //                                                                    even          skewed
-//   up to 24 rows per expert, 1 to 32 tokens, up to 3584 strips       0.83 (0.91)   0.84 (0.92)
-//     33 to 256 tokens, up to 1536 strips of 32 columns               0.75 (0.92)   0.85 (0.96)
-//     257 to 768                                                      0.71 (0.85)   0.87 (1.00)
-//     769 to 1536 (beyond: up to 1.25 under skew)                     0.70 (0.79)   0.92 (1.02)
+//   up to 24 rows per expert, 1 to 32 tokens, up to 3072 strips       0.78 (0.89)   0.80 (0.90)   (3500 strips: up to 1.27)
+//     33 to 256 tokens, up to 1536 strips of 32 columns               0.72 (0.89)   0.82 (0.92)
+//     257 to 768                                                      0.68 (0.81)   0.82 (0.95)
+//     769 to 1536 (beyond: up to 1.25 under skew)                     0.67 (0.76)   0.88 (0.99)
 //     more strips (tile kernels), 33 to 512 tokens: the weights come
 //     from enough workgroups in either form, latency counts less      0.84 (1.15)   0.89 (1.12)
-//   more than 24 rows, up to 384 tokens, few workgroups: one block    0.92 (0.99)   0.90 (1.00)
+//   more than 24 rows, up to 384 tokens, few workgroups: one block    0.88 (0.96)   0.87 (0.96)
 //   three blocks, an even load is one unit of up to 96 rows per
-//   expert in nearly full rounds of one workgroup per CU              0.90 (1.03)   0.91 (1.03)
-// Three blocks: short reductions are all prologue and sum (columns of 376 to 424 in GEMM-2 1.10 to 1.23); in more than one round
-// up to 36 rows only: 38 to 64 are what the tile kernels are cut for (1.00 to 1.11), and a skewed load of more fills their tiles
-// as well (1.05 to 1.17).  One block: 24 to 32 rows on 16 of 936 x 440, where many experts have more than 32, 1.09.
+//   expert in nearly full rounds of one workgroup per CU: one round
+//   of experts with up to 40 rows                                     0.89 (0.99)   0.84 (1.01)
+//     with 62 to 87, i.e. two 64-row tiles for many                   0.78 (0.95)   0.94 (1.01)
+//     with 40 to 62, which a tile holds (tile kernels)                1.01 (1.05)   0.94 (1.05)
+//   more rounds, up to 36 rows                                        0.86 (0.96)   0.86 (0.93)
+//     more rows (tile kernels): 1.00 to 1.11 even, 1.05 to 1.17 skewed
+// Three blocks not with columns of 376 to 424 in GEMM-2 either, which are all prologue and sum (1.10 to 1.23).  One block: 24 to 32
+// rows on 16 of 936 x 440, where many experts have more than 32, 1.09.
 int f32_direct_blocks(const moe_shape *s, const Derived &dv) {
   if (s->dtype != MOE_F32) return 0;
   const int64_t strips = (int64_t)dv.E_loc * ceil_div(s->f, 32), widest = (int64_t)dv.E_loc * ceil_div(std::max(s->d, s->f), 32);
   const double rows = (double)s->T * s->k / s->E;
-  if (rows <= 24.0) return s->T <= 1536 && widest <= (s->T <= 32 ? 3584 : 1536) ? 1 : 0;
+  if (rows <= 24.0) return s->T <= 1536 && widest <= (s->T <= 32 ? 3072 : 1536) ? 1 : 0;
   if (s->T > 384) return 0;
   if (strips * std::ceil(rows / 32) < 256 && strips * std::ceil(1.25 * rows / 32) < 384) return 1;
   const bool full_rounds = strips >= 192 && strips <= 1024 && (strips <= 256 || strips >= 0.9 * 256 * std::ceil(strips / 256.0));
-  return s->d >= 512 && s->f >= 512 && rows <= (strips > 256 ? 36.0 : 87.0) && full_rounds ? 3 : 0;
+  const bool one_tile = rows > 40 && rows < 62, pays = strips > 256 ? rows <= 36 : rows <= 87 && !one_tile;
+  return s->d >= 512 && s->f >= 512 && pays && full_rounds ? 3 : 0;
 }
 
 static int launch_f32_direct(const moe_shape *s, const Derived &dv, int blocks, const void *x, const float *topk_w,
@@ -280,10 +285,11 @@ static int launch_f32_direct(const moe_shape *s, const Derived &dv, int blocks, 
   g2.A = static_cast<const float *>(w.h); g2.W = static_cast<const float *>(packed_down); g2.out = w.o;
   g2.K = s->f; g2.N = s->d;
   const double local = (double)s->T * s->k * dv.E_loc / s->E;  // rows of an even load
-  const auto launch = [&](auto kernel, int mb, int resident, const F32Args &g) {
+  const auto launch = [&](auto kernel, int mb, int resident, F32Args g) {
     // units of any load, or those of an even one and a quarter more, or what the chip holds at once; workgroups take turns
     const int strips = ceil_div(g.N, 32);
     const int64_t most = (mb > 1 ? dv.E_loc : std::min<int64_t>(dv.E_loc, dv.P_cap)) + dv.P_cap / 32;
+    g.most = (int)most;
     const int64_t even = mb > 1 ? dv.E_loc : (int64_t)std::ceil(1.25 * (std::min<double>(dv.E_loc, local) + local / 32));
     const int64_t units = std::min(most, std::max<int64_t>(even, ceil_div(resident, strips)));
     hipLaunchKernelGGL(kernel, dim3(strips, (unsigned)units), dim3(kF32Waves * 64), 0, st, g);

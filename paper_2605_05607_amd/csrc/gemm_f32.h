@@ -169,13 +169,13 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_f32_kernel(const GemmArgs g) 
 // or 32 rows of one with more; the workgroups of a strip take turns over the units of the whole load, which they number from
 // `offsets`.  (With workgroups that each keep to one expert, a large one was turn after turn of a few of them, and the
 // experts without rows scattered the others over the CUs.  Forward call, 414 tokens on 8 of 64 experts of 1024 x 1024, 200 rows
-// on one of them, 81.9 -> 50.1 us, 430 on 16 of 128 of 512 x 1024, 400 rows on one, 126.8 -> 54.2; tile kernels 70.4 and 73.1.)
+// on one of them, 82 -> 49 us, 430 on 16 of 128 of 512 x 1024, 400 rows on one, 127 -> 52; tile kernels 71 and 73.)
 // What bounds it is the latency of the weight stream, so a wave has D groups of 16 reduction indices in flight: with D = 4 all of a
 // range of 512 at once.  MB = 3: experts of 32 to 96 rows in one pass over their weights; such experts are hardly ever empty, so
 // the first weights of each are requested before the tables have been read.
 // Measured, step with weights from HBM, against the kernels above with their tile table: 8 tokens on 8 experts of 512 x 1024
-// 41.2 -> 30.9 us, 32 on 8 of 2048 x 2048 179 -> 107 (402 MB of weights), 64 on 16 of 264 x 2000 88 -> 54; MB = 3: 256 tokens on 8
-// experts of 512 x 1024 60.0 -> 54.8 us.
+// 41.1 -> 30.1 us, 32 on 8 of 2048 x 2048 178 -> 106 (402 MB of weights), 64 on 16 of 264 x 2000 88 -> 51; MB = 3: 256 tokens on 8
+// experts of 512 x 1024 59.9 -> 54.2 us.
 // ------------------------------------------------------------------------------------------------
 struct F32Args {
   const float *A, *W;  // GEMM-1: x [T, K] and the gate, then the up matrices; GEMM-2: h [rows, K] and the down matrices
@@ -184,7 +184,20 @@ struct F32Args {
   const float *topk_w;
   int32_t *error;      // status word of the workspace (cleared by GEMM-1: no wait can give up here)
   int T, k, e_lo, E_loc, P_cap, K, N;
+  int most;            // units of any load
 };
+
+// Sum of the lanes up to and including this one, by data-parallel moves: within the rows of 16 lanes, then the rows' totals.
+// (Every unit starts with it: with lane permutes through the LDS port the two launches of a layer of 8 to 256 columns took 1 us more.)
+__device__ __forceinline__ int f32_lane_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
 
 // Unit `u` of the load: its expert, that expert's first row and rows, the unit's number in the expert; more: whether there may
 // be a unit u + step.  An expert with up to 32 MB rows is one unit, one with more has a unit per 32 rows.  MB > 1 (up to 64
@@ -193,12 +206,19 @@ struct F32Unit { int le, start, rows, number; bool more; };
 template <int MB>
 __device__ __forceinline__ F32Unit f32_unit(const F32Args &g, int u, int step, int base, int lane) {
   F32Unit r{-1, 0, 0, 0, false};
+  const bool some_left = u + step < g.most;
+  const auto bounds = [&](int e0) {
+    const int32_t *at = g.offsets + g.e_lo + min(e0 + lane, g.E_loc - 1);
+    return int2{at[0], at[1]};
+  };
+  int2 next = bounds(0);
   for (int e0 = 0; e0 < g.E_loc; e0 += 64) {
-    const int e = g.e_lo + min(e0 + lane, g.E_loc - 1);
-    const int start = min(max(g.offsets[e] - base, 0), g.P_cap);
-    const int rows = e0 + lane < g.E_loc ? max(min(max(g.offsets[e + 1] - base, 0), g.P_cap) - start, 0) : 0;
+    const int2 cur = next;
+    if (e0 + 64 < g.E_loc) next = bounds(e0 + 64);
+    const int start = min(max(cur.x - base, 0), g.P_cap);
+    const int rows = e0 + lane < g.E_loc ? max(min(max(cur.y - base, 0), g.P_cap) - start, 0) : 0;
     const int n = MB > 1 ? (rows > 32 * MB ? (rows - 1) >> 5 : 0) : (rows + 31) >> 5;
-    const int upto = wave_inclusive_scan(n), all = __builtin_amdgcn_readlane(upto, 63);
+    const int upto = f32_lane_scan(n), all = __builtin_amdgcn_readlane(upto, 63);
     int at = u;  // MB > 1: the lane of the expert whose first unit it is
     if (MB == 1 || u >= g.E_loc) {
       const int i = MB > 1 ? u - g.E_loc : u;
@@ -212,7 +232,7 @@ __device__ __forceinline__ F32Unit f32_unit(const F32Args &g, int u, int step, i
     r.le = e0 + at;
     r.start = __builtin_amdgcn_readlane(start, at);
     r.rows = __builtin_amdgcn_readlane(rows, at);
-    r.more = u + step < all + (MB > 1 ? g.E_loc : 0) || e0 + 64 < g.E_loc;
+    r.more = some_left && (u + step < all + (MB > 1 ? g.E_loc : 0) || e0 + 64 < g.E_loc);
     break;
   }
   return r;

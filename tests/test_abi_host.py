@@ -121,7 +121,7 @@ def test_f32_small_batch_rule():
     # strips enough for two workgroups on every CU
     assert form(256, 1024, 1536, 32, 1, 1) == 1 and form(256, 1024, 1544, 32, 1, 1) == 0
     assert form(256, 1544, 1024, 32, 1, 1) == 0  # those of GEMM-2 count as well
-    assert form(32, 1024, 3584, 32, 1, 1) == 1 and form(32, 1024, 3592, 32, 1, 1) == 0
+    assert form(32, 1024, 3072, 32, 1, 1) == 1 and form(32, 1024, 3080, 32, 1, 1) == 0
     # more than 24 rows per expert: one block where few workgroups exist, three in nearly full rounds
     assert form(384, 1024, 512, 16, 1, 4) == 1 and form(385, 1024, 512, 8, 1, 2) == 0
     assert form(124, 936, 440, 16, 4, 1) == 0  # 31 rows: many experts have more than 32
@@ -129,6 +129,7 @@ def test_f32_small_batch_rule():
     for T, f, blocks in ((288, 1024, 3), (296, 1024, 0)):  # two rounds: up to 36 rows
         assert form(T, 512, f, 16, 2, 1) == blocks, T
     assert form(200, 1944, 384, 16, 4, 1) == 0 and form(200, 1944, 512, 16, 4, 1) != 1  # short reduction of GEMM-2
+    assert [form(T, 512, 1024, 8, 2, 1) for T in (160, 164, 244, 248, 348, 352)] == [3, 0, 0, 3, 3, 0]  # 40, 62, 87 rows
     assert form(600, 512, 1024, 8, 2, 1) == 0 and B.moe_forward_small_batch(good_shape(E=6, R=4)) == 0
     # bf16: the weight-streaming kernels
     assert B.moe_forward_small_batch(good_shape(T=16, d=512, f=512)) == 1

@@ -23,10 +23,11 @@ CASES = {
     "all_local": (1, (65, 33, 97, 64, 96, 63, 31, 63), 2048, 2040, 1, 8),  # turns over experts in both GEMMs
     "turns_of_many": (1, (33,) * 15 + (1,) * 17, 264, 1000, 1, 16),        # two groups in flight, 47 units on 42
     "many_experts": (1, (2,) * 30 + (70,) + (0,) * 89 + (1, 0, 35, 5), 40, 72, 1, 2),  # numbered in two parts
-    "three_blocks_one_round": (3, (64, 65, 96, 97, 33, 1, 0, 20), 520, 1000),
+    "three_blocks_one_round": (3, (64, 33, 97, 96, 1, 0, 20, 3), 520, 1000),
+    "three_blocks_full": (3, (64, 65, 96, 97, 33, 60, 0, 97), 520, 1000, 2, 1),
     "three_blocks_two_rounds": (3, (64, 65, 96, 97, 33, 1, 0, 20, 3, 2, 1, 128, 0, 0, 0, 26), 520, 992, 2, 1),
-    "three_blocks_large_expert": (3, (300, 0, 0, 0, 0, 2, 30, 44), 600, 1000),
-    "three_blocks_turns": (3, (300, 0, 0, 0, 0, 0, 0, 84), 600, 1000),     # a workgroup's second unit, after weights asked for early
+    "three_blocks_large_expert": (3, (230, 0, 0, 0, 0, 2, 30, 44), 600, 1000),
+    "three_blocks_turns": (3, (300, 0, 0, 0, 0, 0, 0, 20), 600, 1000),     # a workgroup's second unit, after weights asked for early
 }
 
 
@@ -69,7 +70,7 @@ def test_f32_small_batch(oracle, name):
             first = y
 
 
-# hot experts: 0.71 to 0.74 of the tile kernels' time; 1.2 to 1.7 x with workgroups that each keep to one expert
+# hot experts: 0.67 to 0.71 of the tile kernels' time; 1.2 to 1.7 x with workgroups that each keep to one expert
 @pytest.mark.parametrize("rows,d,f,R", [((200, 20) + (2,) * 6, 1024, 1024, 8), ((300,) + (3,) * 31, 512, 1024, 8),
                                         ((400,) + (2,) * 15, 512, 1024, 8)])
 def test_f32_small_batch_keeps_up_under_skew(rows, d, f, R):
